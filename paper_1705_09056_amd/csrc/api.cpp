@@ -330,6 +330,9 @@ dpsgd_status dpsgd_set_option(dpsgd_ctx *ctx, const char *key, int64_t value)
     } else if (k == "conv_band_rows") {
         if (!(value == 0 || value == 8 || value == 16)) return DPSGD_EINVAL;
         ctx->opt_conv_band_rows = (int32_t)value;
+    } else if (k == "conv_pad") {
+        ctx->opt_conv_pad = value ? 1 : 0;
+        ctx->ws_model = dpsgd_model_desc();   // another workspace layout
     } else if (k == "ring_chunks") {
         ctx->opt_ring_chunks = value ? 1 : 0;
     } else if (k == "fused_lds") {
@@ -434,14 +437,24 @@ static dpsgd_status grad_or_step(dpsgd_ctx *ctx, const dpsgd_model *model, const
     m.input_is_bf16 = batch->input_is_bf16 ? 1 : 0;
     if (m.input_is_bf16 && m.kind == DPSGD_MODEL_LSQ) return DPSGD_EUNSUPPORTED;
     if (!(m == ctx->ws_model)) {
-        const size_t need = dpsgd::grad_workspace_bytes(ctx, m);
+        ctx->conv_pad_off = false;
+        size_t need = dpsgd::grad_workspace_bytes(ctx, m);
         if (need > ctx->ws_bytes) {
             DPSGD_HIP_TRY(hipStreamSynchronize(ctx->stream));
             if (ctx->ws) (void)hipFree(ctx->ws);
             ctx->ws = nullptr;
             ctx->ws_bytes = 0;
-            if (hipMalloc(&ctx->ws, need) != hipSuccess) {
+            ctx->ws_model = dpsgd_model_desc();   // (no workspace belongs to the previous model any more)
+            hipError_t e = hipMalloc(&ctx->ws, need);
+            if (e != hipSuccess && m.kind == DPSGD_MODEL_RESNET20 && ctx->opt_conv_pad) {
+                (void)hipGetLastError();   // without the padding of odd shapes the activations are smaller
+                ctx->conv_pad_off = true;
+                need = dpsgd::grad_workspace_bytes(ctx, m);
+                e = hipMalloc(&ctx->ws, need);
+            }
+            if (e != hipSuccess) {
                 (void)hipGetLastError();
+                ctx->ws = nullptr;
                 return DPSGD_ENOMEM;
             }
             ctx->ws_bytes = need;

@@ -1,6 +1,7 @@
 // 3x3 convolutions of the CNN workload as implicit GEMMs on bf16 MFMA (gfx950), and their
-// dispatch: MFMA kernels for channel counts 16/32/64 on images whose width is a multiple of 8,
-// the shape-generic kernels otherwise.
+// dispatch: MFMA kernels for tensors stored with 16/32/64 channels, rows of 8/16/32/64 pixels and a
+// multiple of 8 rows (networks of other extents are stored rounded up to that, zeros beyond the real
+// extents: stored_stage in grad_resnet.hip), the shape-generic kernels otherwise.
 //
 // Forward and data gradient share one kernel: out(y,x,o) = sum_{tap,c} P(y*S+ky-1, x*S+kx-1, c) *
 // Weff[o][c][tap], where P is the source tensor (zero outside; for the data gradient of a stride-2
@@ -142,9 +143,23 @@ struct ConvMfmaArgs {
     const bf16_t *actT;     // data gradient: activation whose sign masks the result (shape of dst)
     const unsigned char *sign_in;   // data gradient: the same signs as a bitmap (1 bit per element), or null
     unsigned char *sign_out;        // forward: bitmap of the output's signs, or null
+    int Cr, Hr, Wr;         // forward: the output's real extents
 };
 
-template <int CI, int CO, int STRIDE, int DILATE, bool DGRAD, int TH>
+// Zeros in place of the pixels of a lane's 8 (channel o, row y, pixels x0 .. x0 + 7) that lie beyond the real extents.
+// (The data gradient needs none: the activation whose sign masks it is zero there.)
+__device__ __forceinline__ u32x4 keep_real(u32x4 pk, int o, int y, int x0, int Cr, int Hr, int Wr)
+{
+    const int n = (o < Cr && y < Hr) ? Wr - x0 : 0;
+    unsigned d[4] = {pk.x, pk.y, pk.z, pk.w};
+#pragma unroll
+    for (int h = 0; h < 4; ++h) d[h] &= (n > 2 * h ? 0x0000ffffu : 0u) | (n > 2 * h + 1 ? 0xffff0000u : 0u);
+    return (u32x4){d[0], d[1], d[2], d[3]};
+}
+
+// PAD: the output's real extents are smaller than the stored ones (forward), or the source is wider than the dilated
+// patch (data gradient); a template argument because the test costs the exact shapes 0.5 % of a CNN iteration.
+template <int CI, int CO, int STRIDE, int DILATE, bool DGRAD, int TH, bool PAD>
 __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
 {
     constexpr int KS = ksteps(CI), NT = CO / 16, WC = wave_cols(CI, CO), NTW = NT / WC, WP = 4 / WC;
@@ -234,6 +249,8 @@ __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
                 const unsigned lo[4] = {fa[q].x, fa[q].y, fa[q].z, fa[q].w}, hi[4] = {fb[q].x, fb[q].y, fb[q].z, fb[q].w};
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
+                    // (dilated rows of 8 into rows of 8: the source's second half is padding, its place outside the patch)
+                    if (PAD && DILATE == 2 && (8 * xc + 2 * h) * 2 >= Wd) break;
                     dst[(2 * h) * step] = (lo[h] & 0xffffu) | (hi[h] << 16);
                     dst[(2 * h + 1) * step] = (lo[h] >> 16) | (hi[h] & 0xffff0000u);
                 }
@@ -323,13 +340,13 @@ __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
                         e_sc[t][2 * h] = bf2f((bf16_t)(d[h] & 0xffff));
                         e_sc[t][2 * h + 1] = bf2f((bf16_t)(d[h] >> 16));
                     }
-                } else if (!DGRAD) {   // block input at (2y, 2x): every second of 16 consecutive pixels
+                } else if (!DGRAD && (!PAD || y < a.Hr)) {   // block input at (2y, 2x): every second of 16 consecutive pixels
                     const bf16_t *sp = scT + (o * a.sc.H + 2 * y) * a.sc.W + 2 * x0;
                     const u32x4 v0 = *reinterpret_cast<const u32x4 *>(sp), v1 = *reinterpret_cast<const u32x4 *>(sp + 8);
                     const unsigned d[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
 #pragma unroll
                     for (int i = 0; i < 8; ++i) e_sc[t][i] = bf2f((bf16_t)(d[i] & 0xffff));
-                } else if (!(y & 1)) {   // delta of the block output lands on even pixels only
+                } else if (DGRAD && !(y & 1)) {   // delta of the block output lands on even pixels only
                     const u32x2 v = *reinterpret_cast<const u32x2 *>(scT + (o * a.sc.H + (y >> 1)) * a.sc.W + (x0 >> 1));
                     e_sc[t][0] = bf2f((bf16_t)(v.x & 0xffff));
                     e_sc[t][2] = bf2f((bf16_t)(v.x >> 16));
@@ -371,7 +388,8 @@ __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
                 }
                 r[i] = v;
             }
-            const u32x4 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3]), f2bf_pack(r[4], r[5]), f2bf_pack(r[6], r[7])};
+            u32x4 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3]), f2bf_pack(r[4], r[5]), f2bf_pack(r[6], r[7])};
+            if (!DGRAD && PAD) pk = keep_real(pk, o, y, x0, a.Cr, a.Hr, a.Wr);
             *reinterpret_cast<u32x4 *>(dstT + ((o * a.Hd + y) << lw) + x0) = pk;
             if (!DGRAD && signo) {
                 // from the stored bf16 values, so that both masks agree bit for bit; after the ReLU a value is
@@ -413,9 +431,10 @@ struct ConvBlockArgs {
     int H, W, lw, B;
     const float *X;
     i64 ld, b_off1, b_off2;
+    int Cr, Hr, Wr;                  // the real extents (PAD)
 };
 
-template <int C, int TH, int WMAX>   // WMAX: the widest image a launch may have (sizes the registers u waits in)
+template <int C, int TH, int WMAX, bool PAD>   // WMAX: the widest image a launch may have (sizes the registers u waits in); PAD: real extents below the stored ones
 __global__ void __launch_bounds__(256, C == 16 ? 7 : 1) conv_block_fwd_kernel(ConvBlockArgs a)   // 16 channels: the LDS lets 7 workgroups share a CU
 {
     constexpr int KS = ksteps(C), NT = C / 16, PP = C + 8;
@@ -585,6 +604,7 @@ __global__ void __launch_bounds__(256, C == 16 ? 7 : 1) conv_block_fwd_kernel(Co
                 }
                 u32x4 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3]), f2bf_pack(r[4], r[5]), f2bf_pack(r[6], r[7])};
                 if (!inside) pk = (u32x4){0u, 0u, 0u, 0u};   // a row outside the image is conv2's zero padding
+                if (PAD) pk = keep_real(pk, o, iy, x0, a.Cr, a.Hr, a.Wr);   // and so is what lies beyond the real extents
                 stash[it][t] = pk;
                 if (own) {
                     *reinterpret_cast<u32x4 *>(uT + ((o * H + iy) << lw) + x0) = pk;
@@ -680,7 +700,8 @@ __global__ void __launch_bounds__(256, C == 16 ? 7 : 1) conv_block_fwd_kernel(Co
                     v += bias;
                     r[i] = v > 0.f ? v : 0.f;
                 }
-                const u32x4 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3]), f2bf_pack(r[4], r[5]), f2bf_pack(r[6], r[7])};
+                u32x4 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3]), f2bf_pack(r[4], r[5]), f2bf_pack(r[6], r[7])};
+                if (PAD) pk = keep_real(pk, o, y, x0, a.Cr, a.Hr, a.Wr);
                 *reinterpret_cast<u32x4 *>(yT + ((o * H + y) << lw) + x0) = pk;
                 sign_lds[((q0 >> (lw + 3)) * C + o) * W + ((q0 & (band_px - 1)) >> 3)] = sign_bits(pk);
             }
@@ -705,7 +726,7 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 struct WgradReduceJob {
     const float *part;     // the conv's partial sums, [n][splits][psz]
     i64 w_off, b_off;      // where the conv's weights and its scalar bias sit in a worker's parameter vector
-    int splits, psz, tiles, ci_tiles, CIr;
+    int splits, psz, tiles, ci_tiles, CIr, COr;   // CIr, COr: the conv's real channels
     int block0;            // first blockIdx.x of this job
 };
 constexpr int kMaxReduceJobs = 48;
@@ -716,14 +737,14 @@ struct WgradReduceTable {
 static_assert(sizeof(WgradReduceTable) <= sizeof(WgradReduceList::table), "the caller's storage holds the job table");
 
 struct WgradMfmaArgs {
-    const bf16_t *inT;     // [n*B][CIr][H][W]
+    const bf16_t *inT;     // [n*B][CIs][H][W]
     const bf16_t *doutT;   // [n*B][CO][Ho][Wo]
-    int H, W, Ho, Wo, B, CIr, splits;
+    int H, W, Ho, Wo, B, CIs, splits;
     float *part;           // [n][splits][(CO/16)*(CI/16)*9*256 + 1], accumulator order
 };
 
 // 16-byte units of a band's source rows a thread holds while they are in flight (8-row bands: 10 rows at stride 1,
-// 17 at stride 2; 16-row bands, stride 1 only: 18 rows)
+// 17 at stride 2; 4-row bands: 6 and 9; 16-row bands, stride 1 only: 18 rows)
 __host__ __device__ constexpr int wgrad_stage(int stride, int rb) { return rb == 16 ? 5 : stride == 1 ? 3 : 5; }
 
 __host__ __device__ constexpr int wgrad_channel_pitch(int plane) { return (plane + 119) / 128 * 128 + 8; }
@@ -736,7 +757,7 @@ __host__ __device__ constexpr int wgrad_delta_ahead(int ci) { return ci <= 16 ? 
 // registers (one wave per SIMD); two groups of four waves split them instead.
 constexpr int wgrad_wave_groups(int ci, int co) { return (ci >= 64 && co >= 64) ? 2 : 1; }
 
-// RB: output rows per band, 8 or 16.  Every band costs a workgroup two barriers and the wait for what it requested a
+// RB: output rows per band, 4, 8 or 16.  Every band costs a workgroup two barriers and the wait for what it requested a
 // band earlier (the source rows and the delta operands, both in flight across the barriers); 16-row bands halve their
 // number where the image has them.
 template <int CI, int CO, int STRIDE, int RB>
@@ -775,6 +796,11 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
         u32x4 z = {0u, 0u, 0u, 0u};
         *reinterpret_cast<u32x4 *>(band + ci * CP + row * WPAD + (side ? 8 + a.Wo : 0)) = z;
     }
+    if (STRIDE == 2 && a.W < 2 * a.Wo)   // rows of 8 into rows of 8: staging fills half of each plane, the rest stays zero
+        for (int u = tid; u < CI * ROWS * PLANES; u += NT) {
+            const int row = u % (ROWS * PLANES), ci = u / (ROWS * PLANES);
+            *reinterpret_cast<u32x2 *>(band + ci * CP + row * WPAD + 8 + a.W / 2) = (u32x2){0u, 0u};
+        }
 
     const int x8n = a.W / 8;
     const int kb = RB * a.Wo / 32;   // k-steps per band
@@ -793,8 +819,8 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
             const int x8 = u % x8n, r = (u / x8n) % ROWS, ci = u / (x8n * ROWS);
             const int iy = y0 * STRIDE - 1 + r;
             u32x4 v = {0u, 0u, 0u, 0u};
-            if (u < chunks && ci < a.CIr && iy >= 0 && iy < a.H)
-                v = *reinterpret_cast<const u32x4 *>(a.inT + ((img * a.CIr + ci) * a.H + iy) * a.W + x8 * 8);
+            if (u < chunks && ci < a.CIs && iy >= 0 && iy < a.H)
+                v = *reinterpret_cast<const u32x4 *>(a.inT + ((img * a.CIs + ci) * a.H + iy) * a.W + x8 * 8);
             stg[q] = v;
         }
     };
@@ -979,16 +1005,18 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
     const int run = (jb.CIr - c0 < 16 ? jb.CIr - c0 : 16) * 9;   // floats of one c_out row that exist
     for (int e = tid; e < 16 * 144; e += 256) {
         const int ol = e / 144, r = e % 144;
-        if (r < run) G[(i64)w * ld + jb.w_off + ((i64)(o0 + ol) * jb.CIr + c0) * 9 + r] = tile[e];
+        if (r < run && o0 + ol < jb.COr) G[(i64)w * ld + jb.w_off + ((i64)(o0 + ol) * jb.CIr + c0) * 9 + r] = tile[e];
     }
 }
 
 // Workgroups that share one worker's minibatch (each writes a partial sum of the whole weight gradient): few when
-// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many.
-int wgrad_splits(int B, int co, int stride)
+// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many, and at least
+// enough for seven workgroups per eight CUs where the minibatch has that many images (112 workers x 2 are).
+int wgrad_splits(int n, int B, int co, int stride)
 {
     int m = co >= 64 ? 2 : (co >= 32 ? 4 : 8);
     if (stride == 2 && m < 8) m *= 2;
+    while ((i64)n * m < 224 && m < B) m *= 2;
     return B < m ? B : m;
 }
 
@@ -999,31 +1027,38 @@ size_t wgrad_lds_bytes(int ci, int stride, int rb, int Wo)
 
 // Output rows per band of the weight-gradient kernel: 16 at stride 1 and 32 or more channels where the image has them
 // and the band's source rows fit the staging registers and 64 KB of LDS (32 channels on 16 x 16 images: 45.3 -> 39.8
-// us), else 8 (with 16 channels the two more staging registers do not fit beside four workgroups per CU: 54.4 -> 55.9).
+// us), else 8 (with 16 channels the two more staging registers do not fit beside four workgroups per CU: 54.4 -> 55.9),
+// or 4 where the source rows of 8 do not fit (rows of 64 pixels at 16 channels, of 32 at 32 channels); 0: none fits.
 int wgrad_band_rows(const ConvDesc &c)
 {
-    const int cip = (c.Ci + 15) / 16 * 16;
-    if (c.stride == 1 && cip >= 32 && c.Ho % 16 == 0 && cip * 18 * (c.W / 8) <= wgrad_stage(1, 16) * 256 &&
-        wgrad_lds_bytes(cip, 1, 16, c.Wo) <= 64 * 1024)
-        return 16;
-    return 8;
+    const int cip = (c.Cis + 15) / 16 * 16;
+    const int threads = 256 * wgrad_wave_groups(cip, c.Cos);
+    for (int rb = (c.stride == 1 && cip >= 32) ? 16 : 8; rb >= 4; rb >>= 1)
+        if (c.Hos % rb == 0 && (rb * c.Wos) % 32 == 0 &&
+            cip * ((rb - 1) * c.stride + 3) * (c.Wis / 8) <= wgrad_stage(c.stride, rb) * threads &&
+            wgrad_lds_bytes(cip, c.stride, rb, c.Wos) <= 64 * 1024)
+            return rb;
+    return 0;
 }
+
+// Stored extents the strided convolutions take: rows and columns halve, except that rows of 8 pixels stay 8.
+bool halves(const ConvDesc &c) { return (c.Wis == 2 * c.Wos || (c.Wis == 8 && c.Wos == 8)) && c.His <= 2 * c.Hos; }
 
 bool wgrad_mfma_ok(const ConvDesc &c)
 {
-    const int cip = (c.Ci + 15) / 16 * 16;
-    if (!pow2_channels(c.Co) || !pow2_channels(cip)) return false;
-    if (c.Ho % 8 || c.Wo % 8 || c.W % 8 || c.W > 64) return false;
-    if (cip * (7 * c.stride + 3) * (c.W / 8) > wgrad_stage(c.stride, 8) * 256) return false;   // a band's source rows fit the staging registers
-    if (c.stride == 1) return cip == c.Co;
-    return c.stride == 2 && c.Co == 2 * c.Ci && c.Ci <= 32 && c.W == 2 * c.Wo && c.H == 2 * c.Ho;
+    const int cip = (c.Cis + 15) / 16 * 16;
+    if (!pow2_channels(c.Cos) || !pow2_channels(cip)) return false;
+    if (c.Hos % 8 || c.Wos % 8 || c.Wis % 8 || c.Wis > 64) return false;
+    if (wgrad_band_rows(c) == 0) return false;
+    if (c.stride == 1) return cip == c.Cos || (cip == 16 && c.Cos == 32);
+    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c);
 }
 
 template <int CI, int CO, int STRIDE>
 dpsgd_status launch_wgrad(dpsgd_ctx *ctx, const ConvDesc &c, const WgradMfmaArgs &a, WgradReduceJob *job)
 {
     constexpr int WM = (CO / 16) < 4 ? (CO / 16) : 4, WK = 4 / WM, WT = wgrad_wave_groups(CI, CO), NTI = CI / 16 / WT;
-    const int rb = STRIDE == 1 ? wgrad_band_rows(c) : 8;
+    const int rb = wgrad_band_rows(c);
     size_t shm = wgrad_lds_bytes(CI, STRIDE, rb, a.Wo);
     const size_t red = (size_t)(WK - 1) * WM * NTI * 9 * 256 * sizeof(float);
     if (red > shm) shm = red;
@@ -1031,13 +1066,12 @@ dpsgd_status launch_wgrad(dpsgd_ctx *ctx, const ConvDesc &c, const WgradMfmaArgs
     const dim3 grid((unsigned)a.splits, (unsigned)ctx->n), block(256 * WT);
     if constexpr (STRIDE == 1 && CI >= 32) {
         if (rb == 16) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 16>), grid, block, shm, ctx->stream, a);
-        else hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 8>), grid, block, shm, ctx->stream, a);
-    } else {
-        hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 8>), grid, block, shm, ctx->stream, a);
     }
+    if (rb == 8) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 8>), grid, block, shm, ctx->stream, a);
+    if (rb == 4) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 4>), grid, block, shm, ctx->stream, a);
     constexpr int tiles = (CO / 16) * (CI / 16), psz = tiles * 9 * 256 + 1;
     job->part = a.part; job->w_off = c.w_off; job->b_off = c.b_off; job->splits = a.splits; job->psz = psz;
-    job->tiles = tiles; job->ci_tiles = CI / 16; job->CIr = a.CIr; job->block0 = 0;
+    job->tiles = tiles; job->ci_tiles = CI / 16; job->CIr = c.Ci; job->COr = c.Co; job->block0 = 0;
     return hip_status(hipGetLastError());
 }
 
@@ -1050,23 +1084,22 @@ bool tile_ok(int Hd, int Wd, int stride, int ci)
 }
 
 // The stem (at most 8 input channels) runs on an image padded to 8 channels (NHWC8).
-bool stem_like(const ConvDesc &c) { return c.Ci <= 8 && c.Co == 16 && c.stride == 1; }
+bool stem_like(const ConvDesc &c) { return c.Ci <= 8 && c.Cis == c.Ci && (c.Cos == 16 || c.Cos == 32) && c.stride == 1; }
 
 bool fwd_mfma_ok(const ConvDesc &c)
 {
-    if (stem_like(c)) return tile_ok(c.Ho, c.Wo, 1, 8);
-    if (!pow2_channels(c.Ci) || !pow2_channels(c.Co) || (c.W % 8) != 0) return false;   // source rows in 16-byte units
-    if (c.stride == 1) return c.Ci == c.Co && tile_ok(c.Ho, c.Wo, 1, c.Ci);
-    return c.stride == 2 && c.Co == 2 * c.Ci && c.Ci <= 32 && tile_ok(c.Ho, c.Wo, 2, c.Ci);
+    if (stem_like(c)) return tile_ok(c.Hos, c.Wos, 1, 8);
+    if (!pow2_channels(c.Cis) || !pow2_channels(c.Cos) || (c.Wis % 8) != 0) return false;   // source rows in 16-byte units
+    if (c.stride == 1) return c.Cis == c.Cos && tile_ok(c.Hos, c.Wos, 1, c.Cis);
+    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c) && tile_ok(c.Hos, c.Wos, 2, c.Cis);
 }
 
 bool dgrad_mfma_ok(const ConvDesc &c)
 {
     if (stem_like(c)) return false;
-    if (!pow2_channels(c.Ci) || !pow2_channels(c.Co) || (c.Wo % 8) != 0) return false;
-    if (c.stride == 1) return c.Ci == c.Co && tile_ok(c.H, c.W, 1, c.Co);
-    return c.stride == 2 && c.Co == 2 * c.Ci && c.Ci <= 32 && c.H == 2 * c.Ho && c.W == 2 * c.Wo &&
-           tile_ok(c.H, c.W, 1, c.Co);
+    if (!pow2_channels(c.Cis) || !pow2_channels(c.Cos) || (c.Wos % 8) != 0) return false;
+    if (c.stride == 1) return c.Cis == c.Cos && tile_ok(c.His, c.Wis, 1, c.Cos);
+    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c) && tile_ok(c.His, c.Wis, 1, c.Cos);
 }
 
 // LDS of a workgroup that owns th output rows: the source patch and (forward) the bands' sign bitmap
@@ -1087,38 +1120,49 @@ int conv_band_rows(const dpsgd_ctx *ctx, int Hd, int Wd, int stride, int dilate,
 }
 
 template <int CI, int CO, int STRIDE, int DILATE, bool DGRAD>
-dpsgd_status launch_conv(dpsgd_ctx *ctx, const ConvMfmaArgs &a)
+dpsgd_status launch_conv(dpsgd_ctx *ctx, const ConvMfmaArgs &a, bool padded)
 {
     const int th = conv_band_rows(ctx, a.Hd, a.Wd, STRIDE, DILATE, CI, CO, DGRAD);
     const size_t shm = conv_lds_bytes(th, a.Wd, STRIDE, CI, CO, DGRAD);
     dim3 grid((unsigned)(a.Hd / th), (unsigned)a.B, (unsigned)ctx->n);
-    if (th == 16)
-        hipLaunchKernelGGL((conv3x3_mfma_kernel<CI, CO, STRIDE, DILATE, DGRAD, 16>), grid, dim3(256), shm, ctx->stream, a);
-    else
-        hipLaunchKernelGGL((conv3x3_mfma_kernel<CI, CO, STRIDE, DILATE, DGRAD, 8>), grid, dim3(256), shm, ctx->stream, a);
+#define DPSGD_CONV(TH, PAD) \
+    hipLaunchKernelGGL((conv3x3_mfma_kernel<CI, CO, STRIDE, DILATE, DGRAD, TH, PAD>), grid, dim3(256), shm, ctx->stream, a)
+    if constexpr (!DGRAD || DILATE == 2) {
+        if (padded) {
+            if (th == 16) DPSGD_CONV(16, true);
+            else DPSGD_CONV(8, true);
+            return hip_status(hipGetLastError());
+        }
+    }
+    if (th == 16) DPSGD_CONV(16, false);
+    else DPSGD_CONV(8, false);
+#undef DPSGD_CONV
     return hip_status(hipGetLastError());
 }
 
 }  // namespace
 
 namespace {
-// image [n*B][C][H][W] (fp32 or bf16) -> bf16 channel-major copy (fp32 input only) and NHWC8 copy
+// image [n*B][C][H][W] (fp32 or bf16) -> bf16 channel-major copy [n*B][C][Hs][Ws] and NHWC8 copy [n*B][Hs][Ws][8]
+// (either may be null), zero beyond H x W
 template <bool IN_BF16>
 __global__ void __launch_bounds__(256)
-prep_image_kernel(const void *__restrict__ in, int C, int HW, i64 total, bf16_t *__restrict__ chw, bf16_t *__restrict__ nhwc8)
+prep_image_kernel(const void *__restrict__ in, int C, int H, int W, int Hs, int Ws, i64 total, bf16_t *__restrict__ chw,
+                  bf16_t *__restrict__ nhwc8)
 {
-    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [img][pixel]
+    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [img][stored pixel]
     if (idx >= total) return;
-    const i64 img = idx / HW;
-    const int px = (int)(idx % HW);
+    const i64 img = idx / (Hs * Ws);
+    const int px = (int)(idx % (Hs * Ws)), y = px / Ws, x = px % Ws;
+    const bool real = y < H && x < W;
     bf16_t v[8];
 #pragma unroll
     for (int ch = 0; ch < 8; ++ch) {
         v[ch] = 0;
         if (ch < C) {
-            const i64 src = (img * C + ch) * HW + px;
-            v[ch] = IN_BF16 ? ((const bf16_t *)in)[src] : f2bf(((const float *)in)[src]);
-            if (!IN_BF16 && chw) chw[src] = v[ch];
+            const i64 src = ((img * C + ch) * H + y) * W + x;
+            if (real) v[ch] = IN_BF16 ? ((const bf16_t *)in)[src] : f2bf(((const float *)in)[src]);
+            if (chw) chw[(img * C + ch) * (Hs * Ws) + px] = v[ch];
         }
     }
     if (nhwc8) {
@@ -1139,14 +1183,14 @@ bool conv_forward_writes_sign(const ConvDesc &c, bool is_stem)
 dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const void *image, bool image_is_bf16,
                              bf16_t *chw_bf16, bf16_t *nhwc8)
 {
-    const i64 total = (i64)ctx->n * B * c.H * c.W;
+    const i64 total = (i64)ctx->n * B * c.His * c.Wis;
     if (c.Ci > 8 && nhwc8) return DPSGD_EUNSUPPORTED;
     if (image_is_bf16)
         hipLaunchKernelGGL(prep_image_kernel<true>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, ctx->stream, image,
-                           c.Ci, c.H * c.W, total, chw_bf16, nhwc8);
+                           c.Ci, c.H, c.W, c.His, c.Wis, total, chw_bf16, nhwc8);
     else
         hipLaunchKernelGGL(prep_image_kernel<false>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, ctx->stream, image,
-                           c.Ci, c.H * c.W, total, chw_bf16, nhwc8);
+                           c.Ci, c.H, c.W, c.His, c.Wis, total, chw_bf16, nhwc8);
     return hip_status(hipGetLastError());
 }
 
@@ -1154,15 +1198,15 @@ size_t conv_pack_bytes(const ConvDesc &c, bool dgrad)
 {
     const bool ok = dgrad ? dgrad_mfma_ok(c) : fwd_mfma_ok(c);
     if (!ok) return 0;
-    const int ci = dgrad ? c.Co : (stem_like(c) ? 8 : c.Ci), co = dgrad ? c.Ci : c.Co;
+    const int ci = dgrad ? c.Cos : (stem_like(c) ? 8 : c.Cis), co = dgrad ? c.Cis : c.Cos;
     return (size_t)ksteps(ci) * 32 * co * sizeof(bf16_t);
 }
 
-size_t conv_wgrad_partial_bytes(const ConvDesc &c, int B)
+size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
     if (!wgrad_mfma_ok(c)) return 0;
-    const size_t cip = (size_t)(c.Ci + 15) / 16 * 16;   // partials are stored per 16 x 16 tile of (c_out, padded c_in)
-    return (size_t)wgrad_splits(B, c.Co, c.stride) * ((size_t)c.Co * cip * 9 + 1) * sizeof(float);
+    const size_t cip = (size_t)(c.Cis + 15) / 16 * 16;   // partials are stored per 16 x 16 tile of (c_out, padded c_in)
+    return (size_t)wgrad_splits(ctx->n, B, c.Cos, c.stride) * ((size_t)c.Cos * cip * 9 + 1) * sizeof(float);
 }
 
 dpsgd_status conv_pack_weights(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, const float *X,
@@ -1186,8 +1230,8 @@ dpsgd_status conv_pack_weights(dpsgd_ctx *ctx, const std::vector<ConvDesc> &conv
     };
     for (size_t q = 0; q < convs.size(); ++q) {
         const ConvDesc &c = convs[q];
-        if (fwd_mfma_ok(c)) add(c, stem_like(c) ? 8 : c.Ci, c.Co, false, wpack_f[q]);
-        if (!stem_like(c) && dgrad_mfma_ok(c)) add(c, c.Co, c.Ci, true, wpack_d[q]);
+        if (fwd_mfma_ok(c)) add(c, stem_like(c) ? 8 : c.Cis, c.Cos, false, wpack_f[q]);
+        if (!stem_like(c) && dgrad_mfma_ok(c)) add(c, c.Cos, c.Cis, true, wpack_d[q]);
     }
     flush();
     return hip_status(hipGetLastError());
@@ -1198,18 +1242,20 @@ dpsgd_status conv_forward(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, c
 {
     if (!fwd_mfma_ok(c)) return conv_forward_generic(ctx, c, B, in, X, sc, out);
     ConvMfmaArgs a{};
-    a.src = in.t; a.Hs = c.H; a.Ws = c.W; a.wpack = wpack; a.dstT = out.t; a.Hd = c.Ho; a.Wd = c.Wo;
+    a.src = in.t; a.Hs = c.His; a.Ws = c.Wis; a.wpack = wpack; a.dstT = out.t; a.Hd = c.Hos; a.Wd = c.Wos;
+    a.Cr = c.Co; a.Hr = c.Ho; a.Wr = c.Wo;
     a.B = B; a.X = X; a.ld = ctx->ld; a.b_off = c.b_off; a.sc = sc; a.actT = nullptr;
     a.sign_in = nullptr; a.sign_out = out.sign;
     a.lw = ilog2(a.Wd);
-    if (stem_like(c)) return launch_conv<8, 16, 1, 1, false>(ctx, a);   // `in` is the image padded to 8 channels
+    if (stem_like(c))   // `in` is the image padded to 8 channels
+        return c.Cos == 16 ? launch_conv<8, 16, 1, 1, false>(ctx, a, c.padded_out()) : launch_conv<8, 32, 1, 1, false>(ctx, a, c.padded_out());
     if (c.stride == 1) {
-        if (c.Ci == 16) return launch_conv<16, 16, 1, 1, false>(ctx, a);
-        if (c.Ci == 32) return launch_conv<32, 32, 1, 1, false>(ctx, a);
-        return launch_conv<64, 64, 1, 1, false>(ctx, a);
+        if (c.Cis == 16) return launch_conv<16, 16, 1, 1, false>(ctx, a, c.padded_out());
+        if (c.Cis == 32) return launch_conv<32, 32, 1, 1, false>(ctx, a, c.padded_out());
+        return launch_conv<64, 64, 1, 1, false>(ctx, a, c.padded_out());
     }
-    if (c.Ci == 16) return launch_conv<16, 32, 2, 1, false>(ctx, a);
-    return launch_conv<32, 64, 2, 1, false>(ctx, a);
+    if (c.Cis == 16) return launch_conv<16, 32, 2, 1, false>(ctx, a, c.padded_out());
+    return launch_conv<32, 64, 2, 1, false>(ctx, a, c.padded_out());
 }
 
 namespace {
@@ -1223,19 +1269,20 @@ size_t conv_block_lds_bytes(int C, int W, int th)
 // 16 channels: bands of kBlockRows rows.  32 channels: only images of 16 x 16 pixels, as one band - no row of u is then
 // computed twice (in 8-row bands the launch took 84.7 us against the 81.6 us of the two launches it replaces).
 // 64 channels: images of 8 x 8 pixels, one band.
-int conv_block_rows(const ConvDesc &c) { return c.Co == 16 ? kBlockRows : c.Co == 32 ? 16 : 8; }
+int conv_block_rows(const ConvDesc &c) { return c.Cos == 16 ? kBlockRows : c.Cos == 32 ? 16 : 8; }
 }  // namespace
 
 bool conv_block_forward_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2)
 {
     if (!ctx->opt_conv_block) return false;
     if (c1.stride != 1 || c2.stride != 1 || c1.Ci != c1.Co || c2.Ci != c1.Co || c2.Co != c1.Co) return false;
-    if (!pow2_channels(c1.Co) || !fwd_mfma_ok(c1) || !fwd_mfma_ok(c2)) return false;
-    if (c1.H != c2.H || c1.W != c2.W) return false;
-    if (c1.Co == 16 && (c1.H % kBlockRows || !(c1.W == 16 || c1.W == 32))) return false;
-    if (c1.Co == 32 && !(c1.H == 16 && c1.W == 16)) return false;
-    if (c1.Co == 64 && !(c1.H == 8 && c1.W == 8)) return false;
-    return conv_block_lds_bytes(c1.Co, c1.W, conv_block_rows(c1)) <= 64 * 1024;
+    if (c1.Cis != c1.Cos || c2.Cis != c1.Cos || c2.Cos != c1.Cos) return false;
+    if (!pow2_channels(c1.Cos) || !fwd_mfma_ok(c1) || !fwd_mfma_ok(c2)) return false;
+    if (c1.His != c2.His || c1.Wis != c2.Wis) return false;
+    if (c1.Cos == 16 && (c1.His % kBlockRows || !(c1.Wis == 16 || c1.Wis == 32))) return false;
+    if (c1.Cos == 32 && !(c1.His == 16 && c1.Wis == 16)) return false;
+    if (c1.Cos == 64 && !(c1.His == 8 && c1.Wis == 8)) return false;
+    return conv_block_lds_bytes(c1.Cos, c1.Wis, conv_block_rows(c1)) <= 64 * 1024;
 }
 
 dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B, Tensor in, const float *X,
@@ -1244,13 +1291,22 @@ dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDe
     if (!conv_block_forward_ok(ctx, c1, c2) || !u.sign || !out.sign) return DPSGD_EUNSUPPORTED;
     ConvBlockArgs a{};
     a.src = in.t; a.wpack1 = wpack1; a.wpack2 = wpack2; a.uT = u.t; a.yT = out.t; a.usign = u.sign; a.ysign = out.sign;
-    a.H = c1.H; a.W = c1.W; a.lw = ilog2(c1.W); a.B = B; a.X = X; a.ld = ctx->ld; a.b_off1 = c1.b_off; a.b_off2 = c2.b_off;
+    a.H = c1.His; a.W = c1.Wis; a.lw = ilog2(c1.Wis); a.B = B; a.X = X; a.ld = ctx->ld; a.b_off1 = c1.b_off; a.b_off2 = c2.b_off;
+    a.Cr = c1.Co; a.Hr = c1.Ho; a.Wr = c1.Wo;
     const int th = conv_block_rows(c1);
-    const size_t shm = conv_block_lds_bytes(c1.Co, c1.W, th);
-    const dim3 grid((unsigned)(c1.H / th), (unsigned)B, (unsigned)ctx->n);
-    if (c1.Co == 16) hipLaunchKernelGGL((conv_block_fwd_kernel<16, kBlockRows, 32>), grid, dim3(256), shm, ctx->stream, a);
-    else if (c1.Co == 32) hipLaunchKernelGGL((conv_block_fwd_kernel<32, 16, 16>), grid, dim3(256), shm, ctx->stream, a);
-    else hipLaunchKernelGGL((conv_block_fwd_kernel<64, 8, 8>), grid, dim3(256), shm, ctx->stream, a);
+    const size_t shm = conv_block_lds_bytes(c1.Cos, c1.Wis, th);
+    const dim3 grid((unsigned)(c1.His / th), (unsigned)B, (unsigned)ctx->n);
+#define DPSGD_BLOCK(C, TH, WMAX)                                                                                      \
+    do {                                                                                                               \
+        if (c1.padded_out())                                                                                           \
+            hipLaunchKernelGGL((conv_block_fwd_kernel<C, TH, WMAX, true>), grid, dim3(256), shm, ctx->stream, a);      \
+        else                                                                                                           \
+            hipLaunchKernelGGL((conv_block_fwd_kernel<C, TH, WMAX, false>), grid, dim3(256), shm, ctx->stream, a);     \
+    } while (0)
+    if (c1.Cos == 16) DPSGD_BLOCK(16, kBlockRows, 32);
+    else if (c1.Cos == 32) DPSGD_BLOCK(32, 16, 16);
+    else DPSGD_BLOCK(64, 8, 8);
+#undef DPSGD_BLOCK
     return hip_status(hipGetLastError());
 }
 
@@ -1259,17 +1315,17 @@ dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dou
 {
     if (!dgrad_mfma_ok(c)) return conv_data_grad_generic(ctx, c, B, dout, X, scd, act, din);
     ConvMfmaArgs a{};
-    a.src = dout.t; a.Hs = c.Ho; a.Ws = c.Wo; a.wpack = wpack_d; a.dstT = din.t; a.Hd = c.H; a.Wd = c.W;
+    a.src = dout.t; a.Hs = c.Hos; a.Ws = c.Wos; a.wpack = wpack_d; a.dstT = din.t; a.Hd = c.His; a.Wd = c.Wis;
     a.B = B; a.X = X; a.ld = ctx->ld; a.b_off = 0; a.sc = scd; a.actT = act.t;
     a.sign_in = act.sign; a.sign_out = nullptr;
     a.lw = ilog2(a.Wd);
     if (c.stride == 1) {
-        if (c.Ci == 16) return launch_conv<16, 16, 1, 1, true>(ctx, a);
-        if (c.Ci == 32) return launch_conv<32, 32, 1, 1, true>(ctx, a);
-        return launch_conv<64, 64, 1, 1, true>(ctx, a);
+        if (c.Cis == 16) return launch_conv<16, 16, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
+        if (c.Cis == 32) return launch_conv<32, 32, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
+        return launch_conv<64, 64, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
     }
-    if (c.Ci == 16) return launch_conv<32, 16, 1, 2, true>(ctx, a);
-    return launch_conv<64, 32, 1, 2, true>(ctx, a);
+    if (c.Cis == 16) return launch_conv<32, 16, 1, 2, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
+    return launch_conv<64, 32, 1, 2, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
 }
 
 dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, Tensor dout, float *G, float *partials,
@@ -1281,13 +1337,14 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
         if (st != DPSGD_OK) return st;
     }
     WgradMfmaArgs a{};
-    a.inT = in.t; a.doutT = dout.t; a.H = c.H; a.W = c.W; a.Ho = c.Ho; a.Wo = c.Wo; a.B = B; a.CIr = c.Ci;
-    a.splits = wgrad_splits(B, c.Co, c.stride); a.part = partials;
-    const int cip = (c.Ci + 15) / 16 * 16;
+    a.inT = in.t; a.doutT = dout.t; a.H = c.His; a.W = c.Wis; a.Ho = c.Hos; a.Wo = c.Wos; a.B = B; a.CIs = c.Cis;
+    a.splits = wgrad_splits(ctx->n, B, c.Cos, c.stride); a.part = partials;
+    const int cip = (c.Cis + 15) / 16 * 16;
     WgradReduceJob job{};
     dpsgd_status st;
     if (c.stride == 1) {
-        if (cip == 16) st = launch_wgrad<16, 16, 1>(ctx, c, a, &job);
+        if (cip == 16 && c.Cos == 32) st = launch_wgrad<16, 32, 1>(ctx, c, a, &job);
+        else if (cip == 16) st = launch_wgrad<16, 16, 1>(ctx, c, a, &job);
         else if (cip == 32) st = launch_wgrad<32, 32, 1>(ctx, c, a, &job);
         else st = launch_wgrad<64, 64, 1>(ctx, c, a, &job);
     } else if (cip == 16) {

@@ -54,6 +54,8 @@ struct dpsgd_ctx {
     int32_t opt_conv_block = 1;     // CNN forward: the two convolutions of a resolution-keeping residual block in one launch
     int32_t opt_fused_slab = 1;     // dpsgd_step, bf16 MLP, W without a walk kernel, n <= 64: every worker's tile in LDS (2: also for the torus)
     int32_t opt_class_bwd = 1;      // bf16 MLP: backward of a class layer of at most 16 outputs in one launch
+    int32_t opt_conv_pad = 1;       // CNN: stages of other extents stored rounded up to a shape the MFMA kernels take
+    bool conv_pad_off = false;      // ... not for the current model: its workspace did not fit the device that way
     int32_t opt_conv_band_rows = 0; // output rows per workgroup of the MFMA convolutions: 8, 16, or 0 = chosen per convolution
     std::vector<hipEvent_t> ev;   // pairs (start, stop)
     int64_t ev_pairs = 0, ev_launches = 0;

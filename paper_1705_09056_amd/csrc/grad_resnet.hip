@@ -21,7 +21,7 @@ namespace {
 typedef long long i64;
 
 // ------------------------------------------------------------------------------ forward
-// IN_FP32: the source is the fp32 image (rounded on load), else a bf16 tensor; both channel-major.
+// IN_FP32: the source is the fp32 image (rounded on load), else a bf16 tensor; both channel-major, stored as c says.
 template <bool IN_FP32>
 __global__ void __launch_bounds__(256)
 conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X, i64 ld, ConvDesc c, int B, i64 total,
@@ -30,11 +30,15 @@ conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X
     const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][co][y][x]
     if (idx >= total) return;
     i64 t = idx;
-    const int x = (int)(t % c.Wo); t /= c.Wo;
-    const int y = (int)(t % c.Ho); t /= c.Ho;
-    const int co = (int)(t % c.Co); t /= c.Co;
+    const int x = (int)(t % c.Wos); t /= c.Wos;
+    const int y = (int)(t % c.Hos); t /= c.Hos;
+    const int co = (int)(t % c.Cos); t /= c.Cos;
     const int b = (int)(t % B);
     const int w = (int)(t / B);
+    if (x >= c.Wo || y >= c.Ho || co >= c.Co) {   // beyond the real extent
+        out[idx] = 0;
+        return;
+    }
     const float *Wg = X + (i64)w * ld + c.w_off + (i64)co * c.Ci * 9;
     float acc = 0.f;
     for (int ci = 0; ci < c.Ci; ++ci)
@@ -44,7 +48,7 @@ conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X
             for (int kx = 0; kx < 3; ++kx) {
                 const int ix = x * c.stride + kx - 1;
                 if (ix < 0 || ix >= c.W) continue;
-                const i64 src = ((((i64)w * B + b) * c.Ci + ci) * c.H + iy) * c.W + ix;
+                const i64 src = ((((i64)w * B + b) * c.Cis + ci) * c.His + iy) * c.Wis + ix;
                 const float v = IN_FP32 ? bf2f(f2bf(((const float *)in)[src])) : bf2f(((const bf16_t *)in)[src]);
                 acc = v * bf2f(f2bf(Wg[(ci * 3 + ky) * 3 + kx])) + acc;
             }
@@ -66,11 +70,15 @@ conv_dgrad_generic_kernel(const bf16_t *__restrict__ dout, const float *__restri
     const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][ci][iy][ix]
     if (idx >= total) return;
     i64 t = idx;
-    const int ix = (int)(t % c.W); t /= c.W;
-    const int iy = (int)(t % c.H); t /= c.H;
-    const int ci = (int)(t % c.Ci); t /= c.Ci;
+    const int ix = (int)(t % c.Wis); t /= c.Wis;
+    const int iy = (int)(t % c.His); t /= c.His;
+    const int ci = (int)(t % c.Cis); t /= c.Cis;
     const int b = (int)(t % B);
     const int w = (int)(t / B);
+    if (ix >= c.W || iy >= c.H || ci >= c.Ci) {   // beyond the real extent
+        din[idx] = 0;
+        return;
+    }
     const float *Wg = X + (i64)w * ld + c.w_off;
     float acc = 0.f;
     for (int ky = 0; ky < 3; ++ky) {
@@ -83,9 +91,9 @@ conv_dgrad_generic_kernel(const bf16_t *__restrict__ dout, const float *__restri
             if (tx < 0 || tx % c.stride) continue;
             const int ox = tx / c.stride;
             if (ox >= c.Wo) continue;
-            const bf16_t *dp = dout + ((i64)w * B + b) * c.Co * c.Ho * c.Wo + (i64)oy * c.Wo + ox;
+            const bf16_t *dp = dout + ((i64)w * B + b) * c.Cos * c.Hos * c.Wos + (i64)oy * c.Wos + ox;
             for (int co = 0; co < c.Co; ++co)
-                acc = bf2f(dp[(i64)co * c.Ho * c.Wo]) * bf2f(f2bf(Wg[(((i64)co * c.Ci + ci) * 3 + ky) * 3 + kx])) + acc;
+                acc = bf2f(dp[(i64)co * c.Hos * c.Wos]) * bf2f(f2bf(Wg[(((i64)co * c.Ci + ci) * 3 + ky) * 3 + kx])) + acc;
         }
     }
     if (scd && (iy % scS) == 0 && (ix % scS) == 0 && iy / scS < scH && ix / scS < scW)
@@ -109,7 +117,7 @@ conv_wgrad_generic_kernel(const void *__restrict__ in, const bf16_t *__restrict_
     const int npix = B * c.Ho * c.Wo;
     for (int p = threadIdx.x; p < npix; p += 256) {
         const int x = p % c.Wo, y = (p / c.Wo) % c.Ho, b = p / (c.Wo * c.Ho);
-        const float go = bf2f(dout[((((i64)w * B + b) * c.Co + co) * c.Ho + y) * c.Wo + x]);
+        const float go = bf2f(dout[((((i64)w * B + b) * c.Cos + co) * c.Hos + y) * c.Wos + x]);
         if (go == 0.f) continue;
 #pragma unroll
         for (int ky = 0; ky < 3; ++ky) {
@@ -119,7 +127,7 @@ conv_wgrad_generic_kernel(const void *__restrict__ in, const bf16_t *__restrict_
             for (int kx = 0; kx < 3; ++kx) {
                 const int ix = x * c.stride + kx - 1;
                 if (ix < 0 || ix >= c.W) continue;
-                const i64 src = ((((i64)w * B + b) * c.Ci + ci) * c.H + iy) * c.W + ix;
+                const i64 src = ((((i64)w * B + b) * c.Cis + ci) * c.His + iy) * c.Wis + ix;
                 const float v = IN_FP32 ? bf2f(f2bf(((const float *)in)[src])) : bf2f(((const bf16_t *)in)[src]);
                 acc[ky * 3 + kx] = go * v + acc[ky * 3 + kx];
             }
@@ -161,13 +169,14 @@ sum_delta_kernel(const bf16_t *__restrict__ d, i64 count, float *__restrict__ G,
 }
 
 // ------------------------------------------------------------ head: pool, FC, loss, FC grads
-// Global average pool: a [n*B*C][HW] bf16 -> pool [n*B*C] fp32, one thread per (image, channel), pixels in order.
+// Global average pool: a [n*B][Cs][HW] bf16 (stored extents) -> pool [n*B][C] fp32, one thread per (image, channel),
+// pixels in order; inv = 1 / (real pixels).
 __global__ void __launch_bounds__(256)
-pool_fwd_kernel(const bf16_t *__restrict__ a, int HW, i64 total, float *__restrict__ pool)
+pool_fwd_kernel(const bf16_t *__restrict__ a, int HW, int C, int Cs, float inv, i64 total, float *__restrict__ pool)
 {
     const i64 e = (i64)blockIdx.x * 256 + threadIdx.x;
     if (e >= total) return;
-    const bf16_t *p = a + e * HW;
+    const bf16_t *p = a + (Cs == C ? e : e / C * Cs + e % C) * HW;
     float s = 0.f;
     int t = 0;
     if ((HW & 7) == 0)
@@ -179,7 +188,7 @@ pool_fwd_kernel(const bf16_t *__restrict__ a, int HW, i64 total, float *__restri
             s += bf2f((bf16_t)(v.w & 0xffff)); s += bf2f((bf16_t)(v.w >> 16));
         }
     for (; t < HW; ++t) s += bf2f(p[t]);
-    pool[e] = s * (1.0f / (float)HW);
+    pool[e] = s * inv;
 }
 
 // One workgroup per worker.  pool / dpool: [n][B][C] fp32, z: [n][B][K] fp32.
@@ -256,23 +265,32 @@ head_kernel(const float *__restrict__ X, i64 ld, i64 fcw_off, i64 fcb_off, int B
     }
 }
 
-// dv[w][b][c][t] = round([a > 0] * dpool[w][b][c])   (dpool already divided by H*W)
+// dv[w][b][c][t] = round([a > 0] * dpool[w][b][c])   (dpool already divided by H*W; a is zero beyond the real extents)
+__device__ __forceinline__ float pooled_delta(const float *dpool, i64 plane, int C, int Cs)
+{
+    if (Cs == C) return dpool[plane];
+    const int ch = (int)(plane % Cs);
+    return ch < C ? dpool[plane / Cs * C + ch] : 0.f;
+}
+
 __global__ void __launch_bounds__(256)
-pool_bwd_kernel(const bf16_t *__restrict__ a, const float *__restrict__ dpool, int HW, i64 total, bf16_t *__restrict__ dv)
+pool_bwd_kernel(const bf16_t *__restrict__ a, const float *__restrict__ dpool, int HW, int C, int Cs, i64 total,
+                bf16_t *__restrict__ dv)
 {
     const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w*b][c][t]
     if (idx >= total) return;
-    dv[idx] = bf16_positive(a[idx]) ? f2bf(dpool[idx / HW]) : (bf16_t)0;
+    dv[idx] = bf16_positive(a[idx]) ? f2bf(pooled_delta(dpool, idx / HW, C, Cs)) : (bf16_t)0;
 }
 
 // The same for HW % 8 == 0: a thread takes 8 pixels of one (image, channel) plane, 16 bytes in and out.
 __global__ void __launch_bounds__(256)
-pool_bwd_vec_kernel(const bf16_t *__restrict__ a, const float *__restrict__ dpool, int HW, i64 total8, bf16_t *__restrict__ dv)
+pool_bwd_vec_kernel(const bf16_t *__restrict__ a, const float *__restrict__ dpool, int HW, int C, int Cs, i64 total8,
+                    bf16_t *__restrict__ dv)
 {
     const i64 u = (i64)blockIdx.x * 256 + threadIdx.x;   // over 16-byte units of [w*b][c][t]
     if (u >= total8) return;
     const uint4 v = *reinterpret_cast<const uint4 *>(a + u * 8);
-    const unsigned d = f2bf(dpool[(u * 8) / HW]);
+    const unsigned d = f2bf(pooled_delta(dpool, (u * 8) / HW, C, Cs));
     const unsigned in[4] = {v.x, v.y, v.z, v.w};
     unsigned out[4];
 #pragma unroll
@@ -285,35 +303,63 @@ unsigned blocks_for(i64 total) { return (unsigned)((total + 255) / 256); }
 
 }  // namespace
 
-ResnetPlan make_resnet_plan(const dpsgd_model_desc &m)
+// Stored extents of a stage's tensors.  The MFMA kernels take 16, 32 or 64 channels, rows of 8, 16, 32 or 64 pixels and
+// a multiple of 8 rows; a stage of other extents is stored rounded up to the next such shape, with zeros beyond its
+// real extents, instead of leaving it to the shape-generic kernels, which are slower by far more than the padding costs:
+// 16 workers x 32 images of 1 x 28 x 28, 16 channels, 2 blocks per stage (stored 32 x 32, 16 x 16 and 8 x 8) take 0.56 ms
+// per iteration instead of 15.4.  Channels double from stage to stage, so a base of up to 16 channels is
+// stored as 16 / 32 / 64, up to 32 as 32 / 64, up to 64 as 64; wider stages and rows of more than 64 pixels keep their
+// real extents.  So does a network whose first stage would take more than 16 times its memory (tiny images or channels).
+namespace {
+struct Extent { int C, H, W; };
+Extent stored_stage(int stage, int base, int C, int H, int W)
+{
+    const int cs = (base <= 16 ? 16 : base <= 32 ? 32 : 64) << stage;
+    if (cs > 64 || C > cs || W > 64) return {C, H, W};
+    const int ws = W <= 8 ? 8 : W <= 16 ? 16 : W <= 32 ? 32 : 64;
+    return {cs, (H + 7) / 8 * 8, ws};
+}
+}  // namespace
+
+ResnetPlan make_resnet_plan(const dpsgd_model_desc &m, bool pad)
 {
     ResnetPlan p;
     const int cin = m.widths[0], H0 = m.widths[1], W0 = m.widths[2], base = m.widths[3], blocks = m.widths[4];
     p.classes = m.widths[5];
+    if (pad) {
+        const Extent e = stored_stage(0, base, base, H0, W0);
+        pad = (i64)e.C * e.H * e.W <= 16 * ((i64)base * H0 * W0);
+    }
+    auto stored = [&](int s, int C, int h, int w) { return pad ? stored_stage(s, base, C, h, w) : Extent{C, h, w}; };
     auto out_dim = [](int h, int s) { return (h + 2 - 3) / s + 1; };
     i64 off = 0;
     int H = H0, W = W0, cprev = base;
-    auto add = [&](int Ci, int Co, int h, int w, int s) {
+    auto add = [&](int Ci, int Co, int h, int w, int s, const Extent &in, const Extent &out) {
         ConvDesc c;
         c.Ci = Ci; c.Co = Co; c.H = h; c.W = w; c.stride = s; c.Ho = out_dim(h, s); c.Wo = out_dim(w, s);
+        c.Cis = in.C; c.His = in.H; c.Wis = in.W; c.Cos = out.C; c.Hos = out.H; c.Wos = out.W;
         c.w_off = off; off += (i64)Co * Ci * 9;
         c.b_off = off; off += 1;
         p.convs.push_back(c);
     };
-    add(cin, base, H, W, 1);
+    Extent cur = stored(0, base, H, W);
+    add(cin, base, H, W, 1, Extent{cin, cur.H, cur.W}, cur);
     for (int s = 0; s < 3; ++s) {
         const int c = base << s;
         for (int j = 0; j < blocks; ++j) {
             const int stride = (s > 0 && j == 0) ? 2 : 1;
-            add(cprev, c, H, W, stride);
+            const Extent next = stored(s, c, out_dim(H, stride), out_dim(W, stride));
+            add(cprev, c, H, W, stride, cur, next);
             H = out_dim(H, stride); W = out_dim(W, stride);
-            add(c, c, H, W, 1);
+            add(c, c, H, W, 1, next, next);
             cprev = c;
+            cur = next;
         }
     }
     p.fcw_off = off; off += (i64)p.classes * cprev;
     p.fcb_off = off;
     p.C_last = cprev; p.H_last = H; p.W_last = W;
+    p.Cs_last = cur.C; p.Hs_last = cur.H; p.Ws_last = cur.W;
     p.nblocks = 3 * blocks;
     return p;
 }
@@ -325,7 +371,7 @@ struct Workspace {
     std::vector<Tensor> out;              // output of every conv: out[0] = a_0, out[1+2j] = u_j, out[2+2j] = a_{j+1}
     Tensor delta[3];                      // rotating delta buffers
     std::vector<bf16_t *> wpack_f, wpack_d;
-    bf16_t *image_bf16 = nullptr;         // bf16 copy of an fp32 image (channel-major, as given)
+    bf16_t *image_bf16 = nullptr;         // bf16 copy of the image, channel-major (MFMA stem: fp32 images, padded extents)
     bf16_t *image_nhwc8 = nullptr;        // image padded to 8 channels, pixel-major (MFMA stem only)
     float *pool = nullptr, *dpool = nullptr, *logits = nullptr;
     std::vector<float *> partials;        // per conv: the partial sums of its weight gradient
@@ -345,7 +391,7 @@ Workspace carve(const dpsgd_ctx *ctx, const dpsgd_model_desc &m, const ResnetPla
     size_t biggest = 0;
     std::vector<size_t> part;
     for (const ConvDesc &c : p.convs) {
-        const size_t e = nB * c.Ho * c.Wo * c.Co;
+        const size_t e = nB * c.Hos * c.Wos * c.Cos;
         Tensor t;
         t.t = (bf16_t *)take(e * 2);
         if (conv_forward_writes_sign(c, w.out.empty())) t.sign = (unsigned char *)take(e / 8);
@@ -353,11 +399,15 @@ Workspace carve(const dpsgd_ctx *ctx, const dpsgd_model_desc &m, const ResnetPla
         biggest = e > biggest ? e : biggest;
         w.wpack_f.push_back((bf16_t *)take(conv_pack_bytes(c, false) * ctx->n));
         w.wpack_d.push_back((bf16_t *)take(conv_pack_bytes(c, true) * ctx->n));
-        part.push_back(conv_wgrad_partial_bytes(c, m.batch) * ctx->n);
+        part.push_back(conv_wgrad_partial_bytes(ctx, c, m.batch) * ctx->n);
     }
     for (int i = 0; i < 3; ++i) w.delta[i].t = (bf16_t *)take(biggest * 2);
-    if (!m.input_is_bf16) w.image_bf16 = (bf16_t *)take(nB * p.convs[0].Ci * p.convs[0].H * p.convs[0].W * 2);
-    if (conv_stem_uses_mfma(p.convs[0])) w.image_nhwc8 = (bf16_t *)take(nB * p.convs[0].H * p.convs[0].W * 8 * 2);
+    const ConvDesc &stem = p.convs[0];
+    if (conv_stem_uses_mfma(stem)) {
+        if (!m.input_is_bf16 || stem.His != stem.H || stem.Wis != stem.W)
+            w.image_bf16 = (bf16_t *)take(nB * stem.Ci * stem.His * stem.Wis * 2);
+        w.image_nhwc8 = (bf16_t *)take(nB * stem.His * stem.Wis * 8 * 2);
+    }
     w.pool = (float *)take(nB * p.C_last * 4);
     w.dpool = (float *)take(nB * p.C_last * 4);
     w.logits = (float *)take(nB * p.classes * 4);
@@ -369,7 +419,7 @@ Workspace carve(const dpsgd_ctx *ctx, const dpsgd_model_desc &m, const ResnetPla
 
 size_t resnet_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m)
 {
-    const ResnetPlan p = make_resnet_plan(m);
+    const ResnetPlan p = make_resnet_plan(m, ctx->opt_conv_pad && !ctx->conv_pad_off);
     return carve(ctx, m, p, nullptr).bytes;
 }
 
@@ -377,7 +427,7 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
                                 const void *targets, float *G, float *loss)
 {
     hipStream_t s = ctx->stream;
-    const ResnetPlan p = make_resnet_plan(m);
+    const ResnetPlan p = make_resnet_plan(m, ctx->opt_conv_pad && !ctx->conv_pad_off);
     const int n = ctx->n, B = m.batch;
     const i64 nB = (i64)n * B;
     if (n > 65535 || B > 65535) return DPSGD_EUNSUPPORTED;
@@ -395,7 +445,9 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     // ---- forward
     const bool stem_mfma = conv_stem_uses_mfma(p.convs[0]);
     // the image as bf16, channel-major (what the stem's weight gradient contracts over)
-    const bf16_t *image_chw = m.input_is_bf16 ? (const bf16_t *)inputs : ws.image_bf16;
+    const bf16_t *image_chw = ws.image_bf16 ? ws.image_bf16 : (const bf16_t *)inputs;
+    ConvDesc stem_raw = p.convs[0];   // the generic stem reads the caller's image as it is
+    stem_raw.His = stem_raw.H; stem_raw.Wis = stem_raw.W;
     if (stem_mfma) {
         const ConvDesc &c = p.convs[0];
         if ((st = conv_prep_image(ctx, c, B, inputs, m.input_is_bf16, ws.image_bf16, ws.image_nhwc8)) != DPSGD_OK) return st;
@@ -403,8 +455,8 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         img8.t = ws.image_nhwc8;
         if ((st = conv_forward(ctx, c, B, img8, X, ws.wpack_f[0], none, ws.out[0])) != DPSGD_OK) return st;
     } else {
-        const ConvDesc &c = p.convs[0];
-        const i64 total = nB * c.Ho * c.Wo * c.Co;
+        const ConvDesc &c = stem_raw;
+        const i64 total = nB * c.Hos * c.Wos * c.Cos;
         if (m.input_is_bf16)
             hipLaunchKernelGGL(conv_fwd_generic_kernel<false>, dim3(blocks_for(total)), dim3(256), 0, s, inputs, X, ctx->ld,
                                c, B, total, nullptr, 0, 0, 0, 1, ws.out[0].t);
@@ -421,12 +473,12 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
             continue;
         }
         if ((st = conv_forward(ctx, c1, B, a_of(j), X, ws.wpack_f[1 + 2 * j], none, u_of(j))) != DPSGD_OK) return st;
-        const ShortcutRef sc{a_of(j).t, c1.Ci, c1.H, c1.W, c1.stride};
+        const ShortcutRef sc{a_of(j).t, c1.Cis, c1.His, c1.Wis, c1.stride};
         if ((st = conv_forward(ctx, c2, B, u_of(j), X, ws.wpack_f[2 + 2 * j], sc, a_of(j + 1))) != DPSGD_OK) return st;
     }
-    const int HWl = p.H_last * p.W_last;
-    hipLaunchKernelGGL(pool_fwd_kernel, dim3(blocks_for(nB * p.C_last)), dim3(256), 0, s, a_of(p.nblocks).t, HWl,
-                       nB * p.C_last, ws.pool);
+    const int HWl = p.H_last * p.W_last, HWs = p.Hs_last * p.Ws_last;   // real and stored pixels of the last stage
+    hipLaunchKernelGGL(pool_fwd_kernel, dim3(blocks_for(nB * p.C_last)), dim3(256), 0, s, a_of(p.nblocks).t, HWs, p.C_last,
+                       p.Cs_last, 1.0f / (float)HWl, nB * p.C_last, ws.pool);
     {
         const size_t head_lds = ((size_t)(B + p.classes) * (p.C_last + 1) + (size_t)B * p.classes) * sizeof(float);
         if (head_lds <= 48 * 1024)
@@ -441,13 +493,13 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     Tensor dv = ws.delta[0], du = ws.delta[1], dnext = ws.delta[2];
     WgradReduceList pending;   // the sums over the weight-gradient partials, one launch after the last convolution
     {
-        const i64 total = nB * HWl * p.C_last;
-        if ((HWl & 7) == 0)
-            hipLaunchKernelGGL(pool_bwd_vec_kernel, dim3(blocks_for(total / 8)), dim3(256), 0, s, a_of(p.nblocks).t, ws.dpool, HWl,
-                               total / 8, dv.t);
+        const i64 total = nB * HWs * p.Cs_last;
+        if ((HWs & 7) == 0)
+            hipLaunchKernelGGL(pool_bwd_vec_kernel, dim3(blocks_for(total / 8)), dim3(256), 0, s, a_of(p.nblocks).t, ws.dpool, HWs,
+                               p.C_last, p.Cs_last, total / 8, dv.t);
         else
-            hipLaunchKernelGGL(pool_bwd_kernel, dim3(blocks_for(total)), dim3(256), 0, s, a_of(p.nblocks).t, ws.dpool, HWl,
-                               total, dv.t);
+            hipLaunchKernelGGL(pool_bwd_kernel, dim3(blocks_for(total)), dim3(256), 0, s, a_of(p.nblocks).t, ws.dpool, HWs,
+                               p.C_last, p.Cs_last, total, dv.t);
     }
     for (int j = p.nblocks - 1; j >= 0; --j) {
         const ConvDesc &c1 = p.convs[1 + 2 * j], &c2 = p.convs[2 + 2 * j];
@@ -456,7 +508,7 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         if ((st = conv_data_grad(ctx, c2, B, dv, X, ws.wpack_d[2 + 2 * j], none, u_of(j), du)) != DPSGD_OK) return st;
         // conv1: from du and a_j; next dv = [a_j > 0] * (dgrad(du) + shortcut delta)
         if ((st = conv_weight_grad(ctx, c1, B, a_of(j), du, G, ws.partials[1 + 2 * j], &pending)) != DPSGD_OK) return st;
-        const ShortcutRef scd{dv.t, c2.Co, c2.Ho, c2.Wo, c1.stride};
+        const ShortcutRef scd{dv.t, c2.Cos, c2.Hos, c2.Wos, c1.stride};
         if ((st = conv_data_grad(ctx, c1, B, du, X, ws.wpack_d[1 + 2 * j], scd, a_of(j), dnext)) != DPSGD_OK) return st;
         Tensor t = dv; dv = dnext; dnext = t;
     }
@@ -465,13 +517,13 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         img.t = const_cast<bf16_t *>(image_chw);
         if ((st = conv_weight_grad(ctx, p.convs[0], B, img, dv, G, ws.partials[0], &pending)) != DPSGD_OK) return st;
     } else {
-        const ConvDesc &c = p.convs[0];
+        const ConvDesc &c = stem_raw;
         dim3 grid((unsigned)c.Ci, (unsigned)c.Co, (unsigned)n);
         if (m.input_is_bf16)
             hipLaunchKernelGGL(conv_wgrad_generic_kernel<false>, grid, dim3(256), 0, s, inputs, dv.t, c, B, G, ctx->ld);
         else
             hipLaunchKernelGGL(conv_wgrad_generic_kernel<true>, grid, dim3(256), 0, s, inputs, dv.t, c, B, G, ctx->ld);
-        hipLaunchKernelGGL(sum_delta_kernel, dim3((unsigned)n), dim3(1024), 0, s, dv.t, (i64)B * c.Ho * c.Wo * c.Co, G,
+        hipLaunchKernelGGL(sum_delta_kernel, dim3((unsigned)n), dim3(1024), 0, s, dv.t, (i64)B * c.Hos * c.Wos * c.Cos, G,
                            ctx->ld, c.b_off);
     }
     if ((st = hip_status(hipGetLastError())) != DPSGD_OK) return st;
@@ -482,7 +534,7 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
 dpsgd_status conv_forward_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, const float *X, ShortcutRef sc,
                                   Tensor out)
 {
-    const i64 total = (i64)ctx->n * B * c.Ho * c.Wo * c.Co;
+    const i64 total = (i64)ctx->n * B * c.Hos * c.Wos * c.Cos;
     hipLaunchKernelGGL(conv_fwd_generic_kernel<false>, dim3(blocks_for(total)), dim3(256), 0, ctx->stream, in.t, X, ctx->ld,
                        c, B, total, sc.t, sc.C, sc.H, sc.W, sc.S, out.t);
     return hip_status(hipGetLastError());
@@ -491,7 +543,7 @@ dpsgd_status conv_forward_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tens
 dpsgd_status conv_data_grad_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X,
                                     ShortcutRef scd, Tensor act, Tensor din)
 {
-    const i64 total = (i64)ctx->n * B * c.H * c.W * c.Ci;
+    const i64 total = (i64)ctx->n * B * c.His * c.Wis * c.Cis;
     hipLaunchKernelGGL(conv_dgrad_generic_kernel, dim3(blocks_for(total)), dim3(256), 0, ctx->stream, dout.t, X, ctx->ld, c,
                        B, total, scd.t, scd.C, scd.H, scd.W, scd.S, act.t, din.t);
     return hip_status(hipGetLastError());
@@ -502,7 +554,7 @@ dpsgd_status conv_weight_grad_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, 
     dim3 grid((unsigned)c.Ci, (unsigned)c.Co, (unsigned)ctx->n);
     hipLaunchKernelGGL(conv_wgrad_generic_kernel<false>, grid, dim3(256), 0, ctx->stream, in.t, dout.t, c, B, G, ctx->ld);
     hipLaunchKernelGGL(sum_delta_kernel, dim3((unsigned)ctx->n), dim3(1024), 0, ctx->stream, dout.t,
-                       (i64)B * c.Ho * c.Wo * c.Co, G, ctx->ld, c.b_off);
+                       (i64)B * c.Hos * c.Wos * c.Cos, G, ctx->ld, c.b_off);
     return hip_status(hipGetLastError());
 }
 

@@ -26,20 +26,29 @@ __device__ __forceinline__ bool bf16_positive(bf16_t h) { return (h & 0x7fffu) !
 
 // One 3x3 convolution (zero padding 1): input Ci x H x W, output Co x Ho x Wo, weights at w_off
 // ([Co][Ci][3][3] fp32) and one scalar bias at b_off inside a worker's parameter vector.
+// How its tensors lie in memory: stored channels, rows and columns of the input (Cis x His x Wis) and of the output
+// (Cos x Hos x Wos), each at least the real extent.  What lies beyond the real extent of a stored activation or delta
+// holds zeros.  (The network's input image is the caller's and is stored as it is; the stem's His x Wis are those of
+// the copies the MFMA stem makes of it.)
 struct ConvDesc {
     int Ci, Co, H, W, Ho, Wo, stride;
     long long w_off, b_off;
+    int Cis, His, Wis, Cos, Hos, Wos;
+    bool padded_out() const { return Cos != Co || Hos != Ho || Wos != Wo; }
 };
 
 struct ResnetPlan {
     std::vector<ConvDesc> convs;   // [0] stem, then conv1, conv2 of each block
     long long fcw_off = 0, fcb_off = 0;
     int classes = 0, C_last = 0, H_last = 0, W_last = 0, nblocks = 0;
+    int Cs_last = 0, Hs_last = 0, Ws_last = 0;   // stored extents of the last stage
 };
 
-ResnetPlan make_resnet_plan(const dpsgd_model_desc &m);
+// pad: store the stages that fit them in the shapes the MFMA kernels take (see stored_stage); else every tensor has its
+// real extents.
+ResnetPlan make_resnet_plan(const dpsgd_model_desc &m, bool pad);
 
-// An activation or delta tensor: bf16, channel-major [n][B][C][H][W].  The weight gradient contracts
+// An activation or delta tensor: bf16, channel-major [n][B][C][H][W] (stored extents).  The weight gradient contracts
 // over pixels and reads them contiguously; forward and data gradient contract over channels and
 // transpose their source rows on the way into LDS; epilogues read and write 4 consecutive pixels
 // of one channel.
@@ -74,10 +83,10 @@ dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dou
 // The weight-gradient kernels of the MFMA path leave partial sums (several workgroups per worker); what turns them
 // into G is collected here and done for all convolutions of the network by ONE launch, conv_weight_grad_finish.
 struct WgradReduceList {
-    alignas(8) unsigned char table[2560];   // the job table the reduction kernel takes as its argument
+    alignas(8) unsigned char table[2816];   // the job table the reduction kernel takes as its argument
     int njobs = 0, blocks = 0;
 };
-// G[w_off..] = dout (*) in, G[b_off] = sum(dout).  partials: this conv's own scratch of conv_wgrad_partial_bytes(c, B) * n
+// G[w_off..] = dout (*) in, G[b_off] = sum(dout).  partials: this conv's own scratch of conv_wgrad_partial_bytes(ctx, c, B) * n
 // bytes, which must stay untouched until conv_weight_grad_finish(pending) has run on the same stream; G holds the
 // result only after that call.  Without partials or pending (or for shapes the MFMA kernel does not take) G is
 // written directly.
@@ -87,17 +96,19 @@ dpsgd_status conv_weight_grad_finish(dpsgd_ctx *ctx, WgradReduceList *pending, f
 
 // Bytes per worker of the packed weights of one conv (forward operand, or data-gradient operand).
 size_t conv_pack_bytes(const ConvDesc &c, bool dgrad);
-size_t conv_wgrad_partial_bytes(const ConvDesc &c, int B);
+size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B);
 // Rounds the fp32 weights of every conv and worker to bf16 in MFMA operand order (forward and data-gradient
 // operands, wpack_f[q] / wpack_d[q] for convs[q]; nothing is written for convs the MFMA kernels do not take).
 dpsgd_status conv_pack_weights(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, const float *X,
                                const std::vector<bf16_t *> &wpack_f, const std::vector<bf16_t *> &wpack_d);
 
 // Stem support: whether the first conv runs on MFMA, and the image copies it then needs: a bf16
-// channel-major copy (only made from fp32 images; may be null) and the image padded to 8 channels (NHWC8).
+// channel-major copy (made from fp32 images and where the stored extents differ; may be null) and the image padded to
+// 8 channels (NHWC8).
 bool conv_stem_uses_mfma(const ConvDesc &c);
 // Whether conv_forward fills out.sign for this conv (the stem counts only when it runs on MFMA).
 bool conv_forward_writes_sign(const ConvDesc &c, bool is_stem);
+// chw_bf16 and nhwc8 are His x Wis pixels, zero beyond H x W.
 dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const void *image, bool image_is_bf16,
                              bf16_t *chw_bf16, bf16_t *nhwc8);
 

@@ -185,3 +185,40 @@ def test_residual_block_in_one_launch_changes_no_bit(widths, batch, n):
         out.append((Gd.clone(), loss.clone()))
     assert torch.equal(out[0][1], out[1][1]), "loss differs"
     assert torch.equal(out[0][0], out[1][0]), "gradient differs"
+
+
+@pytest.mark.parametrize("widths,batch,n", [
+    ((1, 28, 28, 16, 1, 10), 3, 2),   # 28 / 14 / 7 pixels stored as 32 / 16 / 8
+    ((3, 13, 21, 16, 1, 10), 3, 2),   # rectangular, odd on every stage
+    ((3, 24, 9, 16, 1, 10), 2, 8),    # rows of 9, 5 and 3 pixels: the strided convolutions meet rows of 16 / 8 and of 8 / 8
+    ((3, 16, 8, 16, 1, 10), 2, 2),    # an exact first stage on padded ones
+    ((2, 9, 48, 8, 1, 5), 3, 2),      # 8 / 16 / 32 channels stored as 16 / 32 / 64; rows of 48: 4-row bands of the weight gradient
+    ((3, 20, 20, 24, 1, 10), 3, 2),   # 24 / 48 channels stored as 32 / 64, the 96 of the last stage as they are
+    ((8, 16, 16, 20, 1, 10), 2, 2),   # the widest image the matrix-kernel stem takes
+    ((3, 1, 9, 16, 1, 3), 3, 2),      # one pixel high
+])
+@pytest.mark.parametrize("bf16_inputs", [True, False])
+def test_padded_extents_agree_with_the_real_ones(widths, batch, n, bf16_inputs):
+    """Stages of other extents than the matrix kernels take are stored rounded up to such extents ("conv_pad" 1, the
+    default) or as they are, on the shape-generic kernels ("conv_pad" 0).  The same products in another order of the
+    fp32 sums: each result is within TIGHT of the oracle, so the two are within twice that of each other."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    ld = synth.padded_stride(d)
+    grad_case(cfg, ld, bf16_inputs=bf16_inputs, plain=False)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    inp_d = bf16_dev(inp) if bf16_inputs else torch.from_numpy(inp).cuda()
+    out = []
+    Xd = to_dev(X, ld)
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=ld) as ctx:   # one context: the layouts follow each other
+        for setting in (0, 1, 0):
+            Gd = torch.full_like(Xd, 777.0)
+            loss = torch.zeros(cfg.n, device="cuda")
+            ctx.set_option("conv_pad", setting)
+            ctx.grad(model, Xd, inp_d, torch.from_numpy(tgt).cuda(), cfg.batch, Gd, loss, input_is_bf16=bf16_inputs)
+            torch.cuda.synchronize()
+            out.append((from_dev(Gd, d), loss.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[2][0]) and np.array_equal(out[0][1], out[2][1])
+    check_close(out[1][0], out[0][0], 2 * TIGHT, "padded vs real extents", flips=True)
+    assert rel_err(out[1][1], out[0][1]) < 2 * TIGHT

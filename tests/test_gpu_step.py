@@ -151,7 +151,8 @@ def test_launch_options_reject_unknown_keys_and_values():
     with B.Dpsgd(8, 64, B.Topology.ring(), 0.1) as ctx:
         for key, good, bad in (("fused_slab", (0, 1, 2), (3, -1)), ("class_bwd", (0, 1), ()), ("fused_lds", (0, 1), ()),
                                ("ring_rows", (0, 1), ()), ("ring_chunks", (0, 1), ()), ("mix_vec", (0, 1, 2, 4), (3, 8)),
-                               ("mix_bands", (0, 16), (17, -1)), ("conv_band_rows", (0, 8, 16), (4, 32))):
+                               ("mix_bands", (0, 16), (17, -1)), ("conv_band_rows", (0, 8, 16), (4, 32)),
+                               ("conv_pad", (0, 1), ())):
             for v in good:
                 ctx.set_option(key, v)
             for v in bad:

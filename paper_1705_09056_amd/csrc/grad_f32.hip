@@ -43,99 +43,386 @@ lsq_grad_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A
 }
 
 // --------------------------------------------------------------- batched strided fp32 GEMM
-// C[w](m,n) = sum_k A[w](m,k) B[w](k,n) (+ bias[w][n]) (ReLU) (masked by mask[w](m,n) > 0),
-// every operand addressed through element strides, so that forward (A W^T), data gradient
-// (dZ W) and weight gradient (dZ^T A) are the same kernel.  64x64 tile, 16-deep k steps,
-// 256 threads x (4x4) outputs, next tile prefetched into registers during the FMAs.
+// C[w](m,n) = sum_k A[w](m,k) B[w](k,n) (+ bias[w][n]) (ReLU) (masked by mask[w](m,n) > 0), every operand addressed
+// through element strides, so that data gradient (dZ W) and weight gradient (dZ^T A) are the same kernel (the forward
+// A W^T has linear_fwd_f32_kernel).  An operand is contiguous along k (sAk / sBk == 1) or along its own dimension
+// (sAm / sBn == 1); rows of C are contiguous.
 struct GemmArgs {
     const float *A; i64 sAw, sAm, sAk;
     const float *B; i64 sBw, sBk, sBn;
-    float *C;       i64 sCw, sCm, sCn;
+    float *C;       i64 sCw, sCm;
     const float *bias; i64 sBiasw;      // may be null
     const float *mask; i64 sMw, sMm;    // may be null; unit stride along n
     int M, N, K, relu;
 };
 
-template <bool A_KFAST, bool B_NFAST>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float: rows need no alignment
+
+// Workgroups are dealt to the 8 XCDs round-robin by linear id and every XCD has its own L2: with a multiple of 8 workers
+// the ids of a (tiles n, tiles m, workers) grid are renumbered so that one XCD computes all tiles of a worker, whose
+// operands then come into one L2.
+__device__ __forceinline__ void worker_tile(int &w, int &tile_m, int &tile_n)
 {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
-    const int w = blockIdx.z;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const float *A = g.A + (i64)w * g.sAw;
-    const float *Bm = g.B + (i64)w * g.sBw;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {};
-    float ra[4], rb[4];
-
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q;
-            const int ka = A_KFAST ? (e & 15) : (e >> 6), ma = A_KFAST ? (e >> 4) : (e & 63);
-            ra[q] = (m0 + ma < g.M && k0 + ka < g.K) ? A[(i64)(m0 + ma) * g.sAm + (i64)(k0 + ka) * g.sAk] : 0.f;
-            const int kb = B_NFAST ? (e >> 6) : (e & 15), nb = B_NFAST ? (e & 63) : (e >> 4);
-            rb[q] = (n0 + nb < g.N && k0 + kb < g.K) ? Bm[(i64)(k0 + kb) * g.sBk + (i64)(n0 + nb) * g.sBn] : 0.f;
-        }
-    };
-    auto stage = [&]() {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q;
-            const int ka = A_KFAST ? (e & 15) : (e >> 6), ma = A_KFAST ? (e >> 4) : (e & 63);
-            As[ka][ma] = ra[q];
-            const int kb = B_NFAST ? (e >> 6) : (e & 15), nb = B_NFAST ? (e & 63) : (e >> 4);
-            Bs[kb][nb] = rb[q];
-        }
-    };
-
-    fetch(0);
-    for (int k0 = 0; k0 < g.K; k0 += 16) {
-        stage();
-        __syncthreads();
-        if (k0 + 16 < g.K) fetch(k0 + 16);
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = a[i] * b[j] + acc[i][j];
-        }
-        __syncthreads();
+    w = blockIdx.z; tile_n = blockIdx.x; tile_m = blockIdx.y;
+    if ((gridDim.z & 7) == 0) {
+        const unsigned per = gridDim.x * gridDim.y;
+        const unsigned id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+        const unsigned xcd = id & 7, slot = id >> 3, within = slot % per;
+        w = (int)((slot / per) * 8 + xcd);
+        tile_n = (int)(within % gridDim.x);
+        tile_m = (int)(within / gridDim.x);
     }
+}
+
+// Four consecutive elements of which only the first `have` exist, as a load whose first element was clamped to the
+// extent's last four left them: element i sits 4 - have places further on when 0 < have < 4.  Zeros for the rest.
+__device__ __forceinline__ f32x4 mend4(f32x4 v, int have)
+{
+    f32x4 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= g.N) continue;
-            float v = acc[i][j];
-            if (g.bias) v += g.bias[(i64)w * g.sBiasw + n];
-            if (g.relu) v = v > 0.f ? v : 0.f;
-            if (g.mask) v = g.mask[(i64)w * g.sMw + (i64)m * g.sMm + n] > 0.f ? v : 0.f;
-            g.C[(i64)w * g.sCw + (i64)m * g.sCm + (i64)n * g.sCn] = v;
-        }
+        float x = v[i];
+        if (have == 3) x = i < 3 ? v[i + 1 < 4 ? i + 1 : 3] : 0.f;
+        if (have == 2) x = i < 2 ? v[i + 2 < 4 ? i + 2 : 3] : 0.f;
+        if (have == 1) x = i < 1 ? v[3] : 0.f;
+        if (have <= 0) x = 0.f;
+        o[i] = x;
     }
+    return o;
+}
+
+// Matrix instructions on fp32 operands (v_mfma_f32_32x32x2_f32: fp32 products and sums, a sixteenth of the bf16 rate but
+// the whole fp32 rate of the chip, which a thread-per-4x4-block kernel does not come near).  A workgroup owns a
+// [32 WM][32 WN] tile; its WM x WN x WK waves take one 32 x 32 tile each, and the WK waves of a tile split every chunk
+// of 32 WK contraction elements (their sums meet in LDS in wave order): small tiles with a split contraction where a
+// product would otherwise leave CUs idle.  A chunk waits in registers while the one before it is multiplied.  In LDS an
+// operand keeps the direction it is contiguous in: along k a lane reads 4 consecutive elements at once, along its own
+// dimension 4 times one, in both cases elements 8 q + 4 (lane / 32) + j of the chunk for the j-th of four instructions
+// (the order of the contraction is free as long as both operands agree).
+// Measured at 16 workers, 3072 x 1024 weights, 64 samples: see gemm_f32.
+template <int WM, int WN, int WK, int KW, bool A_KFAST, bool B_NFAST, bool TINY, bool AHEAD2>
+__global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
+{
+    constexpr int NT = 64 * WM * WN * WK, TM = 32 * WM, TN = 32 * WN, TK = KW * WK;
+    constexpr int AQ = TM * TK / 4 / NT, BQ = TN * TK / 4 / NT;   // 16-byte units per thread
+    constexpr int PK = TK + 4, PA = TM + 8, PB = TN + 8;          // pitches: conflict-free reads either way
+    constexpr int ASZ = A_KFAST ? TM * PK : TK * PA, BSZ = B_NFAST ? TK * PB : TN * PK;
+    constexpr int RED = (WK - 1) * WM * WN * 16 * 64, BUF = ASZ + BSZ;
+    static_assert(AQ >= 1 && BQ >= 1 && TM * TK % (4 * NT) == 0 && TN * TK % (4 * NT) == 0, "whole 16-byte units per thread");
+    __shared__ __attribute__((aligned(16))) float lds[2 * BUF > RED ? 2 * BUF : RED];   // two chunks: operand A, operand B
+    int w, tile_m, tile_n;
+    worker_tile(w, tile_m, tile_n);
+    const int m0 = tile_m * TM, n0 = tile_n * TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, half = lane >> 5;
+    const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+    const float *A = g.A + (i64)w * g.sAw, *Bm = g.B + (i64)w * g.sBw;
+
+    struct Chunk { f32x4 a[AQ], b[BQ]; };
+    Chunk even, odd;   // chunks on their way
+    // Unit u of an operand tile: 4 elements along the operand's contiguous direction.  The loads are free of branches:
+    // row and first element are clamped into the matrix (the contiguous extent is at least 4, TINY aside), and what was
+    // fetched for an element outside is moved and zeroed on the way to LDS, where a branch stalls nothing.
+    auto unit = [](int u, bool kfast, int T, int &row, int &kk) {   // row: along M or N
+        row = kfast ? u / (TK / 4) : u % (T / 4) * 4;
+        kk = kfast ? u % (TK / 4) * 4 : u / (T / 4);
+    };
+    auto load = [&](const float *base, bool kfast, int T, int u, int r0, int k0, int R, i64 sr, i64 sk) {
+        int row, kk;
+        unit(u, kfast, T, row, kk);
+        const int r = r0 + row, k = k0 + kk;
+        if (TINY) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ri = kfast ? r : r + i, ki = kfast ? k + i : k;
+                if (ri < R && ki < g.K) v[i] = base[kfast ? (i64)ri * sr + ki : (i64)ki * sk + ri];
+            }
+            return v;
+        }
+        const int rc = min(r, kfast ? R - 1 : R - 4), kc = min(k, kfast ? g.K - 4 : g.K - 1);
+        const f32x4_a4 v = *reinterpret_cast<const f32x4_a4 *>(base + (kfast ? (i64)rc * sr + kc : (i64)kc * sk + rc));
+        return (f32x4){v.x, v.y, v.z, v.w};
+    };
+    auto mend = [&](f32x4 v, bool kfast, int T, int u, int r0, int k0, int R) {
+        int row, kk;
+        unit(u, kfast, T, row, kk);
+        const int r = r0 + row, k = k0 + kk;
+        return mend4(v, kfast ? (r < R ? g.K - k : 0) : (k < g.K ? R - r : 0));
+    };
+    const bool full_mn = m0 + TM <= g.M && n0 + TN <= g.N;
+    auto fetch = [&](int k0, Chunk &r) {
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) r.a[q] = load(A, A_KFAST, TM, tid + NT * q, m0, k0, g.M, g.sAm, g.sAk);
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) r.b[q] = load(Bm, !B_NFAST, TN, tid + NT * q, n0, k0, g.N, g.sBn, g.sBk);
+    };
+    auto stage = [&](int buf, Chunk &r, int k0) {
+        float *As = lds + buf * BUF, *Bs = As + ASZ;
+        if (!TINY && !(full_mn && k0 + TK <= g.K)) {
+#pragma unroll
+            for (int q = 0; q < AQ; ++q) r.a[q] = mend(r.a[q], A_KFAST, TM, tid + NT * q, m0, k0, g.M);
+#pragma unroll
+            for (int q = 0; q < BQ; ++q) r.b[q] = mend(r.b[q], !B_NFAST, TN, tid + NT * q, n0, k0, g.N);
+        }
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) {
+            int row, kk;
+            unit(tid + NT * q, A_KFAST, TM, row, kk);
+            *reinterpret_cast<f32x4 *>(A_KFAST ? As + row * PK + kk : As + kk * PA + row) = r.a[q];
+        }
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) {
+            int row, kk;
+            unit(tid + NT * q, !B_NFAST, TN, row, kk);
+            *reinterpret_cast<f32x4 *>(B_NFAST ? Bs + kk * PB + row : Bs + row * PK + kk) = r.b[q];
+        }
+    };
+
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    // workgroups start their walk over the contraction at different chunks: started together they would all read the
+    // same columns of rows that lie a multiple of 4 KB apart
+    const int nchunks = (g.K + TK - 1) / TK;
+    const int start = A_KFAST && !B_NFAST ? (int)((unsigned)(tile_n * 5 + w * 3) % (unsigned)nchunks) : 0;
+    auto chunk_k = [&](int c) { const int cc = c + start; return (cc >= nchunks ? cc - nchunks : cc) * TK; };
+    fetch(chunk_k(0), even);
+    if (AHEAD2 && nchunks > 1) fetch(chunk_k(1), odd);
+    stage(0, even, chunk_k(0));
+    if (nchunks > (AHEAD2 ? 2 : 1)) fetch(chunk_k(AHEAD2 ? 2 : 1), even);
+    __syncthreads();
+    // chunk c is multiplied, chunk c + 1 (in r) goes to LDS and chunk c + 2 or c + 3 is requested into its registers
+    auto step = [&](int c, Chunk &r) {
+        const float *As = lds + (c & 1) * BUF, *Bs = As + ASZ;
+        const int kw = KW * wk + 4 * half;
+        const float *Ar = A_KFAST ? As + (wm * 32 + l32) * PK + kw : As + kw * PA + wm * 32 + l32;
+        const float *Br = B_NFAST ? Bs + kw * PB + wn * 32 + l32 : Bs + (wn * 32 + l32) * PK + kw;
+#pragma unroll
+        for (int q = 0; q < KW / 8; ++q) {
+            f32x4 a, b;
+            if (A_KFAST) a = *reinterpret_cast<const f32x4 *>(Ar + 8 * q);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j] = Ar[(8 * q + j) * PA];
+            if (!B_NFAST) b = *reinterpret_cast<const f32x4 *>(Br + 8 * q);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) b[j] = Br[(8 * q + j) * PB];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
+        }
+        // (AHEAD2, for long walks: past the end the last chunk again, never used - a branch around the loads costs 10 %)
+        if (AHEAD2 || c + 1 < nchunks) stage((c & 1) ^ 1, r, chunk_k(min(c + 1, nchunks - 1)));   // its last readers have passed a barrier
+        if (AHEAD2 || c + 2 < nchunks) fetch(chunk_k(min(c + (AHEAD2 ? 3 : 2), nchunks - 1)), r);
+        __syncthreads();
+    };
+    if (AHEAD2) {
+        for (int c = 0; c < nchunks; c += 2) {
+            step(c, odd);
+            if (c + 1 < nchunks) step(c + 1, even);
+        }
+    } else {
+        for (int c = 0; c < nchunks; ++c) step(c, even);
+    }
+    if (WK > 1) {   // the waves that split the contraction: their sums meet in wave order
+        if (wk > 0)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lds[(((wk - 1) * WM * WN + wm * WN + wn) * 16 + v) * 64 + lane] = acc[v];
+        __syncthreads();
+        if (wk > 0) return;
+        for (int q = 0; q < WK - 1; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] += lds[((q * WM * WN + wm * WN + wn) * 16 + v) * 64 + lane];
+    }
+    // register v of lane l: row (v / 4) * 8 + (l / 32) * 4 + v % 4, column l % 32
+    const int m1 = m0 + wm * 32 + half * 4, n = n0 + wn * 32 + l32;
+    if (n >= g.N) return;
+    const float bias = g.bias ? g.bias[(i64)w * g.sBiasw + n] : 0.f;
+    float *c = g.C + (i64)w * g.sCw + (i64)m1 * g.sCm + n;
+    if (full_mn && !g.relu && !g.mask) {   // (the weight gradient: nothing but stores)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(acc[v] + bias, c + (i64)((v >> 2) * 8 + (v & 3)) * g.sCm);
+        return;
+    }
+    const float *mask = g.mask ? g.mask + (i64)w * g.sMw + (i64)m1 * g.sMm + n : nullptr;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int dm = (v >> 2) * 8 + (v & 3);
+        if (m1 + dm >= g.M) continue;
+        float r = acc[v] + bias;
+        if (g.relu) r = r > 0.f ? r : 0.f;
+        if (mask) r = mask[(i64)dm * g.sMm] > 0.f ? r : 0.f;
+        c[(i64)dm * g.sCm] = r;
+    }
+}
+
+template <int WM, int WN, int WK, int KW, bool AHEAD2 = false, bool TINY = false>
+dpsgd_status gemm_f32_launch(hipStream_t s, int nworkers, const GemmArgs &g)
+{
+    constexpr int TM = 32 * WM, TN = 32 * WN;
+    dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
+    if (grid.y > 65535u || grid.z > 65535u) return DPSGD_EUNSUPPORTED;
+    const dim3 block(64 * WM * WN * WK);
+    const bool akf = g.sAk == 1, bnf = g.sBn == 1;
+    if (!TINY && !bnf) return DPSGD_EUNSUPPORTED;   // (a forward product: linear_fwd_f32)
+    if (akf && bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, true, TINY, AHEAD2>), grid, block, 0, s, g);
+    else if (bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, false, true, TINY, AHEAD2>), grid, block, 0, s, g);
+    else if constexpr (TINY) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, false, TINY, AHEAD2>), grid, block, 0, s, g);
+    return hip_status(hipGetLastError());
 }
 
 dpsgd_status gemm_f32(hipStream_t s, int nworkers, const GemmArgs &g)
 {
-    dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64), (unsigned)nworkers);
+    const int ea = g.sAk == 1 ? g.K : g.M, eb = g.sBn == 1 ? g.N : g.K;   // contiguous extents
+    if (ea < 4 || eb < 4) return gemm_f32_launch<1, 1, 4, 16, false, true>(s, nworkers, g);
+    // 16 workers x 64 samples x 3072 x 1024 (us; before: with a thread per 4 x 4 block on the vector units): weight
+    // gradient 118 -> 79 with 64 x 64 tiles and no split (its contraction is the minibatch; a second wave per tile: 93); a
+    // contraction of 3072 70 with the contraction split over two waves, 76 without.  10 rows x 3072 x 128 samples (a class
+    // layer's weight gradient): 19 -> 10.9 with 32 x 64 tiles, 64 x 64: 14.  Results that leave most CUs without such a
+    // tile take 32 x 32 ones and four waves each.
+    const i64 tn = (g.N + 63) / 64 * (i64)nworkers;
+    constexpr i64 few = 256;   // 4 workers, 3072-1024-10, 128 samples: 137 us per gradient and mix against 163 with 128
+    if (g.M <= 32) {
+        if (tn < few) return gemm_f32_launch<1, 1, 4, 16>(s, nworkers, g);
+        return gemm_f32_launch<1, 2, 2, 16>(s, nworkers, g);
+    }
+    if (tn * ((g.M + 63) / 64) < few) return gemm_f32_launch<1, 1, 4, 16>(s, nworkers, g);
+    if (g.K >= 512) return gemm_f32_launch<2, 2, 2, 16, true>(s, nworkers, g);
+    return gemm_f32_launch<2, 2, 1, 32>(s, nworkers, g);
+}
+
+// Forward of a hidden layer, C[w](m,n) = ReLU(sum_k A[w](m,k) B[w](n,k) + bias): both operands contiguous along k.  The
+// contraction is one chain of fused multiply-adds per element, k ascending, which is what v_mfma_f32_16x16x4_f32 does
+// inside an instruction as well: the sums, and with them every ReLU decision, are those of the plain loop.  (A sum in
+// another order differs in its last bits, and a unit that such a difference moves across zero changes a whole row of the
+// weight gradient.)  The small instruction keeps the chain short in time: 8 cycles per element of the contraction
+// against 32 of the 32 x 32 one; a wave owns RM x RN independent tiles.  Lane l of an operand holds row (column) l % 16
+// and element l / 16 of the four; in LDS the elements of a group of 16 are ordered by k % 4, so that a lane reads its
+// elements of four instructions as 16 bytes.  Register i of lane l is row 4 (l / 16) + i, column l % 16.
+// grid (ceil(N / TN), ceil(M / TM), n), block 64 WM WN.
+template <int RM, int RN, int WM, int WN, int TK>
+__global__ void __launch_bounds__(64 * WM * WN) linear_fwd_f32_kernel(GemmArgs g)
+{
+    constexpr int NT = 64 * WM * WN, TM = 16 * RM * WM, TN = 16 * RN * WN, PK = TK + 4;
+    constexpr int AQ = TM * TK / 4 / NT, BQ = TN * TK / 4 / NT, BUF = (TM + TN) * PK;
+    static_assert(AQ >= 1 && BQ >= 1 && TM * TK % (4 * NT) == 0 && TN * TK % (4 * NT) == 0, "whole 16-byte units per thread");
+    __shared__ __attribute__((aligned(16))) float lds[2 * BUF];
+    int w, tile_m, tile_n;
+    worker_tile(w, tile_m, tile_n);
+    const int m0 = tile_m * TM, n0 = tile_n * TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, g4 = lane >> 4, wm = wave / WN, wn = wave % WN;
+    const float *A = g.A + (i64)w * g.sAw, *Bm = g.B + (i64)w * g.sBw;
+    struct Chunk { f32x4 a[AQ], b[BQ]; };
+    Chunk even, odd;
+    // unit u of an operand tile: row u / (TK / 4), elements 4 (u % (TK / 4)) .. + 3; clamped and mended as in gemm_f32_kernel
+    auto load = [&](const float *base, i64 sr, int R, int r0, int k0, int u) {
+        const int r = min(r0 + u / (TK / 4), R - 1), k = min(k0 + u % (TK / 4) * 4, g.K - 4);
+        const f32x4_a4 v = *reinterpret_cast<const f32x4_a4 *>(base + (i64)r * sr + k);
+        return (f32x4){v.x, v.y, v.z, v.w};
+    };
+    auto fetch = [&](int k0, Chunk &r) {
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) r.a[q] = load(A, g.sAm, g.M, m0, k0, tid + NT * q);
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) r.b[q] = load(Bm, g.sBn, g.N, n0, k0, tid + NT * q);
+    };
+    const bool full_mn = m0 + TM <= g.M && n0 + TN <= g.N;
+    auto put = [&](float *tile, f32x4 v, int R, int r0, int k0, int u, bool full) {
+        const int row = u / (TK / 4), kk = u % (TK / 4) * 4;
+        if (!full) v = mend4(v, r0 + row < R ? g.K - (k0 + kk) : 0);
+        float *d = tile + row * PK + (kk & ~15) + ((kk & 15) >> 2);   // element e of the unit (k % 4 == e): e groups of 4 further
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[4 * e] = v[e];
+    };
+    auto stage = [&](int buf, const Chunk &r, int k0) {
+        float *As = lds + buf * BUF, *Bs = As + TM * PK;
+        const bool full = full_mn && k0 + TK <= g.K;
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) put(As, r.a[q], g.M, m0, k0, tid + NT * q, full);
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) put(Bs, r.b[q], g.N, n0, k0, tid + NT * q, full);
+    };
+    f32x4 acc[RM][RN];
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+        for (int j = 0; j < RN; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const int nchunks = (g.K + TK - 1) / TK, last = nchunks - 1;
+    fetch(0, even);
+    fetch(min(1, last) * TK, odd);
+    stage(0, even, 0);
+    fetch(min(2, last) * TK, even);
+    __syncthreads();
+    // chunk c is multiplied, chunk c + 1 (in r) goes to LDS, chunk c + 3 is requested into its registers (past the end:
+    // the last chunk again, never used - no branch around a load)
+    auto step = [&](int c, Chunk &r) {
+        const float *As = lds + (c & 1) * BUF + (wm * RM * 16 + l16) * PK + 4 * g4;
+        const float *Bs = lds + (c & 1) * BUF + TM * PK + (wn * RN * 16 + l16) * PK + 4 * g4;
+#pragma unroll
+        for (int q = 0; q < TK / 16; ++q) {
+            f32x4 a[RM], b[RN];
+#pragma unroll
+            for (int i = 0; i < RM; ++i) a[i] = *reinterpret_cast<const f32x4 *>(As + 16 * i * PK + 16 * q);
+#pragma unroll
+            for (int j = 0; j < RN; ++j) b[j] = *reinterpret_cast<const f32x4 *>(Bs + 16 * j * PK + 16 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+        }
+        stage((c & 1) ^ 1, r, min(c + 1, last) * TK);
+        fetch(min(c + 3, last) * TK, r);
+        __syncthreads();
+    };
+    for (int c = 0; c < nchunks; c += 2) {
+        step(c, odd);
+        if (c + 1 < nchunks) step(c + 1, even);
+    }
+#pragma unroll
+    for (int j = 0; j < RN; ++j) {
+        const int n = n0 + (wn * RN + j) * 16 + l16;
+        if (n >= g.N) continue;
+        const float bias = g.bias ? g.bias[(i64)w * g.sBiasw + n] : 0.f;
+#pragma unroll
+        for (int i = 0; i < RM; ++i) {
+            const int m1 = m0 + (wm * RM + i) * 16 + 4 * g4;
+            float *c = g.C + (i64)w * g.sCw + (i64)m1 * g.sCm + n;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (m1 + v >= g.M) continue;
+                float r = acc[i][j][v] + bias;
+                if (g.relu) r = r > 0.f ? r : 0.f;
+                c[(i64)v * g.sCm] = r;
+            }
+        }
+    }
+}
+
+template <int RM, int RN, int WM, int WN, int TK>
+dpsgd_status linear_fwd_launch(hipStream_t s, int nworkers, const GemmArgs &g)
+{
+    constexpr int TM = 16 * RM * WM, TN = 16 * RN * WN;
+    dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
     if (grid.y > 65535u || grid.z > 65535u) return DPSGD_EUNSUPPORTED;
-    const bool akf = g.sAk == 1, bnf = g.sBn == 1;
-    if (akf && bnf) hipLaunchKernelGGL((gemm_f32_kernel<true, true>), grid, dim3(256), 0, s, g);
-    else if (akf) hipLaunchKernelGGL((gemm_f32_kernel<true, false>), grid, dim3(256), 0, s, g);
-    else if (bnf) hipLaunchKernelGGL((gemm_f32_kernel<false, true>), grid, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((gemm_f32_kernel<false, false>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((linear_fwd_f32_kernel<RM, RN, WM, WN, TK>), grid, dim3(64 * WM * WN), 0, s, g);
     return hip_status(hipGetLastError());
+}
+
+dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
+{
+    if (g.K < 4) return gemm_f32(s, nworkers, g);
+    // 16 workers x 64 samples x 3072 x 1024: 73 us with 64 x 32 tiles and eight waves, 83 with 32 x 32 tiles and four (the
+    // thread-per-4x4-block kernel: 333); 4 workers x 3072-1024-10 x 128 samples: 133 us per gradient and mix either way;
+    // minibatches of at most 32 samples or few tiles: the smaller ones (32 x 3072-512-512-10 x 32: 279 against 323).
+    if (g.M > 32 && (i64)((g.M + 63) / 64) * ((g.N + 31) / 32) * nworkers >= 256)
+        return linear_fwd_launch<1, 1, 4, 2, 64>(s, nworkers, g);
+    return linear_fwd_launch<1, 1, 2, 2, 64>(s, nworkers, g);
 }
 
 // Forward of a layer with few outputs (O <= 16, e.g. the 10 classes): one workgroup per worker and R sample rows; its
@@ -151,7 +438,7 @@ __global__ void __launch_bounds__(256)
 linear_fwd_skinny_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,
                          int O, int relu, float *__restrict__ out)
 {
-    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef f32x4 f4;
     __shared__ float part[4][R][OMAX];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row0 = blockIdx.x * R;   // first sample row inside the worker
@@ -336,7 +623,7 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         GemmArgs g{};
         g.A = act[l]; g.sAw = (i64)B * I; g.sAm = I; g.sAk = 1;
         g.B = X + woff[l]; g.sBw = ctx->ld; g.sBk = 1; g.sBn = I;
-        g.C = (float *)act[l + 1]; g.sCw = (i64)B * O; g.sCm = O; g.sCn = 1;
+        g.C = (float *)act[l + 1]; g.sCw = (i64)B * O; g.sCm = O;
         g.bias = X + boff[l]; g.sBiasw = ctx->ld;
         g.M = B; g.N = O; g.K = I; g.relu = (l < L - 1);
         if (O <= 16 && I >= 256) {
@@ -353,7 +640,7 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
             if ((st = hip_status(hipGetLastError())) != DPSGD_OK) return st;
             continue;
         }
-        if ((st = gemm_f32(s, n, g)) != DPSGD_OK) return st;
+        if ((st = linear_fwd_f32(s, n, g)) != DPSGD_OK) return st;
     }
     const int C = m.widths[L];
     hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)n), dim3(256), 0, s, act[L], (const int *)targets, B, C, dz,
@@ -363,7 +650,7 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         GemmArgs g{};   // weight gradient: dW[o][i] = sum_b dz[b][o] act_l[b][i]
         g.A = dz; g.sAw = (i64)B * O; g.sAm = 1; g.sAk = O;
         g.B = act[l]; g.sBw = (i64)B * I; g.sBk = I; g.sBn = 1;
-        g.C = G + woff[l]; g.sCw = ctx->ld; g.sCm = I; g.sCn = 1;
+        g.C = G + woff[l]; g.sCw = ctx->ld; g.sCm = I;
         g.M = O; g.N = I; g.K = B;
         if ((st = gemm_f32(s, n, g)) != DPSGD_OK) return st;
         if (l < L - 1)   // (the class layer's came with the softmax launch)
@@ -373,7 +660,7 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
             GemmArgs h{};
             h.A = dz; h.sAw = (i64)B * O; h.sAm = O; h.sAk = 1;
             h.B = X + woff[l]; h.sBw = ctx->ld; h.sBk = I; h.sBn = 1;
-            h.C = dz2; h.sCw = (i64)B * I; h.sCm = I; h.sCn = 1;
+            h.C = dz2; h.sCw = (i64)B * I; h.sCm = I;
             h.mask = act[l]; h.sMw = (i64)B * I; h.sMm = I;
             h.M = B; h.N = I; h.K = O;
             if ((st = gemm_f32(s, n, h)) != DPSGD_OK) return st;

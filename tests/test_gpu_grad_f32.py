@@ -75,6 +75,23 @@ def test_mlp_fp32(widths, batch, n):
     grad_case(cfg, synth.padded_stride(d), spread=0.3)
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((3, 2, 3), 5, 2),            # extents below the 4 elements of a load
+    ((5, 4, 4), 1, 1),            # exactly 4, one sample
+    ((64, 32, 16), 32, 2),        # whole tiles, few of them: 32 x 32, four waves each
+    ((515, 130, 7), 40, 9),       # a long ragged contraction on small tiles
+    ((640, 97, 70, 33), 33, 160), # 32-row tiles and 64-row tiles side by side, a contraction of 640 in two waves
+    ((513, 1030, 10), 65, 16),    # a multiple of 8 workers (tiles of a worker on one XCD), every extent ragged
+])
+def test_mlp_fp32_tiles_and_remainders(widths, batch, n):
+    """The matrix-instruction product behind forward, data and weight gradient: every tile shape of its dispatch, with
+    remainders in all three directions, on padded and on odd row strides."""
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False)
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(cfg, synth.padded_stride(d), spread=0.3)
+    grad_case(cfg, d | 1, spread=0.3)
+
+
 def test_bf16_inputs_with_fp32_arithmetic():
     cfg = shrink(CONFIGS[2], widths=(96, 50, 10), batch=24, n=3, bf16=True)
     d = synth.model_dim(MODEL_MLP, cfg.widths)

@@ -12,8 +12,8 @@
  * Conventions shared by every call
  *   - Rows are workers: X and G are n x d fp32, row-major with a row stride of `ld` floats
  *     (ld >= d).  This is the transpose of Section 3's X_k (columns = nodes); the two agree
- *     because W is symmetric.  Vectorised kernels are used when ld is a multiple of 4 and the
- *     base pointers are 16-byte aligned; any other ld still works (scalar path).
+ *     because W is symmetric.  Any ld and any float alignment works; rows that start on 128-byte
+ *     lines (dpsgd_recommended_ld) are read and written fastest.
  *   - "device" pointers are HIP device memory owned by the caller; "host" pointers are
  *     ordinary host memory.  The library owns only the context (device copy of W and its
  *     workspace) and frees it in dpsgd_destroy.
@@ -241,8 +241,7 @@ dpsgd_status dpsgd_mix_step_momentum(dpsgd_ctx *ctx, const float *X_in, const fl
  * registers), on DPSGD_TOPO_TORUS2D with dim0 >= 3 and 3 <= dim1 <= 16 (a walk down the grid columns), and on every
  * other W of at most 64 workers - DPSGD_TOPO_RING_CHORD, DPSGD_TOPO_COMPLETE, DPSGD_TOPO_CSR, the remaining rings and
  * tori - through a kernel that holds every worker's tile in LDS; for every layer with at least 2^20 weights whose
- * outputs are a multiple of 32 and whose inputs are a multiple of 128 (ring) or of 32 (any other W; also 8-byte
- * aligned rows); the remaining parameters of such a model (small layers, biases) take the ordinary gradient kernels
+ * outputs are a multiple of 32 and whose inputs are a multiple of 128 (ring) or of 32 (any other W); the remaining parameters of such a model (small layers, biases) take the ordinary gradient kernels
  * and the mix kernels on their column ranges inside the same call.
  * Not fused - the call runs dpsgd_grad and an in-place dpsgd_mix_step back to back, same results: a W other than
  * those two walks with more than 64 workers, fp32 arithmetic (compute_bf16 = 0), LSQ and RESNET20 models, and the

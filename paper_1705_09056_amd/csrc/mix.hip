@@ -25,14 +25,20 @@ template <int V> struct VecT;
 template <> struct VecT<1> { typedef float type; };
 template <> struct VecT<2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct VecT<4> { typedef float type __attribute__((ext_vector_type(4))); };
+// The same in memory, at any float: rows of odd length or stride need no alignment (30 workers x 5 000 001 parameters
+// without padding on a ring: 459 us with 4-byte accesses, 395 with 16-byte ones; with padded rows 350).
+template <int V> struct MemT;
+template <> struct MemT<1> { typedef float type; };
+template <> struct MemT<2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+template <> struct MemT<4> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
 
 template <int V> __device__ __forceinline__ typename VecT<V>::type vload(const float *p)
 {
-    return *reinterpret_cast<const typename VecT<V>::type *>(p);
+    return *reinterpret_cast<const typename MemT<V>::type *>(p);
 }
 template <int V> __device__ __forceinline__ void vstore(float *p, typename VecT<V>::type v)
 {
-    *reinterpret_cast<typename VecT<V>::type *>(p) = v;
+    *reinterpret_cast<typename MemT<V>::type *>(p) = v;
 }
 // a * x + y with one rounding, spelled out so that every ring kernel rounds the same way (left to the compiler,
 // two kernels may fuse different products of  w x_{i-1} + w x_i + w x_{i+1} - gamma g)
@@ -135,6 +141,7 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
                                           float *__restrict__ Vel, float mu, float *lds, i64 grp, i64 part)
 {
     typedef typename VecT<V>::type vec;
+    typedef typename MemT<V>::type mem;
     const int lane = threadIdx.x & 63;
     const int band = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const i64 c0 = (grp * 64 + lane) * V;
@@ -184,7 +191,7 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
             vec xs[U], gs[U], vs[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                gs[u] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(gp + (i64)u * ld));
+                gs[u] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(gp + (i64)u * ld));
                 if (MOM) vs[u] = vload<V>(vp + (i64)u * ld);
                 xs[u] = vload<V>(xp + (i64)u * ld);
             }
@@ -202,7 +209,7 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
             op += (i64)U * ld;
         }
         for (; row < rlast; ++row) {
-            vec g = step_dir(__builtin_nontemporal_load(reinterpret_cast<const vec *>(gp)), vp);
+            vec g = step_dir(__builtin_nontemporal_load(reinterpret_cast<const mem *>(gp)), vp);
             vec xn = vload<V>(xp);
             form(xn, g, op);
             xp += ld;
@@ -210,7 +217,7 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
             if (MOM) vp += ld;
             op += ld;
         }
-        form(xhalo, step_dir(__builtin_nontemporal_load(reinterpret_cast<const vec *>(gp)), vp), op);
+        form(xhalo, step_dir(__builtin_nontemporal_load(reinterpret_cast<const mem *>(gp)), vp), op);
     }
     if (CONS) {
         combine_bands<V>(st, lds, band, lane, bands);
@@ -259,6 +266,7 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
                     double *__restrict__ partials, float *__restrict__ Vel, float mu)
 {
     typedef VecT<4>::type vec;
+    typedef MemT<4>::type mem;
     const int lane = threadIdx.x;
     constexpr i64 kPerSuper = kFatStride / (kFatChunkLanes * 4);   // workgroups per super-block: 64
     constexpr i64 kStep = (64 / kFatChunkLanes) * kFatStride;      // floats between a lane's column groups q and q + 1
@@ -278,7 +286,7 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
     auto form = [&](int row, int q, vec xs, vec g) {
         const vec xn = row + 1 < n ? xs : x0[q];   // the ring closes on worker 0's original row
         const vec o = ring_update(w, xm[q], xc[q], xn, gamma, g);
-        __builtin_nontemporal_store(o, reinterpret_cast<vec *>(Xout + (i64)row * ld + c0 + (i64)q * kStep));
+        __builtin_nontemporal_store(o, reinterpret_cast<mem *>(Xout + (i64)row * ld + c0 + (i64)q * kStep));
         if (CONS) {
             const vec e = o - x0[q];
             s1[q] += e;
@@ -292,7 +300,7 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
     auto step_dir = [&](int row, int q, vec g, vec v) {
         if (MOM) {
             g = mu * v + g;
-            __builtin_nontemporal_store(g, reinterpret_cast<vec *>(Vel + (i64)row * ld + c0 + (i64)q * kStep));
+            __builtin_nontemporal_store(g, reinterpret_cast<mem *>(Vel + (i64)row * ld + c0 + (i64)q * kStep));
         }
         return g;
     };
@@ -304,9 +312,9 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
 #pragma unroll
             for (int q = 0; q < P; ++q) {
                 const i64 c = c0 + (i64)q * kStep;
-                gs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(G + (i64)(row + u) * ld + c));
-                if (MOM) vs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(Vel + (i64)(row + u) * ld + c));
-                xs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(Xin + (i64)rn * ld + c));
+                gs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(G + (i64)(row + u) * ld + c));
+                if (MOM) vs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(Vel + (i64)(row + u) * ld + c));
+                xs[u][q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(Xin + (i64)rn * ld + c));
             }
         }
 #pragma unroll
@@ -319,9 +327,9 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
 #pragma unroll
         for (int q = 0; q < P; ++q) {
             const i64 c = c0 + (i64)q * kStep;
-            const vec g = __builtin_nontemporal_load(reinterpret_cast<const vec *>(G + (i64)row * ld + c));
-            const vec v = MOM ? __builtin_nontemporal_load(reinterpret_cast<const vec *>(Vel + (i64)row * ld + c)) : g;
-            const vec x = __builtin_nontemporal_load(reinterpret_cast<const vec *>(Xin + (i64)rn * ld + c));
+            const vec g = __builtin_nontemporal_load(reinterpret_cast<const mem *>(G + (i64)row * ld + c));
+            const vec v = MOM ? __builtin_nontemporal_load(reinterpret_cast<const mem *>(Vel + (i64)row * ld + c)) : g;
+            const vec x = __builtin_nontemporal_load(reinterpret_cast<const mem *>(Xin + (i64)rn * ld + c));
             form(row, q, x, step_dir(row, q, g, v));
         }
     }
@@ -346,6 +354,7 @@ mix_csr_slab_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
                     float gamma, int rgroups, double *__restrict__ partials, float *__restrict__ Vel, float mu)
 {
     typedef typename VecT<V>::type vec;
+    typedef typename MemT<V>::type mem;
     extern __shared__ float lds[];
     vec *slab = reinterpret_cast<vec *>(lds);   // [n][64]
     const int lane = threadIdx.x & 63;
@@ -387,7 +396,7 @@ mix_csr_slab_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
         };
         auto gload = [&](int row) {
             if (SWAPPED) return (vec)(0.f);
-            vec g = __builtin_nontemporal_load(reinterpret_cast<const vec *>(gin + (i64)row * ld));
+            vec g = __builtin_nontemporal_load(reinterpret_cast<const mem *>(gin + (i64)row * ld));
             if (Vel) {
                 float *vdst = Vel + c0 + (i64)row * ld;
                 g = mu * vload<V>(vdst) + g;
@@ -429,6 +438,7 @@ mix_csr_slab_wide_kernel(const float *Xin, const float *__restrict__ G, float *X
                          float gamma, int rgroups, double *__restrict__ partials, float *__restrict__ Vel, float mu)
 {
     typedef VecT<4>::type vec;
+    typedef MemT<4>::type mem;
     extern __shared__ float lds[];
     vec *slab = reinterpret_cast<vec *>(lds);
     const int lane = threadIdx.x & 63;
@@ -438,7 +448,7 @@ mix_csr_slab_wide_kernel(const float *Xin, const float *__restrict__ G, float *X
     auto stage = [&](int row, vec (&x)[SP]) {
 #pragma unroll
         for (int q = 0; q < SP; ++q) {
-            x[q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(Xin + (i64)row * ld + c0 + q * 16384));
+            x[q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(Xin + (i64)row * ld + c0 + q * 16384));
             if (SWAPPED) x[q] = x[q] - gamma * vload<4>(G + (i64)row * ld + c0 + q * 16384);
         }
     };
@@ -470,7 +480,7 @@ mix_csr_slab_wide_kernel(const float *Xin, const float *__restrict__ G, float *X
 #pragma unroll
         for (int q = 0; q < SP; ++q) {
             if (SWAPPED) { g[q] = (vec)(0.f); continue; }
-            g[q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(G + (i64)row * ld + c0 + q * 16384));
+            g[q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(G + (i64)row * ld + c0 + q * 16384));
             if (Vel) {
                 float *vdst = Vel + (i64)row * ld + c0 + q * 16384;
                 g[q] = mu * vload<4>(vdst) + g[q];
@@ -492,7 +502,7 @@ mix_csr_slab_wide_kernel(const float *Xin, const float *__restrict__ G, float *X
 #pragma unroll
         for (int q = 0; q < SP; ++q) {
             const vec o = SWAPPED ? acc[q] : acc[q] - gamma * g[q];
-            __builtin_nontemporal_store(o, reinterpret_cast<vec *>(Xout + (i64)row * ld + c0 + q * 16384));
+            __builtin_nontemporal_store(o, reinterpret_cast<mem *>(Xout + (i64)row * ld + c0 + q * 16384));
             if (CONS) st[q].add(o);
         }
     };
@@ -562,6 +572,7 @@ column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int b
                     float *__restrict__ xbar, double *__restrict__ partials)
 {
     typedef typename VecT<V>::type vec;
+    typedef typename MemT<V>::type mem;
     extern __shared__ float lds[];
     const int lane = threadIdx.x & 63;
     const int band = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -575,7 +586,7 @@ column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int b
         const float *x = X + c0;
 #pragma unroll 4
         for (int row = r0; row < r1; ++row) {
-            vec v = __builtin_nontemporal_load(reinterpret_cast<const vec *>(x + (i64)row * ld));
+            vec v = __builtin_nontemporal_load(reinterpret_cast<const mem *>(x + (i64)row * ld));
             if (MEAN) sum += v;
             if (CONS) st.add(v);
         }
@@ -602,12 +613,13 @@ column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int b
 
 // The node average of a wide matrix with fat lanes and the chunked column ownership of mix_ring_fat_kernel (one wave
 // per workgroup, P float4 column groups per lane, 512-byte chunks 32 KB apart): the same sums in the same order
-// (rows ascending), read faster.  grid.x = 64 x (ncols / fat_super<P>()), block 64; 16-byte aligned rows.
+// (rows ascending), read faster.  grid.x = 64 x (ncols / fat_super<P>()), block 64; 16-byte accesses at any float.
 template <int P>
 __global__ void __launch_bounds__(64)
 column_mean_fat_kernel(const float *__restrict__ X, int n, i64 ld, float inv_n, float *__restrict__ xbar)
 {
     typedef VecT<4>::type vec;
+    typedef MemT<4>::type mem;
     const int lane = threadIdx.x;
     constexpr i64 kPerSuper = kFatStride / (kFatChunkLanes * 4);
     constexpr i64 kStep = (64 / kFatChunkLanes) * kFatStride;
@@ -622,8 +634,8 @@ column_mean_fat_kernel(const float *__restrict__ X, int n, i64 ld, float inv_n, 
         vec a[P], b[P];
 #pragma unroll
         for (int q = 0; q < P; ++q) {
-            a[q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(X + (i64)row * ld + c0 + (i64)q * kStep));
-            b[q] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(X + (i64)(row + 1) * ld + c0 + (i64)q * kStep));
+            a[q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(X + (i64)row * ld + c0 + (i64)q * kStep));
+            b[q] = __builtin_nontemporal_load(reinterpret_cast<const mem *>(X + (i64)(row + 1) * ld + c0 + (i64)q * kStep));
         }
 #pragma unroll
         for (int q = 0; q < P; ++q) {
@@ -634,7 +646,7 @@ column_mean_fat_kernel(const float *__restrict__ X, int n, i64 ld, float inv_n, 
     for (; row < n; ++row)
 #pragma unroll
         for (int q = 0; q < P; ++q)
-            sum[q] += __builtin_nontemporal_load(reinterpret_cast<const vec *>(X + (i64)row * ld + c0 + (i64)q * kStep));
+            sum[q] += __builtin_nontemporal_load(reinterpret_cast<const mem *>(X + (i64)row * ld + c0 + (i64)q * kStep));
 #pragma unroll
     for (int q = 0; q < P; ++q) vstore<4>(xbar + c0 + (i64)q * kStep, sum[q] * inv_n);
 }
@@ -706,19 +718,13 @@ struct Plan {
     i64 tail_cols;  // remaining columns, handled with vec = 1
 };
 
-bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
-
-int pick_vec(const dpsgd_ctx *ctx, std::initializer_list<const void *> ptrs, int cap)
+// Floats per lane: 4 (16-byte accesses work at any float) unless the option or the LDS slab allows less.
+int pick_vec(const dpsgd_ctx *ctx, int64_t cols, int cap)
 {
     int v = 4;
     if (ctx->opt_mix_vec) v = ctx->opt_mix_vec;
     if (v > cap) v = cap;
-    while (v > 1) {
-        bool ok = (ctx->ld % v) == 0;
-        for (const void *p : ptrs) ok = ok && aligned(p, sizeof(float) * (size_t)v);
-        if (ok && ctx->d >= v) break;
-        v >>= 1;
-    }
+    while (v > 1 && cols < v) v >>= 1;
     return v;
 }
 
@@ -808,6 +814,14 @@ dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
 
 constexpr size_t kSlabLdsBudget = 64 * 1024;
 
+// Whether pieces of rows that start a multiple of 32 floats behind these pointers are whole 128-byte lines in every row.
+bool whole_lines(const dpsgd_ctx *ctx, std::initializer_list<const void *> ptrs)
+{
+    bool ok = (ctx->ld % 32) == 0;
+    for (const void *p : ptrs) ok = ok && (reinterpret_cast<uintptr_t>(p) % 128) == 0;
+    return ok;
+}
+
 // Wide part of a slab launch: whole super-blocks with SP float4 per lane.  Returns the columns it took (0: none).
 template <int SP, bool SWAPPED>
 dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float *Xout, i64 col0, i64 ncols, bool cons,
@@ -819,23 +833,17 @@ dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, 
     const int rgroups = ctx->n < 8 ? ctx->n : (SP > 1 ? 8 : 4);
     size_t shm = (size_t)ctx->n * 64 * SP * 16;
     if (cons && stats_lds_bytes(rgroups, 4) > shm) shm = stats_lds_bytes(rgroups, 4);
-    if (cons) {
-        auto k = mix_csr_slab_wide_kernel<SP, true, SWAPPED>;
+    auto launch = [&](auto k) {
         if (shm > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
             return DPSGD_EDEVICE;
         hipLaunchKernelGGL(k, dim3((unsigned)groups), dim3(64u * (unsigned)rgroups), shm, ctx->stream, Xin + col0, G + col0,
                            Xout + col0, ctx->n, ctx->ld, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals, ctx->gamma, rgroups,
                            partials, vel, mu);
-    } else {
-        auto k = mix_csr_slab_wide_kernel<SP, false, SWAPPED>;
-        if (shm > 64 * 1024 &&
-            hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
-            return DPSGD_EDEVICE;
-        hipLaunchKernelGGL(k, dim3((unsigned)groups), dim3(64u * (unsigned)rgroups), shm, ctx->stream, Xin + col0, G + col0,
-                           Xout + col0, ctx->n, ctx->ld, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals, ctx->gamma, rgroups,
-                           partials, vel, mu);
-    }
+        return hip_status(hipGetLastError());
+    };
+    const dpsgd_status st = cons ? launch(mix_csr_slab_wide_kernel<SP, true, SWAPPED>) : launch(mix_csr_slab_wide_kernel<SP, false, SWAPPED>);
+    if (st != DPSGD_OK) return st;
     *cols_done = supers * slab_super<SP>();
     *parts = groups;
     return hip_status(hipGetLastError());
@@ -850,7 +858,9 @@ dpsgd_status slab_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     float *vel = Vel ? Vel + col0 : nullptr;
     // wide matrices: whole super-blocks of columns with the chunked column ownership, the rest consecutively
     i64 done = 0, parts = 0;
-    if (V == 4 && !ctx->opt_mix_narrow) {
+    // (chunks that share cache lines with the chunk of another workgroup lose more than the channels gain: 24 workers x
+    // 1 250 003 without padding, momentum and mean: 139 us against 118 with consecutive columns, padded 112)
+    if (V == 4 && !ctx->opt_mix_narrow && whole_lines(ctx, {Xin + col0, G + col0, Xout + col0})) {
         dpsgd_status st = DPSGD_OK;
         if (ncols / slab_super<2>() >= 16 && (size_t)ctx->n * 64 * 2 * 16 <= kSlabWideLdsBudget && ctx->opt_mix_vec != 1)
             st = slab_wide_launch<2, SWAPPED>(ctx, Xin, G, Xout, col0, ncols, cons, partials, vel, mu, &done, &parts);
@@ -861,7 +871,10 @@ dpsgd_status slab_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     const i64 groups = groups_for(ncols - done, V);
     if (groups > 0x7fffffffLL) return DPSGD_EUNSUPPORTED;
     if (groups > 0) {
-        int rgroups = ctx->n < 4 ? ctx->n : 4;
+        // a wave per four rows, 4 to 16 of them: with many workers the slab leaves a CU one or two workgroups, and what
+        // a wave waits for (112 x 268 365: 117 us with 4 waves, 90 with 8, 79 with 16; 24 x 1 500 000: 85 either way)
+        int rgroups = ctx->n / 4 < 4 ? 4 : ctx->n / 4 > 16 ? 16 : ctx->n / 4;
+        if (rgroups > ctx->n) rgroups = ctx->n;
         size_t shm = (size_t)ctx->n * 64 * V * sizeof(float);
         const size_t stats = stats_lds_bytes(rgroups, V);
         if (cons && stats > shm) shm = stats;
@@ -925,7 +938,7 @@ dpsgd_status finalize_consensus(dpsgd_ctx *ctx, i64 count, float *consensus)
 // cannot accumulate it).
 dpsgd_status consensus_of(dpsgd_ctx *ctx, const float *X, float *consensus)
 {
-    const int vec = pick_vec(ctx, {X}, 4);
+    const int vec = pick_vec(ctx, ctx->d, 4);
     const Plan p = make_plan(ctx, vec);
     i64 n1 = 0, n2 = 0;
     dpsgd_status st = DPSGD_OK;
@@ -958,7 +971,7 @@ dpsgd_status launch_mix(dpsgd_ctx *ctx, const float *Xin, const float *G, float 
     dpsgd_status st = DPSGD_OK;
 
     if (ring) {
-        const int vec = pick_vec(ctx, {Xin, G, Xout, Vel ? Vel : Xin}, 4);
+        const int vec = pick_vec(ctx, ctx->d, 4);
         const Plan p = make_plan(ctx, vec);
         // the columns beyond the last whole vector ride along in the bulk launch (its last workgroup)
         const int tail = (int)p.tail_cols;
@@ -977,7 +990,9 @@ dpsgd_status launch_mix(dpsgd_ctx *ctx, const float *Xin, const float *G, float 
     int cap = 4;
     while (cap >= 1 && (size_t)ctx->n * 64 * cap * sizeof(float) > kSlabLdsBudget) cap >>= 1;
     if (cap >= 1) {
-        const int vec = pick_vec(ctx, {Xin, G, Xout, Vel ? Vel : Xin}, cap);
+        int vec = pick_vec(ctx, ctx->d, cap);
+        if (!ctx->opt_mix_vec)   // narrow matrix: more, narrower column groups (64 x 30 730 on a torus: 24 -> 13.5 us; twice as many: 13.6)
+            while (vec > 1 && groups_for(ctx->d, vec) < 128) vec >>= 1;
         const Plan p = make_plan(ctx, vec);
 #define DPSGD_SLAB(V, C0, NC, PART, NP)                                                              \
     (swapped ? slab_launch<V, true>(ctx, Xin, G, Xout, C0, NC, cons, PART, NP)                       \
@@ -1022,13 +1037,8 @@ dpsgd_status launch_mix_range(dpsgd_ctx *ctx, const float *Xin, const float *G, 
         while (cap >= 1 && (size_t)ctx->n * 64 * cap * sizeof(float) > kSlabLdsBudget) cap >>= 1;
         if (cap < 1) return DPSGD_EUNSUPPORTED;
     }
-    int vec = cap;
-    while (vec > 1) {
-        const bool ok = (ctx->ld % vec) == 0 && aligned(Xin + col0, 4u * vec) && aligned(G + col0, 4u * vec) &&
-                        aligned(Xout + col0, 4u * vec) && ncols >= vec;
-        if (ok) break;
-        vec >>= 1;
-    }
+    int vec = cap;   // (the mix_vec option selects among whole-matrix launches only)
+    while (vec > 1 && ncols < vec) vec >>= 1;
     const i64 bulk = ncols - ncols % vec, tail = ncols - bulk;
     if (*nparts + groups_for(bulk, vec) + groups_for(tail, 1) + 2 > ctx->partials_cap - kStage1Blocks) return DPSGD_EINVAL;
     i64 n1 = 0, n2 = 0;
@@ -1061,7 +1071,7 @@ dpsgd_status launch_consensus_finalize(dpsgd_ctx *ctx, int64_t count, float *con
 
 dpsgd_status launch_mean(dpsgd_ctx *ctx, const float *X, float *xbar)
 {
-    const int vec = pick_vec(ctx, {X, xbar}, 4);
+    const int vec = pick_vec(ctx, ctx->d, 4);
     const Plan p = make_plan(ctx, vec);
     i64 np = 0;
     dpsgd_status st = DPSGD_OK;

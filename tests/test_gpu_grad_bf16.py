@@ -80,6 +80,37 @@ def test_mlp_bf16_ragged(widths, batch, n):
     grad_case(cfg, d + 1, bf16_inputs=False)     # odd row stride, fp32 inputs converted on the device
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((784, 500, 300, 10), 50, 3),      # small tiles forward and backward, class layer on rows of odd alignment
+    ((3, 2, 3), 5, 2),                 # rows of fewer than the 4 elements of a load
+    ((5, 4, 4), 33, 3),                # exactly 4
+    ((259, 130, 301, 10), 70, 2),      # small tiles of 64 samples, every extent ragged
+    ((513, 300, 26), 20, 2),           # a class layer of 26 outputs, 513 inputs copied to padded rows
+    ((64, 1001, 1003, 10), 32, 17),    # enough workers for the streaming tiles, on unaligned rows
+    ((60, 515, 258, 10), 65, 30),      # ... with minibatches of more than 64
+])
+def test_mlp_bf16_rows_at_any_alignment(widths, batch, n):
+    """Rows without padding (every layer starts at an odd float), bf16 inputs at an odd address too: the kernels that
+    load 16 bytes at any alignment, their small-tile variants, and the clamped ends of rows."""
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(cfg, d | 1)
+    X, inp, tgt = mlp_inputs(cfg)
+    Xd, tgt_d = to_dev(X, d | 1), torch.from_numpy(tgt).cuda()
+    flat = bf16_dev(inp).reshape(-1)
+    odd = torch.empty(flat.numel() + 1, dtype=torch.bfloat16, device="cuda")
+    odd[1:] = flat
+    got = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d | 1) as ctx:
+        for a in (flat, odd[1:]):
+            Gd, loss = torch.zeros_like(Xd), torch.zeros(n, device="cuda")
+            ctx.grad(B.Model(cfg.model_kind, cfg.widths, compute_bf16=True), Xd, a, tgt_d, batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            got.append((Gd.cpu().numpy()[:, :d], loss.cpu().numpy()))
+    # (another forward kernel may take the misaligned inputs: another order of the same sums)
+    check_close(got[1][0], got[0][0], 2 * TIGHT, "inputs at an odd address", flips=True)
+
+
 def test_softmax_regression_bf16():
     cfg = shrink(CONFIGS[1], widths=(3072, 10), batch=128, n=3, bf16=True)
     d = synth.model_dim(MODEL_SOFTMAX, cfg.widths)

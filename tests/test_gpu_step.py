@@ -177,8 +177,7 @@ def test_step_falls_back_on_other_topologies_and_fp32():
 
 
 def test_step_with_odd_row_stride():
-    """Row stride d + 1: rows are only 4-byte aligned.  The ring kernel still fuses (4-byte accesses); the torus
-    kernel needs 8-byte aligned rows and hands over to the two calls."""
+    """Row stride d + 1: rows are only 4-byte aligned, which the fused kernels' wider accesses do not mind."""
     for cfg in (shrink(CONFIGS[2], widths=(1024, 1024, 10), batch=32, n=5),
                 shrink(CONFIG3_TORUS, widths=(1024, 1024, 10), batch=32, n=12, torus_dims=(3, 4))):
         step_case(cfg, ld=synth.model_dim(cfg.model_kind, cfg.widths) + 1)

@@ -969,6 +969,100 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
     }
 }
 
+// The weight gradient of minibatches of more than 64 samples, where the kernel above is bound by the operands it pulls
+// from L2, 2 KB per matrix instruction (8 workers x 512 samples x 3072 x 1024: 120 us; here 57, with four steps of operands
+// in flight and half the workgroups per CU 69; its 26 GFLOP and 100 MB of results are worth about 25 each).  A workgroup
+// owns a [128 o][128 k] tile, each of its four waves 64 x 64 of it; the operands travel from L2 into LDS asynchronously
+// (16 bytes per lane, no registers), kWgStep steps of 16 samples at a time into the other of two buffers, and are shared
+// by two waves each: 512 bytes from L2 per instruction.  The same instructions on the same operands in the same order: the
+// same bits.
+// grid (ceil(K / 128), ceil(O / 128), n), block 256, dynamic LDS 2 x kWgStep x 8 KB.
+constexpr int kWgStep = 2;
+
+__global__ void __launch_bounds__(256, 4) mlp_wgrad_big_kernel(WgradArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    u32x4 *lds = reinterpret_cast<u32x4 *>(smem);   // [2][kWgStep][8 groups: 4 of o, 4 of k][64]
+    const int w = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int o0 = blockIdx.y * 128, k0 = blockIdx.x * 128;
+    const int wo = wave >> 1, wk = wave & 1;
+    const int steps = g.Bp / 16;
+    // wave v brings the groups v (of o) and 4 + v (of k); groups beyond the matrix repeat the last one (never stored)
+    const int og = min((o0 >> 5) + wave, (g.O + 31) / 32 - 1), kg = min((k0 >> 5) + wave, (g.K + 31) / 32 - 1);
+    const bf16_t *ao = g.dzt + tfrag_worker(w, g.O, g.Bp) + (i64)og * steps * 512 + lane * 8;
+    const bf16_t *ak = g.at + tfrag_worker(w, g.K, g.Bp) + (i64)kg * steps * 512 + lane * 8;
+    auto request = [&](int buf, int st0) {
+#pragma unroll
+        for (int e = 0; e < kWgStep; ++e) {
+            if (st0 + e >= steps) break;
+            u32x4 *dst = lds + (buf * kWgStep + e) * 512;
+            __builtin_amdgcn_global_load_lds(ao + (i64)(st0 + e) * 512, dst + wave * 64, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(ak + (i64)(st0 + e) * 512, dst + (4 + wave) * 64, 16, 0, 0);
+        }
+    };
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    request(0, 0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    for (int st0 = 0, buf = 0; st0 < steps; st0 += kWgStep, buf ^= 1) {
+        if (st0 + kWgStep < steps) request(buf ^ 1, st0 + kWgStep);   // (its readers passed the barrier below)
+#pragma unroll
+        for (int e = 0; e < kWgStep; ++e) {
+            if (st0 + e >= steps) break;
+            const u32x4 *src = lds + (buf * kWgStep + e) * 512 + lane;
+            bf16x8 a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i] = __builtin_bit_cast(bf16x8, src[(2 * wo + i) * 64]);
+                b[i] = __builtin_bit_cast(bf16x8, src[(4 + 2 * wk + i) * 64]);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0);   // what was requested has arrived, for every wave, before anyone reads it
+        __syncthreads();
+    }
+    if (blockIdx.x == 0 && wk == 0) {   // bias gradient: gb[o] = sum_b dZ[b][o]
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int o = o0 + wo * 64 + i * 32 + l32;
+            if (o0 + wo * 64 + i * 32 >= g.O) continue;
+            const bf16_t *p = g.dzt + tfrag_worker(w, g.O, g.Bp) + (i64)(o >> 5) * steps * 512 + lane * 8;
+            float s = 0.f;
+            for (int st = 0; st < steps; ++st)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s += bf2f(p[st * 512 + j]);
+            s += __shfl_down(s, 32, 64);
+            if (half == 0 && o < g.O) g.G[(i64)w * g.ld + g.boff + o] = s;
+        }
+    }
+    float *Gw = g.G + (i64)w * g.ld + g.woff;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = k0 + wk * 64 + j * 32 + l32;
+        if (k >= g.K) continue;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int o = o0 + wo * 64 + i * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+                if (o >= g.O) continue;
+                if (g.whole_lines) __builtin_nontemporal_store(acc[i][j][v], Gw + (i64)o * g.K + k);
+                else Gw[(i64)o * g.K + k] = acc[i][j][v];
+            }
+    }
+}
+
 // ------------------------------------------------------------------------- data gradient
 struct DgradArgs {
     const bf16_t *dz;     // [n][B][act_pitch(O)]
@@ -1277,12 +1371,12 @@ __global__ void __launch_bounds__(256) mlp_dgrad_small_kernel(DgradArgs g)
 // and the bias gradient of the layer below are each a few FMAs per element of the activation matrix h below it, and
 // as three launches of the tiled kernels above they are 3/4 padding.  Here a thread owns one column k of h and the
 // SG groups of 256 / SG threads of a workgroup deal the samples among themselves in octets (group s takes octets s,
-// s + SG, ...; SG = 4 for minibatches of 64 rows and more, else 1: a thread walks all samples):
+// s + SG, ...; SG = 8 for minibatches of 256 rows and more, 4 from 64 rows, else 1: a thread walks all samples):
 // dW[c][k] += dZ[b][c] h[b][k], dZ'[b][k] = [h[b][k] > 0] sum_c dZ[b][c] bf16(W[c][k]), db'[k] += bf16(dZ'[b][k]) -
 // the operands and roundings of the kernels it replaces (bf16 deltas, activations and weights, fp32 sums).  A thread
 // requests up to 32 samples of its column at once (the launch is bound by that round trip, not by arithmetic); the
 // SG partial sums of dW and db' meet in LDS and are added in group order.  The worker's deltas sit in LDS as fp32.
-// grid (ceil(act_pitch(K) SG / 256), n), block 256; C <= CP <= 16 (the arithmetic is unrolled for CP outputs), Bp <= 256.
+// grid (ceil(act_pitch(K) SG / 256), n), block 256; C <= CP <= 16 (the arithmetic is unrolled for CP outputs).
 struct ClassBwdArgs {
     const bf16_t *dz;     // [n][B][act_pitch(C)] deltas of the class layer
     const bf16_t *h;      // [n][B][act_pitch(K)] post-ReLU activations of the layer below
@@ -1308,16 +1402,6 @@ __global__ void __launch_bounds__(256) mlp_class_bwd_kernel(ClassBwdArgs g)
     const int w = blockIdx.y, k = blockIdx.x * NCOL + lane;
     const bool k_ok = k < g.K;
     const int ldk = act_pitch(g.K), ldc = act_pitch(g.C);
-    for (int e = threadIdx.x; e < g.Bp * 16; e += 256) {
-        const int b = e >> 4, c = e & 15;
-        dzs[b][c] = (b < g.B && c < g.C) ? bf2f(g.dz[((i64)w * g.B + b) * ldc + c]) : 0.f;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0 && (int)threadIdx.x < g.C) {   // bias gradient of the class layer
-        float s = 0.f;
-        for (int b = 0; b < g.B; ++b) s += dzs[b][threadIdx.x];
-        g.G[(i64)w * g.ld + g.boff + threadIdx.x] = s;
-    }
     if (blockIdx.x == 0 && threadIdx.x == 64 && g.loss_part && g.loss) {   // the worker's loss: partial sums in order
         float s = 0.f;
         for (int c = 0; c < g.chunks; ++c) s += g.loss_part[(i64)w * g.chunks + c];
@@ -1331,44 +1415,67 @@ __global__ void __launch_bounds__(256) mlp_class_bwd_kernel(ClassBwdArgs g)
     }
     const bf16_t *hp = g.h + (i64)w * g.B * ldk + (k_ok ? k : 0);
     bf16_t *dst_t = g.dzpt + tfrag_worker(w, g.K, g.Bp);
-    float db = 0.f;
-    const int noct = g.Bp >> 3;
-    for (int base = 0; base < noct; base += 4 * SG) {
-        bf16_t hv[4][8];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int b0 = (base + SG * jj + sg) * 8;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) hv[jj][j] = b0 + j < g.B ? hp[(i64)(b0 + j) * ldk] : (bf16_t)0;
+    float db = 0.f, dbc = 0.f;
+    for (int part = 0; part < g.Bp; part += 256) {   // the deltas of up to 256 samples at a time in LDS
+        const int np = g.Bp - part < 256 ? g.Bp - part : 256;
+        if (part > 0) __syncthreads();
+        for (int e = threadIdx.x; e < np * 16; e += 256) {
+            const int b = part + (e >> 4), c = e & 15;
+            dzs[e >> 4][c] = (b < g.B && c < g.C) ? bf2f(g.dz[((i64)w * g.B + b) * ldc + c]) : 0.f;
         }
+        __syncthreads();
+        if (blockIdx.x == 0) {   // bias gradient of the class layer: 16 threads a class, meeting below (dzs is zero beyond B)
+            const int c = threadIdx.x & 15;
+            for (int b = threadIdx.x >> 4; b < np; b += 16) dbc += dzs[b][c];
+        }
+        const int noct = np >> 3;
+        for (int base = 0; base < noct; base += 4 * SG) {
+            bf16_t hv[4][8];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int oc = base + SG * jj + sg;
-            if (oc >= noct) break;
-            const int b0 = oc * 8;
-            unsigned short out[8];
+            for (int jj = 0; jj < 4; ++jj) {
+                const int b0 = part + (base + SG * jj + sg) * 8;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int b = b0 + j;
-                const bf16_t hraw = hv[jj][j];
-                const float hf = bf2f(hraw);
-                float da = 0.f;
-#pragma unroll
-                for (int c = 0; c < CP; ++c) {
-                    const float d = dzs[b][c];
-                    da = __builtin_fmaf(d, wb[c], da);
-                    gw[c] = __builtin_fmaf(d, hf, gw[c]);
-                }
-                const bool pos = (hraw & 0x7fffu) != 0 && (hraw & 0x8000u) == 0;   // ReLU'(z) = [z > 0]
-                const bf16_t v = f2bf(pos ? da : 0.f);
-                out[j] = v;
-                db += bf2f(v);
-                if (g.dzp && b < g.B && k < ldk) g.dzp[((i64)w * g.B + b) * ldk + k] = k_ok ? v : (bf16_t)0;
+                for (int j = 0; j < 8; ++j) hv[jj][j] = b0 + j < g.B ? hp[(i64)(b0 + j) * ldk] : (bf16_t)0;
             }
-            const u32x4 pk = {(unsigned)out[0] | ((unsigned)out[1] << 16), (unsigned)out[2] | ((unsigned)out[3] << 16),
-                              (unsigned)out[4] | ((unsigned)out[5] << 16), (unsigned)out[6] | ((unsigned)out[7] << 16)};
-            if (k_ok) *reinterpret_cast<u32x4 *>(dst_t + tfrag_off(k, b0, g.Bp)) = pk;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int oc = base + SG * jj + sg;
+                if (oc >= noct) break;
+                const int b0 = part + oc * 8;
+                unsigned short out[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int b = b0 + j;
+                    const bf16_t hraw = hv[jj][j];
+                    const float hf = bf2f(hraw);
+                    float da = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CP; ++c) {
+                        const float d = dzs[oc * 8 + j][c];
+                        da = __builtin_fmaf(d, wb[c], da);
+                        gw[c] = __builtin_fmaf(d, hf, gw[c]);
+                    }
+                    const bool pos = (hraw & 0x7fffu) != 0 && (hraw & 0x8000u) == 0;   // ReLU'(z) = [z > 0]
+                    const bf16_t v = f2bf(pos ? da : 0.f);
+                    out[j] = v;
+                    db += bf2f(v);
+                    if (g.dzp && b < g.B && k < ldk) g.dzp[((i64)w * g.B + b) * ldk + k] = k_ok ? v : (bf16_t)0;
+                }
+                const u32x4 pk = {(unsigned)out[0] | ((unsigned)out[1] << 16), (unsigned)out[2] | ((unsigned)out[3] << 16),
+                                  (unsigned)out[4] | ((unsigned)out[5] << 16), (unsigned)out[6] | ((unsigned)out[7] << 16)};
+                if (k_ok) *reinterpret_cast<u32x4 *>(dst_t + tfrag_off(k, b0, g.Bp)) = pk;
+            }
         }
+    }
+    if (blockIdx.x == 0) {   // sums of threads 16 apart: within a wave by shuffles, then over the four waves
+        dbc += __shfl_down(dbc, 32, 64);
+        dbc += __shfl_down(dbc, 16, 64);
+        __syncthreads();
+        float *bs = &dzs[0][0];
+        if ((threadIdx.x & 63) < 16) bs[(threadIdx.x >> 6) * 16 + (threadIdx.x & 15)] = dbc;
+        __syncthreads();
+        if ((int)threadIdx.x < g.C)
+            g.G[(i64)w * g.ld + g.boff + threadIdx.x] = (bs[threadIdx.x] + bs[16 + threadIdx.x]) + (bs[32 + threadIdx.x] + bs[48 + threadIdx.x]);
     }
     if (SG == 1) {
         if (!k_ok) return;
@@ -2379,7 +2486,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
     auto may_copy = [&](int l) { return fuse && l > 0 && ctx->ring_uniform && layer_fusable(ctx, m.widths[l], m.widths[l + 1], woff[l]); };
     // a class layer of at most 16 outputs on top of a hidden layer: its backward is one launch (mlp_class_bwd_kernel)
     // and the softmax rides in its forward launch
-    const bool class_path = L > 1 && m.widths[L] <= 16 && Bp <= 256 && ctx->opt_class_bwd &&
+    const bool class_path = L > 1 && m.widths[L] <= 16 && ctx->opt_class_bwd &&
                             !(fuse && layer_fusable(ctx, m.widths[L - 1], m.widths[L], woff[L - 1]));
     bool softmax_in_fwd = false;
     for (int l = 0; l < L && st == DPSGD_OK; ++l) {
@@ -2434,9 +2541,13 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             ca.dzpt = ws.dzt[l];
             ca.B = B; ca.Bp = Bp; ca.K = K; ca.C = O;
             ca.loss_part = softmax_in_fwd ? ws.loss_part : nullptr; ca.chunks = (B + 31) / 32; ca.loss = loss;
-            const int sgroups = Bp >= 64 ? 4 : 1;   // sample groups per workgroup, 256 / sgroups columns each
+            // sample groups per workgroup, 256 / sgroups columns each
+            const int sgroups = Bp >= 256 ? 8 : Bp >= 64 ? 4 : 1;
             const dim3 cgrid((unsigned)(((i64)act_pitch(K) * sgroups + 255) / 256), (unsigned)n);
-            if (sgroups == 4) {
+            if (sgroups == 8) {
+                if (O <= 10) hipLaunchKernelGGL((mlp_class_bwd_kernel<10, 8>), cgrid, dim3(256), 0, s, ca);
+                else hipLaunchKernelGGL((mlp_class_bwd_kernel<16, 8>), cgrid, dim3(256), 0, s, ca);
+            } else if (sgroups == 4) {
                 if (O <= 10) hipLaunchKernelGGL((mlp_class_bwd_kernel<10, 4>), cgrid, dim3(256), 0, s, ca);
                 else hipLaunchKernelGGL((mlp_class_bwd_kernel<16, 4>), cgrid, dim3(256), 0, s, ca);
             } else {
@@ -2457,7 +2568,14 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             wa.dzt = ws.dzt[l + 1]; wa.at = actt[l]; wa.G = G; wa.ld = ctx->ld; wa.woff = woff[l]; wa.boff = boff[l];
             wa.Bp = Bp; wa.K = K; wa.O = O;
             wa.whole_lines = (K % 32) == 0 && (woff[l] % 32) == 0 && (ctx->ld % 32) == 0 && (reinterpret_cast<uintptr_t>(G) % 128) == 0;
-            if (O <= 32) {
+            const dim3 wgrid_big((unsigned)((K + 127) / 128), (unsigned)((O + 127) / 128), (unsigned)n);
+            // 128 x 128 tiles for minibatches of more than 64 samples where they leave no CU idle.  us per step with smaller
+            // tiles / with these: 4 x 1024-4096-10 x 65 (1024 workgroups) 125 / 117, 6 x 1024-1024-10 x 256 (384) 98.3 / 96.4,
+            // 4 x 1024-1024-10 x 128 (256) 65.8 / 66.4; below 256 12 x 784-300-100-10 x 512 (252) 181 / 187,
+            // 4 x 784-500-300-10 x 100 (112) 83.8 / 87.2, 1 x 3072-1024-10 x 512 (192) 96.4 / 94.4
+            if (Bp > 64 && O >= 64 && K >= 64 && (i64)wgrid_big.x * wgrid_big.y * n >= 256) {
+                hipLaunchKernelGGL(mlp_wgrad_big_kernel, wgrid_big, dim3(256), (size_t)2 * kWgStep * 8192, s, wa);
+            } else if (O <= 32) {
                 dim3 wgrid((unsigned)((K + 127) / 128), (unsigned)((O + 31) / 32), (unsigned)n);
                 hipLaunchKernelGGL(mlp_wgrad_kernel<true>, wgrid, dim3(256), 0, s, wa);
             } else {

@@ -81,6 +81,18 @@ def test_mlp_bf16_ragged(widths, batch, n):
 
 
 @pytest.mark.parametrize("widths,batch,n", [
+    ((200, 130, 257, 10), 70, 64),     # 256 and 384 weight-gradient tiles of 128 x 128, every extent ragged, 6 steps of 16
+    ((96, 64, 128, 16), 300, 256),     # exact halves and wholes of a tile; class layer over two parts of 256 samples
+    ((64, 96, 10), 513, 2),            # ... over three, the last of one sample
+])
+def test_mlp_bf16_large_minibatches(widths, batch, n):
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(cfg, synth.padded_stride(d))
+    grad_case(cfg, d | 1)
+
+
+@pytest.mark.parametrize("widths,batch,n", [
     ((784, 500, 300, 10), 50, 3),      # small tiles forward and backward, class layer on rows of odd alignment
     ((3, 2, 3), 5, 2),                 # rows of fewer than the 4 elements of a load
     ((5, 4, 4), 33, 3),                # exactly 4

@@ -669,15 +669,22 @@ __global__ void __launch_bounds__(256) mlp_fwd_ksplit_kernel(FwdArgs g)
 }
 
 // Few workers or narrow layers, where the tiles of the kernels above would leave most CUs without one and a workgroup
-// would walk the whole contraction alone: 32 outputs x 32 MT samples per workgroup, whose four waves each take a quarter
-// of every 128-wide chunk and meet in LDS at the end (in wave order).  Rows at any alignment, of any length from 4 on.
+// would walk the whole contraction alone: 32 outputs x 32 MT samples per workgroup, 128 elements of the contraction staged
+// per step by all four waves, three steps ahead.  The sums are formed in the order of the kernel it stands in for (the same
+// bits: a unit whose input changes in its last bit may change sides at zero), whose tiles are `tcols` wide and whose walk
+// starts at a chunk of `chunk` elements that depends on the tile: wave 0 and, with MT = 2, wave 1 walk it for 32 samples
+// each; with MT = 1 wave 1 takes the upper half of every chunk, as in the k-split kernel.  Four waves with a quarter of
+// every chunk each, in an order of their own, gain little (a step of 12 x 784-500-300-10 x 50, rows not padded: 94.9
+// against 97.2 us; the launch is bound by the round trips of its loads) and moved one worker's gradient by 7e-3 of its
+// norm in 58 x 552-448-3239-224-10 x 64.
+// Rows at any alignment, of any length from 4 on.
 // grid (ceil(act_pitch(O) / 32), ceil(B / (32 MT)), n), block 256.
 template <int MT, bool LAST>
-__global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g)
+__global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g, int tcols, int chunk)
 {
     constexpr int TO = 32, MBLK = 32 * MT, WQ = TO * KC2 / 4 / 256, AQ = MBLK * KC2 / 8 / 256;
-    constexpr int BUF = (TO + MBLK) * PITCH2, RED = 4 * MT * 16 * 64 * 2;   // bf16 elements
-    __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF > RED ? 2 * BUF : RED];
+    constexpr int BUF = (TO + MBLK) * PITCH2;   // bf16 elements
+    __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF];
     int w, tile;
     worker_tile_on_one_xcd(tile, w);
     const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
@@ -685,27 +692,36 @@ __global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g)
     const int l32 = lane & 31, half = lane >> 5;
     const float *Wg = g.X + (i64)w * g.ld + g.woff;
     const bf16_t *Ag = g.act + (i64)w * g.B * g.lda;
+    // the walk over the contraction in pieces of 64: piece p holds the elements from piece_k(p) on (past the last one: none)
+    const int per = chunk / 64, pieces = (g.K + chunk - 1) / chunk * per;
+    const int start = (int)((unsigned)(o0 / tcols * 5 + w * 3) % (unsigned)(pieces / per)) * per;
+    auto piece_k = [&](int p) {
+        const int q = p + start;
+        return p >= pieces ? g.K + 64 : (q >= pieces ? q - pieces : q) * 64;
+    };
     struct Chunk { f32x4 w[WQ]; u32x4 a[AQ]; };
     Chunk even, odd;   // chunks on their way
-    auto fetch = [&](int k0, Chunk &r) {
+    auto fetch = [&](int c, Chunk &r) {
+        const int klo = piece_k(2 * c), khi = piece_k(2 * c + 1) - 64;
 #pragma unroll
         for (int q = 0; q < AQ; ++q) {
-            const int u = tid + 256 * q, b = b0 + (u >> 4), k = k0 + (u & 15) * 8;
+            const int u = tid + 256 * q, b = b0 + (u >> 4), kq = (u & 15) * 8, k = (kq < 64 ? klo : khi) + kq;
             r.a[q] = *reinterpret_cast<const u32x4_a2 *>(Ag + (i64)min(b, g.B - 1) * g.lda + (k < g.lda ? k : 0));
         }
 #pragma unroll
         for (int q = 0; q < WQ; ++q) {
-            const int u = tid + 256 * q, o = o0 + (u >> 5), k = k0 + (u & 31) * 4;
-            r.w[q] = load4(Wg + (i64)min(o, g.O - 1) * g.K, k, g.K);
+            const int u = tid + 256 * q, o = o0 + (u >> 5), kq = (u & 31) * 4;
+            r.w[q] = load4(Wg + (i64)min(o, g.O - 1) * g.K, (kq < 64 ? klo : khi) + kq, g.K);
         }
     };
-    auto stage = [&](int buf, int k0, Chunk &r) {
+    auto stage = [&](int buf, int c, Chunk &r) {
         bf16_t *Wt = smem + buf * BUF, *At = Wt + TO * PITCH2;
-        if (o0 + TO > g.O || k0 + KC2 > g.K) {
+        const int klo = piece_k(2 * c), khi = piece_k(2 * c + 1) - 64;
+        if (o0 + TO > g.O || klo + 64 > g.K || khi + KC2 > g.K) {
 #pragma unroll
             for (int q = 0; q < WQ; ++q) {
-                const int u = tid + 256 * q;
-                r.w[q] = mend4(r.w[q], o0 + (u >> 5) < g.O ? g.K - (k0 + (u & 31) * 4) : 0);
+                const int u = tid + 256 * q, kq = (u & 31) * 4;
+                r.w[q] = mend4(r.w[q], o0 + (u >> 5) < g.O ? g.K - ((kq < 64 ? klo : khi) + kq) : 0);
             }
         }
 #pragma unroll
@@ -716,56 +732,52 @@ __global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g)
         }
 #pragma unroll
         for (int q = 0; q < AQ; ++q) {
-            const int u = tid + 256 * q;
+            const int u = tid + 256 * q, kq = (u & 15) * 8;
             u32x4 v = r.a[q];
-            if (!(b0 + (u >> 4) < g.B && k0 + (u & 15) * 8 < g.lda)) v = (u32x4){0u, 0u, 0u, 0u};
-            *reinterpret_cast<u32x4 *>(At + (u >> 4) * PITCH2 + (u & 15) * 8) = v;
+            if (!(b0 + (u >> 4) < g.B && (kq < 64 ? klo : khi) + kq < g.lda)) v = (u32x4){0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4 *>(At + (u >> 4) * PITCH2 + kq) = v;
         }
     };
-    f32x16 acc[MT];
+    f32x16 acc;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[m][v] = 0.f;
-    const int nchunks = (g.K + KC2 - 1) / KC2, last = nchunks - 1;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    const int nchunks = (pieces + 1) / 2, last = nchunks - 1;
     fetch(0, even);
-    fetch(min(1, last) * KC2, odd);
+    fetch(min(1, last), odd);
     stage(0, 0, even);
-    fetch(min(2, last) * KC2, even);
+    fetch(min(2, last), even);
     __syncthreads();
+    const int mofs = MT == 2 ? wave * 32 : 0, kofs = MT == 1 ? wave * 64 : 0;
     // chunk c is multiplied, chunk c + 1 (in r) goes to LDS, chunk c + 3 is requested (past the end the last one again)
     auto step = [&](int c, Chunk &r) {
-        const bf16_t *Wb = smem + (c & 1) * BUF + l32 * PITCH2 + wave * 32 + 8 * half, *Ab = Wb + TO * PITCH2;
+        if (wave < 2) {
+            const bf16_t *Wb = smem + (c & 1) * BUF + l32 * PITCH2 + kofs + 8 * half, *Ab = Wb + (TO + mofs) * PITCH2;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 bw = frag(Wb + ks * 16);
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(Ab + m * 32 * PITCH2 + ks * 16), bw, acc[m], 0, 0, 0);
+            for (int ks = 0; ks < (MT == 1 ? 4 : 8); ++ks)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(Ab + ks * 16), frag(Wb + ks * 16), acc, 0, 0, 0);
         }
-        stage((c & 1) ^ 1, min(c + 1, last) * KC2, r);
-        fetch(min(c + 3, last) * KC2, r);
+        stage((c & 1) ^ 1, min(c + 1, last), r);
+        fetch(min(c + 3, last), r);
         __syncthreads();
     };
     for (int c = 0; c < nchunks; c += 2) {
         step(c, odd);
         if (c + 1 < nchunks) step(c + 1, even);
     }
-    float *red = reinterpret_cast<float *>(smem);   // [wave][MT][16][64]
+    if (MT == 1) {
+        float *red = reinterpret_cast<float *>(smem);   // [16][64]
+        if (wave == 1) {
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+            for (int v = 0; v < 16; ++v) red[v * 64 + lane] = acc[v];
+        }
+        __syncthreads();
+        if (wave > 0) return;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) red[((wave * MT + m) * 16 + v) * 64 + lane] = acc[m][v];
-    __syncthreads();
-    if (wave >= MT) return;   // wave m finishes M tile m
-    f32x16 sum;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        sum[v] = red[(wave * 16 + v) * 64 + lane];
-#pragma unroll
-        for (int q = 1; q < 4; ++q) sum[v] += red[((q * MT + wave) * 16 + v) * 64 + lane];
+        for (int v = 0; v < 16; ++v) acc[v] += red[v * 64 + lane];
+    } else if (wave >= 2) {
+        return;
     }
-    fwd_store_tile<LAST>(g, w, o0 + l32, b0 + wave * 32, half, sum);
+    fwd_store_tile<LAST>(g, w, o0 + l32, b0 + mofs, half, acc);
 }
 
 // Class layer (at most 32 outputs): the tile above would be 3/4 padding and one workgroup per worker
@@ -2512,10 +2524,11 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             // (aligned rows and at most 32 samples: the k-split kernel already has 64-wide tiles and splits the contraction)
             const dim3 sgrid((unsigned)((act_pitch(a.O) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                              (unsigned)n);
-            if (t.mt == 1 && last) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, true>), sgrid, dim3(256), 0, s, a);
-            else if (t.mt == 1) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, false>), sgrid, dim3(256), 0, s, a);
-            else if (last) hipLaunchKernelGGL((mlp_fwd_small_kernel<2, true>), sgrid, dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((mlp_fwd_small_kernel<2, false>), sgrid, dim3(256), 0, s, a);
+            const int tcols = t.mt > 1 && t.wm == 1 ? 128 : 64, chunk = t.mt == 1 || (t.wm == 2 && vec) ? KC2 : KC;
+            if (t.mt == 1 && last) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, true>), sgrid, dim3(256), 0, s, a, tcols, chunk);
+            else if (t.mt == 1) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, false>), sgrid, dim3(256), 0, s, a, tcols, chunk);
+            else if (last) hipLaunchKernelGGL((mlp_fwd_small_kernel<2, true>), sgrid, dim3(256), 0, s, a, tcols, chunk);
+            else hipLaunchKernelGGL((mlp_fwd_small_kernel<2, false>), sgrid, dim3(256), 0, s, a, tcols, chunk);
             st = hip_status(hipGetLastError());
         } else if (t.mt == 1 || a.K < 4) st = fwd_ksplit_launch(s, n, a, vec, last);
         else if (t.wm == 1) st = fwd_launch<1, 4, 2>(s, n, a, vec, last);

@@ -131,14 +131,30 @@ __device__ __forceinline__ void combine_bands(ColStats<V> &st, float *lds, int b
     }
 }
 
+// A workgroup's consensus partial v (thread 0) goes to partials[part]; a launch of one workgroup forms the consensus
+// distance v / n from it (f.out set) instead of leaving that to a launch of its own: 8 x 64 least squares, gradient and
+// mix, 17.0 -> 13.5 us.  (With more workgroups, counted as their partials arrive so that the last one adds them up: no
+// faster than the extra launch, 16 x 30 730 48.2 against 47.3 us.)
+struct Finish {
+    float *out;      // consensus, or null: a later launch adds the partials up
+    double inv_n;
+};
+
+__device__ __forceinline__ void leave_partial(const Finish &f, double v, double *__restrict__ partials, i64 part)
+{
+    if (threadIdx.x != 0) return;
+    if (f.out) f.out[0] = (float)(v * f.inv_n);
+    else partials[part] = v;
+}
+
 // ------------------------------------------------------------------------------- ring
 // One column group of 64*V columns (group `grp`), walked by a workgroup of 64 * bands threads; wave b owns rows
-// [b*rpb, min(n,(b+1)*rpb)).  The group's consensus partial goes to partials[part].
+// [b*rpb, min(n,(b+1)*rpb)).  Returns the group's consensus partial (thread 0).
 // MOM: heavy-ball variant, the step uses v = mu * Vel + g and Vel is overwritten with it.
 template <int V, int U, bool CONS, bool MOM>
-__device__ __forceinline__ void ring_walk(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld,
-                                          float w, float gamma, int bands, int rpb, double *__restrict__ partials,
-                                          float *__restrict__ Vel, float mu, float *lds, i64 grp, i64 part)
+__device__ __forceinline__ double ring_walk(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld,
+                                            float w, float gamma, int bands, int rpb, float *__restrict__ Vel, float mu,
+                                            float *lds, i64 grp)
 {
     typedef typename VecT<V>::type vec;
     typedef typename MemT<V>::type mem;
@@ -219,13 +235,9 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
         }
         form(xhalo, step_dir(__builtin_nontemporal_load(reinterpret_cast<const mem *>(gp)), vp), op);
     }
-    if (CONS) {
-        combine_bands<V>(st, lds, band, lane, bands);
-        if (band == 0) {
-            double v = wave_sum((double)st.m2());
-            if (lane == 0) partials[part] = v;
-        }
-    }
+    if (!CONS) return 0.0;
+    combine_bands<V>(st, lds, band, lane, bands);
+    return band == 0 ? wave_sum((double)st.m2()) : 0.0;
 }
 
 // grid.x = column groups of 64*V columns (+ 1 when tail > 0); block = 64 * bands threads.  ncols is a multiple of V.
@@ -234,15 +246,17 @@ __device__ __forceinline__ void ring_walk(const float *Xin, const float *__restr
 template <int V, int U, bool CONS, bool MOM>
 __global__ void __launch_bounds__(512)
 mix_ring_kernel(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld, float w,
-                float gamma, int bands, int rpb, double *__restrict__ partials, float *__restrict__ Vel, float mu, int tail)
+                float gamma, int bands, int rpb, double *__restrict__ partials, float *__restrict__ Vel, float mu, int tail,
+                Finish fin)
 {
-    extern __shared__ float lds[];
-    if (V > 1 && tail > 0 && blockIdx.x == gridDim.x - 1) {
-        ring_walk<1, U, CONS, MOM>(Xin + ncols, G + ncols, Xout + ncols, n, tail, ld, w, gamma, bands, rpb, partials,
-                                   MOM ? Vel + ncols : nullptr, mu, lds, 0, blockIdx.x);
-        return;
-    }
-    ring_walk<V, U, CONS, MOM>(Xin, G, Xout, n, ncols, ld, w, gamma, bands, rpb, partials, Vel, mu, lds, blockIdx.x, blockIdx.x);
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    double v;
+    if (V > 1 && tail > 0 && blockIdx.x == gridDim.x - 1)
+        v = ring_walk<1, U, CONS, MOM>(Xin + ncols, G + ncols, Xout + ncols, n, tail, ld, w, gamma, bands, rpb,
+                                       MOM ? Vel + ncols : nullptr, mu, lds, 0);
+    else
+        v = ring_walk<V, U, CONS, MOM>(Xin, G, Xout, n, ncols, ld, w, gamma, bands, rpb, Vel, mu, lds, blockIdx.x);
+    if (CONS) leave_partial(fin, v, partials, blockIdx.x);
 }
 
 // The same walk for wide matrices with fat lanes: one wave per workgroup, every lane owns P float4 column groups, U
@@ -344,22 +358,21 @@ mix_ring_fat_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
 }
 
 // ------------------------------------------------------------------------ CSR via LDS slab
-// grid.x = column groups of 64*V columns; block = 64 * RG threads; lane = column vector,
-// wave = row group (rows rg, rg+RG, ...).  Dynamic LDS: n * 64 * V floats (+ stats region).
-// Vel != NULL (not with SWAPPED): heavy-ball variant, as in the ring kernel.
+// One column group of 64*V columns (group `grp`) by a workgroup of 64 * rgroups threads; lane = column vector,
+// wave = row group (rows rg, rg+RG, ...).  lds: n * 64 * V floats (+ stats region).  Returns the group's consensus
+// partial (thread 0).  Vel != NULL (not with SWAPPED): heavy-ball variant, as in the ring kernel.
 template <int V, bool CONS, bool SWAPPED>
-__global__ void __launch_bounds__(1024)
-mix_csr_slab_kernel(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld,
-                    const int *__restrict__ rowptr, const int *__restrict__ colidx, const float *__restrict__ vals,
-                    float gamma, int rgroups, double *__restrict__ partials, float *__restrict__ Vel, float mu)
+__device__ __forceinline__ double slab_walk(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld,
+                                            const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                            const float *__restrict__ vals, float gamma, int rgroups, float *__restrict__ Vel,
+                                            float mu, float *lds, i64 grp)
 {
     typedef typename VecT<V>::type vec;
     typedef typename MemT<V>::type mem;
-    extern __shared__ float lds[];
     vec *slab = reinterpret_cast<vec *>(lds);   // [n][64]
     const int lane = threadIdx.x & 63;
     const int rg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const i64 c0 = ((i64)blockIdx.x * 64 + lane) * V;
+    const i64 c0 = (grp * 64 + lane) * V;
     const bool active = c0 + V <= ncols;
     const float *xin = Xin + c0;
     const float *gin = G + c0;
@@ -414,14 +427,30 @@ mix_csr_slab_kernel(const float *Xin, const float *__restrict__ G, float *Xout, 
         }
         for (; row < n; row += rgroups) form(row, gload(row));
     }
-    if (CONS) {
-        __syncthreads();   // slab no longer needed; reuse LDS for the statistics
-        combine_bands<V>(st, lds, rg, lane, rgroups);
-        if (rg == 0) {
-            double v = wave_sum((double)st.m2());
-            if (lane == 0) partials[blockIdx.x] = v;
-        }
-    }
+    if (!CONS) return 0.0;
+    __syncthreads();   // slab no longer needed; reuse LDS for the statistics
+    combine_bands<V>(st, lds, rg, lane, rgroups);
+    return rg == 0 ? wave_sum((double)st.m2()) : 0.0;
+}
+
+// grid.x = column groups of 64*V columns (+ 1 when tail > 0, as in mix_ring_kernel), block = 64 * rgroups threads.  The columns
+// beyond the last whole vector in a launch of their own cost about 5 us (24 x 1 250 003, momentum mix and mean, one such
+// launch each: 151 -> 142 us a step).
+template <int V, bool CONS, bool SWAPPED>
+__global__ void __launch_bounds__(1024)
+mix_csr_slab_kernel(const float *Xin, const float *__restrict__ G, float *Xout, int n, i64 ncols, i64 ld,
+                    const int *__restrict__ rowptr, const int *__restrict__ colidx, const float *__restrict__ vals,
+                    float gamma, int rgroups, double *__restrict__ partials, float *__restrict__ Vel, float mu, int tail,
+                    Finish fin)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    double v;
+    if (V > 1 && tail > 0 && blockIdx.x == gridDim.x - 1)
+        v = slab_walk<1, CONS, SWAPPED>(Xin + ncols, G + ncols, Xout + ncols, n, tail, ld, rowptr, colidx, vals, gamma, rgroups,
+                                        Vel ? Vel + ncols : nullptr, mu, lds, 0);
+    else
+        v = slab_walk<V, CONS, SWAPPED>(Xin, G, Xout, n, ncols, ld, rowptr, colidx, vals, gamma, rgroups, Vel, mu, lds, blockIdx.x);
+    if (CONS) leave_partial(fin, v, partials, blockIdx.x);
 }
 
 // The same for wide matrices, 16-byte accesses, whole super-blocks of columns: every lane owns SP float4 column
@@ -565,18 +594,16 @@ mix_csr_gather_kernel(const float *__restrict__ Xin, const float *__restrict__ G
 
 // ---------------------------------------------------------------- column statistics / mean
 // Same slab ownership as the ring kernel (lane = V columns, wave = row band), read only.
-// MEAN: writes xbar.  CONS: writes the per-workgroup partial of sum_i ||x_i - xbar||^2.
+// MEAN: writes xbar.  CONS: returns the group's partial of sum_i ||x_i - xbar||^2 (thread 0).
 template <int V, bool MEAN, bool CONS>
-__global__ void __launch_bounds__(512)
-column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int bands, int rpb, float inv_n,
-                    float *__restrict__ xbar, double *__restrict__ partials)
+__device__ __forceinline__ double stats_walk(const float *__restrict__ X, int n, i64 ncols, i64 ld, int bands, int rpb,
+                                             float inv_n, float *__restrict__ xbar, float *lds, i64 grp)
 {
     typedef typename VecT<V>::type vec;
     typedef typename MemT<V>::type mem;
-    extern __shared__ float lds[];
     const int lane = threadIdx.x & 63;
     const int band = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const i64 c0 = ((i64)blockIdx.x * 64 + lane) * V;
+    const i64 c0 = (grp * 64 + lane) * V;
     const bool active = c0 + V <= ncols;
     const int r0 = band * rpb, r1 = min(n, r0 + rpb);
     ColStats<V> st;
@@ -602,13 +629,24 @@ column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int b
         }
         if (band == 0 && active) vstore<V>(xbar + c0, sum * inv_n);
     }
-    if (CONS) {
-        combine_bands<V>(st, lds, band, lane, bands);
-        if (band == 0) {
-            double v = wave_sum((double)st.m2());
-            if (lane == 0) partials[blockIdx.x] = v;
-        }
-    }
+    if (!CONS) return 0.0;
+    combine_bands<V>(st, lds, band, lane, bands);
+    return band == 0 ? wave_sum((double)st.m2()) : 0.0;
+}
+
+// grid.x = column groups of 64*V columns (+ 1 when tail > 0, as in mix_ring_kernel), block = 64 * bands threads.
+template <int V, bool MEAN, bool CONS>
+__global__ void __launch_bounds__(512)
+column_stats_kernel(const float *__restrict__ X, int n, i64 ncols, i64 ld, int bands, int rpb, float inv_n,
+                    float *__restrict__ xbar, double *__restrict__ partials, int tail)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    double v;
+    if (V > 1 && tail > 0 && blockIdx.x == gridDim.x - 1)
+        v = stats_walk<1, MEAN, CONS>(X + ncols, n, tail, ld, bands, rpb, inv_n, MEAN ? xbar + ncols : nullptr, lds, 0);
+    else
+        v = stats_walk<V, MEAN, CONS>(X, n, ncols, ld, bands, rpb, inv_n, xbar, lds, blockIdx.x);
+    if (CONS && threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
 // The node average of a wide matrix with fat lanes and the chunked column ownership of mix_ring_fat_kernel (one wave
@@ -758,11 +796,29 @@ int pick_bands(const dpsgd_ctx *ctx, i64 groups)
 
 size_t stats_lds_bytes(int bands, int vec) { return bands > 1 ? (size_t)bands * 64 * (3 * vec + 1) * sizeof(float) : 0; }
 
+// Where the consensus distance goes (out null: not wanted), and whether a launch has formed it.
+struct Consensus {
+    float *out = nullptr;
+    bool done = false;
+};
+
+// For a launch of `groups` workgroups after `before` others that left partials: whether it forms the distance itself.
+Finish finish_for(const dpsgd_ctx *ctx, Consensus *c, i64 before, i64 groups)
+{
+    Finish f{};
+    if (!c || !c->out || before > 0 || groups != 1) return f;
+    f.out = c->out;
+    f.inv_n = 1.0 / (double)ctx->n;
+    c->done = true;
+    return f;
+}
+
 // tail: columns right after [col0, col0 + ncols) that the same launch walks one per lane (V > 1, tail < V)
+// fin: nothing else leaves partials for this consensus distance (null: something does)
 template <int V>
 dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float *Xout, i64 col0, i64 ncols,
                          bool cons, double *partials, i64 *nparts, float *Vel = nullptr, float mu = 0.f,
-                         bool narrow = false, int tail = 0)
+                         bool narrow = false, int tail = 0, Consensus *fin = nullptr)
 {
     const i64 groups = groups_for(ncols, V);
     const int bands = pick_bands(ctx, groups);
@@ -799,10 +855,11 @@ dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     dim3 grid((unsigned)wgs), block(64u * (unsigned)used);
     if (wgs > 0x7fffffffLL || tail >= V) return DPSGD_EUNSUPPORTED;
     const size_t shm = cons ? stats_lds_bytes(used, V) : 0;
+    const Finish f = finish_for(ctx, cons ? fin : nullptr, 0, wgs);
     float *vel = Vel ? Vel + col0 : nullptr;
 #define DPSGD_RING(CONS, MOM)                                                                                        \
     hipLaunchKernelGGL((mix_ring_kernel<V, 4, CONS, MOM>), grid, block, shm, ctx->stream, Xin + col0, G + col0,      \
-                       Xout + col0, ctx->n, ncols, ctx->ld, ctx->ring_w, ctx->gamma, used, rpb, partials, vel, mu, tail)
+                       Xout + col0, ctx->n, ncols, ctx->ld, ctx->ring_w, ctx->gamma, used, rpb, partials, vel, mu, tail, f)
     if (cons && vel) DPSGD_RING(true, true);
     else if (cons) DPSGD_RING(true, false);
     else if (vel) DPSGD_RING(false, true);
@@ -853,7 +910,8 @@ constexpr size_t kSlabWideLdsBudget = 128 * 1024;   // one workgroup per CU with
 
 template <int V, bool SWAPPED>
 dpsgd_status slab_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float *Xout, i64 col0, i64 ncols,
-                         bool cons, double *partials, i64 *nparts, float *Vel = nullptr, float mu = 0.f)
+                         bool cons, double *partials, i64 *nparts, float *Vel = nullptr, float mu = 0.f, int tail = 0,
+                         Consensus *fin = nullptr)
 {
     float *vel = Vel ? Vel + col0 : nullptr;
     // wide matrices: whole super-blocks of columns with the chunked column ownership, the rest consecutively
@@ -868,38 +926,42 @@ dpsgd_status slab_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
             st = slab_wide_launch<1, SWAPPED>(ctx, Xin, G, Xout, col0, ncols, cons, partials, vel, mu, &done, &parts);
         if (st != DPSGD_OK) return st;
     }
-    const i64 groups = groups_for(ncols - done, V);
-    if (groups > 0x7fffffffLL) return DPSGD_EUNSUPPORTED;
-    if (groups > 0) {
-        // a wave per four rows, 4 to 16 of them: with many workers the slab leaves a CU one or two workgroups, and what
-        // a wave waits for (112 x 268 365: 117 us with 4 waves, 90 with 8, 79 with 16; 24 x 1 500 000: 85 either way)
-        int rgroups = ctx->n / 4 < 4 ? 4 : ctx->n / 4 > 16 ? 16 : ctx->n / 4;
-        if (rgroups > ctx->n) rgroups = ctx->n;
-        size_t shm = (size_t)ctx->n * 64 * V * sizeof(float);
-        const size_t stats = stats_lds_bytes(rgroups, V);
-        if (cons && stats > shm) shm = stats;
-        dim3 grid((unsigned)groups), block(64u * (unsigned)rgroups);
-        const float *xi = Xin + col0 + done, *gi = G + col0 + done;
-        float *xo = Xout + col0 + done, *ve = vel ? vel + done : nullptr;
-        if (cons)
-            hipLaunchKernelGGL((mix_csr_slab_kernel<V, true, SWAPPED>), grid, block, shm, ctx->stream, xi, gi, xo, ctx->n,
-                               ncols - done, ctx->ld, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals, ctx->gamma, rgroups,
-                               partials + parts, ve, mu);
-        else
-            hipLaunchKernelGGL((mix_csr_slab_kernel<V, false, SWAPPED>), grid, block, shm, ctx->stream, xi, gi, xo, ctx->n,
-                               ncols - done, ctx->ld, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals, ctx->gamma, rgroups,
-                               partials + parts, ve, mu);
+    if (done == ncols) {   // the wide kernel took every whole vector
+        i64 rest = 0;
+        dpsgd_status st = DPSGD_OK;
+        if (tail) st = slab_launch<1, SWAPPED>(ctx, Xin, G, Xout, col0 + ncols, tail, cons, partials + parts, &rest, Vel, mu);
+        *nparts = parts + rest;
+        return st;
     }
+    const i64 groups = groups_for(ncols - done, V) + ((V > 1 && tail > 0) ? 1 : 0);
+    if (groups > 0x7fffffffLL || tail >= V) return DPSGD_EUNSUPPORTED;
+    // a wave per four rows, 4 to 16 of them: with many workers the slab leaves a CU one or two workgroups, and what
+    // a wave waits for (112 x 268 365: 117 us with 4 waves, 90 with 8, 79 with 16; 24 x 1 500 000: 85 either way)
+    int rgroups = ctx->n / 4 < 4 ? 4 : ctx->n / 4 > 16 ? 16 : ctx->n / 4;
+    if (rgroups > ctx->n) rgroups = ctx->n;
+    size_t shm = (size_t)ctx->n * 64 * V * sizeof(float);
+    const size_t stats = stats_lds_bytes(rgroups, V);
+    if (cons && stats > shm) shm = stats;
+    const Finish f = finish_for(ctx, cons ? fin : nullptr, parts, groups);
+    dim3 grid((unsigned)groups), block(64u * (unsigned)rgroups);
+    const float *xi = Xin + col0 + done, *gi = G + col0 + done;
+    float *xo = Xout + col0 + done, *ve = vel ? vel + done : nullptr;
+    auto launch = [&](auto k) {
+        hipLaunchKernelGGL(k, grid, block, shm, ctx->stream, xi, gi, xo, ctx->n, ncols - done, ctx->ld, ctx->d_rowptr,
+                           ctx->d_colidx, ctx->d_vals, ctx->gamma, rgroups, partials + parts, ve, mu, tail, f);
+    };
+    if (cons) launch(mix_csr_slab_kernel<V, true, SWAPPED>);
+    else launch(mix_csr_slab_kernel<V, false, SWAPPED>);
     *nparts = parts + groups;
     return hip_status(hipGetLastError());
 }
 
 template <int V, bool MEAN, bool CONS>
 dpsgd_status stats_launch(dpsgd_ctx *ctx, const float *X, i64 col0, i64 ncols, float *xbar, double *partials,
-                          i64 *nparts)
+                          i64 *nparts, int tail = 0)
 {
-    const i64 groups = groups_for(ncols, V);
-    if (groups > 0x7fffffffLL) return DPSGD_EUNSUPPORTED;
+    const i64 groups = groups_for(ncols, V) + ((V > 1 && tail > 0) ? 1 : 0);
+    if (groups > 0x7fffffffLL || tail >= V) return DPSGD_EUNSUPPORTED;
     const int bands = pick_bands(ctx, groups);
     const int rpb = (ctx->n + bands - 1) / bands;
     const int used = (ctx->n + rpb - 1) / rpb;
@@ -908,7 +970,7 @@ dpsgd_status stats_launch(dpsgd_ctx *ctx, const float *X, i64 col0, i64 ncols, f
     if (CONS && stats_lds_bytes(used, V) > shm) shm = stats_lds_bytes(used, V);
     hipLaunchKernelGGL((column_stats_kernel<V, MEAN, CONS>), dim3((unsigned)groups), dim3(64u * (unsigned)used), shm,
                        ctx->stream, X + col0, ctx->n, ncols, ctx->ld, used, rpb, 1.0f / (float)ctx->n,
-                       xbar ? xbar + col0 : nullptr, partials);
+                       xbar ? xbar + col0 : nullptr, partials, tail);
     *nparts = groups;
     return hip_status(hipGetLastError());
 }
@@ -940,17 +1002,14 @@ dpsgd_status consensus_of(dpsgd_ctx *ctx, const float *X, float *consensus)
 {
     const int vec = pick_vec(ctx, ctx->d, 4);
     const Plan p = make_plan(ctx, vec);
-    i64 n1 = 0, n2 = 0;
-    dpsgd_status st = DPSGD_OK;
-    if (p.bulk_cols) {
-        if (vec == 4) st = stats_launch<4, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1);
-        else if (vec == 2) st = stats_launch<2, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1);
-        else st = stats_launch<1, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1);
-    }
-    if (st == DPSGD_OK && p.tail_cols)
-        st = stats_launch<1, false, true>(ctx, X, p.bulk_cols, p.tail_cols, nullptr, ctx->d_partials + n1, &n2);
+    i64 n1 = 0;
+    dpsgd_status st;
+    const int tail = (int)p.tail_cols;
+    if (vec == 4) st = stats_launch<4, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1, tail);
+    else if (vec == 2) st = stats_launch<2, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1, tail);
+    else st = stats_launch<1, false, true>(ctx, X, 0, p.bulk_cols, nullptr, ctx->d_partials, &n1);
     if (st != DPSGD_OK) return st;
-    return finalize_consensus(ctx, n1 + n2, consensus);
+    return finalize_consensus(ctx, n1, consensus);
 }
 
 }  // namespace
@@ -967,23 +1026,21 @@ dpsgd_status launch_mix(dpsgd_ctx *ctx, const float *Xin, const float *G, float 
     if (Vel && swapped) return DPSGD_EUNSUPPORTED;
     const bool cons = consensus != nullptr;
     const bool ring = ctx->ring_uniform && !ctx->opt_mix_force_csr && !swapped;
-    i64 n1 = 0, n2 = 0;
+    i64 n1 = 0;
     dpsgd_status st = DPSGD_OK;
+    Consensus fin;
+    fin.out = consensus;
 
+    // (the columns beyond the last whole vector ride along in the bulk launch, its last workgroup)
     if (ring) {
         const int vec = pick_vec(ctx, ctx->d, 4);
         const Plan p = make_plan(ctx, vec);
-        // the columns beyond the last whole vector ride along in the bulk launch (its last workgroup)
         const int tail = (int)p.tail_cols;
-        if (p.bulk_cols) {
-            if (vec == 4) st = ring_launch<4>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, tail);
-            else if (vec == 2) st = ring_launch<2>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, tail);
-            else st = ring_launch<1>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu);
-        }
-        if (st == DPSGD_OK && p.tail_cols && (!p.bulk_cols || vec == 1))
-            st = ring_launch<1>(ctx, Xin, G, Xout, p.bulk_cols, p.tail_cols, cons, ctx->d_partials + n1, &n2, Vel, mu);
+        if (vec == 4) st = ring_launch<4>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, tail, &fin);
+        else if (vec == 2) st = ring_launch<2>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, tail, &fin);
+        else st = ring_launch<1>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, 0, &fin);
         if (st != DPSGD_OK) return st;
-        return cons ? finalize_consensus(ctx, n1 + n2, consensus) : DPSGD_OK;
+        return cons && !fin.done ? finalize_consensus(ctx, n1, consensus) : DPSGD_OK;
     }
 
     // widest vector whose n-row slab fits the LDS budget
@@ -994,18 +1051,16 @@ dpsgd_status launch_mix(dpsgd_ctx *ctx, const float *Xin, const float *G, float 
         if (!ctx->opt_mix_vec)   // narrow matrix: more, narrower column groups (64 x 30 730 on a torus: 24 -> 13.5 us; twice as many: 13.6)
             while (vec > 1 && groups_for(ctx->d, vec) < 128) vec >>= 1;
         const Plan p = make_plan(ctx, vec);
-#define DPSGD_SLAB(V, C0, NC, PART, NP)                                                              \
-    (swapped ? slab_launch<V, true>(ctx, Xin, G, Xout, C0, NC, cons, PART, NP)                       \
-             : slab_launch<V, false>(ctx, Xin, G, Xout, C0, NC, cons, PART, NP, Vel, mu))
-        if (p.bulk_cols) {
-            if (vec == 4) st = DPSGD_SLAB(4, 0, p.bulk_cols, ctx->d_partials, &n1);
-            else if (vec == 2) st = DPSGD_SLAB(2, 0, p.bulk_cols, ctx->d_partials, &n1);
-            else st = DPSGD_SLAB(1, 0, p.bulk_cols, ctx->d_partials, &n1);
-        }
-        if (st == DPSGD_OK && p.tail_cols) st = DPSGD_SLAB(1, p.bulk_cols, p.tail_cols, ctx->d_partials + n1, &n2);
+        const int tail = (int)p.tail_cols;
+#define DPSGD_SLAB(V)                                                                                                          \
+    (swapped ? slab_launch<V, true>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, nullptr, 0.f, tail, &fin)   \
+             : slab_launch<V, false>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, tail, &fin))
+        if (vec == 4) st = DPSGD_SLAB(4);
+        else if (vec == 2) st = DPSGD_SLAB(2);
+        else st = DPSGD_SLAB(1);
 #undef DPSGD_SLAB
         if (st != DPSGD_OK) return st;
-        return cons ? finalize_consensus(ctx, n1 + n2, consensus) : DPSGD_OK;
+        return cons && !fin.done ? finalize_consensus(ctx, n1, consensus) : DPSGD_OK;
     }
 
     // n too large for an LDS slab: gather from global memory, out of place only
@@ -1041,26 +1096,20 @@ dpsgd_status launch_mix_range(dpsgd_ctx *ctx, const float *Xin, const float *G, 
     while (vec > 1 && ncols < vec) vec >>= 1;
     const i64 bulk = ncols - ncols % vec, tail = ncols - bulk;
     if (*nparts + groups_for(bulk, vec) + groups_for(tail, 1) + 2 > ctx->partials_cap - kStage1Blocks) return DPSGD_EINVAL;
-    i64 n1 = 0, n2 = 0;
+    i64 n1 = 0;
     dpsgd_status st = DPSGD_OK;
     double *part = ctx->d_partials + *nparts;
+    const int rest = (int)tail;
     if (ring) {
-        if (bulk) {
-            if (vec == 4) st = ring_launch<4>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, false, (int)tail);
-            else if (vec == 2) st = ring_launch<2>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, false, (int)tail);
-            else st = ring_launch<1>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
-        }
-        if (st == DPSGD_OK && tail && (!bulk || vec == 1))
-            st = ring_launch<1>(ctx, Xin, G, Xout, col0 + bulk, tail, cons, part + n1, &n2);
+        if (vec == 4) st = ring_launch<4>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, false, rest);
+        else if (vec == 2) st = ring_launch<2>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, false, rest);
+        else st = ring_launch<1>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
     } else {
-        if (bulk) {
-            if (vec == 4) st = slab_launch<4, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
-            else if (vec == 2) st = slab_launch<2, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
-            else st = slab_launch<1, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
-        }
-        if (st == DPSGD_OK && tail) st = slab_launch<1, false>(ctx, Xin, G, Xout, col0 + bulk, tail, cons, part + n1, &n2);
+        if (vec == 4) st = slab_launch<4, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, rest);
+        else if (vec == 2) st = slab_launch<2, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1, nullptr, 0.f, rest);
+        else st = slab_launch<1, false>(ctx, Xin, G, Xout, col0, bulk, cons, part, &n1);
     }
-    if (cons) *nparts += n1 + n2;
+    if (cons) *nparts += n1;
     return st;
 }
 
@@ -1073,6 +1122,7 @@ dpsgd_status launch_mean(dpsgd_ctx *ctx, const float *X, float *xbar)
 {
     const int vec = pick_vec(ctx, ctx->d, 4);
     const Plan p = make_plan(ctx, vec);
+    const int tail = (int)p.tail_cols;   // rides along in the last launch
     i64 np = 0;
     dpsgd_status st = DPSGD_OK;
     constexpr int kMeanP = 4;
@@ -1085,14 +1135,14 @@ dpsgd_status launch_mean(dpsgd_ctx *ctx, const float *X, float *xbar)
                            1.0f / (float)ctx->n, xbar);
         st = hip_status(hipGetLastError());
         if (st == DPSGD_OK && fat_cols < p.bulk_cols)
-            st = stats_launch<4, true, false>(ctx, X, fat_cols, p.bulk_cols - fat_cols, xbar, nullptr, &np);
-    } else if (p.bulk_cols) {
-        if (vec == 4) st = stats_launch<4, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np);
-        else if (vec == 2) st = stats_launch<2, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np);
-        else st = stats_launch<1, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np);
+            st = stats_launch<4, true, false>(ctx, X, fat_cols, p.bulk_cols - fat_cols, xbar, nullptr, &np, tail);
+        else if (st == DPSGD_OK && tail)
+            st = stats_launch<1, true, false>(ctx, X, p.bulk_cols, tail, xbar, nullptr, &np);
+        return st;
     }
-    if (st == DPSGD_OK && p.tail_cols) st = stats_launch<1, true, false>(ctx, X, p.bulk_cols, p.tail_cols, xbar, nullptr, &np);
-    return st;
+    if (vec == 4) return stats_launch<4, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np, tail);
+    if (vec == 2) return stats_launch<2, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np, tail);
+    return stats_launch<1, true, false>(ctx, X, 0, p.bulk_cols, xbar, nullptr, &np);
 }
 
 // ------------------------------------------------------------------ allocation-free entry point

@@ -86,6 +86,16 @@ def test_torus(dims, inplace):
         run_mix(n, d, ld, B.Topology.torus(*dims), oracle.torus(*dims).with_fp32_values(), n + d, inplace, True)
 
 
+@pytest.mark.parametrize("d", [1, 3, 63, 64, 65, 255, 256, 257, 32768, 32769, 32770, 32771])
+def test_columns_beyond_the_last_vector_and_single_workgroups(d):
+    """Whole vectors only and one to three columns more (the last workgroup walks them one per lane), and launches of one
+    workgroup, which form the consensus distance themselves: ring, general W in both orders, mean."""
+    run_mix(8, d, d, B.Topology.ring(), oracle.ring(8).with_fp32_values(), 50 + d, True, True)
+    run_mix(8, d, d + 1, B.Topology.ring_chord(), oracle.ring_chord(8).with_fp32_values(), 51 + d, False, True)
+    run_mix(8, d, d, B.Topology.ring_chord(), oracle.ring_chord(8).with_fp32_values(), 52 + d, True, True, swapped=True)
+    test_mean(8, d, d)
+
+
 @pytest.mark.parametrize("inplace", [False, True])
 def test_wide_matrices_through_the_slab_kernel(inplace):
     """Wide matrices: the LDS-slab kernel deals whole super-blocks of columns to its workgroups as 512-byte chunks

@@ -425,7 +425,69 @@ dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
     return linear_fwd_launch<1, 1, 2, 2, 64>(s, nworkers, g);
 }
 
-// Forward of a layer with few outputs (O <= 16, e.g. the 10 classes): one workgroup per worker and R sample rows; its
+// The class layer (O <= 16): 16 samples x 16 outputs per workgroup on v_mfma_f32_16x16x4_f32, whose 16 waves deal the
+// contraction among themselves in pieces of 64 elements (256 bytes of a row); a wave requests NP pieces of both operands at
+// once, straight from global memory, and the waves' sums meet in LDS in wave order.  What bounds it is the round trip of
+// those loads and 64 bytes per sample and output from L2 for every 16 elements of the contraction.  No unit's sign hangs
+// on the order of these sums, unlike in the layers below.  Lane l holds 4 consecutive elements of row l % 16 from
+// 4 (l / 16) on; the e-th of four instructions takes the e-th element of both operands.
+// 16 workers x 128 samples x 3072 -> 10: 13.1 us, linear_fwd_skinny_kernel 23.5 (a step 36.7 against 47.3).
+// grid (ceil(B / 16), n), block 1024; I >= 4, rows at any alignment.
+template <int NP>
+__global__ void __launch_bounds__(1024)
+linear_fwd_class_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,
+                        int O, float *__restrict__ out)
+{
+    constexpr int NW = 16;
+    __shared__ float red[NW][256];
+    const int w = blockIdx.y, b0 = blockIdx.x * 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const float *a = act + ((i64)w * B + min(b0 + l16, B - 1)) * I;
+    const float *x = X + (i64)w * ld + woff + (i64)min(l16, O - 1) * I;
+    const int pieces = (I + 63) / 64;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p = wave; p < pieces; p += NW * NP) {
+        f32x4 va[NP][4], vx[NP][4];
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = min((p + NW * j) * 64 + q * 16 + g4 * 4, I - 4);
+                const f32x4_a4 ta = *reinterpret_cast<const f32x4_a4 *>(a + k), tx = *reinterpret_cast<const f32x4_a4 *>(x + k);
+                va[j][q] = (f32x4){ta.x, ta.y, ta.z, ta.w};
+                vx[j][q] = (f32x4){tx.x, tx.y, tx.z, tx.w};
+            }
+        __builtin_amdgcn_sched_barrier(0);   // every load is on its way before the first is waited for
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            if ((p + NW * j) * 64 + 64 > I) {   // the last piece, or one beyond it
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int have = I - ((p + NW * j) * 64 + q * 16 + g4 * 4);
+                    va[j][q] = mend4(va[j][q], have);
+                    vx[j][q] = mend4(vx[j][q], have);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[j][q][e], vx[j][q][e], acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][(4 * g4 + v) * 16 + l16] = acc[v];   // row (sample) 4 g4 + v, column (output) l16
+    __syncthreads();
+    if (threadIdx.x >= 256) return;
+    const int b = b0 + (threadIdx.x >> 4), o = threadIdx.x & 15;
+    if (b >= B || o >= O) return;
+    float s = red[0][threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) s += red[q][threadIdx.x];
+    out[((i64)w * B + b) * O + o] = s + X[(i64)w * ld + boff + o];
+}
+
+// Forward of a hidden layer with few outputs (O <= 16): one workgroup per worker and R sample rows; its
 // four waves take every fourth 1 KB piece of the rows (lanes stride over the inputs with 16-byte loads), every lane
 // keeps R x O partial sums, a wave reduction and a sum over the four waves (in wave order) finish them.  The tiled GEMM
 // above would launch only a handful of workgroups for such a shape.  With a whole row per wave the launch was short of
@@ -626,6 +688,18 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         g.C = (float *)act[l + 1]; g.sCw = (i64)B * O; g.sCm = O;
         g.bias = X + boff[l]; g.sBiasw = ctx->ld;
         g.M = B; g.N = O; g.K = I; g.relu = (l < L - 1);
+        if (O <= 16 && I >= 256 && l == L - 1) {
+            const dim3 cgrid((unsigned)((B + 15) / 16), (unsigned)n);
+            const int np = ((I + 63) / 64 + 15) / 16;   // pieces per wave
+            auto launch = [&](auto k) {
+                hipLaunchKernelGGL(k, cgrid, dim3(1024), 0, s, act[l], X, ctx->ld, woff[l], boff[l], B, I, O, (float *)act[l + 1]);
+            };
+            if (np == 1) launch(linear_fwd_class_kernel<1>);
+            else if (np == 2) launch(linear_fwd_class_kernel<2>);
+            else launch(linear_fwd_class_kernel<3>);
+            if ((st = hip_status(hipGetLastError())) != DPSGD_OK) return st;
+            continue;
+        }
         if (O <= 16 && I >= 256) {
             const bool vec = (I % 4) == 0 && (woff[l] % 4) == 0 && (ctx->ld % 4) == 0 &&
                              (reinterpret_cast<uintptr_t>(X) % 16) == 0 && (reinterpret_cast<uintptr_t>(act[l]) % 16) == 0;

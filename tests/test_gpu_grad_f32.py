@@ -68,6 +68,16 @@ def test_softmax_ragged(widths, batch, n):
     grad_case(cfg, synth.padded_stride(d))
 
 
+@pytest.mark.parametrize("widths,batch,n", [((256, 16), 1, 2), ((1025, 10), 17, 3), ((2049, 3), 33, 2), ((3139, 10), 16, 2),
+                                            ((300, 257, 1), 18, 2)])
+def test_class_layer_contractions_of_every_length(widths, batch, n):
+    """One, two and three pieces of 64 elements per wave, a second round of pieces, ragged last pieces and sample tiles."""
+    cfg = shrink(CONFIGS[2 if len(widths) > 2 else 1], widths=widths, batch=batch, n=n, bf16=False)
+    d = synth.model_dim(cfg.model_kind, widths)
+    grad_case(cfg, d)
+    grad_case(cfg, synth.padded_stride(d))
+
+
 @pytest.mark.parametrize("widths,batch,n", [((48, 40, 10), 16, 3), ((100, 70, 33, 5), 37, 4), ((3072, 128, 10), 128, 2)])
 def test_mlp_fp32(widths, batch, n):
     cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False)

@@ -69,9 +69,10 @@ def test_softmax_ragged(widths, batch, n):
 
 
 @pytest.mark.parametrize("widths,batch,n", [((256, 16), 1, 2), ((1025, 10), 17, 3), ((2049, 3), 33, 2), ((3139, 10), 16, 2),
-                                            ((300, 257, 1), 18, 2)])
+                                            ((300, 257, 1), 18, 2), ((300, 12, 5), 9, 2)])
 def test_class_layer_contractions_of_every_length(widths, batch, n):
-    """One, two and three pieces of 64 elements per wave, a second round of pieces, ragged last pieces and sample tiles."""
+    """One, two and three pieces of 64 elements per wave, a second round of pieces, ragged last pieces and sample tiles;
+    a hidden layer of as few outputs keeps its own kernel."""
     cfg = shrink(CONFIGS[2 if len(widths) > 2 else 1], widths=widths, batch=batch, n=n, bf16=False)
     d = synth.model_dim(cfg.model_kind, widths)
     grad_case(cfg, d)

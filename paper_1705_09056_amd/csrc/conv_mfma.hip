@@ -1051,7 +1051,9 @@ bool wgrad_mfma_ok(const ConvDesc &c)
     if (c.Hos % 8 || c.Wos % 8 || c.Wis % 8 || c.Wis > 64) return false;
     if (wgrad_band_rows(c) == 0) return false;
     if (c.stride == 1) return cip == c.Cos || (cip == 16 && c.Cos == 32);
-    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c);
+    // (8 channels into 16, as a base of 4 or 8 has them in its real extents, are not the 16 into 32 they would round up to:
+    // that kernel would read the deltas of 32 channels and write twice the partial sums there is room for)
+    return c.stride == 2 && pow2_channels(c.Cis) && c.Cos == 2 * c.Cis && halves(c);
 }
 
 template <int CI, int CO, int STRIDE>

@@ -196,6 +196,9 @@ def test_residual_block_in_one_launch_changes_no_bit(widths, batch, n):
     ((3, 20, 20, 24, 1, 10), 3, 2),   # 24 / 48 channels stored as 32 / 64, the 96 of the last stage as they are
     ((8, 16, 16, 20, 1, 10), 2, 2),   # the widest image the matrix-kernel stem takes
     ((3, 1, 9, 16, 1, 3), 3, 2),      # one pixel high
+    ((3, 32, 32, 8, 1, 10), 3, 2),    # as they are: 8 channels into 16 halving to rows of 16 and to rows of 8 pixels, on the
+    ((1, 16, 16, 8, 1, 10), 4, 3),    # generic weight gradient although 16 into 32 of these extents has a matrix kernel
+    ((3, 32, 32, 4, 1, 10), 2, 2),    # ... in the last stage
 ])
 @pytest.mark.parametrize("bf16_inputs", [True, False])
 def test_padded_extents_agree_with_the_real_ones(widths, batch, n, bf16_inputs):
@@ -219,6 +222,7 @@ def test_padded_extents_agree_with_the_real_ones(widths, batch, n, bf16_inputs):
             ctx.grad(model, Xd, inp_d, torch.from_numpy(tgt).cuda(), cfg.batch, Gd, loss, input_is_bf16=bf16_inputs)
             torch.cuda.synchronize()
             out.append((from_dev(Gd, d), loss.cpu().numpy()))
+            print(f"  conv_pad {setting} done", flush=True)
     assert np.array_equal(out[0][0], out[2][0]) and np.array_equal(out[0][1], out[2][1])
     check_close(out[1][0], out[0][0], 2 * TIGHT, "padded vs real extents", flips=True)
     assert rel_err(out[1][1], out[0][1]) < 2 * TIGHT

@@ -1543,7 +1543,7 @@ dpsgd_status fwd_launch(hipStream_t s, int n, const FwdArgs &a, bool vec, bool l
 {
     constexpr int TO = 32 * WN, MBLK = 32 * WM * MT;
     static_assert(TO % 16 == 0, "the tiles cover the padding of the activations they write");
-    if (WM == 2 && WN == 2 && MT == 2 && vec && !a.wb) {   // 128-row minibatch blocks: 512-byte row pieces
+    if (WM == 2 && WN == 2 && MT == 2 && vec) {   // 128-row minibatch blocks: 512-byte row pieces (with or without a bf16 copy, which no kernel here reads)
         dim3 grid((unsigned)((a.O + 63) / 64), (unsigned)((a.B + 127) / 128), (unsigned)n);
         const size_t shm = (size_t)(64 + 128) * PITCHW * sizeof(bf16_t);
         if (last) hipLaunchKernelGGL(mlp_fwd_wide_kernel<true>, grid, dim3(256), shm, s, a);
@@ -2497,8 +2497,9 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
     }
     const Tiling t = pick_tiling(B);
     dpsgd_status st = DPSGD_OK;
-    // layers whose weights a step may read from a bf16 copy: the results with and without the copy are the same bits, so
-    // both come from the kernels that can read one
+    // layers whose weights a step may read from a bf16 copy.  The results with and without the copy are the same bits: which
+    // kernel a layer takes does not depend on whether there is one, and these layers take the kernels that can read it
+    // (the k-split forward, the data gradient; the forward of more than 32 samples reads fp32 either way).
     auto may_copy = [&](int l) { return fuse && l > 0 && ctx->ring_uniform && layer_fusable(ctx, m.widths[l], m.widths[l + 1], woff[l]); };
     // a class layer of at most 16 outputs on top of a hidden layer: its backward is one launch (mlp_class_bwd_kernel)
     // and the softmax rides in its forward launch

@@ -435,6 +435,8 @@ def test_operands_through_lds_change_no_bit(widths, batch, n):
     ((1024, 1024, 1152, 1024, 10), 32),   # two of them, 36 and 32 output tiles
     ((1024, 1024, 1120, 10), 32),     # 35 output tiles: written, but the readers want multiples of 64 and use fp32
     ((1024, 1024, 1024, 10), 64),     # minibatch 64: the forward of that tiling reads fp32, the data gradient the copy
+    ((1024, 1024, 1024, 10), 65),     # ... of more than 64: the forward's 128-row blocks read fp32 as well
+    ((1024, 2048, 1024, 10), 128),
 ])
 @pytest.mark.parametrize("ring_rows", [1, 0])
 def test_bf16_shadow_option_on_other_shapes(widths, batch, ring_rows):

@@ -1527,15 +1527,22 @@ Tiling pick_tiling(int B)
 }
 
 // Whether the streaming kernels' tiles (64 or 128 features x 32, 64 or 128 samples) of a product with `features` outputs
-// would leave CUs without a workgroup.  us per step with the line at 64 / 128 / 256 / 512 workgroups: 4 x 3072-1024-10 x 128
-// 113 / 87 / 87 / 87, 8 x 1024-1024-1024-10 x 32 120 / 119 / 100 / 100, 3 x 2048-2048-10 x 512 189 / 188 / 188 / 221,
-// 8 x 3072-99-3636-10 x 128 189 / 189 / 189 / 198; 12 x 784-500-300-10 x 50 without padded rows 107 at any (195 before).
-bool few_tiles(int features, int B, int n)
+// leave so many CUs without a workgroup that the small tiles are faster: at most 128 of them, or fewer than 256 of the
+// forward of up to 64 samples on unaligned rows (`longer`), where both get slower, the streaming kernel by more.
+// us per gradient, streaming / small tiles:
+//   forward, aligned, B <= 64    1024-1024 x 40 x 16 workers (128 workgroups) 60.4 / 55.5, 512-1536 x 50 x 12 (144) 48.0 / 49.7
+//   ... unaligned                3072-1536 x 50 x 12 (144) 176 / 170, 1024-3072 x 64 x 12 (288) 154 / 151
+//   forward, aligned, B > 64     2048-1024 x 128 x 8 (128) 79.3 / 73.0, 784-2048 x 200 x 4 (256) 74.0 / 80.4
+//   ... unaligned                512-2048 x 100 x 4 (128) 56.9 / 55.3, 3072-2048 x 200 x 3 (192) 117 / 130
+//   data gradient, B <= 32       1024 <- 784 x 24 x 16 (128) 77.5 / 74.4, 2048 <- 512 x 32 x 12 (192) 99.5 / 102.8
+//   ... B <= 64                  1024 <- 784 x 64 x 16 (128) 104.4 / 94.4, 2048 <- 784 x 64 x 12 (192) 151 / 161
+//   ... B > 64                   2048 <- 1024 x 100 x 4 (128) 119 / 109, 1536 <- 3072 x 100 x 6 (144) 176 / 187
+bool few_tiles(int features, int B, int n, bool longer)
 {
     const Tiling t = pick_tiling(B);
     const int tf = t.wn * 32 == 128 && t.mt == 1 ? 64 : t.wn * 32;   // (the k-split forward's tile is 64 wide)
     const i64 wgs = (i64)((features + tf - 1) / tf) * ((B + 32 * t.wm * t.mt - 1) / (32 * t.wm * t.mt)) * n;
-    return wgs < 256;
+    return wgs <= (longer ? 255 : 128);
 }
 
 template <int WM, int WN, int MT>
@@ -2498,8 +2505,8 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
     const Tiling t = pick_tiling(B);
     dpsgd_status st = DPSGD_OK;
     // layers whose weights a step may read from a bf16 copy.  The results with and without the copy are the same bits: which
-    // kernel a layer takes does not depend on whether there is one, and these layers take the kernels that can read it
-    // (the k-split forward, the data gradient; the forward of more than 32 samples reads fp32 either way).
+    // kernel a layer takes does not depend on whether there is one.  The data gradient of these layers takes the kernels that
+    // can read it; of the forward kernels only the k-split one of up to 32 aligned samples can, which has no stand-in.
     auto may_copy = [&](int l) { return fuse && l > 0 && ctx->ring_uniform && layer_fusable(ctx, m.widths[l], m.widths[l + 1], woff[l]); };
     // a class layer of at most 16 outputs on top of a hidden layer: its backward is one launch (mlp_class_bwd_kernel)
     // and the softmax rides in its forward launch
@@ -2525,7 +2532,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             if (vec && (a.K % 16) == 0) hipLaunchKernelGGL(mlp_fwd_last_kernel<true>, lgrid, dim3(512), 0, s, a);
             else hipLaunchKernelGGL(mlp_fwd_last_kernel<false>, lgrid, dim3(512), 0, s, a);
             st = hip_status(hipGetLastError());
-        } else if (a.K >= 4 && (!vec || t.mt > 1) && !may_copy(l) && few_tiles(a.O, B, n)) {
+        } else if (a.K >= 4 && (!vec || t.mt > 1) && few_tiles(a.O, B, n, !vec && B <= 64)) {
             // (aligned rows and at most 32 samples: the k-split kernel already has 64-wide tiles and splits the contraction)
             const dim3 sgrid((unsigned)((act_pitch(a.O) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                              (unsigned)n);
@@ -2617,7 +2624,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             da.wb = wb_use[l];
             da.wb_strips = strips_use[l];
             const bool vec = base_ok && (K % 4) == 0 && (woff[l] % 4) == 0;
-            if (K >= 4 && !may_copy(l) && few_tiles(K, B, n)) {
+            if (K >= 4 && !may_copy(l) && few_tiles(K, B, n, false)) {
                 const dim3 sgrid((unsigned)((act_pitch(K) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                                  (unsigned)n);
                 if (t.mt == 1) hipLaunchKernelGGL(mlp_dgrad_small_kernel<1>, sgrid, dim3(256), 0, s, da);

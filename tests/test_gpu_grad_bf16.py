@@ -123,6 +123,35 @@ def test_mlp_bf16_rows_at_any_alignment(widths, batch, n):
     check_close(got[1][0], got[0][0], 2 * TIGHT, "inputs at an odd address", flips=True)
 
 
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("widths,batch,n", [
+    ((512, 1024, 10), 32, 32),     # k-split tiles (aligned rows have no stand-in) or 32-sample small tiles below 256 of them
+    ((784, 1024, 10), 50, 32),     # 64 samples, 128 features wide
+    ((259, 1030, 10), 64, 32),
+    ((512, 512, 10), 100, 17),     # more than 64 samples; 64 against 272 weight-gradient tiles of 128 x 128
+    ((300, 520, 10), 200, 17),     # two blocks of samples, every extent ragged
+])
+def test_a_worker_does_not_depend_on_how_many_there_are(widths, batch, n, aligned):
+    """Four workers take the small forward tiles and the small weight-gradient tiles, many the streaming ones: the same
+    sums in the same order, so loss and gradient of the first four are the same bits.  (One hidden layer: the tiled data
+    gradients of deeper networks, whose two kernels add up in different orders, do not take part.)"""
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_MLP, widths)
+    ld = synth.padded_stride(d) if aligned else d | 1
+    X, inp, tgt = mlp_inputs(cfg)
+    Xd, inp_d, tgt_d = to_dev(X, ld), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    got = []
+    for m in (4, n):
+        Gd, loss = torch.full((m, ld), 777.0, device="cuda"), torch.zeros(m, device="cuda")
+        with B.Dpsgd(m, d, B.Topology.ring(), cfg.gamma, ld=ld) as ctx:
+            ctx.grad(B.Model(cfg.model_kind, cfg.widths, compute_bf16=True), Xd[:m], inp_d[:m], tgt_d[:m], batch, Gd, loss,
+                     input_is_bf16=True)
+            torch.cuda.synchronize()
+        got.append((Gd[:4, :d], loss[:4]))
+    assert torch.equal(got[0][1], got[1][1]), "loss"
+    assert torch.equal(got[0][0], got[1][0]), f"gradient: max {float((got[0][0] - got[1][0]).abs().max()):.3e}"
+
+
 def test_softmax_regression_bf16():
     cfg = shrink(CONFIGS[1], widths=(3072, 10), batch=128, n=3, bf16=True)
     d = synth.model_dim(MODEL_SOFTMAX, cfg.widths)

@@ -129,11 +129,13 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
         row = kfast ? u / (TK / 4) : u % (T / 4) * 4;
         kk = kfast ? u % (TK / 4) * 4 : u / (T / 4);
     };
+    // (TINY, undivided contraction: an operand whose contiguous extent is at least 4 is still loaded that way)
+    auto whole = [&](bool kfast, int R) { return !TINY || (WK == 1 && (kfast ? g.K : R) >= 4); };
     auto load = [&](const float *base, bool kfast, int T, int u, int r0, int k0, int R, i64 sr, i64 sk) {
         int row, kk;
         unit(u, kfast, T, row, kk);
         const int r = r0 + row, k = k0 + kk;
-        if (TINY) {
+        if (!whole(kfast, R)) {
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -150,6 +152,7 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
         int row, kk;
         unit(u, kfast, T, row, kk);
         const int r = r0 + row, k = k0 + kk;
+        if (!whole(kfast, R)) return v;
         return mend4(v, kfast ? (r < R ? g.K - k : 0) : (k < g.K ? R - r : 0));
     };
     const bool full_mn = m0 + TM <= g.M && n0 + TN <= g.N;
@@ -161,7 +164,7 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
     };
     auto stage = [&](int buf, Chunk &r, int k0) {
         float *As = lds + buf * BUF, *Bs = As + ASZ;
-        if (!TINY && !(full_mn && k0 + TK <= g.K)) {
+        if (!(TINY && WK > 1) && !(full_mn && k0 + TK <= g.K)) {
 #pragma unroll
             for (int q = 0; q < AQ; ++q) r.a[q] = mend(r.a[q], A_KFAST, TM, tid + NT * q, m0, k0, g.M);
 #pragma unroll
@@ -277,7 +280,13 @@ dpsgd_status gemm_f32_launch(hipStream_t s, int nworkers, const GemmArgs &g)
 dpsgd_status gemm_f32(hipStream_t s, int nworkers, const GemmArgs &g)
 {
     const int ea = g.sAk == 1 ? g.K : g.M, eb = g.sBn == 1 ? g.N : g.K;   // contiguous extents
-    if (ea < 4 || eb < 4) return gemm_f32_launch<1, 1, 4, 16, false, true>(s, nworkers, g);
+    if (ea < 4 || eb < 4) {
+        // a contraction of less than 4 (the data gradient of 2 or 3 classes) takes 64 x 64 tiles and chunks of 16: 32 workers x
+        // 64-2048-2 x 100 samples 134 us per gradient and mix, 183 with 32 x 32 tiles whose four waves share it; so do rows
+        // beyond what grid.y holds of 32-row tiles
+        if (g.K < 4 || g.M > 32 * 65535) return gemm_f32_launch<2, 2, 1, 16, false, true>(s, nworkers, g);
+        return gemm_f32_launch<1, 1, 4, 16, false, true>(s, nworkers, g);
+    }
     // 16 workers x 64 samples x 3072 x 1024 (us; before: with a thread per 4 x 4 block on the vector units): weight
     // gradient 118 -> 79 with 64 x 64 tiles and no split (its contraction is the minibatch; a second wave per tile: 93); a
     // contraction of 3072 70 with the contraction split over two waves, 76 without.  10 rows x 3072 x 128 samples (a class

@@ -103,6 +103,46 @@ def test_mlp_fp32_tiles_and_remainders(widths, batch, n):
     grad_case(cfg, d | 1, spread=0.3)
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((64, 300, 2), 70, 3),        # data gradient of two classes: a contraction of 2
+    ((20, 65, 3), 64, 2),         # ... of 3, an input more than a tile
+    ((9, 3, 4), 33, 2),           # three inputs of the data gradient
+])
+def test_two_and_three_classes(widths, batch, n):
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False)
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(cfg, synth.padded_stride(d), spread=0.3)
+    grad_case(cfg, d | 1, spread=0.3)
+
+
+def test_weight_gradient_of_more_rows_than_32_row_tiles_fit_a_grid():
+    """A hidden layer of 2 097 153 outputs on 3 inputs: its weight gradient has more rows than 65535 tiles of 32.  No
+    unit's input lies within 1e-5 of zero (bias 1, weights of 0.1), so no sign hangs on a rounding.  Tolerance: a logit is a sum of 2^21 terms of
+    1e-4 (0.15 in all) in chains of 2^21 / (16 waves x 4) and errs by about sqrt(2^15) 2^-24 of that, 1.6e-6; softmax and
+    the bias gradients add a few roundings."""
+    I, O, C, batch = 3, 32 * 65535 + 33, 2, 4
+    d = O * I + O + C * O + C
+    g = torch.Generator().manual_seed(17)
+    x = torch.cat([0.1 * torch.randn(O * I, generator=g), torch.ones(O), 1e-4 * torch.randn(C * O, generator=g), torch.zeros(C)])
+    a = torch.randn(batch, I, generator=g)
+    y = torch.tensor([0, 1, 1, 0], dtype=torch.int32)
+    xr = x.double().requires_grad_(True)
+    h = torch.relu(a.double() @ xr[:O * I].view(O, I).t() + xr[O * I:O * I + O])
+    assert float((a.double() @ xr[:O * I].view(O, I).t() + 1).abs().min()) > 1e-5
+    z = h @ xr[O * I + O:O * I + O + C * O].view(C, O).t() + xr[d - C:]
+    ref = torch.nn.functional.cross_entropy(z, y.long())
+    ref.backward()
+    X, G, loss = x.cuda()[None], torch.full((1, d), 777.0, device="cuda"), torch.zeros(1, device="cuda")
+    print("launching", flush=True)
+    with B.Dpsgd(1, d, B.Topology.complete(), 0.1, ld=d) as ctx:
+        ctx.grad(B.Model(MODEL_MLP, (I, O, C), compute_bf16=False), X, a.cuda()[None], y.cuda()[None], batch, G, loss)
+        torch.cuda.synchronize()
+    assert abs(float(loss) - float(ref)) < 1e-5
+    got, want = G[0].cpu().double(), xr.grad
+    for lo, hi in ((0, O * I), (O * I, O * I + O), (O * I + O, d - C), (d - C, d)):
+        assert float((got[lo:hi] - want[lo:hi]).norm() / want[lo:hi].norm()) < 2e-5
+
+
 def test_bf16_inputs_with_fp32_arithmetic():
     cfg = shrink(CONFIGS[2], widths=(96, 50, 10), batch=24, n=3, bf16=True)
     d = synth.model_dim(MODEL_MLP, cfg.widths)

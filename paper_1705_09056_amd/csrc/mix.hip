@@ -813,6 +813,15 @@ Finish finish_for(const dpsgd_ctx *ctx, Consensus *c, i64 before, i64 groups)
     return f;
 }
 
+// Whether pieces of rows that start a multiple of 32 floats behind these pointers are whole 128-byte lines, or whole
+// 64-byte halves of them, in every row.
+bool whole_lines(const dpsgd_ctx *ctx, std::initializer_list<const void *> ptrs, int bytes)
+{
+    bool ok = (ctx->ld % (bytes / 4)) == 0;
+    for (const void *p : ptrs) ok = ok && (reinterpret_cast<uintptr_t>(p) % bytes) == 0;
+    return ok;
+}
+
 // tail: columns right after [col0, col0 + ncols) that the same launch walks one per lane (V > 1, tail < V)
 // fin: nothing else leaves partials for this consensus distance (null: something does)
 template <int V>
@@ -824,7 +833,12 @@ dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     const int bands = pick_bands(ctx, groups);
     constexpr int kFatP = 8;              // float4 groups per lane of the fat-lane kernel
     constexpr i64 kFatMinSupers = 64;     // 64 x 64 single-wave workgroups: enough to fill the chip
-    if (V == 4 && bands == 1 && !narrow && !ctx->opt_mix_narrow && ctx->opt_mix_bands == 0 && ctx->n >= 3 &&
+    // (rows whose pieces share halves of cache lines with those of other workgroups, updated in place: consecutive columns
+    // are faster.  5 workers x 12 101 282 columns 160 us with fat lanes, 123 with consecutive columns, 10 x 13 066 066
+    // 358 / 313, with momentum 3 x 10 104 793 134 / 105; halves that are whole: 20 x 11 695 280 536 / 611; into another
+    // matrix 12 x 20 217 899 682 / 686, 10 x 43 918 948 1172 / 1230)
+    const bool fat = Xin != Xout || whole_lines(ctx, {Xin + col0, G + col0, Xout + col0}, 64);
+    if (V == 4 && fat && bands == 1 && !narrow && !ctx->opt_mix_narrow && ctx->opt_mix_bands == 0 && ctx->n >= 3 &&
         ncols / fat_super<kFatP>() >= kFatMinSupers) {
         // wide matrix: whole super-blocks of columns go to the fat-lane kernel, the rest to the kernel below
         const i64 supers = ncols / fat_super<kFatP>(), fat_cols = supers * fat_super<kFatP>();
@@ -871,14 +885,6 @@ dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
 
 constexpr size_t kSlabLdsBudget = 64 * 1024;
 
-// Whether pieces of rows that start a multiple of 32 floats behind these pointers are whole 128-byte lines in every row.
-bool whole_lines(const dpsgd_ctx *ctx, std::initializer_list<const void *> ptrs)
-{
-    bool ok = (ctx->ld % 32) == 0;
-    for (const void *p : ptrs) ok = ok && (reinterpret_cast<uintptr_t>(p) % 128) == 0;
-    return ok;
-}
-
 // Wide part of a slab launch: whole super-blocks with SP float4 per lane.  Returns the columns it took (0: none).
 template <int SP, bool SWAPPED>
 dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float *Xout, i64 col0, i64 ncols, bool cons,
@@ -906,6 +912,30 @@ dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, 
     return hip_status(hipGetLastError());
 }
 
+// Whether the slab kernels deal the columns out as chunks (mix_csr_slab_wide_kernel) or consecutively.  Rows of whole
+// cache lines: chunks, which the channels serve faster.  Rows whose chunks share lines with the chunks of other
+// workgroups: consecutive columns, unless the rows are 16-byte aligned and the call streams half a gigabyte or more
+// through other matrices than the one it overwrites (a gigabyte through rows of whole 64-byte halves in place); a W of
+// more than 40 entries per row is bound by its sums, which the consecutive kernel gives more waves.
+// us, chunks / consecutive:
+//   in place        8 x 8 882 808, 3 entries per row 186 / 139; 48 x 5 719 348 797 / 740; whole halves 24 x 9 972 176 566 / 614
+//   out of place    12 x 2 500 368 (360 MB) 77 / 61; 20 x 17 969 616 (4.3 GB) 810 / 906; 48 x 6 805 752 (3.9 GB) 878 / 920
+//   swapped         16 x 1 058 596 out of place (203 MB) 50 / 38; 16 x 3 052 820 (586 MB) 116 / 130
+//   momentum        20 x 1 344 628 in place (323 MB) 114 / 98, 20 x 3 511 576 (843 MB) 274 / 313; 16 x 3 977 520 out of place
+//                   (1 GB) 217 / 278; 64 x 1 682 544 in place, 64 entries per row 929 / 565
+//   4-byte aligned  24 x 1 250 003, momentum in place and mean 139 / 118
+bool slab_chunks(const dpsgd_ctx *ctx, const float *Xin, const float *G, const float *Xout, i64 ncols, const float *vel, bool swapped)
+{
+    if (whole_lines(ctx, {Xin, G, Xout}, 128)) return true;
+    const uintptr_t low = reinterpret_cast<uintptr_t>(Xin) | reinterpret_cast<uintptr_t>(G) | reinterpret_cast<uintptr_t>(Xout) |
+                          reinterpret_cast<uintptr_t>(vel);
+    if ((ctx->ld % 4) != 0 || (low % 16) != 0) return false;
+    const bool in_place = Xin == Xout, plain = in_place && !vel && !swapped;
+    if (plain && !whole_lines(ctx, {Xin, G, Xout}, 64)) return false;
+    const i64 matrices = 2 + (in_place ? 0 : 1) + (vel ? 1 : 0);
+    return matrices * 4 * ctx->n * ncols >= ((i64)1 << (plain ? 30 : 29)) && (i64)ctx->colidx.size() <= (i64)40 * ctx->n;
+}
+
 constexpr size_t kSlabWideLdsBudget = 128 * 1024;   // one workgroup per CU with two float4 per lane
 
 template <int V, bool SWAPPED>
@@ -916,9 +946,7 @@ dpsgd_status slab_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     float *vel = Vel ? Vel + col0 : nullptr;
     // wide matrices: whole super-blocks of columns with the chunked column ownership, the rest consecutively
     i64 done = 0, parts = 0;
-    // (chunks that share cache lines with the chunk of another workgroup lose more than the channels gain: 24 workers x
-    // 1 250 003 without padding, momentum and mean: 139 us against 118 with consecutive columns, padded 112)
-    if (V == 4 && !ctx->opt_mix_narrow && whole_lines(ctx, {Xin + col0, G + col0, Xout + col0})) {
+    if (V == 4 && !ctx->opt_mix_narrow && slab_chunks(ctx, Xin + col0, G + col0, Xout + col0, ncols, vel, SWAPPED)) {
         dpsgd_status st = DPSGD_OK;
         if (ncols / slab_super<2>() >= 16 && (size_t)ctx->n * 64 * 2 * 16 <= kSlabWideLdsBudget && ctx->opt_mix_vec != 1)
             st = slab_wide_launch<2, SWAPPED>(ctx, Xin, G, Xout, col0, ncols, cons, partials, vel, mu, &done, &parts);
@@ -1126,7 +1154,11 @@ dpsgd_status launch_mean(dpsgd_ctx *ctx, const float *X, float *xbar)
     i64 np = 0;
     dpsgd_status st = DPSGD_OK;
     constexpr int kMeanP = 4;
-    if (vec == 4 && !ctx->opt_mix_narrow && p.bulk_cols / fat_super<kMeanP>() >= 64) {
+    // (rows that share cache lines with the chunks of other workgroups: consecutive columns up to 768 MB; ring mix and mean
+    // of 4 x 10 283 863 129 us with fat lanes, 123 with consecutive columns, of 20 x 9 309 083 596 / 580, of
+    // 16 x 17 275 729 901 / 912)
+    const bool fat = whole_lines(ctx, {X}, 64) || (i64)ctx->n * p.bulk_cols > (i64)192 << 20;
+    if (vec == 4 && fat && !ctx->opt_mix_narrow && p.bulk_cols / fat_super<kMeanP>() >= 64) {
         // wide matrix: whole super-blocks of columns go to the fat-lane kernel, the rest to the kernel below
         const i64 supers = p.bulk_cols / fat_super<kMeanP>(), fat_cols = supers * fat_super<kMeanP>();
         const i64 groups = supers * (kFatStride / (kFatChunkLanes * 4));

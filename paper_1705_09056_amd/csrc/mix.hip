@@ -1061,7 +1061,8 @@ dpsgd_status launch_mix(dpsgd_ctx *ctx, const float *Xin, const float *G, float 
 
     // (the columns beyond the last whole vector ride along in the bulk launch, its last workgroup)
     if (ring) {
-        const int vec = pick_vec(ctx, ctx->d, 4);
+        int vec = pick_vec(ctx, ctx->d, 4);
+        if (!ctx->opt_mix_vec && ctx->d <= 64 && (ctx->d % vec) != 0) vec = 1;   // one workgroup without a tail: it forms the consensus itself
         const Plan p = make_plan(ctx, vec);
         const int tail = (int)p.tail_cols;
         if (vec == 4) st = ring_launch<4>(ctx, Xin, G, Xout, 0, p.bulk_cols, cons, ctx->d_partials, &n1, Vel, mu, false, tail, &fin);

@@ -177,8 +177,8 @@ dpsgd_status dpsgd_set_gamma(dpsgd_ctx *ctx, float gamma);
  * "conv_block" (default 1: CNN forward, residual blocks that keep the resolution (16 channels, 32 on 16 x 16 or 64 on 8 x 8
  * pixels): both convolutions of
  * the block in one launch, the activation between them kept in LDS for the second one; 0: two launches.  Same bits),
- * "conv_pad" (default 1: CNN stages of at most 64 channels and 64 pixels per row whose extents the matrix kernels do not
- * take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple of 8 rows - are kept in the
+ * "conv_pad" (default 1: CNN stages of at most 64 channels and 64 pixels per row (more than 32 channels: 32 pixels) whose
+ * extents the matrix kernels do not take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple of 8 rows - are kept in the
  * workspace rounded up to such extents, zeros beyond the real ones; 0: in their real extents, which leaves them to slower
  * kernels.  Results agree to fp32 rounding of the sums.  Where the device cannot hold the larger workspace, 0 is taken),
  * "conv_band_rows" (output rows of an image per workgroup of the CNN's 3 x 3 convolution kernels: 8, 16, or 0 = chosen

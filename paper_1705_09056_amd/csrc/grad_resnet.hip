@@ -309,15 +309,21 @@ unsigned blocks_for(i64 total) { return (unsigned)((total + 255) / 256); }
 // 16 workers x 32 images of 1 x 28 x 28, 16 channels, 2 blocks per stage (stored 32 x 32, 16 x 16 and 8 x 8) take 0.56 ms
 // per iteration instead of 15.4.  Channels double from stage to stage, so a base of up to 16 channels is
 // stored as 16 / 32 / 64, up to 32 as 32 / 64, up to 64 as 64; wider stages and rows of more than 64 pixels keep their
-// real extents.  So does a network whose first stage would take more than 16 times its memory (tiny images or channels).
+// real extents.  So do 64 channels with rows of 64 pixels, whose source patch no kernel has the LDS for (4 workers x 16
+// images of 3 x 40 x 40, base 64: 30.8 ms padded, 27.0 as they are), and a network whose first stage would take more than 16
+// times its memory (tiny images or channels).  32 channels with rows of 64 pixels have a matrix kernel for forward and data
+// gradient but none for the weight gradient, which pays as long as the padding stays below 3.5 times the memory (4 x 8 images
+// of 3 x 40 x 40, base 32, 1.6 times: 3.05 ms against 3.97; 8 x 16 of 38 x 38, base 17, 3.3 times: 0.80 of the time; 3 x 8 of
+// 12 x 26 x 39, base 17, 3.8 times: 1.28 ms against 1.01; 16 x 4 of 9 x 39, base 17, 5.5 times: 1.035 of the time).
 namespace {
 struct Extent { int C, H, W; };
 Extent stored_stage(int stage, int base, int C, int H, int W)
 {
     const int cs = (base <= 16 ? 16 : base <= 32 ? 32 : 64) << stage;
-    if (cs > 64 || C > cs || W > 64) return {C, H, W};
-    const int ws = W <= 8 ? 8 : W <= 16 ? 16 : W <= 32 ? 32 : 64;
-    return {cs, (H + 7) / 8 * 8, ws};
+    if (cs > 64 || C > cs || W > (cs == 64 ? 32 : 64)) return {C, H, W};
+    const int ws = W <= 8 ? 8 : W <= 16 ? 16 : W <= 32 ? 32 : 64, hs = (H + 7) / 8 * 8;
+    if (cs == 32 && ws == 64 && (i64)cs * hs * ws * 2 > 7 * ((i64)C * H * W)) return {C, H, W};
+    return {cs, hs, ws};
 }
 }  // namespace
 

@@ -196,6 +196,7 @@ def test_residual_block_in_one_launch_changes_no_bit(widths, batch, n):
     ((3, 20, 20, 24, 1, 10), 3, 2),   # 24 / 48 channels stored as 32 / 64, the 96 of the last stage as they are
     ((8, 16, 16, 20, 1, 10), 2, 2),   # the widest image the matrix-kernel stem takes
     ((3, 1, 9, 16, 1, 3), 3, 2),      # one pixel high
+    ((2, 9, 34, 30, 1, 4), 2, 2),     # 30 channels stored as 32 x 64 pixels: generic weight gradient between matrix kernels
     ((3, 32, 32, 8, 1, 10), 3, 2),    # as they are: 8 channels into 16 halving to rows of 16 and to rows of 8 pixels, on the
     ((1, 16, 16, 8, 1, 10), 4, 3),    # generic weight gradient although 16 into 32 of these extents has a matrix kernel
     ((3, 32, 32, 4, 1, 10), 2, 2),    # ... in the last stage
@@ -226,3 +227,26 @@ def test_padded_extents_agree_with_the_real_ones(widths, batch, n, bf16_inputs):
     assert np.array_equal(out[0][0], out[2][0]) and np.array_equal(out[0][1], out[2][1])
     check_close(out[1][0], out[0][0], 2 * TIGHT, "padded vs real extents", flips=True)
     assert rel_err(out[1][1], out[0][1]) < 2 * TIGHT
+
+
+@pytest.mark.parametrize("widths", [(2, 9, 34, 33, 1, 4),      # 33 channels x 34 pixels: no kernel takes 64 x 64
+                                    (2, 5, 33, 17, 1, 4)])     # 17 x 33: 6 times the memory in 32 x 64, for two kernels of three
+def test_extents_no_kernel_takes_are_kept_as_they_are(widths):
+    """The same launches with and without "conv_pad" in every stage that is not padded: the same bits.  (No bar against the
+    oracle: its own gradient of the first network moves by 5.6e-3, one element by 0.62 rms, when its scalar biases move by
+    1e-6.)  The second network pads its later stages, whose loss alone is compared."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=2, n=2)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            ctx.set_option("conv_pad", setting)
+            ctx.grad(B.Model(cfg.model_kind, cfg.widths, compute_bf16=True), Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append((Gd, loss))
+    assert rel_err(out[1][1].cpu().numpy(), out[0][1].cpu().numpy()) < 2 * TIGHT
+    if 2 * widths[3] > 64:
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

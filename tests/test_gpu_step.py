@@ -20,7 +20,7 @@ TOL = 2e-2
 TIGHT = 2e-3
 
 
-def step_case(cfg, bf16=True, spread=0.3, options=(), ld=0, expect_fused=None, topos=None):
+def step_case(cfg, bf16=True, spread=0.3, options=(), ld=0, expect_fused=None, topos=None, base=0):
     d = synth.model_dim(cfg.model_kind, cfg.widths)
     ld = ld or synth.padded_stride(d)
     X = synth.make_replicas(cfg, spread=spread)
@@ -36,7 +36,12 @@ def step_case(cfg, bf16=True, spread=0.3, options=(), ld=0, expect_fused=None, t
     inp_d = bf16_dev(inp) if bf16 else torch.from_numpy(inp).cuda()
     tgt_d = torch.from_numpy(tgt).cuda()
     Xa, Xb = to_dev(X, ld), to_dev(X, ld)
-    Ga, Gb = torch.full_like(Xa, 777.0), torch.full_like(Xa, 777.0)
+    if base:   # the matrix the step works on starts that many floats behind a 16-byte boundary
+        flat = torch.empty(base + Xa.numel(), device="cuda")
+        flat[base:] = Xa.view(-1)
+        Xa = flat[base:].view(Xa.shape)
+        assert Xa.data_ptr() % 16 == 4 * base
+    Ga, Gb = torch.full_like(Xb, 777.0), torch.full_like(Xb, 777.0)
     la, lb = torch.zeros(cfg.n, device="cuda"), torch.zeros(cfg.n, device="cuda")
     ca, cb = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
     xbar = torch.zeros(d, device="cuda")
@@ -180,7 +185,25 @@ def test_step_with_odd_row_stride():
     """Row stride d + 1: rows are only 4-byte aligned, which the fused kernels' wider accesses do not mind."""
     for cfg in (shrink(CONFIGS[2], widths=(1024, 1024, 10), batch=32, n=5),
                 shrink(CONFIG3_TORUS, widths=(1024, 1024, 10), batch=32, n=12, torus_dims=(3, 4))):
-        step_case(cfg, ld=synth.model_dim(cfg.model_kind, cfg.widths) + 1)
+        step_case(cfg, ld=synth.model_dim(cfg.model_kind, cfg.widths) + 1, expect_fused=True)
+
+
+@pytest.mark.parametrize("topology,n,dims,widths,batch,odd,base", [
+    ("ring", 5, None, (1024, 1024, 10), 48, 1, 1),          # [16][1 KB] rows want 32 samples: operands through LDS
+    ("ring", 4, None, (1024, 1024, 1024, 10), 32, 2, 3),    # 8-byte aligned rows behind a 12-byte offset
+    ("ring", 3, None, (1152, 1024, 10), 200, 1, 2),         # inputs a multiple of 128 only
+    ("torus", 12, (3, 4), (1056, 1024, 10), 40, 0, 1),      # aligned stride, base at an odd float
+    ("ring_chord", 8, None, (1024, 1024, 10), 32, 1, 1),    # slab of 4 column groups a workgroup
+    ("ring_chord", 16, None, (1024, 1024, 10), 48, 1, 3),   # of 2
+    ("ring_chord", 40, None, (1024, 1024, 10), 32, 3, 1),   # of 1
+    ("ring_chord", 6, None, (1056, 1024, 10), 32, 2, 0),    # of 1: 33 column groups
+])
+def test_fused_step_at_any_float(topology, n, dims, widths, batch, odd, base):
+    """Replicas whose rows and base pointer are aligned to 4 or 8 bytes only: the fused kernel of every kind of W runs."""
+    kw = dict(torus_dims=dims) if topology == "torus" else dict(topology=topology)
+    cfg = shrink(CONFIG3_TORUS if topology == "torus" else CONFIGS[2], widths=widths, batch=batch, n=n, **kw)
+    d = synth.model_dim(cfg.model_kind, cfg.widths)
+    step_case(cfg, ld=(d + 3) // 4 * 4 + odd, expect_fused=True, base=base)
 
 
 @pytest.mark.parametrize("topology", ["ring", "torus"])
@@ -439,10 +462,11 @@ def test_operands_through_lds_change_no_bit(widths, batch, n):
     ((1024, 2048, 1024, 10), 128),
 ])
 @pytest.mark.parametrize("ring_rows", [1, 0])
-def test_bf16_shadow_option_on_other_shapes(widths, batch, ring_rows):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_bf16_shadow_option_on_other_shapes(widths, batch, ring_rows, odd):
     cfg = shrink(CONFIGS[3], widths=widths, batch=batch, n=4, iters=3)
     d = synth.model_dim(cfg.model_kind, cfg.widths)
-    ld = synth.padded_stride(d)
+    ld = synth.padded_stride(d) + odd     # odd: the copy is written but only aligned rows have kernels that read it
     model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
     X0 = to_dev(synth.make_replicas(cfg), ld)
     runs = []

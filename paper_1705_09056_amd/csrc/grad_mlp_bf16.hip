@@ -2013,6 +2013,18 @@ __global__ void __launch_bounds__(256, 3) mlp_fused_ring_rows_kernel(FusedArgs a
     }
 }
 
+// Two floats of a row on their way out of the torus and slab kernels.  LINES: the 128-byte pieces of a row are whole
+// 64-byte halves of lines (fused_lines) and leave non-temporally; pieces that share halves with their neighbours leave
+// through the caches, which join them.  us per step, non-temporal / through the caches: 4 x 4 torus, 32 samples,
+// 3072-4096-4096-10 aligned 1244 / 1286, odd stride 2457 / 2118; ring with a far link, 16 x the same aligned 1325 / 1384, odd
+// stride 2510 / 2042; 16 x 1024-1024-1024-10 odd stride 236 / 193 and 241 / 194 (gradient and mix in two calls: 215).
+template <bool LINES> __device__ __forceinline__ void put2(float *p, float x, float y)
+{
+    const f32x2_a4 v = {x, y};
+    if (LINES) __builtin_nontemporal_store(v, reinterpret_cast<f32x2_a4 *>(p));
+    else *reinterpret_cast<f32x2_a4 *>(p) = v;
+}
+
 // ---------------------------------------- torus fusion, one wave per grid column (C <= 16 columns)
 // A workgroup owns one 16 x 32 tile (outputs x inputs) of the weight matrix for ALL workers; wave c takes grid
 // column c and walks down it like the ring kernel walks the ring: the tiles of workers (r-1, c), (r, c),
@@ -2034,7 +2046,7 @@ struct FusedTorusColArgs {
     double *partials;    // one per workgroup (CONS only)
 };
 
-template <bool CONS, int KT, int MAXC>   // MAXC: the most grid columns (waves per group) a launch may have
+template <bool CONS, int KT, int MAXC, bool LINES>   // MAXC: the most grid columns (waves per group) a launch may have; LINES: put2
 __global__ void __launch_bounds__(64 * MAXC * KT) mlp_fused_torus_cols_kernel(FusedTorusColArgs a)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -2141,8 +2153,8 @@ __global__ void __launch_bounds__(64 * MAXC * KT) mlp_fused_torus_cols_kernel(Fu
                 cur[v] = down[v];
                 down[v] = ahead[v];
             }
-            __builtin_nontemporal_store((f32x2){o4[0], o4[1]}, reinterpret_cast<f32x2_a4 *>(dst + (i64)(2 * h) * a.K));
-            __builtin_nontemporal_store((f32x2){o4[2], o4[3]}, reinterpret_cast<f32x2_a4 *>(dst + (i64)(2 * h + 1) * a.K));
+            put2<LINES>(dst + (i64)(2 * h) * a.K, o4[0], o4[1]);
+            put2<LINES>(dst + (i64)(2 * h + 1) * a.K, o4[2], o4[3]);
         }
     }
     if (CONS) {
@@ -2197,7 +2209,7 @@ struct FusedSlabArgs {
     double *partials;    // one per workgroup (CONS only)
 };
 
-template <bool CONS, int M, int NW>
+template <bool CONS, int M, int NW, bool LINES>   // LINES: put2
 __global__ void __launch_bounds__(64 * NW) mlp_fused_slab_kernel(FusedSlabArgs a)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -2321,7 +2333,7 @@ __global__ void __launch_bounds__(64 * NW) mlp_fused_slab_kernel(FusedSlabArgs a
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                __builtin_nontemporal_store((f32x2){o8[2 * i], o8[2 * i + 1]}, reinterpret_cast<f32x2_a4 *>(dst + 32 * m + (i64)i * a.K));
+                put2<LINES>(dst + 32 * m + (i64)i * a.K, o8[2 * i], o8[2 * i + 1]);
         }
     }
     if (CONS) {
@@ -2414,6 +2426,12 @@ bool layer_fusable(const dpsgd_ctx *ctx, int K, int O, i64 woff)
     if (torus_cols(ctx) || slab_fusion(ctx))
         return (K % 32) == 0 && (O % 32) == 0;
     return false;
+}
+
+// Whether the rows of a fused layer's weights (a multiple of 32 floats each) start on 64-byte halves of cache lines.
+bool fused_lines(const dpsgd_ctx *ctx, const float *X, i64 woff)
+{
+    return (woff % 16) == 0 && (ctx->ld % 16) == 0 && (reinterpret_cast<uintptr_t>(X) % 64) == 0;
 }
 
 dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, const void *inputs, const void *targets,
@@ -2696,6 +2714,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                 else hipLaunchKernelGGL((mlp_fused_ring_kernel<false, false>), grid, dim3(256), 0, s, fa);
             }
         } else if (slab_fusion(ctx)) {
+            const bool lines = fused_lines(ctx, X, woff[l]);
             FusedSlabArgs fa{};
             fa.X = X; fa.ld = ctx->ld; fa.woff = woff[l]; fa.dzt = ws.dzt[l + 1]; fa.at = actt[l];
             fa.rowptr = ctx->d_rowptr; fa.colidx = ctx->d_colidx; fa.vals = ctx->d_vals;
@@ -2713,7 +2732,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             const size_t shm = slab > red ? slab : red;
 #define DPSGD_SLAB_ONE(CONS, MG, NWV)                                                                                              \
     do {                                                                                                                        \
-        auto kern = mlp_fused_slab_kernel<CONS, MG, NWV>;                                                                       \
+        auto kern = lines ? mlp_fused_slab_kernel<CONS, MG, NWV, true> : mlp_fused_slab_kernel<CONS, MG, NWV, false>;           \
         if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                                        \
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)         \
             return DPSGD_EDEVICE;                                                                                               \
@@ -2731,6 +2750,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
 #undef DPSGD_SLAB
 #undef DPSGD_SLAB_ONE
         } else {
+            const bool lines = fused_lines(ctx, X, woff[l]);
             FusedTorusColArgs fa{};
             fa.X = X; fa.ld = ctx->ld; fa.woff = woff[l]; fa.dzt = ws.dzt[l + 1]; fa.at = actt[l];
             fa.R = ctx->dim0; fa.C = ctx->dim1; fa.K = K; fa.O = O; fa.Bp = Bp; fa.w = ctx->torus_w; fa.gamma = ctx->gamma;
@@ -2741,16 +2761,20 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             np = (i64)grid.x * grid.y * kt;
             if (nparts + np > ctx->partials_cap - 256) return DPSGD_EINVAL;
             const size_t shm = (size_t)2 * fa.C * 2048 * kt;
+#define DPSGD_TORUS(CONS, KT, MAXC)                                                                                              \
+    hipLaunchKernelGGL((lines ? mlp_fused_torus_cols_kernel<CONS, KT, MAXC, true> : mlp_fused_torus_cols_kernel<CONS, KT, MAXC, false>), \
+                       grid, dim3(64u * KT * fa.C), shm, s, fa)
             if (kt == 2) {
-                if (cons) hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<true, 2, 8>), grid, dim3(128u * fa.C), shm, s, fa);
-                else hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<false, 2, 8>), grid, dim3(128u * fa.C), shm, s, fa);
+                if (cons) DPSGD_TORUS(true, 2, 8);
+                else DPSGD_TORUS(false, 2, 8);
             } else if (fa.C <= 8) {
-                if (cons) hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<true, 1, 8>), grid, dim3(64u * fa.C), shm, s, fa);
-                else hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<false, 1, 8>), grid, dim3(64u * fa.C), shm, s, fa);
+                if (cons) DPSGD_TORUS(true, 1, 8);
+                else DPSGD_TORUS(false, 1, 8);
             } else {
-                if (cons) hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<true, 1, 16>), grid, dim3(64u * fa.C), shm, s, fa);
-                else hipLaunchKernelGGL((mlp_fused_torus_cols_kernel<false, 1, 16>), grid, dim3(64u * fa.C), shm, s, fa);
+                if (cons) DPSGD_TORUS(true, 1, 16);
+                else DPSGD_TORUS(false, 1, 16);
             }
+#undef DPSGD_TORUS
         }
         if (cons) nparts += np;
         st = hip_status(hipGetLastError());

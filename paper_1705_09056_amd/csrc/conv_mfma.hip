@@ -1322,12 +1322,13 @@ dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dou
     a.sign_in = act.sign; a.sign_out = nullptr;
     a.lw = ilog2(a.Wd);
     if (c.stride == 1) {
-        if (c.Cis == 16) return launch_conv<16, 16, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
-        if (c.Cis == 32) return launch_conv<32, 32, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
-        return launch_conv<64, 64, 1, 1, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
+        if (c.Cis == 16) return launch_conv<16, 16, 1, 1, true>(ctx, a, false);
+        if (c.Cis == 32) return launch_conv<32, 32, 1, 1, true>(ctx, a, false);
+        return launch_conv<64, 64, 1, 1, true>(ctx, a, false);
     }
-    if (c.Cis == 16) return launch_conv<32, 16, 1, 2, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
-    return launch_conv<64, 32, 1, 2, true>(ctx, a, c.stride == 2 && c.Wis < 2 * c.Wos);
+    const bool padded = c.Wis < 2 * c.Wos;   // (rows of 8 from rows of 8)
+    if (c.Cis == 16) return launch_conv<32, 16, 1, 2, true>(ctx, a, padded);
+    return launch_conv<64, 32, 1, 2, true>(ctx, a, padded);
 }
 
 dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, Tensor dout, float *G, float *partials,

@@ -56,9 +56,7 @@ struct GemmArgs {
     int M, N, K, relu;
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float: rows need no alignment
 
 // Workgroups are dealt to the 8 XCDs round-robin by linear id and every XCD has its own L2: with a multiple of 8 workers
 // the ids of a (tiles n, tiles m, workers) grid are renumbered so that one XCD computes all tiles of a worker, whose
@@ -74,23 +72,6 @@ __device__ __forceinline__ void worker_tile(int &w, int &tile_m, int &tile_n)
         tile_n = (int)(within % gridDim.x);
         tile_m = (int)(within / gridDim.x);
     }
-}
-
-// Four consecutive elements of which only the first `have` exist, as a load whose first element was clamped to the
-// extent's last four left them: element i sits 4 - have places further on when 0 < have < 4.  Zeros for the rest.
-__device__ __forceinline__ f32x4 mend4(f32x4 v, int have)
-{
-    f32x4 o;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float x = v[i];
-        if (have == 3) x = i < 3 ? v[i + 1 < 4 ? i + 1 : 3] : 0.f;
-        if (have == 2) x = i < 2 ? v[i + 2 < 4 ? i + 2 : 3] : 0.f;
-        if (have == 1) x = i < 1 ? v[3] : 0.f;
-        if (have <= 0) x = 0.f;
-        o[i] = x;
-    }
-    return o;
 }
 
 // Matrix instructions on fp32 operands (v_mfma_f32_32x32x2_f32: fp32 products and sums, a sixteenth of the bf16 rate but
@@ -187,15 +168,11 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    // workgroups start their walk over the contraction at different chunks: started together they would all read the
-    // same columns of rows that lie a multiple of 4 KB apart
     const int nchunks = (g.K + TK - 1) / TK;
-    const int start = A_KFAST && !B_NFAST ? (int)((unsigned)(tile_n * 5 + w * 3) % (unsigned)nchunks) : 0;
-    auto chunk_k = [&](int c) { const int cc = c + start; return (cc >= nchunks ? cc - nchunks : cc) * TK; };
-    fetch(chunk_k(0), even);
-    if (AHEAD2 && nchunks > 1) fetch(chunk_k(1), odd);
-    stage(0, even, chunk_k(0));
-    if (nchunks > (AHEAD2 ? 2 : 1)) fetch(chunk_k(AHEAD2 ? 2 : 1), even);
+    fetch(0, even);
+    if (AHEAD2 && nchunks > 1) fetch(TK, odd);
+    stage(0, even, 0);
+    if (nchunks > (AHEAD2 ? 2 : 1)) fetch((AHEAD2 ? 2 : 1) * TK, even);
     __syncthreads();
     // chunk c is multiplied, chunk c + 1 (in r) goes to LDS and chunk c + 2 or c + 3 is requested into its registers
     auto step = [&](int c, Chunk &r) {
@@ -218,8 +195,8 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
             for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
         }
         // (AHEAD2, for long walks: past the end the last chunk again, never used - a branch around the loads costs 10 %)
-        if (AHEAD2 || c + 1 < nchunks) stage((c & 1) ^ 1, r, chunk_k(min(c + 1, nchunks - 1)));   // its last readers have passed a barrier
-        if (AHEAD2 || c + 2 < nchunks) fetch(chunk_k(min(c + (AHEAD2 ? 3 : 2), nchunks - 1)), r);
+        if (AHEAD2 || c + 1 < nchunks) stage((c & 1) ^ 1, r, min(c + 1, nchunks - 1) * TK);   // its last readers have passed a barrier
+        if (AHEAD2 || c + 2 < nchunks) fetch(min(c + (AHEAD2 ? 3 : 2), nchunks - 1) * TK, r);
         __syncthreads();
     };
     if (AHEAD2) {
@@ -245,7 +222,9 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
     if (n >= g.N) return;
     const float bias = g.bias ? g.bias[(i64)w * g.sBiasw + n] : 0.f;
     float *c = g.C + (i64)w * g.sCw + (i64)m1 * g.sCm + n;
-    if (full_mn && !g.relu && !g.mask) {   // (the weight gradient: nothing but stores)
+    // (the weight gradient: nothing but stores, non-temporal at any alignment of the rows: 50 workers x 64 x 784-1966 on tight
+    // rows 131 us, 141 with plain stores; 16 x 64 x 3072-1023-10 the other way round, a step 307 against 300)
+    if (full_mn && !g.relu && !g.mask) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(acc[v] + bias, c + (i64)((v >> 2) * 8 + (v & 3)) * g.sCm);
         return;
@@ -269,11 +248,11 @@ dpsgd_status gemm_f32_launch(hipStream_t s, int nworkers, const GemmArgs &g)
     dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
     if (grid.y > 65535u || grid.z > 65535u) return DPSGD_EUNSUPPORTED;
     const dim3 block(64 * WM * WN * WK);
-    const bool akf = g.sAk == 1, bnf = g.sBn == 1;
-    if (!TINY && !bnf) return DPSGD_EUNSUPPORTED;   // (a forward product: linear_fwd_f32)
+    const bool akf = g.sAk == 1, bnf = g.sBn == 1;   // (B contiguous along k: a forward product, only of less than 4 inputs)
     if (akf && bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if (bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, false, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if constexpr (TINY) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, false, TINY, AHEAD2>), grid, block, 0, s, g);
+    else return DPSGD_EUNSUPPORTED;
     return hip_status(hipGetLastError());
 }
 
@@ -496,14 +475,13 @@ linear_fwd_class_kernel(const float *__restrict__ act, const float *__restrict__
     out[((i64)w * B + b) * O + o] = s + X[(i64)w * ld + boff + o];
 }
 
-// Forward of a hidden layer with few outputs (O <= 16): one workgroup per worker and R sample rows; its
-// four waves take every fourth 1 KB piece of the rows (lanes stride over the inputs with 16-byte loads), every lane
-// keeps R x O partial sums, a wave reduction and a sum over the four waves (in wave order) finish them.  The tiled GEMM
-// above would launch only a handful of workgroups for such a shape.  With a whole row per wave the launch was short of
-// waves (2048 rows at 128 samples x 16 workers: two waves per SIMD, each a chain of twelve dependent round trips to
-// L2: 36.8 us); with the row split over four waves the weights every workgroup pulls from L2 (120 KB, 245 MB per
-// launch) set the time (30.1 us), so a workgroup takes two rows per weight piece (23.5 us; four rows, or a wave per
-// 1 KB piece with four rows: 27.6 and 40.5 us).
+// Forward of a hidden layer with few outputs (O <= 16) and 256 inputs or more: one workgroup per worker and R sample rows;
+// its four waves take every fourth 1 KB piece of the rows (VEC: lanes stride over the inputs with 16-byte loads; else one
+// float each), every lane keeps R x O partial sums, a wave reduction and a sum over the four waves (in wave order) finish
+// them.  The tiled product above would launch only a handful of workgroups for such a shape.  Two rows share a weight
+// piece: of 16 workers x 128 samples x 3072 inputs x 10 outputs the weights that every workgroup pulls from L2 set the
+// time, 30.1 us with a row each, 23.5 with two, 27.6 with four (and 36.8 with a whole row per wave: two waves per SIMD, each
+// a chain of twelve dependent round trips).
 template <int OMAX, bool VEC, int R>   // R sample rows per workgroup: a weight piece fetched from L2 serves R rows
 __global__ void __launch_bounds__(256)
 linear_fwd_skinny_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,

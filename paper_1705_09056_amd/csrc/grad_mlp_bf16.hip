@@ -33,12 +33,10 @@ typedef long long i64;
 typedef unsigned short bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 // 16-byte accesses at any element (the hardware needs no more than that): rows of odd length or stride
-typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef unsigned int u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 
@@ -77,21 +75,6 @@ __device__ __forceinline__ f32x4 load4(const float *row, int k, int K)
     const f32x4_a4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4 *>(row + min(k, K - 4)));
     return (f32x4){v.x, v.y, v.z, v.w};
 }
-__device__ __forceinline__ f32x4 mend4(f32x4 v, int have)
-{
-    f32x4 o;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float x = v[i];
-        if (have == 3) x = i < 3 ? v[i + 1 < 4 ? i + 1 : 3] : 0.f;
-        if (have == 2) x = i < 2 ? v[i + 2 < 4 ? i + 2 : 3] : 0.f;
-        if (have == 1) x = i < 1 ? v[3] : 0.f;
-        if (have <= 0) x = 0.f;
-        o[i] = x;
-    }
-    return o;
-}
-
 // Transposed operand copies ("T copies": minibatch index fastest) are stored in MFMA fragment order so
 // that a wave fetches one operand of v_mfma_f32_32x32x16_bf16 as 1 KB of consecutive memory: rows
 // (features) in groups of 32, samples in groups of 16; inside a group first the half (samples 0-7,

@@ -909,7 +909,7 @@ dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, 
     if (st != DPSGD_OK) return st;
     *cols_done = supers * slab_super<SP>();
     *parts = groups;
-    return hip_status(hipGetLastError());
+    return DPSGD_OK;
 }
 
 // Whether the slab kernels deal the columns out as chunks (mix_csr_slab_wide_kernel) or consecutively.  Rows of whole

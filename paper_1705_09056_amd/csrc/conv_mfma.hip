@@ -1010,13 +1010,16 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
 }
 
 // Workgroups that share one worker's minibatch (each writes a partial sum of the whole weight gradient): few when
-// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many, and at least
-// enough for seven workgroups per eight CUs where the minibatch has that many images (112 workers x 2 are).
+// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many, and twice as many as
+// long as a CU gets no second one, where the minibatch has that many images.  That makes the reduction of the partials
+// the largest launch of a few workers' pass, and pays all the same: 16 workers x 32 images of 28 x 28, 2 blocks per stage,
+// weight gradients 375 -> 202 us, reduction 11 -> 50, a step 673 -> 549; 3 blocks on 32 x 32, 16 images: 28 workers 784 -> 749,
+// 64 workers 1163 -> 1157; beyond 256 workgroups 72 workers 1280 -> 1325.
 int wgrad_splits(int n, int B, int co, int stride)
 {
     int m = co >= 64 ? 2 : (co >= 32 ? 4 : 8);
     if (stride == 2 && m < 8) m *= 2;
-    while ((i64)n * m < 224 && m < B) m *= 2;
+    while ((i64)n * m * 2 <= 256 && m < B) m *= 2;
     return B < m ? B : m;
 }
 

@@ -813,8 +813,8 @@ Finish finish_for(const dpsgd_ctx *ctx, Consensus *c, i64 before, i64 groups)
     return f;
 }
 
-// Whether pieces of rows that start a multiple of 32 floats behind these pointers are whole 128-byte lines, or whole
-// 64-byte halves of them, in every row.
+// Whether pieces of rows that start a multiple of 32 floats behind these pointers are whole 128-byte lines, whole 64-byte
+// halves of them, or 16-byte aligned at least, in every row.
 bool whole_lines(const dpsgd_ctx *ctx, std::initializer_list<const void *> ptrs, int bytes)
 {
     bool ok = (ctx->ld % (bytes / 4)) == 0;
@@ -834,10 +834,12 @@ dpsgd_status ring_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, float
     constexpr int kFatP = 8;              // float4 groups per lane of the fat-lane kernel
     constexpr i64 kFatMinSupers = 64;     // 64 x 64 single-wave workgroups: enough to fill the chip
     // (rows whose pieces share halves of cache lines with those of other workgroups, updated in place: consecutive columns
-    // are faster.  5 workers x 12 101 282 columns 160 us with fat lanes, 123 with consecutive columns, 10 x 13 066 066
-    // 358 / 313, with momentum 3 x 10 104 793 134 / 105; halves that are whole: 20 x 11 695 280 536 / 611; into another
-    // matrix 12 x 20 217 899 682 / 686, 10 x 43 918 948 1172 / 1230)
-    const bool fat = Xin != Xout || whole_lines(ctx, {Xin + col0, G + col0, Xout + col0}, 64);
+    // are faster, unless with momentum half a gigabyte of 16-byte aligned rows streams by.  5 workers x 12 101 282 columns
+    // 160 us with fat lanes, 123 with consecutive columns, 10 x 13 066 066 358 / 313, with momentum 3 x 10 104 793 134 / 105,
+    // 3 x 13 077 836 169 / 140, 3 x 20 944 408 237 / 247; halves that are whole: 20 x 11 695 280 536 / 611; into another matrix
+    // 12 x 20 217 899 682 / 686, 10 x 43 918 948 1172 / 1230)
+    const bool fat = Xin != Xout || whole_lines(ctx, {Xin + col0, G + col0, Xout + col0}, 64) ||
+                     (Vel && (i64)12 * ctx->n * ncols >= ((i64)1 << 29) && whole_lines(ctx, {Xin + col0, G + col0, Vel + col0}, 16));
     if (V == 4 && fat && bands == 1 && !narrow && !ctx->opt_mix_narrow && ctx->opt_mix_bands == 0 && ctx->n >= 3 &&
         ncols / fat_super<kFatP>() >= kFatMinSupers) {
         // wide matrix: whole super-blocks of columns go to the fat-lane kernel, the rest to the kernel below
@@ -915,25 +917,25 @@ dpsgd_status slab_wide_launch(dpsgd_ctx *ctx, const float *Xin, const float *G, 
 // Whether the slab kernels deal the columns out as chunks (mix_csr_slab_wide_kernel) or consecutively.  Rows of whole
 // cache lines: chunks, which the channels serve faster.  Rows whose chunks share lines with the chunks of other
 // workgroups: consecutive columns, unless the rows are 16-byte aligned and the call streams half a gigabyte or more
-// through other matrices than the one it overwrites (a gigabyte through rows of whole 64-byte halves in place); a W of
-// more than 40 entries per row is bound by its sums, which the consecutive kernel gives more waves.
+// (swapped: 384 MB) through other matrices than the one it overwrites, or a gigabyte through rows of whole 64-byte halves in
+// place; short of whole halves, up to 16 workers also write another matrix in consecutive columns.  A W of more than 40
+// entries per row is bound by its sums, which the consecutive kernel gives more waves.
 // us, chunks / consecutive:
 //   in place        8 x 8 882 808, 3 entries per row 186 / 139; 48 x 5 719 348 797 / 740; whole halves 24 x 9 972 176 566 / 614
-//   out of place    12 x 2 500 368 (360 MB) 77 / 61; 20 x 17 969 616 (4.3 GB) 810 / 906; 48 x 6 805 752 (3.9 GB) 878 / 920
-//   swapped         16 x 1 058 596 out of place (203 MB) 50 / 38; 16 x 3 052 820 (586 MB) 116 / 130
+//   out of place    12 x 2 500 368 (360 MB) 77 / 61; 12 x 15 250 212 504 / 481; whole halves 12 x 31 785 424 821 / 954;
+//                   20 x 17 969 616 (4.3 GB) 810 / 906; 48 x 6 805 752 (3.9 GB) 878 / 920
+//   swapped         16 x 1 058 596 out of place (203 MB) 50 / 38; 4 x 8 661 336 (416 MB) 77 / 83; 16 x 3 052 820 116 / 130
 //   momentum        20 x 1 344 628 in place (323 MB) 114 / 98, 20 x 3 511 576 (843 MB) 274 / 313; 16 x 3 977 520 out of place
 //                   (1 GB) 217 / 278; 64 x 1 682 544 in place, 64 entries per row 929 / 565
 //   4-byte aligned  24 x 1 250 003, momentum in place and mean 139 / 118
 bool slab_chunks(const dpsgd_ctx *ctx, const float *Xin, const float *G, const float *Xout, i64 ncols, const float *vel, bool swapped)
 {
     if (whole_lines(ctx, {Xin, G, Xout}, 128)) return true;
-    const uintptr_t low = reinterpret_cast<uintptr_t>(Xin) | reinterpret_cast<uintptr_t>(G) | reinterpret_cast<uintptr_t>(Xout) |
-                          reinterpret_cast<uintptr_t>(vel);
-    if ((ctx->ld % 4) != 0 || (low % 16) != 0) return false;
+    if (!whole_lines(ctx, {Xin, G, Xout, vel}, 16)) return false;   // (no velocity: null)
     const bool in_place = Xin == Xout, plain = in_place && !vel && !swapped;
-    if (plain && !whole_lines(ctx, {Xin, G, Xout}, 64)) return false;
+    if (!vel && !swapped && (in_place || ctx->n <= 16) && !whole_lines(ctx, {Xin, G, Xout}, 64)) return false;
     const i64 matrices = 2 + (in_place ? 0 : 1) + (vel ? 1 : 0);
-    return matrices * 4 * ctx->n * ncols >= ((i64)1 << (plain ? 30 : 29)) && (i64)ctx->colidx.size() <= (i64)40 * ctx->n;
+    return matrices * 4 * ctx->n * ncols >= ((i64)(plain ? 8 : swapped ? 3 : 4) << 27) && (i64)ctx->colidx.size() <= (i64)40 * ctx->n;
 }
 
 constexpr size_t kSlabWideLdsBudget = 128 * 1024;   // one workgroup per CU with two float4 per lane

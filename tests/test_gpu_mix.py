@@ -327,6 +327,45 @@ def test_fat_lane_ring_kernel_matches_the_narrow_one_bitwise(n, with_consensus):
     assert torch.equal(Xi[:, :d], outs[0][:, :d])
 
 
+@pytest.mark.parametrize("topology,n,d,call,in_place", [
+    ("ring", 3, 8_390_000, "mix", False), ("ring", 3, 8_390_000, "mix", True), ("ring", 3, 8_390_000, "momentum", True),
+    ("ring", 6, 8_390_000, "momentum", True),            # 604 MB
+    ("ring_chord", 4, 11_000_000, "mix", False), ("ring_chord", 4, 11_000_000, "swapped", False),     # 528 MB
+    ("ring_chord", 4, 11_000_000, "momentum", False), ("ring_chord", 4, 11_000_000, "momentum", True),   # 704, 528 MB
+    ("ring_chord", 8, 17_000_000, "mix", True),          # 1.09 GB
+])
+@pytest.mark.parametrize("align", [1, 2, 4, 16, 32])   # floats that divide the row stride: 4 bytes to whole cache lines
+def test_columns_dealt_by_alignment_give_the_same_iterate(topology, n, d, call, in_place, align):
+    """Which kernel owns which columns (fat lanes, chunks, consecutive columns) follows alignment, size and whether the call
+    overwrites its input; with "mix_narrow" it is consecutive columns throughout.  Same products in the same order: the
+    same bits of iterate and velocity.  The node average of the columns that whole blocks leave over is summed in bands of
+    rows: another order of n terms, n roundings of at most 2^-24 of the largest partial sum, which n max|x| bounds, over n.
+    The consensus distance adds other partial sums up."""
+    ld = d // 32 * 32 + 32 + align % 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d + align)
+    X, G, V = (torch.randn(n, ld, device="cuda", generator=g) for _ in range(3))
+    print(f"{topology} n={n} d={d} ld={ld} {call} in_place={in_place}", flush=True)
+    got = []
+    for narrow in (0, 1):
+        Xi, Vi = X.clone(), V.clone()
+        out = Xi if in_place else torch.full_like(X, 777.0)
+        cons, xbar = torch.zeros(1, device="cuda"), torch.zeros(d, device="cuda")
+        with B.Dpsgd(n, d, getattr(B.Topology, topology)(), 0.1, ld=ld) as ctx:
+            ctx.set_option("mix_narrow", narrow)
+            if call == "momentum":
+                ctx.mix_step_momentum(Xi, G, Vi, 0.9, out, cons)
+            else:
+                ctx.mix_step(Xi, G, out, cons, swapped=call == "swapped")
+            ctx.mean(out, xbar)
+            torch.cuda.synchronize()
+        assert torch.equal(out[:, d:], X[:, d:]) if in_place else bool((out[:, d:] == 777.0).all())
+        got.append((out, Vi, xbar, float(cons)))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert float((got[0][2] - got[1][2]).abs().max()) <= n * 2.0 ** -24 * float(got[0][0][:, :d].abs().max())
+    assert got[0][3] == pytest.approx(got[1][3], rel=1e-5)
+
+
 # ------------------------------------------------------------------ momentum variant (dpsgd_mix_step_momentum)
 def run_momentum(n, d, ld, topo_b, topo_o, seed, inplace, mu=0.9, gamma=0.05, steps=3, options=()):
     rng = np.random.default_rng(seed)

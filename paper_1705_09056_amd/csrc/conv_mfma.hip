@@ -1010,16 +1010,17 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
 }
 
 // Workgroups that share one worker's minibatch (each writes a partial sum of the whole weight gradient): few when
-// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many, and twice as many as
-// long as a CU gets no second one, where the minibatch has that many images.  That makes the reduction of the partials
-// the largest launch of a few workers' pass, and pays all the same: 16 workers x 32 images of 28 x 28, 2 blocks per stage,
-// weight gradients 375 -> 202 us, reduction 11 -> 50, a step 673 -> 549; 3 blocks on 32 x 32, 16 images: 28 workers 784 -> 749,
-// 64 workers 1163 -> 1157; beyond 256 workgroups 72 workers 1280 -> 1325.
+// the gradient is large (the partials are HBM traffic), more when the source rows of a band are many, and doubled, where the
+// minibatch has that many images, until seven of eight CUs have one (64 output channels, whose partials are the largest: as
+// long as no CU gets a second one).  That makes the reduction of the partials the largest launch of a few workers' pass, and
+// pays all the same: 16 workers x 32 images of 28 x 28, 2 blocks per stage, weight gradients 375 -> 202 us, reduction
+// 11 -> 50, a step 673 -> 549.  A second workgroup per CU: gradient and mix of 20 workers x 9 images, 16 and 32 channels 352
+// with, 396 without; 64 channels of 72 workers x 16 images of 32 x 32, 3 blocks, 1325 with, 1280 without.
 int wgrad_splits(int n, int B, int co, int stride)
 {
     int m = co >= 64 ? 2 : (co >= 32 ? 4 : 8);
     if (stride == 2 && m < 8) m *= 2;
-    while ((i64)n * m * 2 <= 256 && m < B) m *= 2;
+    while ((co >= 64 ? (i64)n * m * 2 <= 256 : (i64)n * m < 224) && m < B) m *= 2;
     return B < m ? B : m;
 }
 

@@ -178,9 +178,11 @@ dpsgd_status dpsgd_set_gamma(dpsgd_ctx *ctx, float gamma);
  * pixels): both convolutions of
  * the block in one launch, the activation between them kept in LDS for the second one; 0: two launches.  Same bits),
  * "conv_pad" (default 1: CNN stages of at most 64 channels and 64 pixels per row (more than 32 channels: 32 pixels) whose
- * extents the matrix kernels do not take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple of 8 rows - are kept in the
- * workspace rounded up to such extents, zeros beyond the real ones; 0: in their real extents, which leaves them to slower
- * kernels.  Results agree to fp32 rounding of the sums.  Where the device cannot hold the larger workspace, 0 is taken),
+ * extents the matrix kernels do not take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple
+ * of 8 rows - are kept in the workspace rounded up to such extents, zeros beyond the real ones; 0: in their real extents,
+ * which leaves them to kernels that may be an order of magnitude slower.  Results agree to fp32 rounding of the sums.  Where
+ * the device cannot hold the larger workspace at the first call of a model, that model runs as with 0: set 0 where results
+ * must not depend, bit for bit, on how much memory was free),
  * "conv_band_rows" (output rows of an image per workgroup of the CNN's 3 x 3 convolution kernels: 8, 16, or 0 = chosen
  * per convolution, the default; every setting gives the same bits),
  * "time_fused" (see dpsgd_read_timing). */
@@ -234,7 +236,8 @@ dpsgd_status dpsgd_mix_step_momentum(dpsgd_ctx *ctx, const float *X_in, const fl
                                      float *X_out, float *consensus);
 
 /* One whole iteration of Algorithm 1 in place: X <- W X - gamma * grad(X), i.e. the result of dpsgd_grad(X -> G)
- * followed by dpsgd_mix_step(X, G -> X), up to the order of floating-point sums.  Footnote [b] observes that steps 3
+ * followed by dpsgd_mix_step(X, G -> X), up to the order of floating-point sums (a data gradient may take another kernel
+ * than in dpsgd_grad, and in either call another one with few workers than with many).  Footnote [b] observes that steps 3
  * and 4 are independent; here they share one pass over X wherever a kernel exists for it.
  * Fused (the weight gradient of a layer is formed inside the mix kernel and never written to memory): model MLP or
  * SOFTMAX with compute_bf16 = 1, on DPSGD_TOPO_RING with n >= 3 (a walk around the ring with three rows in

@@ -267,7 +267,7 @@ dpsgd_status gemm_f32(hipStream_t s, int nworkers, const GemmArgs &g)
         return gemm_f32_launch<1, 1, 4, 16, false, true>(s, nworkers, g);
     }
     // 16 workers x 64 samples x 3072 x 1024 (us; before: with a thread per 4 x 4 block on the vector units): weight
-    // gradient 118 -> 79 with 64 x 64 tiles and no split (its contraction is the minibatch; a second wave per tile: 93); a
+    // gradient 118 -> 83-87 with 64 x 64 tiles and no split (its contraction is the minibatch; a second wave per tile: 93); a
     // contraction of 3072 70 with the contraction split over two waves, 76 without.  10 rows x 3072 x 128 samples (a class
     // layer's weight gradient): 19 -> 10.9 with 32 x 64 tiles, 64 x 64: 14.  Results that leave most CUs without such a
     // tile take 32 x 32 ones and four waves each.
@@ -405,7 +405,7 @@ dpsgd_status linear_fwd_launch(hipStream_t s, int nworkers, const GemmArgs &g)
 dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
 {
     if (g.K < 4) return gemm_f32(s, nworkers, g);
-    // 16 workers x 64 samples x 3072 x 1024: 73 us with 64 x 32 tiles and eight waves, 83 with 32 x 32 tiles and four (the
+    // 16 workers x 64 samples x 3072 x 1024: 73-79 us with 64 x 32 tiles and eight waves, 83 with 32 x 32 tiles and four (the
     // thread-per-4x4-block kernel: 333); 4 workers x 3072-1024-10 x 128 samples: 133 us per gradient and mix either way;
     // minibatches of at most 32 samples or few tiles: the smaller ones (32 x 3072-512-512-10 x 32: 279 against 323).
     if (g.M > 32 && (i64)((g.M + 63) / 64) * ((g.N + 31) / 32) * nworkers >= 256)

@@ -1520,10 +1520,10 @@ Tiling pick_tiling(int B)
 //   data gradient, B <= 32       1024 <- 784 x 24 x 16 (128) 77.5 / 74.4, 2048 <- 512 x 32 x 12 (192) 99.5 / 102.8
 //   ... B <= 64                  1024 <- 784 x 64 x 16 (128) 104.4 / 94.4, 2048 <- 784 x 64 x 12 (192) 151 / 161
 //   ... B > 64                   2048 <- 1024 x 100 x 4 (128) 119 / 109, 1536 <- 3072 x 100 x 6 (144) 176 / 187
-bool few_tiles(int features, int B, int n, bool longer)
+bool few_tiles(int features, int B, int n, bool forward, bool longer)
 {
     const Tiling t = pick_tiling(B);
-    const int tf = t.wn * 32 == 128 && t.mt == 1 ? 64 : t.wn * 32;   // (the k-split forward's tile is 64 wide)
+    const int tf = forward && t.mt == 1 ? 64 : t.wn * 32;   // (the k-split forward's tile is 64 wide)
     const i64 wgs = (i64)((features + tf - 1) / tf) * ((B + 32 * t.wm * t.mt - 1) / (32 * t.wm * t.mt)) * n;
     return wgs <= (longer ? 255 : 128);
 }
@@ -2533,7 +2533,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             if (vec && (a.K % 16) == 0) hipLaunchKernelGGL(mlp_fwd_last_kernel<true>, lgrid, dim3(512), 0, s, a);
             else hipLaunchKernelGGL(mlp_fwd_last_kernel<false>, lgrid, dim3(512), 0, s, a);
             st = hip_status(hipGetLastError());
-        } else if (a.K >= 4 && (!vec || t.mt > 1) && few_tiles(a.O, B, n, !vec && B <= 64)) {
+        } else if (a.K >= 4 && (!vec || t.mt > 1) && few_tiles(a.O, B, n, true, !vec && B <= 64)) {
             // (aligned rows and at most 32 samples: the k-split kernel already has 64-wide tiles and splits the contraction)
             const dim3 sgrid((unsigned)((act_pitch(a.O) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                              (unsigned)n);
@@ -2625,7 +2625,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             da.wb = wb_use[l];
             da.wb_strips = strips_use[l];
             const bool vec = base_ok && (K % 4) == 0 && (woff[l] % 4) == 0;
-            if (K >= 4 && !may_copy(l) && few_tiles(K, B, n, false)) {
+            if (K >= 4 && !may_copy(l) && few_tiles(K, B, n, false, false)) {
                 const dim3 sgrid((unsigned)((act_pitch(K) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                                  (unsigned)n);
                 if (t.mt == 1) hipLaunchKernelGGL(mlp_dgrad_small_kernel<1>, sgrid, dim3(256), 0, s, da);

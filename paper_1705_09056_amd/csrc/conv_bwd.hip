@@ -1,0 +1,600 @@
+// Backward of the CNN's 3x3 convolutions of stride 1 (gfx950): weight gradient, bias gradient and data gradient of one
+// convolution in one launch, or of both convolutions of a residual block that keeps the resolution.
+//
+// A workgroup owns some images of one worker and takes NI of them at a time, whole, so no halo row is fetched twice.
+// Deltas and activations are channel-major in memory and pixel-major in LDS (the transposition happens on the way in: a
+// thread fetches 4 pixels of 8 channels); from there
+//   * the data gradient reads its operand as 16 bytes per lane (8 channels of one pixel and tap),
+//   * the weight gradient, which contracts over pixels, reads both operands with ds_read_b64_tr_b16: 16 lanes fetch 4
+//     pixels x 16 channels and each ends up with 4 pixels of one channel, at any pixel, so that the nine taps are nine
+//     plain reads.
+// Its sums stay in registers over all images of the workgroup and leave as one partial sum.
+// BLOCK: dv is the delta of the block output; half of the waves form the weight gradient of conv2 while the others form
+// du = [u > 0] conv2^T(dv) into LDS, then these the weight gradient of conv1 and the first half
+// din = [in > 0] (conv1^T(du) + dv): dv, u and the block input are read once, din is written once and du never reaches memory.
+// Four launches read and wrote these tensors nine times.
+// The same matrix instructions on the same operands in the same order as conv3x3_mfma_kernel for the deltas, so they carry
+// the same bits; the weight gradient's sums over images are split differently.
+// What bounds it: one workgroup of 8 waves per CU, two waves per SIMD, i.e. the latency of a wave's LDS reads.  So operands are
+// read a batch of matrix instructions ahead (left to itself the compiler waited for each one: du of a block of 16 channels
+// 53 us, 28 with batches), images are requested a phase ahead with no branch around the loads, and what an epilogue needs
+// comes from LDS instead of memory (din of that block 67 -> 42 us).  Memory alone, the images in and nothing else, is 71 us of
+// the block's 147 at 16 channels.
+// 112 workers x 32 images, 16 channels x 32 x 32, a block: 229 us in four launches, 147 here; 32 channels x 16 x 16: 157 and
+// 110; one convolution of 32 channels 82 and 64, of 64 channels x 8 x 8 77 and 55.  16 waves of half the registers at 16
+// channels spill (321 us); 64 channels as a block would need the sums of four tiles per wave.
+#include "resnet_common.h"
+
+namespace dpsgd {
+namespace {
+
+typedef long long i64;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int ksteps(int ci) { return (9 * ci + 31) / 32; }
+
+struct ConvBwdArgs {
+    const bf16_t *dv;        // delta of the output [n*B][C][H][W]
+    const bf16_t *u;         // BLOCK: the inner activation; else the convolution's input
+    const bf16_t *in;        // BLOCK: the block input
+    const bf16_t *scd;       // not BLOCK: delta added to the result before the mask, or null
+    bf16_t *din;
+    const bf16_t *wd2, *wd1; // packed data-gradient operands [n][KS][C/16][64][8]; wd1: BLOCK only
+    float *part2, *part1;    // partial sums [n][splits][(C/16)^2 * 9 * 256 + 1]
+    int H, B, splits;
+};
+
+// Pixels per LDS row: the image and its halo; rows of 8 pixels are padded so that a row is a multiple of 256 bytes
+// (the pixel right of a row and the one left of the next are the same: both are zero)
+__host__ __device__ constexpr int row_pixels(int C, int W) { return W >= 16 ? W + 1 : (C == 16 ? 16 : C == 32 ? 12 : 10); }
+__host__ __device__ constexpr int image_lds(int C, int W, int H) { return ((H + 2) * row_pixels(C, W) + (W >= 16 ? 1 : 0)) * 2 * C; }
+
+// A group of 8 channels goes to 16-byte unit (group ^ swizzle(column)) of its pixel.  An LDS access of 16 bytes per lane is
+// served in four phases, lanes 0-3, 12-15 and 20-27 first, 4-11, 16-19 and 28-31 second, the other half alike; with these, lanes
+// reading the same channels of 16 consecutive pixels (or of 8 pixels in each of two rows) at any column meet in no bank, nor
+// do the 16-channel rows of 8 consecutive pixels that 32 lanes of a transposing read touch.
+template <int C>
+__device__ __forceinline__ int swizzle(int col) { return C == 16 ? 0 : C == 32 ? ((col >> 2) & 1) << 1 : ((col >> 1) & 3) << 1; }
+
+// HT: rows of an image, or 0: a.H of them and one image at a time.
+template <int C, int W, int HT, int NI, bool BLOCK, int NT>
+__global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
+{
+    constexpr int KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
+    constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
+    constexpr int RW = NT / (BLOCK ? 128 : 64);       // waves that share a gradient (BLOCK: half of them each)
+    constexpr int TW = C == 64 ? 16 / RW : 1;               // weight gradient: input-channel tiles per wave
+    constexpr int KSPLIT = RW * TW / (CT * CT);       // waves that split its contraction
+    constexpr int DS = RW / CT;                       // data gradient: waves that split the pixels
+    static_assert(HT > 0 || NI == 1, "several images at a time are of a fixed size");
+    static_assert(KSPLIT >= 1 && DS >= 1, "every tile has a wave");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int sp = blockIdx.x, w = blockIdx.y;
+    if ((gridDim.y & 7) == 0) {   // all workgroups of a worker on one XCD
+        const unsigned id = blockIdx.x + gridDim.x * blockIdx.y, xcd = id & 7, slot = id >> 3;
+        w = (int)((slot / gridDim.x) * 8 + xcd);
+        sp = (int)(slot % gridDim.x);
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int role = BLOCK ? wave8 / RW : 0, wave = wave8 & (RW - 1);
+    const int n16 = lane & 15, g = lane >> 4;
+    const int H = HT ? HT : a.H, HW = H * W, G = HW / 32;   // groups of 32 pixels of an image
+    const int LR = H + 2;                             // LDS rows of an image
+    const int BUF = NI * image_lds(C, W, H);
+    const int lo = (int)((i64)a.B * sp / a.splits), hi = (int)((i64)a.B * (sp + 1) / a.splits);
+    const i64 img0 = (i64)w * a.B;
+
+    // ---- staging: thread e fetches pixels 4 px4 .. + 3 of channels TC ct .. + TC - 1 of image im_t of every tensor (SIDE: half
+    // of the threads take the deltas, the others the activations)
+    constexpr int TC = NT == 1024 ? 4 : 8;
+    constexpr bool SIDE = !BLOCK && HT > 0 && NI * HT * W * C <= NT / 2 * 4 * TC;
+    const int tpi = (C / TC) * (HW / 4);
+    const int tid_t = SIDE ? tid & (NT / 2 - 1) : tid, second = SIDE ? tid / (NT / 2) : 0;
+    const int im_t = NI > 1 ? tid_t / tpi : 0, rem = NI > 1 ? tid_t % tpi : tid_t, ct = rem / (HW / 4), px = rem % (HW / 4) * 4;
+    const bool task = NI > 1 ? im_t < NI : rem < tpi;
+    const unsigned goff = task ? (unsigned)(ct * TC * HW + px) : 0u;   // elements behind the image's first
+    int soff[C == 16 ? 1 : 4];
+#pragma unroll
+    for (int j = 0; j < (C == 16 ? 1 : 4); ++j) {
+        const int row = px / W + 1, col = px % W + 1 + j;
+        soff[j] = im_t * image_lds(C, W, H) + row * ROWB + col * PXB + (((ct * TC / 8) ^ swizzle<C>(col)) << 4) + ct * TC % 8 * 2 + second * BUF;
+    }
+    struct Stage { u32x2 v[TC]; };
+    // No branch around the loads (behind one the compiler would wait for them at once): past the last image it is fetched
+    // again, and zeros go to LDS.
+    auto fetch = [&](Stage &st, const bf16_t *p, int i) {
+        const int im = i + im_t < hi ? i + im_t : hi - 1;
+        p += (img0 + im) * C * HW;
+#pragma unroll
+        for (int c = 0; c < TC; ++c) st.v[c] = *reinterpret_cast<const u32x2 *>(p + goff + c * HW);
+    };
+    auto commit = [&](const Stage &st, unsigned char *buf, int i) {   // i: what was fetched
+        if (!task) return;
+        const bool there = NI == 1 || i + im_t < hi;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            unsigned d[TC / 2];
+#pragma unroll
+            for (int k = 0; k < TC / 2; ++k) {
+                const unsigned l = j < 2 ? st.v[2 * k].x : st.v[2 * k].y, h = j < 2 ? st.v[2 * k + 1].x : st.v[2 * k + 1].y;
+                d[k] = there ? __builtin_amdgcn_perm(h, l, (j & 1) ? 0x07060302u : 0x05040100u) : 0u;
+            }
+            unsigned char *q = buf + (C == 16 ? soff[0] + j * PXB : soff[j]);
+            if constexpr (TC == 8) *reinterpret_cast<u32x4 *>(q) = (u32x4){d[0], d[1], d[2], d[3]};
+            else *reinterpret_cast<u32x2 *>(q) = (u32x2){d[0], d[1]};
+        }
+    };
+
+    // ---- data gradient: this wave's input-channel tile and weights, the offsets of its operands
+    const int dt = wave % CT, dq = wave / CT;
+    bf16x8 wf[KS];
+    {
+        const bf16_t *wd = (BLOCK && role == 0 ? a.wd1 : a.wd2) + (i64)w * (KS * CT * 512) + dt * 512 + lane * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wf[s] = *reinterpret_cast<const bf16x8 *>(wd + s * CT * 512);
+    }
+    // offset, from the group's first row, of the operand of k-step s at MFMA row (column) n16 of a tile whose pixel there is p
+    auto operand = [&](int s, int p) {
+        const int kk = 32 * s + 8 * g;
+        const int tap = kk / C > 8 ? 8 : kk / C;   // padded taps carry zero weights; read finite data
+        const int row = p / W + tap / 3, col = p % W + tap % 3;
+        return row * ROWB + col * PXB + (((kk % C) / 8 ^ swizzle<C>(col)) << 4);
+    };
+    // 16 channels: a lane's tap depends on the lane; else the tap is the k-step's
+    constexpr int NOFF = C == 16 ? KS : 3;
+    struct Off { int v[NOFF]; };
+    auto offsets = [&](int p) {
+        Off o;
+#pragma unroll
+        for (int k = 0; k < NOFF; ++k) o.v[k] = operand(C == 16 ? k : k * (C / 32), p);
+        return o;
+    };
+    // Two tiles of 16 pixels make a group.  ROWS (data_out): MFMA row r of tile tt is pixel 8 (r / 4) + 4 tt + r % 4, so that a lane
+    // ends up with 8 consecutive pixels of one channel; else (data_inner) pixel 16 tt + r.
+    auto at = [&](const Off &o, int s, int tt, bool rows) {
+        const int tap = s / (C / 32 ? C / 32 : 1), ky = tap / 3, kx = tap % 3;
+        const int v = C == 16 ? o.v[s] : (o.v[kx] ^ (C == 64 ? (s & 1) << 6 : 0) ^ (rows && tt ? (C == 64 ? 64 : 32) : 0)) + ky * ROWB;
+        return v + tt * (rows ? 4 * PXB : W == 32 ? 16 * PXB : (16 / W) * ROWB);
+    };
+    const bool inner = BLOCK && role == 1;   // (which of the two this wave computes)
+    const Off off = offsets(inner ? n16 : 8 * (n16 >> 2) + (n16 & 3));
+    auto group_lds = [&](int q) {   // LDS offset of group q's first row (the row above it)
+        return NI > 1 ? (q / G) * image_lds(C, W, H) + (q % G) * R32 * ROWB : q * R32 * ROWB;
+    };
+
+    // ---- weight gradient: offsets of the transposing reads, by kx; the second 16 pixels of a group lie HALF further
+    const int co = C == 64 ? wave & 3 : C == 32 ? (wave >> 1) & 1 : 0, ci0 = C == 64 ? TW * (wave >> 2) : C == 32 ? wave & 1 : 0;
+    const int kq = C == 64 ? 0 : C == 32 ? wave >> 2 : wave;
+    constexpr int HALF = W == 32 ? 16 * PXB : (16 / W) * ROWB;
+    auto tr_offset = [&](int kx, int tile) {
+        const int p = 4 * g, row = p / W, col = p % W + (n16 >> 2) + kx, q = n16 & 3;
+        return row * ROWB + col * PXB + (((2 * tile + (q >> 1)) ^ swizzle<C>(col)) << 4) + (q & 1) * 8;
+    };
+    int toff[C == 16 ? 1 : 3];
+#pragma unroll
+    for (int kx = 0; kx < (C == 16 ? 1 : 3); ++kx) toff[kx] = tr_offset(kx, ci0);
+    auto tap_offset = [&](int kx) { return C == 16 ? toff[0] + kx * PXB : toff[kx]; };
+    const int doff = (C == 16 ? toff[0] + PXB : toff[C == 16 ? 0 : 1] ^ ((co ^ ci0) << 5)) + ROWB;
+    auto read_tr = [&](const unsigned char *p0, const unsigned char *p1) {
+        typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
+        const s16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0)), h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p1));
+        const u32x2 x = __builtin_bit_cast(u32x2, l), y = __builtin_bit_cast(u32x2, h);
+        return __builtin_bit_cast(bf16x8, (u32x4){x.x, x.y, y.x, y.y});
+    };
+    auto read_pixels = [&](const unsigned char *p) { return read_tr(p, p + HALF); };   // a group's 32, of 16 channels
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+    f32x4 sum[TW][9], bsum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sum[t][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto read_act = [&](const unsigned char *row, int t, int ky, int kx) {   // (tiles ci0, ci0 + 1, ..: ci0 is a multiple of TW)
+        return read_pixels(row + ky * ROWB + (tap_offset(kx) ^ (t << 5)));
+    };
+    auto wgrad = [&](const unsigned char *delta, const unsigned char *act) {
+        const int total = NI * G, per = (total + KSPLIT - 1) / KSPLIT;
+        int q0 = kq * per;
+        const int q1 = q0 + per < total ? q0 + per : total;
+        if (W == 32 && HT == 32) {
+            // four rows at a time: every source row is read once and serves the output rows above, at and below it
+#pragma unroll 1
+            for (; q0 < q1; q0 += 4) {
+                const unsigned char *dp = delta + q0 * ROWB, *ap = act + q0 * ROWB;
+                bf16x8 d[4];
+#pragma unroll
+                for (int r = 0; r < 6; ++r) {
+                    if (r < 4) d[r] = read_pixels(dp + r * ROWB + doff);
+                    bf16x8 b[3];
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) b[kx] = read_act(ap + r * ROWB, 0, 0, kx);
+                    if (r < 4) bsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[r], ones, bsum, 0, 0, 0);
+#pragma unroll
+                    for (int ky = 0; ky < 3; ++ky)
+                        if (r - ky >= 0 && r - ky < 4)
+#pragma unroll
+                            for (int kx = 0; kx < 3; ++kx)
+                                sum[0][ky * 3 + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[r - ky], b[kx], sum[0][ky * 3 + kx], 0, 0, 0);
+                }
+            }
+            return;
+        }
+        // The operands of a (tile, ky) are read two of them ahead of their matrix instructions (past the end: the last group's)
+        if (q0 >= q1) return;
+        constexpr int NB = 3 * TW;
+        if constexpr (C == 64) {
+#pragma unroll 1
+            for (int q = q0; q < q1; ++q) {
+                const unsigned char *dp = delta + group_lds(q), *ap = act + group_lds(q);
+                const bf16x8 d = read_pixels(dp + doff);
+                if (ci0 == 0) bsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, ones, bsum, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < TW; ++t) {
+#pragma unroll
+                    for (int k = 0; k < 9; ++k)
+                        sum[t][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, read_act(ap, t, k / 3, k % 3), sum[t][k], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            return;
+        }
+        bf16x8 d = read_pixels(delta + group_lds(q0) + doff), b[3][3];
+        auto read_batch = [&](int q, int k) {
+            const unsigned char *ap = act + group_lds(q < q1 ? q : q1 - 1);
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) b[k % 3][kx] = read_act(ap, k / 3, k % 3, kx);
+        };
+        read_batch(q0, 0);
+        read_batch(q0, 1);
+#pragma unroll 1
+        for (int q = q0; q < q1; ++q) {
+            bf16x8 dn;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                if (k == NB - 2) dn = read_pixels(delta + group_lds(q + 1 < q1 ? q + 1 : q) + doff);
+                read_batch(k + 2 < NB ? q : q + 1, (k + 2) % NB);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k == 0 && (C == 16 || ci0 == 0)) bsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, ones, bsum, 0, 0, 0);
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx)
+                    sum[k / 3][k % 3 * 3 + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, b[k % 3][kx], sum[k / 3][k % 3 * 3 + kx], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            d = dn;
+        }
+    };
+
+    // ---- data gradient: operands of the k-steps a batch takes, read a batch ahead of their matrix instructions
+    constexpr int NBT = C == 16 ? 1 : C == 32 ? 2 : 6, KB = (KS + NBT - 1) / NBT;
+    struct Batch { bf16x8 v[KB][2]; };
+    auto read_ops = [&](Batch &b, const unsigned char *p, int k, bool rows) {
+        if (C == 64) return;
+#pragma unroll
+        for (int s = 0; s < KB; ++s)
+            if (k * KB + s < KS)
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt) b.v[s][tt] = *reinterpret_cast<const bf16x8 *>(p + at(off, k * KB + s, tt, rows));
+    };
+    // the products of the group at p; next: the group whose first batch is read meanwhile (ops[0] holds this one's)
+    Batch ops[NBT > 1 ? 2 : 1];
+    auto products = [&](f32x4 (&acc)[2], const unsigned char *p, const unsigned char *next, bool rows) {
+        acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if constexpr (C == 64) {   // (no registers for operands read ahead: the compiler takes what there are)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt)
+                    acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(p + at(off, s, tt, rows)), wf[s], acc[tt], 0, 0, 0);
+                if (s % 6 == 5) __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < NBT; ++k) {
+            if (NBT > 1) {
+                if (k + 1 < NBT) read_ops(ops[(k + 1) & 1], p, k + 1, rows);
+                else read_ops(ops[0], next, 0, rows);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int s = 0; s < KB; ++s)
+                if (k * KB + s < KS)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) {
+                        const bf16x8 x = ops[k & 1].v[s][tt], wv = wf[k * KB + s];
+                        acc[tt] = rows ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, wv, acc[tt], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, x, acc[tt], 0, 0, 0);
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (NBT == 1) {
+            read_ops(ops[0], next, 0, rows);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // Two packed results where the activation, which a ReLU left, is not zero
+    auto masked = [](unsigned r, unsigned act) {
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        const u16x2 one = {1, 1}, m = __builtin_elementwise_min(__builtin_bit_cast(u16x2, act), one);
+        return __builtin_bit_cast(unsigned, (u16x2)(__builtin_bit_cast(u16x2, r) * m));
+    };
+
+    // ---- din: a lane owns 8 consecutive pixels of channel 16 dt + n16 in memory, and reads the activation (and BLOCK: dv) there
+    // from LDS by transposing reads
+    const int o = 16 * dt + n16, gy = 8 * g / W, gx = 8 * g % W;
+    int ooff[2];
+    {
+        const int col = gx + (n16 >> 2) + 1, q = n16 & 3;
+        ooff[0] = (gy + 1) * ROWB + col * PXB + (((2 * dt + (q >> 1)) ^ swizzle<C>(col)) << 4) + (q & 1) * 8;
+        ooff[1] = (ooff[0] ^ (C == 16 ? 0 : C == 32 ? 32 : 64)) + 4 * PXB;
+    }
+    auto read_own = [&](const unsigned char *buf, int q) {
+        return __builtin_bit_cast(u32x4, read_tr(buf + group_lds(q) + ooff[0], buf + group_lds(q) + ooff[1]));
+    };
+    constexpr int NSC = BLOCK ? 1 : (512 * 32 / C) / 32 / DS;   // groups of a wave, at most
+    struct Shortcut { u32x4 v[NSC]; };
+    auto request = [&](int i) {   // not BLOCK: the deltas to be added, for all groups of this wave
+        Shortcut sc;
+        const int end = NI > 1 ? (hi - i < NI ? hi - i : NI) * G : G;
+#pragma unroll
+        for (int k = 0; k < NSC; ++k) {
+            sc.v[k] = (u32x4){0u, 0u, 0u, 0u};
+            const int q = dq + DS * k, qc = q < end ? q : end - 1, y = (NI > 1 ? qc % G : qc) * R32 + gy;
+            if (!BLOCK && a.scd)
+                sc.v[k] = *reinterpret_cast<const u32x4 *>(a.scd + ((img0 + i + (NI > 1 ? qc / G : 0)) * C + o) * HW + y * W + gx);
+        }
+        return sc;
+    };
+    auto data_out = [&](const unsigned char *delta, const unsigned char *act, const unsigned char *dv, Shortcut sc, int i) {
+        const int end = NI > 1 ? (hi - i < NI ? hi - i : NI) * G : G;
+        read_ops(ops[0], delta + group_lds(dq < end ? dq : end - 1), 0, true);
+#pragma unroll 1
+        for (int q = dq; q < end; q += DS) {
+            const u32x4 m = read_own(act, q);
+            u32x4 d4;
+            if (BLOCK) d4 = read_own(dv, q);
+            else {
+                d4 = sc.v[0];
+#pragma unroll
+                for (int k = 0; k + 1 < NSC; ++k) sc.v[k] = sc.v[k + 1];
+            }
+            f32x4 acc[2];
+            products(acc, delta + group_lds(q), delta + group_lds(q + DS < end ? q + DS : q), true);
+            const unsigned d[4] = {d4.x, d4.y, d4.z, d4.w};
+            unsigned r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                r[k] = f2bf_pack(acc[k >> 1][2 * k & 3] + __uint_as_float(d[k] << 16), acc[k >> 1][(2 * k + 1) & 3] + __uint_as_float(d[k] & 0xffff0000u));
+            const int y = (NI > 1 ? q % G : q) * R32 + gy;
+            *reinterpret_cast<u32x4 *>(a.din + ((img0 + i + (NI > 1 ? q / G : 0)) * C + o) * HW + y * W + gx) =
+                (u32x4){masked(r[0], m.x), masked(r[1], m.y), masked(r[2], m.z), masked(r[3], m.w)};
+        }
+    };
+
+    // ---- du (BLOCK): weights as the left operand, so that a lane owns channels 16 dt + 4 g .. + 3 of one pixel in LDS
+    auto data_inner = [&](const unsigned char *delta, const unsigned char *act, unsigned char *du) {
+        const int row = n16 / W + 1, col = n16 % W + 1;
+        const int own = row * ROWB + col * PXB + (((2 * dt + (g >> 1)) ^ swizzle<C>(col)) << 4) + (g & 1) * 8;
+        read_ops(ops[0], delta + group_lds(dq < NI * G ? dq : 0), 0, false);
+#pragma unroll 1
+        for (int q = dq; q < NI * G; q += DS) {
+            const int base = group_lds(q);
+            u32x2 m[2];
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) m[tt] = *reinterpret_cast<const u32x2 *>(act + base + own + tt * HALF);
+            f32x4 acc[2];
+            products(acc, delta + base, delta + group_lds(q + DS < NI * G ? q + DS : q), false);
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt)
+                *reinterpret_cast<u32x2 *>(du + base + own + tt * HALF) =
+                    (u32x2){masked(f2bf_pack(acc[tt].x, acc[tt].y), m[tt].x), masked(f2bf_pack(acc[tt].z, acc[tt].w), m[tt].y)};
+        }
+    };
+
+    // ---- the halos stay zero from here on; what follows writes the images' own pixels only
+    for (int e = tid; e < 4 * BUF / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
+    Stage sd, su;
+    auto fetch_pair = [&](int i) {
+        fetch(sd, second ? a.u : a.dv, i);
+        if constexpr (!SIDE) fetch(su, a.u, i);
+    };
+    auto commit_pair = [&](unsigned char *buf, int i) {
+        commit(sd, buf, i);
+        if constexpr (!SIDE) commit(su, buf + BUF, i);
+    };
+    fetch_pair(lo);
+    __syncthreads();
+    commit_pair(smem, lo);
+    if constexpr (BLOCK) {
+        // buffers: dv, u, in, du.  While dv and u are multiplied, in reaches its buffer; in the other half the next dv takes u's
+        // place (dv itself is still added to the result), and the next u its.
+        unsigned char *DV = smem, *U = smem + BUF, *const IN = smem + 2 * BUF, *const DU = smem + 3 * BUF;
+        Stage si;
+        fetch(si, a.in, lo);
+        for (int i = lo; i < hi; i += NI) {
+            __syncthreads();
+            fetch_pair(i + NI);
+            commit(si, IN, i);
+            if (role == 0) wgrad(DV, U);
+            else data_inner(DV, U, DU);
+            __syncthreads();
+            commit(sd, U, i + NI);
+            fetch(si, a.in, i + NI);
+            if (role == 0) data_out(DU, IN, DV, Shortcut(), i);
+            else wgrad(DU, IN);
+            __syncthreads();
+            commit(su, DV, i + NI);
+            unsigned char *t = DV; DV = U; U = t;
+        }
+    } else {
+        // two pairs of buffers take turns
+        fetch_pair(lo + NI);
+        int cur = 0;
+        for (int i = lo; i < hi; i += NI) {
+            __syncthreads();
+            unsigned char *const DV = smem + 2 * cur * BUF, *const U = DV + BUF;
+            cur ^= 1;
+            const Shortcut sc = request(i);
+            commit_pair(smem + 2 * cur * BUF, i + NI);
+            fetch_pair(i + 2 * NI);
+            wgrad(DV, U);
+            data_out(DV, U, nullptr, sc, i);
+        }
+    }
+
+    // ---- the waves that split a contraction meet in wave order, then the partial sums leave (BLOCK: conv2's from the first
+    // four waves, conv1's from the others)
+    __syncthreads();
+    constexpr int RED = 9 * 256;   // floats of a tile
+    float *red = reinterpret_cast<float *>(smem) + role * (KSPLIT - 1) * CT * CT * RED;
+    const int tile = co * CT + ci0;
+    constexpr int psz = CT * CT * 9 * 256 + 1;
+    float *out = (BLOCK && role == 1 ? a.part1 : a.part2) + ((i64)w * a.splits + sp) * psz;
+    if (KSPLIT > 1) {
+        if (kq > 0)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) *reinterpret_cast<f32x4 *>(red + ((kq - 1) * CT * CT + tile) * RED + (k * 64 + lane) * 4) = sum[0][k];
+        __syncthreads();
+        if (kq == 0)
+            for (int q = 1; q < KSPLIT; ++q)
+#pragma unroll
+                for (int k = 0; k < 9; ++k) sum[0][k] += *reinterpret_cast<const f32x4 *>(red + ((q - 1) * CT * CT + tile) * RED + (k * 64 + lane) * 4);
+        __syncthreads();
+    }
+    if (kq == 0)
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) *reinterpret_cast<f32x4 *>(out + (((tile + t) * 9 + k) * 64 + lane) * 4) = sum[t][k];
+    // bias: every column of the product with ones is the sum over pixels; rows 4 g .. + 3 are in lane 16 g
+    float b = (bsum.x + bsum.y) + (bsum.z + bsum.w);
+    b += __shfl_down(b, 32, 64);
+    b += __shfl_down(b, 16, 64);
+    float *bias = reinterpret_cast<float *>(smem);
+    if (lane == 0) bias[wave8] = (C == 16 || ci0 == 0) ? b : 0.f;
+    __syncthreads();
+    if (lane == 0 && wave == 0) {
+        float t = 0.f;
+        for (int k = 0; k < RW; ++k) t += bias[role * RW + k];
+        out[psz - 1] = t;
+    }
+}
+
+constexpr int threads_of(int C) { return 512; }
+
+// Images a workgroup takes at a time: as many as give every thread a staging task, where their size is a usual one
+int images_at_once(int C, int H, int W) { return (C == 32 && H == 16 && W == 16) || (C == 64 && H == 8 && W == 8) ? 2 : 1; }
+
+size_t lds_bytes(int C, int H, int W, bool block)
+{
+    const size_t img = (size_t)4 * images_at_once(C, H, W) * image_lds(C, W, H);
+    const size_t waves = threads_of(C) / 64, tiles = C == 64 ? 1 : (C / 16) * (C / 16);   // waves that hand their sums to others
+    const size_t red = C == 64 ? 64 : (waves - (block ? 2 : 1) * tiles) * 9 * 1024;
+    return img > red ? img : red;
+}
+
+bool shape_ok(const dpsgd_ctx *ctx, const ConvDesc &c, bool block)
+{
+    if (!ctx->opt_conv_bwd || c.stride != 1) return false;
+    if (c.Ci != c.Co || c.Cis != c.Cos || c.His != c.Hos || c.Wis != c.Wos) return false;
+    const int C = c.Cos, W = c.Wos, H = c.Hos;
+    // (a staging task of 32 elements per thread)
+    if (H < 8 || H % 8 || H * W * C > 512 * 32) return false;
+    if (!((C == 16 && (W == 8 || W == 16 || W == 32)) || ((C == 32 || C == 64) && (W == 8 || W == 16)))) return false;
+    return lds_bytes(C, H, W, block) <= 160 * 1024;
+}
+
+template <int C, int W, int HT, int NI, bool BLOCK>
+dpsgd_status launch(dpsgd_ctx *ctx, const ConvBwdArgs &a)
+{
+    const size_t shm = lds_bytes(C, a.H, W, BLOCK);
+    constexpr int NT = threads_of(C);
+    auto k = conv_bwd_kernel<C, W, HT, NI, BLOCK, NT>;
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+        return DPSGD_EDEVICE;
+    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(NT), shm, ctx->stream, a);
+    return hip_status(hipGetLastError());
+}
+
+template <bool BLOCK>
+dpsgd_status launch_any(dpsgd_ctx *ctx, int C, int W, const ConvBwdArgs &a)
+{
+    if (C == 16) {
+        if (W == 32) return a.H == 32 ? launch<16, 32, 32, 1, BLOCK>(ctx, a) : launch<16, 32, 0, 1, BLOCK>(ctx, a);
+        return W == 16 ? launch<16, 16, 0, 1, BLOCK>(ctx, a) : launch<16, 8, 0, 1, BLOCK>(ctx, a);
+    }
+    if (C == 32) {
+        if (W == 16) return a.H == 16 ? launch<32, 16, 16, 2, BLOCK>(ctx, a) : launch<32, 16, 0, 1, BLOCK>(ctx, a);
+        return launch<32, 8, 0, 1, BLOCK>(ctx, a);
+    }
+    if constexpr (!BLOCK) {
+        if (W == 16) return launch<64, 16, 0, 1, BLOCK>(ctx, a);
+        return a.H == 8 ? launch<64, 8, 8, 2, BLOCK>(ctx, a) : launch<64, 8, 0, 1, BLOCK>(ctx, a);
+    }
+    return DPSGD_EUNSUPPORTED;
+}
+
+dpsgd_status add_job(dpsgd_ctx *ctx, const ConvDesc &c, int splits, float *partials, float *G, WgradReduceList *pending)
+{
+    WgradReduceJob job{};
+    const int t = c.Cos / 16;
+    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = splits; job.psz = t * t * 9 * 256 + 1;
+    job.tiles = t * t; job.ci_tiles = t; job.CIr = c.Ci; job.COr = c.Co;
+    return conv_weight_grad_add(ctx, pending, job, G);
+}
+}  // namespace
+
+bool conv_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c) { return shape_ok(ctx, c, false); }
+
+bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2)
+{
+    // (64 channels: a wave would hold the sums of four tiles)
+    return shape_ok(ctx, c1, true) && shape_ok(ctx, c2, true) && c1.Cos == c2.Cos && c1.Cos <= 32 && c1.Hos == c2.Hos &&
+           c1.Wos == c2.Wos && c1.Co == c2.Co;
+}
+
+// Workgroups per worker, each with a CU to itself: as many as keep the last round of workgroups over the CUs full, counting
+// two images' time for a workgroup's start and its partial sums.
+int conv_bwd_splits(int n, int B)
+{
+    int best = 1;
+    i64 cost = -1;
+    for (int m = 1; m <= B && m <= 32; ++m) {
+        const i64 c = ((i64)n * m + 255) / 256 * ((B + m - 1) / m + 2);
+        if (cost < 0 || c < cost) {
+            cost = c;
+            best = m;
+        }
+    }
+    return best;
+}
+
+dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
+                      Tensor din, float *G, float *partials, WgradReduceList *pending)
+{
+    if (!conv_bwd_ok(ctx, c)) return DPSGD_EUNSUPPORTED;
+    ConvBwdArgs a{};
+    a.dv = dout.t; a.u = act.t; a.scd = scd; a.din = din.t; a.wd2 = wpack_d; a.part2 = partials;
+    a.H = c.Hos; a.B = B; a.splits = conv_bwd_splits(ctx->n, B);
+    const dpsgd_status st = launch_any<false>(ctx, c.Cos, c.Wos, a);
+    return st == DPSGD_OK ? add_job(ctx, c, a.splits, partials, G, pending) : st;
+}
+
+dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B, Tensor dv, const bf16_t *wpack_d1,
+                            const bf16_t *wpack_d2, Tensor u, Tensor in, Tensor din, float *G, float *partials1, float *partials2,
+                            WgradReduceList *pending)
+{
+    if (!conv_block_bwd_ok(ctx, c1, c2)) return DPSGD_EUNSUPPORTED;
+    ConvBwdArgs a{};
+    a.dv = dv.t; a.u = u.t; a.in = in.t; a.din = din.t; a.wd2 = wpack_d2; a.wd1 = wpack_d1;
+    a.part2 = partials2; a.part1 = partials1; a.H = c2.Hos; a.B = B; a.splits = conv_bwd_splits(ctx->n, B);
+    dpsgd_status st = launch_any<true>(ctx, c2.Cos, c2.Wos, a);
+    if (st == DPSGD_OK) st = add_job(ctx, c2, a.splits, partials2, G, pending);
+    return st == DPSGD_OK ? add_job(ctx, c1, a.splits, partials1, G, pending) : st;
+}
+
+}  // namespace dpsgd

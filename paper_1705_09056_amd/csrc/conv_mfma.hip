@@ -723,19 +723,6 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 // neighbouring dword.  Waves split the output-channel tiles first, then the pixels; a workgroup
 // owns a strided subset of the worker's images and writes its partial sums, which
 // wgrad_reduce_kernel adds in a fixed order.
-struct WgradReduceJob {
-    const float *part;     // the conv's partial sums, [n][splits][psz]
-    i64 w_off, b_off;      // where the conv's weights and its scalar bias sit in a worker's parameter vector
-    int splits, psz, tiles, ci_tiles, CIr, COr;   // CIr, COr: the conv's real channels
-    int block0;            // first blockIdx.x of this job
-};
-constexpr int kMaxReduceJobs = 48;
-struct WgradReduceTable {
-    WgradReduceJob job[kMaxReduceJobs];
-    int njobs;
-};
-static_assert(sizeof(WgradReduceTable) <= sizeof(WgradReduceList::table), "the caller's storage holds the job table");
-
 struct WgradMfmaArgs {
     const bf16_t *inT;     // [n*B][CIs][H][W]
     const bf16_t *doutT;   // [n*B][CO][Ho][Wo]
@@ -1212,7 +1199,10 @@ size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
     if (!wgrad_mfma_ok(c)) return 0;
     const size_t cip = (size_t)(c.Cis + 15) / 16 * 16;   // partials are stored per 16 x 16 tile of (c_out, padded c_in)
-    return (size_t)wgrad_splits(ctx->n, B, c.Cos, c.stride) * ((size_t)c.Cos * cip * 9 + 1) * sizeof(float);
+    int splits = wgrad_splits(ctx->n, B, c.Cos, c.stride);
+    const int m = conv_bwd_splits(ctx->n, B);   // (whichever kernel takes the convolution)
+    splits = m > splits ? m : splits;
+    return (size_t)splits * ((size_t)c.Cos * cip * 9 + 1) * sizeof(float);
 }
 
 dpsgd_status conv_pack_weights(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, const float *X,
@@ -1339,10 +1329,6 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
                               WgradReduceList *pending)
 {
     if (!wgrad_mfma_ok(c) || !partials || !pending) return conv_weight_grad_generic(ctx, c, B, in, dout, G);
-    if (pending->njobs >= kMaxReduceJobs) {   // (a network of more than 48 convolutions: sum what is pending first)
-        const dpsgd_status st = conv_weight_grad_finish(ctx, pending, G);
-        if (st != DPSGD_OK) return st;
-    }
     WgradMfmaArgs a{};
     a.inT = in.t; a.doutT = dout.t; a.H = c.His; a.W = c.Wis; a.Ho = c.Hos; a.Wo = c.Wos; a.B = B; a.CIs = c.Cis;
     a.splits = wgrad_splits(ctx->n, B, c.Cos, c.stride); a.part = partials;
@@ -1360,11 +1346,19 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
         st = launch_wgrad<32, 64, 2>(ctx, c, a, &job);
     }
     if (st != DPSGD_OK) return st;
-    WgradReduceTable *tbl = reinterpret_cast<WgradReduceTable *>(pending->table);
-    job.block0 = pending->blocks;
-    tbl->job[pending->njobs] = job;
-    pending->njobs += 1;
-    tbl->njobs = pending->njobs;
+    return conv_weight_grad_add(ctx, pending, job, G);
+}
+
+dpsgd_status conv_weight_grad_add(dpsgd_ctx *ctx, WgradReduceList *pending, const WgradReduceJob &job, float *G)
+{
+    if (pending->njobs >= kMaxReduceJobs) {   // (a network of more than 48 convolutions: sum what is pending first)
+        const dpsgd_status st = conv_weight_grad_finish(ctx, pending, G);
+        if (st != DPSGD_OK) return st;
+    }
+    WgradReduceJob &jb = pending->table.job[pending->njobs++];
+    jb = job;
+    jb.block0 = pending->blocks;
+    pending->table.njobs = pending->njobs;
     pending->blocks += job.tiles + 1;
     return DPSGD_OK;
 }
@@ -1372,8 +1366,7 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
 dpsgd_status conv_weight_grad_finish(dpsgd_ctx *ctx, WgradReduceList *pending, float *G)
 {
     if (!pending || pending->njobs == 0) return DPSGD_OK;
-    const WgradReduceTable *tbl = reinterpret_cast<const WgradReduceTable *>(pending->table);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)pending->blocks, (unsigned)ctx->n), dim3(256), 0, ctx->stream, *tbl, G,
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)pending->blocks, (unsigned)ctx->n), dim3(256), 0, ctx->stream, pending->table, G,
                        ctx->ld);
     pending->njobs = 0;
     pending->blocks = 0;

@@ -509,13 +509,28 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     }
     for (int j = p.nblocks - 1; j >= 0; --j) {
         const ConvDesc &c1 = p.convs[1 + 2 * j], &c2 = p.convs[2 + 2 * j];
+        float *p1 = ws.partials[1 + 2 * j], *p2 = ws.partials[2 + 2 * j];
+        const bf16_t *wd1 = ws.wpack_d[1 + 2 * j], *wd2 = ws.wpack_d[2 + 2 * j];
+        if (conv_block_bwd_ok(ctx, c1, c2)) {   // the whole block, du in LDS
+            if ((st = conv_block_bwd(ctx, c1, c2, B, dv, wd1, wd2, u_of(j), a_of(j), dnext, G, p1, p2, &pending)) != DPSGD_OK) return st;
+            Tensor t = dv; dv = dnext; dnext = t;
+            continue;
+        }
         // conv2: weight and bias gradient from dv and u; du = [u > 0] * dgrad(dv)
-        if ((st = conv_weight_grad(ctx, c2, B, u_of(j), dv, G, ws.partials[2 + 2 * j], &pending)) != DPSGD_OK) return st;
-        if ((st = conv_data_grad(ctx, c2, B, dv, X, ws.wpack_d[2 + 2 * j], none, u_of(j), du)) != DPSGD_OK) return st;
+        if (conv_bwd_ok(ctx, c2)) {
+            if ((st = conv_bwd(ctx, c2, B, dv, wd2, nullptr, u_of(j), du, G, p2, &pending)) != DPSGD_OK) return st;
+        } else {
+            if ((st = conv_weight_grad(ctx, c2, B, u_of(j), dv, G, p2, &pending)) != DPSGD_OK) return st;
+            if ((st = conv_data_grad(ctx, c2, B, dv, X, wd2, none, u_of(j), du)) != DPSGD_OK) return st;
+        }
         // conv1: from du and a_j; next dv = [a_j > 0] * (dgrad(du) + shortcut delta)
-        if ((st = conv_weight_grad(ctx, c1, B, a_of(j), du, G, ws.partials[1 + 2 * j], &pending)) != DPSGD_OK) return st;
-        const ShortcutRef scd{dv.t, c2.Cos, c2.Hos, c2.Wos, c1.stride};
-        if ((st = conv_data_grad(ctx, c1, B, du, X, ws.wpack_d[1 + 2 * j], scd, a_of(j), dnext)) != DPSGD_OK) return st;
+        if (conv_bwd_ok(ctx, c1)) {
+            if ((st = conv_bwd(ctx, c1, B, du, wd1, dv.t, a_of(j), dnext, G, p1, &pending)) != DPSGD_OK) return st;
+        } else {
+            if ((st = conv_weight_grad(ctx, c1, B, a_of(j), du, G, p1, &pending)) != DPSGD_OK) return st;
+            const ShortcutRef scd{dv.t, c2.Cos, c2.Hos, c2.Wos, c1.stride};
+            if ((st = conv_data_grad(ctx, c1, B, du, X, wd1, scd, a_of(j), dnext)) != DPSGD_OK) return st;
+        }
         Tensor t = dv; dv = dnext; dnext = t;
     }
     if (stem_mfma) {   // stem: weight and bias gradient only

@@ -80,12 +80,26 @@ dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDe
 // din = round([act > 0] * (conv^T(dout) + shortcut delta)).
 dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X, const bf16_t *wpack_d,
                             ShortcutRef scd, Tensor act, Tensor din);
-// The weight-gradient kernels of the MFMA path leave partial sums (several workgroups per worker); what turns them
-// into G is collected here and done for all convolutions of the network by ONE launch, conv_weight_grad_finish.
+// The weight-gradient kernels of the MFMA path leave partial sums (several workgroups per worker), in accumulator order:
+// [co tile][ci tile][tap][lane][4] floats, then the sum of the deltas.  What turns them into G is collected here and done
+// for all convolutions of the network by ONE launch, conv_weight_grad_finish.
+struct WgradReduceJob {
+    const float *part;         // the conv's partial sums, [n][splits][psz]
+    long long w_off, b_off;    // where the conv's weights and its scalar bias sit in a worker's parameter vector
+    int splits, psz, tiles, ci_tiles, CIr, COr;   // CIr, COr: the conv's real channels
+    int block0;                // first blockIdx.x of this job
+};
+constexpr int kMaxReduceJobs = 48;
+struct WgradReduceTable {      // an argument of the reduction kernel
+    WgradReduceJob job[kMaxReduceJobs];
+    int njobs;
+};
 struct WgradReduceList {
-    alignas(8) unsigned char table[2816];   // the job table the reduction kernel takes as its argument
+    WgradReduceTable table;
     int njobs = 0, blocks = 0;
 };
+// Adds a job (its block0 is set here); what is pending goes out first where the table is full.
+dpsgd_status conv_weight_grad_add(dpsgd_ctx *ctx, WgradReduceList *pending, const WgradReduceJob &job, float *G);
 // G[w_off..] = dout (*) in, G[b_off] = sum(dout).  partials: this conv's own scratch of conv_wgrad_partial_bytes(ctx, c, B) * n
 // bytes, which must stay untouched until conv_weight_grad_finish(pending) has run on the same stream; G holds the
 // result only after that call.  Without partials or pending (or for shapes the MFMA kernel does not take) G is
@@ -111,6 +125,19 @@ bool conv_forward_writes_sign(const ConvDesc &c, bool is_stem);
 // chw_bf16 and nhwc8 are His x Wis pixels, zero beyond H x W.
 dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const void *image, bool image_is_bf16,
                              bf16_t *chw_bf16, bf16_t *nhwc8);
+
+// Weight and data gradient of a 3x3 convolution of stride 1 in one launch (conv_bwd.hip), or of both convolutions of a
+// residual block that keeps the resolution, whose inner delta then stays in LDS.  _ok: whether the shapes allow it.
+bool conv_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c);
+bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2);
+int conv_bwd_splits(int n, int B);   // workgroups (partial sums) per worker
+// din = round([act > 0] * (conv^T(dout) + scd)), dW and bias gradient from (act, dout); scd may be null
+dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
+                      Tensor din, float *G, float *partials, WgradReduceList *pending);
+// conv_bwd(c2, dv, u -> du), conv_bwd(c1, du, in -> din, shortcut dv)
+dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B, Tensor dv, const bf16_t *wpack_d1,
+                            const bf16_t *wpack_d2, Tensor u, Tensor in, Tensor din, float *G, float *partials1, float *partials2,
+                            WgradReduceList *pending);
 
 dpsgd_status conv_forward_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, const float *X, ShortcutRef sc,
                                   Tensor out);

@@ -250,3 +250,46 @@ def test_extents_no_kernel_takes_are_kept_as_they_are(widths):
     assert rel_err(out[1][1].cpu().numpy(), out[0][1].cpu().numpy()) < 2 * TIGHT
     if 2 * widths[3] > 64:
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("widths,batch,n", [
+    ((3, 32, 32, 16, 2, 10), 5, 2),    # whole blocks of 16 and 32 channels; an odd number of images where two are taken at a time
+    ((1, 28, 28, 16, 2, 10), 7, 9),    # zeros beyond the real extents
+    ((3, 16, 16, 16, 2, 10), 5, 3),    # rows of 16 pixels at 16 channels, of 8 at 32
+    ((3, 8, 8, 16, 2, 10), 3, 2),      # less groups of pixels than waves
+    ((3, 24, 16, 8, 2, 10), 3, 8),     # rows that no constant covers; 8 workers: one XCD per worker
+    ((3, 16, 40, 16, 2, 10), 3, 2),    # 64 channels with rows of 16 pixels; wider stages on the other kernels
+    ((3, 48, 32, 16, 2, 10), 2, 2),    # 24 rows of 16 pixels, 16 rows of 8
+    ((3, 8, 8, 32, 1, 10), 2, 130),    # one workgroup per worker takes all its images
+])
+def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
+    """Weight and data gradient of a convolution (or a residual block) in one launch ("conv_bwd") against a launch each.  The
+    deltas come from the same matrix instructions on the same operands: what the kernels that are the same in both make of
+    them (the stem's and the strided convolutions' gradients) has the same bits.  The weight gradients add up the same
+    products in another order: fp32 sums of at most 32 * 1024 of them, whose error grows like the root of their number
+    in units of 2^-24, 1e-5 of a layer's norm."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    lay = synth.param_layout(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_bwd={setting} widths={widths} n={n} B={batch}", flush=True)
+            ctx.set_option("conv_bwd", setting)
+            ctx.grad(model, Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append(from_dev(Gd, d))
+    assert np.array_equal(out[1], out[2]), "not the same twice"
+    scale = np.abs(np.concatenate([out[0][:, p.offset:p.offset + p.size] for p in lay if p.size == 1], axis=1)).max()
+    for p in lay:
+        a, b = (o[:, p.offset:p.offset + p.size] for o in out[:2])
+        if p.name.startswith("stem") or p.name in ("s1b0.W1", "s2b0.W1"):
+            assert np.array_equal(a, b), p.name
+        elif p.size == 1:
+            assert np.abs(a - b).max() <= 1e-5 * scale, p.name
+        else:
+            assert rel_err(b, a) < 1e-5, p.name

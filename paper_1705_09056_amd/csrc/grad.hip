@@ -31,7 +31,9 @@ dpsgd_status launch_step(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, co
     // everything else: the two calls of the boundary, back to back, in place.  X changes without the fused kernels
     // seeing it, so a bf16 weight copy they left for this X is stale from here on.
     ctx->shadow_valid = false;
-    dpsgd_status st = launch_grad(ctx, m, X, inputs, targets, G, loss);
+    dpsgd_status st;
+    if (launch_step_lsq(ctx, m, X, inputs, targets, G, loss, consensus, &st)) return st;
+    st = launch_grad(ctx, m, X, inputs, targets, G, loss);
     if (st != DPSGD_OK) return st;
     return launch_mix(ctx, X, G, X, consensus, false);
 }

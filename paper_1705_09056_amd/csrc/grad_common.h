@@ -37,6 +37,9 @@ size_t f32_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m);
 dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const float *X, const void *inputs,
                              const void *targets, float *G, float *loss);
 
+bool launch_step_lsq(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, const void *inputs, const void *targets, float *G,
+                     float *loss, float *consensus, dpsgd_status *st);
+
 size_t mlp_bf16_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m);
 dpsgd_status launch_grad_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const float *X, const void *inputs,
                                   const void *targets, float *G, float *loss);

@@ -10,35 +10,195 @@ namespace {
 typedef long long i64;
 
 // ------------------------------------------------------------------------- least squares
-// One workgroup per worker.  F = (1/(2B)) ||A x - y||^2, grad = A^T (A x - y) / B.
-// Phase 1: residuals r_b (one wave per sample row) into LDS; phase 2: one thread per feature.
+// F = (1/(2B)) ||A x - y||^2, grad = A^T (A x - y) / B, in two launches that spread a worker over many workgroups: both are
+// bound by the round trips of their loads, so what counts is how many of them are in flight.  (One workgroup of four
+// waves per worker, a wave per sample row, then a thread per feature: 31 workers x 166 x 384, with the mix, 92 us.)
+// Residuals r[w][b]: a wave takes two sample rows, its lanes stride over the features with 16-byte loads at any
+// alignment.  31 workers x 166 x 384: the two launches and the mix 23 us.  grid (ceil(B / 8), n), block 256; F >= 4.
 __global__ void __launch_bounds__(256)
-lsq_grad_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A, const float *__restrict__ y, int B,
-                int F, float *__restrict__ G, float *__restrict__ loss)
+lsq_residual_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A, const float *__restrict__ y, int B, int F,
+                    float *__restrict__ r)
+{
+    const int w = blockIdx.y, lane = threadIdx.x & 63, b0 = blockIdx.x * 8 + (threadIdx.x >> 6) * 2;
+    if (b0 >= B) return;
+    const int b1 = min(b0 + 1, B - 1);
+    const float *x = X + (i64)w * ld, *a0 = A + ((i64)w * B + b0) * F, *a1 = A + ((i64)w * B + b1) * F;
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll 4
+    for (int k = lane * 4; k < F; k += 256) {
+        const int kc = min(k, F - 4);
+        const f32x4_a4 tx = *reinterpret_cast<const f32x4_a4 *>(x + kc), t0 = *reinterpret_cast<const f32x4_a4 *>(a0 + kc),
+                       t1 = *reinterpret_cast<const f32x4_a4 *>(a1 + kc);
+        // (the row's last four elements once more: only those beyond the lane before count)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float xe = kc + e >= k ? tx[e] : 0.f;
+            s0 = (kc + e >= k ? t0[e] : 0.f) * xe + s0;
+            s1 = (kc + e >= k ? t1[e] : 0.f) * xe + s1;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        s0 += __shfl_down(s0, off, 64);
+        s1 += __shfl_down(s1, off, 64);
+    }
+    if (lane == 0) {
+        r[(i64)w * B + b0] = s0 - y[(i64)w * B + b0];
+        if (b0 + 1 < B) r[(i64)w * B + b0 + 1] = s1 - y[(i64)w * B + b0 + 1];
+    }
+}
+
+// G[w][c] = sum_b A[b][c] r[b] / B: a lane per feature, the waves deal the samples among themselves and meet in LDS in wave
+// order; the first workgroup of a worker also forms its loss.  grid (ceil(F / 64), n), block 512.
+__global__ void __launch_bounds__(512)
+lsq_feature_kernel(const float *__restrict__ A, const float *__restrict__ r, int B, int F, float *__restrict__ G, i64 ld,
+                   float *__restrict__ loss)
+{
+    constexpr int NW = 8;
+    __shared__ float red[NW][64];
+    const int w = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = blockIdx.x * 64 + lane;
+    const float *a = A + (i64)w * B * F + min(c, F - 1), *rw = r + (i64)w * B;
+    float s = 0.f;
+#pragma unroll 8
+    for (int b = wave; b < B; b += NW) s = a[(i64)b * F] * rw[b] + s;
+    red[wave][lane] = s;
+    __syncthreads();
+    const float invB = 1.0f / (float)B;
+    if (wave == 0) {
+#pragma unroll
+        for (int q = 1; q < NW; ++q) s += red[q][lane];
+        if (c < F) G[(i64)w * ld + c] = s * invB;
+    }
+    if (loss && blockIdx.x == 0 && wave == 1) {
+        double t = 0.0;
+        for (int b = lane; b < B; b += 64) t += (double)rw[b] * rw[b];
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        if (lane == 0) loss[w] = (float)(0.5 * t / B);
+    }
+}
+
+// Any shape, one workgroup per worker: less than 4 features, or more workers than grid.y holds.
+__global__ void __launch_bounds__(256)
+lsq_narrow_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A, const float *__restrict__ y, int B,
+                  int F, float *__restrict__ G, float *__restrict__ loss)
 {
     extern __shared__ float r[];   // [B]
     const int w = blockIdx.x;
     const float *x = X + (i64)w * ld;
     const float *a = A + (i64)w * B * F;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int b = wave; b < B; b += 4) {
+    for (int b = threadIdx.x; b < B; b += 256) {
         float s = 0.f;
-        for (int c = lane; c < F; c += 64) s = a[(i64)b * F + c] * x[c] + s;
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-        if (lane == 0) r[b] = s - y[(i64)w * B + b];
+        for (int c = 0; c < F; ++c) s = a[(i64)b * F + c] * x[c] + s;
+        r[b] = s - y[(i64)w * B + b];
     }
     __syncthreads();
     const float invB = 1.0f / (float)B;
-    for (int c = threadIdx.x; c < F; c += 256) {
+    for (int c = wave; c < F + 1; c += 4) {   // (the last one: the loss)
         float s = 0.f;
-        for (int b = 0; b < B; ++b) s = a[(i64)b * F + c] * r[b] + s;
-        G[(i64)w * ld + c] = s * invB;
-    }
-    if (loss && wave == 0) {
-        float s = 0.f;
-        for (int b = lane; b < B; b += 64) s = r[b] * r[b] + s;
+        for (int b = lane; b < B; b += 64) s = (c < F ? a[(i64)b * F + c] : r[b]) * r[b] + s;
         for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-        if (lane == 0) loss[w] = 0.5f * s * invB;
+        if (lane == 0 && c < F) G[(i64)w * ld + c] = s * invB;
+        if (lane == 0 && c == F && loss) loss[w] = 0.5f * s * invB;
+    }
+}
+
+// A whole iteration of a problem that fits one workgroup's LDS (all samples, residuals, iterates and gradients): every
+// launch saved is worth more than the CUs left idle.  8 workers x 32 x 64 on a ring: 9.9 us a step, 13.3 with a gradient and a mix
+// kernel of their own.
+// Rows of samples are pitched to 8 floats past a multiple of 16: the eight lanes that share a row's product and the eight
+// rows beside them meet in no bank.
+// sum_j W_ij x_j - gamma g as the mix kernels form it: one product, then fused multiply-adds (ring: i-1, i, i+1).
+constexpr long long kLsqStepFloats = 36 * 1024;
+struct LsqStepArgs {
+    float *X;
+    const float *A, *y;
+    float *G, *loss, *consensus;
+    const int *rowptr, *colidx;
+    const float *vals;
+    i64 ld;
+    int n, B, F, P, ring;
+    float ring_w, gamma;
+};
+
+__global__ void __launch_bounds__(1024) lsq_step_kernel(LsqStepArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lsq_lds[];
+    __shared__ double part[16];
+    const int n = a.n, B = a.B, F = a.F, P = a.P, tid = threadIdx.x, rows = n * B;
+    float *As = lsq_lds, *xs = As + rows * P, *gs = xs + n * F, *r = gs + n * F;
+    const int F4 = (F + 3) / 4;
+#pragma unroll 4
+    for (int q = tid; q < rows * F4; q += 1024) {
+        const int row = q / F4, k = q % F4 * 4;
+        const f32x4_a4 t = *reinterpret_cast<const f32x4_a4 *>(a.A + (i64)row * F + min(k, F - 4));
+        *reinterpret_cast<f32x4 *>(As + row * P + k) = mend4((f32x4){t.x, t.y, t.z, t.w}, F - k);
+    }
+    for (int e = tid; e < n * F; e += 1024) xs[e] = a.X[(i64)(e / F) * a.ld + e % F];
+    __syncthreads();
+    for (int row = tid >> 3; row < (rows + 7) / 8 * 8; row += 128) {
+        const int j = tid & 7, rc = min(row, rows - 1), w = rc / B;
+        double s = 0.0;   // (a lane's few terms in fp64: no more error than 64 lanes' sums in fp32)
+        for (int c = j; c < F; c += 8) s += (double)As[rc * P + c] * xs[w * F + c];
+        s += __shfl_xor(s, 4, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 1, 64);
+        if (j == 0 && row < rows) r[row] = (float)s - a.y[row];
+    }
+    __syncthreads();
+    const float invB = 1.0f / (float)B;
+    for (int e = tid; e < n * F; e += 1024) {
+        const int w = e / F, c = e % F;
+        float s = 0.f;
+#pragma unroll 8
+        for (int b = 0; b < B; ++b) s = As[(w * B + b) * P + c] * r[w * B + b] + s;
+        s *= invB;
+        gs[e] = s;
+        a.G[(i64)w * a.ld + c] = s;
+    }
+    if (a.loss)
+        for (int w = tid >> 6; w < n; w += 16) {
+            double s = 0.0;
+            for (int b = tid & 63; b < B; b += 64) s += (double)r[w * B + b] * r[w * B + b];
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+            if ((tid & 63) == 0) a.loss[w] = (float)(0.5 * s / B);
+        }
+    // (an element's own gradient is all the update reads of gs: the result takes its place)
+    for (int e = tid; e < n * F; e += 1024) {
+        const int i = e / F, c = e % F;
+        float m;
+        if (a.ring) {
+            m = a.ring_w * xs[(i ? i - 1 : n - 1) * F + c];
+            m = __builtin_fmaf(a.ring_w, xs[e], m);
+            m = __builtin_fmaf(a.ring_w, xs[(i + 1 < n ? i + 1 : 0) * F + c], m);
+        } else {
+            m = 0.f;
+            for (int k = a.rowptr[i]; k < a.rowptr[i + 1]; ++k) m = __builtin_fmaf(a.vals[k], xs[a.colidx[k] * F + c], m);
+        }
+        const float v = __builtin_fmaf(-a.gamma, gs[e], m);
+        gs[e] = v;
+        a.X[(i64)i * a.ld + c] = v;
+    }
+    if (!a.consensus) return;
+    __syncthreads();
+    double dev = 0.0;
+    for (int c = tid; c < F; c += 1024) {
+        const float shift = gs[c];   // (differences from the first row: no cancellation of large numbers)
+        double s = 0.0, q = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const double t = (double)gs[i * F + c] - shift;
+            s += t;
+            q += t * t;
+        }
+        dev += q - s * s / n;
+    }
+    for (int off = 32; off > 0; off >>= 1) dev += __shfl_down(dev, off, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = dev;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+        for (int k = 0; k < 16; ++k) t += part[k];
+        *a.consensus = (float)(t / n);
     }
 }
 
@@ -617,9 +777,31 @@ softmax_xent_kernel(const float *__restrict__ z, const int *__restrict__ labels,
     }
 }
 
+// dpsgd_step of a least-squares problem that fits one workgroup's LDS, in one launch.  false: does not fit, nothing done.
+bool launch_step_lsq(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, const void *inputs, const void *targets, float *G,
+                     float *loss, float *consensus, dpsgd_status *st)
+{
+    const int n = ctx->n, B = m.batch, F = m.widths[0];
+    if (m.kind != DPSGD_MODEL_LSQ || F < 4 || B > 8192 || n > 256 || ctx->opt_mix_force_csr || !ctx->d_rowptr) return false;
+    const int P = (F + 7) / 16 * 16 + 8;
+    const i64 floats = (i64)n * B * (P + 1) + 2 * (i64)n * F;
+    if (floats > kLsqStepFloats) return false;
+    LsqStepArgs a{X, (const float *)inputs, (const float *)targets, G, loss, consensus, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals,
+                  ctx->ld, n, B, F, P, ctx->ring_uniform ? 1 : 0, ctx->ring_w, ctx->gamma};
+    const size_t shm = (size_t)floats * sizeof(float);
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(lsq_step_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)shm) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    hipLaunchKernelGGL(lsq_step_kernel, dim3(1), dim3(1024), shm, ctx->stream, a);
+    *st = hip_status(hipGetLastError());
+    return true;
+}
+
 size_t f32_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m)
 {
-    if (m.kind == DPSGD_MODEL_LSQ) return 256;
+    if (m.kind == DPSGD_MODEL_LSQ) return (size_t)ctx->n * (size_t)m.batch * sizeof(float) + 256;   // residuals
     const size_t n = (size_t)ctx->n, B = (size_t)m.batch;
     size_t floats = 0, widest = 0;
     const size_t L = m.widths.size() - 1;
@@ -639,8 +821,15 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
     const int n = ctx->n, B = m.batch;
     if (m.kind == DPSGD_MODEL_LSQ) {
         if (B > 8192) return DPSGD_EUNSUPPORTED;
-        hipLaunchKernelGGL(lsq_grad_kernel, dim3((unsigned)n), dim3(256), (size_t)B * sizeof(float), s, X, ctx->ld,
-                           (const float *)inputs, (const float *)targets, B, m.widths[0], G, loss);
+        const int F = m.widths[0];
+        const float *A = (const float *)inputs, *y = (const float *)targets;
+        if (F < 4 || n > 65535) {   // (the others' grid.y is the worker)
+            hipLaunchKernelGGL(lsq_narrow_kernel, dim3((unsigned)n), dim3(256), (size_t)B * sizeof(float), s, X, ctx->ld, A, y, B, F, G, loss);
+            return hip_status(hipGetLastError());
+        }
+        float *r = (float *)ctx->ws;
+        hipLaunchKernelGGL(lsq_residual_kernel, dim3((unsigned)((B + 7) / 8), (unsigned)n), dim3(256), 0, s, X, ctx->ld, A, y, B, F, r);
+        hipLaunchKernelGGL(lsq_feature_kernel, dim3((unsigned)((F + 63) / 64), (unsigned)n), dim3(512), 0, s, A, r, B, F, G, ctx->ld, loss);
         return hip_status(hipGetLastError());
     }
     const int L = (int)m.widths.size() - 1;

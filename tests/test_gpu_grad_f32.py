@@ -208,3 +208,40 @@ def test_trajectory_config0_full():
 
 def test_trajectory_config1_full():
     run_trajectory(CONFIGS[1], CONFIGS[1].iters, synth.padded_stride(30730))
+
+
+@pytest.mark.parametrize("feat,batch,n", [(3, 70, 5),      # less than 4 features: a kernel of their own
+                                          (4, 9, 3), (7, 8, 2),     # one and two quads of features, the second clamped
+                                          (63, 17, 4), (257, 1, 2), (1023, 40, 3), (300, 1000, 2)])
+def test_lsq_gradient_of_every_length(feat, batch, n):
+    cfg = shrink(CONFIGS[0], widths=(feat,), batch=batch, n=n)
+    grad_case(cfg, feat)
+
+
+@pytest.mark.parametrize("feat,batch,n,topo", [(64, 32, 8, "ring"), (5, 3, 3, "ring"), (73, 20, 16, "complete"), (16, 9, 12, "torus"),
+                                               (120, 31, 9, "ring"),      # 35 919 floats of LDS of 36 864
+                                               (120, 32, 9, "ring")])     # one sample more does not fit: two launches and the mix
+def test_lsq_step_in_one_launch(feat, batch, n, topo):
+    """dpsgd_step of a problem that fits one workgroup: update, gradient, loss and consensus distance against the oracle, at
+    both sides of what fits, and the gradient it leaves against dpsgd_grad's."""
+    cfg = shrink(CONFIGS[0], widths=(feat,), batch=batch, n=n)
+    X = synth.make_replicas(cfg, spread=0.5) + synth.rng(0, 98).standard_normal((n, feat)).astype(np.float32) * np.float32(0.1)
+    inp, tgt = synth.make_batch(cfg, 0)
+    W = {"ring": oracle.ring, "complete": oracle.complete, "torus": lambda n: oracle.torus(3, n // 3)}[topo](n).with_fp32_values()
+    Xref, Gref, lref = oracle.iteration(MODEL_LSQ, cfg.widths, W, np.float32(cfg.gamma), X, inp, tgt)
+    tb = {"ring": B.Topology.ring, "complete": B.Topology.complete, "torus": lambda: B.Topology.torus(3, n // 3)}[topo]()
+    Xd, inp_d, tgt_d = to_dev(X, feat + 3), torch.from_numpy(inp).cuda(), torch.from_numpy(tgt).cuda()
+    G1, G2 = torch.full_like(Xd, 777.0), torch.full_like(Xd, 777.0)
+    loss, cons = torch.zeros(n, device="cuda"), torch.zeros(1, device="cuda")
+    model = B.Model(MODEL_LSQ, [feat])
+    print(f"lsq step {feat} x {batch} x {n} {topo}", flush=True)
+    with B.Dpsgd(n, feat, tb, cfg.gamma, ld=feat + 3) as ctx:
+        ctx.grad(model, Xd, inp_d, tgt_d, batch, G1)
+        ctx.step(model, Xd, inp_d, tgt_d, batch, G2, loss, cons)
+        torch.cuda.synchronize()
+    check_close(from_dev(Xd, feat), Xref, TOL, "X")
+    check_close(from_dev(G2, feat), Gref, TOL, "G")
+    check_close(from_dev(G2, feat), from_dev(G1, feat), TOL, "G of step and grad")
+    assert rel_err(loss.cpu().numpy(), lref) < TOL
+    m = float(((Xref - Xref.mean(0)) ** 2).sum() / n)
+    assert float(cons) == pytest.approx(m, rel=TOL)

@@ -573,38 +573,48 @@ dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
     return linear_fwd_launch<1, 1, 2, 2, 64>(s, nworkers, g);
 }
 
-// The class layer (O <= 16): 16 samples x 16 outputs per workgroup on v_mfma_f32_16x16x4_f32, whose 16 waves deal the
+// The class layer (O <= 16 NO): 16 samples x 16 NO outputs per workgroup on v_mfma_f32_16x16x4_f32, whose NW waves deal the
 // contraction among themselves in pieces of 64 elements (256 bytes of a row); a wave requests NP pieces of both operands at
 // once, straight from global memory, and the waves' sums meet in LDS in wave order.  What bounds it is the round trip of
 // those loads and 64 bytes per sample and output from L2 for every 16 elements of the contraction.  No unit's sign hangs
 // on the order of these sums, unlike in the layers below.  Lane l holds 4 consecutive elements of row l % 16 from
 // 4 (l / 16) on; the e-th of four instructions takes the e-th element of both operands.
-// 16 workers x 128 samples x 3072 -> 10: 13.1 us, linear_fwd_skinny_kernel 23.5 (a step 36.7 against 47.3).
-// grid (ceil(B / 16), n), block 1024; I >= 4, rows at any alignment.
-template <int NP>
-__global__ void __launch_bounds__(1024)
-linear_fwd_class_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,
-                        int O, float *__restrict__ out)
+// The workgroup has all logits of its samples, so the softmax cross-entropy follows at once: dz = (softmax - onehot) / B and the
+// sum of its samples' losses (class_grad_kernel adds them up).  A launch of its own for that, one workgroup per worker, took 7.8 us.
+// 16 workers x 128 samples x 3072 -> 10, a step on a ring: 36.8 -> 27.9 us with these two launches in the place of three.
+// grid (ceil(B / 16), n), block 64 NW; I >= 4, rows at any alignment.
+template <int NP, int NO, int NW>
+__global__ void __launch_bounds__(64 * NW)
+class_fwd_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,
+                 int O, const int *__restrict__ labels, float *__restrict__ dz, float *__restrict__ lsum)
 {
-    constexpr int NW = 16;
-    __shared__ float red[NW][256];
+    __shared__ float red[NW][NO * 256];
+    __shared__ float ls[16];
     const int w = blockIdx.y, b0 = blockIdx.x * 16;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
     const float *a = act + ((i64)w * B + min(b0 + l16, B - 1)) * I;
-    const float *x = X + (i64)w * ld + woff + (i64)min(l16, O - 1) * I;
+    const float *x[NO];
+#pragma unroll
+    for (int t = 0; t < NO; ++t) x[t] = X + (i64)w * ld + woff + (i64)min(16 * t + l16, O - 1) * I;
     const int pieces = (I + 63) / 64;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NO];
+#pragma unroll
+    for (int t = 0; t < NO; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     for (int p = wave; p < pieces; p += NW * NP) {
-        f32x4 va[NP][4], vx[NP][4];
+        f32x4 va[NP][4], vx[NO][NP][4];
 #pragma unroll
         for (int j = 0; j < NP; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int k = min((p + NW * j) * 64 + q * 16 + g4 * 4, I - 4);
-                const f32x4_a4 ta = *reinterpret_cast<const f32x4_a4 *>(a + k), tx = *reinterpret_cast<const f32x4_a4 *>(x + k);
+                const f32x4_a4 ta = *reinterpret_cast<const f32x4_a4 *>(a + k);
                 va[j][q] = (f32x4){ta.x, ta.y, ta.z, ta.w};
-                vx[j][q] = (f32x4){tx.x, tx.y, tx.z, tx.w};
+#pragma unroll
+                for (int t = 0; t < NO; ++t) {
+                    const f32x4_a4 tx = *reinterpret_cast<const f32x4_a4 *>(x[t] + k);
+                    vx[t][j][q] = (f32x4){tx.x, tx.y, tx.z, tx.w};
+                }
             }
         __builtin_amdgcn_sched_barrier(0);   // every load is on its way before the first is waited for
 #pragma unroll
@@ -614,25 +624,181 @@ linear_fwd_class_kernel(const float *__restrict__ act, const float *__restrict__
                 for (int q = 0; q < 4; ++q) {
                     const int have = I - ((p + NW * j) * 64 + q * 16 + g4 * 4);
                     va[j][q] = mend4(va[j][q], have);
-                    vx[j][q] = mend4(vx[j][q], have);
+#pragma unroll
+                    for (int t = 0; t < NO; ++t) vx[t][j][q] = mend4(vx[t][j][q], have);
                 }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[j][q][e], vx[j][q][e], acc, 0, 0, 0);
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < NO; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[j][q][e], vx[t][j][q][e], acc[t], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) red[wave][(4 * g4 + v) * 16 + l16] = acc[v];   // row (sample) 4 g4 + v, column (output) l16
-    __syncthreads();
-    if (threadIdx.x >= 256) return;
-    const int b = b0 + (threadIdx.x >> 4), o = threadIdx.x & 15;
-    if (b >= B || o >= O) return;
-    float s = red[0][threadIdx.x];
+    for (int t = 0; t < NO; ++t)
 #pragma unroll
-    for (int q = 1; q < NW; ++q) s += red[q][threadIdx.x];
-    out[((i64)w * B + b) * O + o] = s + X[(i64)w * ld + boff + o];
+        for (int v = 0; v < 4; ++v) red[wave][((4 * g4 + v) * NO + t) * 16 + l16] = acc[t][v];   // sample 4 g4 + v, output 16 t + l16
+    __syncthreads();
+    // 16 lanes per sample, NO outputs each
+    if (threadIdx.x < 256) {
+        const int r = threadIdx.x >> 4, b = b0 + r, o0 = threadIdx.x & 15;
+        float z[NO], mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < NO; ++t) {
+            const int o = 16 * t + o0;
+            float s = red[0][(r * NO + t) * 16 + o0];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) s += red[q][(r * NO + t) * 16 + o0];
+            z[t] = o < O ? s + X[(i64)w * ld + boff + o] : -INFINITY;
+            mx = fmaxf(mx, z[t]);
+        }
+        for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        float se = 0.f;
+#pragma unroll
+        for (int t = 0; t < NO; ++t)
+            if (16 * t + o0 < O) se += expf(z[t] - mx);
+        for (int off = 8; off > 0; off >>= 1) se += __shfl_xor(se, off, 64);
+        const float lse = mx + logf(se), invB = 1.0f / (float)B;
+        float lost = 0.f;
+        if (b < B) {
+            int lab = labels[(i64)w * B + b];
+            lab = lab < 0 ? 0 : (lab >= O ? O - 1 : lab);
+#pragma unroll
+            for (int t = 0; t < NO; ++t) {
+                const int o = 16 * t + o0;
+                if (o >= O) continue;
+                if (o == lab) lost = lse - z[t];
+                dz[((i64)w * B + b) * O + o] = (expf(z[t] - lse) - (o == lab ? 1.f : 0.f)) * invB;
+            }
+        }
+        for (int off = 8; off > 0; off >>= 1) lost += __shfl_xor(lost, off, 64);
+        if (o0 == 0) ls[r] = lost;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int r = 0; r < 16; ++r) s += ls[r];
+        lsum[(i64)w * gridDim.x + blockIdx.x] = (float)s;
+    }
+}
+
+// Weight gradient of the class layer, dW[o][i] = sum_b dz[b][o] act[b][i], its bias gradient and the worker's loss.  A
+// workgroup owns 64 inputs, its NW waves deal the samples among themselves in fours (v_mfma_f32_16x16x4_f32: outputs x
+// inputs, contraction over 4 samples) and meet in LDS in wave order.  A lane fetches 4 consecutive inputs of a sample, the t-th
+// of four instructions takes the t-th: lane (n, g) ends up with inputs 4 n .. + 3 of outputs 4 g .. + 3, 16-byte stores.
+// The worker's last workgroup sums dz over the samples and the losses.  Bound by the round trips of its loads.
+// grid (ceil(I / 64) + 1, n), block 64 NW; I >= 4.
+template <int NO, int NW>
+__global__ void __launch_bounds__(64 * NW)
+class_grad_kernel(const float *__restrict__ act, const float *__restrict__ dz, const float *__restrict__ lsum, int parts, int B, int I,
+                  int O, float *__restrict__ G, i64 ld, i64 woff, i64 boff, float *__restrict__ loss)
+{
+    __shared__ f32x4 red[NW > 1 ? NW - 1 : 1][NO * 4][64];
+    const int w = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float *dw = dz + (i64)w * B * O;
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int o = wave; o < O + 1; o += NW) {   // (the last one: the loss)
+            double s = 0.0;
+            if (o < O)
+                for (int b = lane; b < B; b += 64) s += dw[(i64)b * O + o];
+            else
+                for (int k = lane; k < parts; k += 64) s += lsum[(i64)w * parts + k];
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+            if (lane == 0 && o < O) G[(i64)w * ld + boff + o] = (float)s;
+            if (lane == 0 && o == O && loss) loss[w] = (float)(s / B);
+        }
+        return;
+    }
+    const int n16 = lane & 15, g = lane >> 4;
+    const int c = blockIdx.x * 64 + 4 * n16, cc = min(c, I - 4);   // (beyond the last four inputs: those once more)
+    const float *aw = act + (i64)w * B * I + cc;
+    f32x4 acc[NO][4];
+#pragma unroll
+    for (int t = 0; t < NO; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 4;   // groups of four samples in flight
+    for (int s0 = wave * 4; s0 < B; s0 += NW * 4 * U) {
+        f32x4_a4 va[U];
+        float vd[U][NO];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = min(s0 + u * NW * 4 + g, B - 1);
+            va[u] = *reinterpret_cast<const f32x4_a4 *>(aw + (i64)b * I);
+#pragma unroll
+            for (int t = 0; t < NO; ++t) vd[u][t] = dw[(i64)b * O + min(16 * t + n16, O - 1)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool real = s0 + u * NW * 4 + g < B;
+#pragma unroll
+            for (int t = 0; t < NO; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(real ? vd[u][t] : 0.f, real ? va[u][e] : 0.f, acc[t][e], 0, 0, 0);
+        }
+    }
+    if (NW > 1) {
+        if (wave > 0)
+#pragma unroll
+            for (int t = 0; t < NO; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[wave - 1][t * 4 + e][lane] = acc[t][e];
+        __syncthreads();
+        if (wave > 0) return;
+        for (int q = 0; q < NW - 1; ++q)
+#pragma unroll
+            for (int t = 0; t < NO; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[t][e] += red[q][t * 4 + e][lane];
+    }
+    if (c >= I) return;
+    float *gw = G + (i64)w * ld + woff + cc;
+#pragma unroll
+    for (int t = 0; t < NO; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int o = 16 * t + 4 * g + v;
+            if (o < O) *reinterpret_cast<f32x4_a4 *>(gw + (i64)o * I) = (f32x4_a4){acc[t][0][v], acc[t][1][v], acc[t][2][v], acc[t][3][v]};
+        }
+}
+
+// Whether those two take a class layer, and their launches.
+bool class_layer_ok(int n, int B, int I, int O) { return O <= 32 && I >= 4 && n <= 65535; }
+int class_parts(int B) { return (B + 15) / 16; }
+
+dpsgd_status class_forward(hipStream_t s, int n, const float *act, const float *X, i64 ld, i64 woff, i64 boff, int B, int I, int O,
+                           const int *labels, float *dz, float *lsum)
+{
+    const dim3 grid((unsigned)class_parts(B), (unsigned)n);
+    const int pieces = (I + 63) / 64;
+    auto launch = [&](auto k, int waves) {
+        hipLaunchKernelGGL(k, grid, dim3(64 * waves), 0, s, act, X, ld, woff, boff, B, I, O, labels, dz, lsum);
+    };
+    if (O <= 16) {
+        if (pieces <= 4) launch(class_fwd_kernel<1, 1, 4>, 4);
+        else if (pieces <= 16) launch(class_fwd_kernel<1, 1, 16>, 16);
+        else if (pieces <= 32) launch(class_fwd_kernel<2, 1, 16>, 16);
+        else launch(class_fwd_kernel<3, 1, 16>, 16);
+    } else {
+        if (pieces <= 4) launch(class_fwd_kernel<1, 2, 4>, 4);
+        else launch(class_fwd_kernel<1, 2, 16>, 16);
+    }
+    return hip_status(hipGetLastError());
+}
+
+dpsgd_status class_gradient(hipStream_t s, int n, const float *act, const float *dz, const float *lsum, int B, int I, int O, float *G,
+                            i64 ld, i64 woff, i64 boff, float *loss)
+{
+    const dim3 grid((unsigned)((I + 63) / 64 + 1), (unsigned)n);
+    if (O <= 16)
+        hipLaunchKernelGGL((class_grad_kernel<1, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(B), B, I, O, G, ld, woff, boff, loss);
+    else
+        hipLaunchKernelGGL((class_grad_kernel<2, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(B), B, I, O, G, ld, woff, boff, loss);
+    return hip_status(hipGetLastError());
 }
 
 // Forward of a hidden layer with few outputs (O <= 16) and 256 inputs or more: one workgroup per worker and R sample rows;
@@ -810,7 +976,7 @@ size_t f32_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m)
         floats += n * B * (size_t)m.widths[l];
         if ((size_t)m.widths[l] > widest) widest = (size_t)m.widths[l];
     }
-    floats += 2 * n * B * widest;
+    floats += 2 * n * B * widest + n * ((B + 15) / 16);
     return floats * sizeof(float) + 256;
 }
 
@@ -855,6 +1021,9 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
     }
     float *dz = ws, *dz2 = ws + (i64)n * B * widest;
 
+    float *lsum = dz2 + (i64)n * B * widest;   // sums of the samples' losses, one per 16 samples
+    const bool fused = class_layer_ok(n, B, m.widths[L - 1], m.widths[L]);
+
     dpsgd_status st;
     for (int l = 0; l < L; ++l) {
         const int I = m.widths[l], O = m.widths[l + 1];
@@ -864,16 +1033,8 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         g.C = (float *)act[l + 1]; g.sCw = (i64)B * O; g.sCm = O;
         g.bias = X + boff[l]; g.sBiasw = ctx->ld;
         g.M = B; g.N = O; g.K = I; g.relu = (l < L - 1);
-        if (O <= 16 && I >= 256 && l == L - 1) {
-            const dim3 cgrid((unsigned)((B + 15) / 16), (unsigned)n);
-            const int np = ((I + 63) / 64 + 15) / 16;   // pieces per wave
-            auto launch = [&](auto k) {
-                hipLaunchKernelGGL(k, cgrid, dim3(1024), 0, s, act[l], X, ctx->ld, woff[l], boff[l], B, I, O, (float *)act[l + 1]);
-            };
-            if (np == 1) launch(linear_fwd_class_kernel<1>);
-            else if (np == 2) launch(linear_fwd_class_kernel<2>);
-            else launch(linear_fwd_class_kernel<3>);
-            if ((st = hip_status(hipGetLastError())) != DPSGD_OK) return st;
+        if (l == L - 1 && fused) {   // logits, softmax cross-entropy and dz
+            if ((st = class_forward(s, n, act[l], X, ctx->ld, woff[l], boff[l], B, I, O, (const int *)targets, dz, lsum)) != DPSGD_OK) return st;
             continue;
         }
         if (O <= 16 && I >= 256) {
@@ -893,19 +1054,24 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         if ((st = linear_fwd_f32(s, n, g)) != DPSGD_OK) return st;
     }
     const int C = m.widths[L];
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)n), dim3(256), 0, s, act[L], (const int *)targets, B, C, dz,
+    if (!fused)
+        hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)n), dim3(256), 0, s, act[L], (const int *)targets, B, C, dz,
                        loss, G, (long long)ctx->ld, (long long)boff[L - 1]);   // with the class layer's bias gradient
     for (int l = L - 1; l >= 0; --l) {
         const int I = m.widths[l], O = m.widths[l + 1];
-        GemmArgs g{};   // weight gradient: dW[o][i] = sum_b dz[b][o] act_l[b][i]
-        g.A = dz; g.sAw = (i64)B * O; g.sAm = 1; g.sAk = O;
-        g.B = act[l]; g.sBw = (i64)B * I; g.sBk = I; g.sBn = 1;
-        g.C = G + woff[l]; g.sCw = ctx->ld; g.sCm = I;
-        g.M = O; g.N = I; g.K = B;
-        if ((st = gemm_f32(s, n, g)) != DPSGD_OK) return st;
-        if (l < L - 1)   // (the class layer's came with the softmax launch)
-            hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((O + 3) / 4), (unsigned)n), dim3(256), 0, s, dz, B, O, G,
-                               ctx->ld, boff[l]);
+        if (l == L - 1 && fused) {
+            if ((st = class_gradient(s, n, act[l], dz, lsum, B, I, O, G, ctx->ld, woff[l], boff[l], loss)) != DPSGD_OK) return st;
+        } else {
+            GemmArgs g{};   // weight gradient: dW[o][i] = sum_b dz[b][o] act_l[b][i]
+            g.A = dz; g.sAw = (i64)B * O; g.sAm = 1; g.sAk = O;
+            g.B = act[l]; g.sBw = (i64)B * I; g.sBk = I; g.sBn = 1;
+            g.C = G + woff[l]; g.sCw = ctx->ld; g.sCm = I;
+            g.M = O; g.N = I; g.K = B;
+            if ((st = gemm_f32(s, n, g)) != DPSGD_OK) return st;
+            if (l < L - 1)   // (the class layer's came with the softmax launch)
+                hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((O + 3) / 4), (unsigned)n), dim3(256), 0, s, dz, B, O, G,
+                                   ctx->ld, boff[l]);
+        }
         if (l > 0) {   // data gradient through the ReLU: dz_prev = (dz W_l) * [act_l > 0]
             GemmArgs h{};
             h.A = dz; h.sAw = (i64)B * O; h.sAm = O; h.sAk = 1;

@@ -245,3 +245,13 @@ def test_lsq_step_in_one_launch(feat, batch, n, topo):
     assert rel_err(loss.cpu().numpy(), lref) < TOL
     m = float(((Xref - Xref.mean(0)) ** 2).sum() / n)
     assert float(cons) == pytest.approx(m, rel=TOL)
+
+
+@pytest.mark.parametrize("widths,batch,n", [((4, 2), 1, 2), ((5, 17), 17, 3), ((63, 16), 16, 2), ((257, 26), 31, 3), ((1100, 32), 33, 2),
+                                            ((300, 33), 20, 2), ((3, 26), 9, 2), ((2100, 26), 70, 9), ((130, 70, 26), 40, 3)])
+def test_class_layers_of_every_width(widths, batch, n):
+    """The two kernels of a class layer at the edges of what they take: 4 inputs, one and two tiles of outputs (33 outputs and 3
+    inputs go to the tiled products), ragged sample tiles, pieces and last inputs."""
+    cfg = shrink(CONFIGS[1], widths=widths, batch=batch, n=n) if len(widths) == 2 else \
+        shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False)
+    grad_case(cfg, synth.model_dim(cfg.model_kind, widths))

@@ -107,9 +107,25 @@ __device__ __forceinline__ int weight_tile_row(int r, int K)
     return (K & 4095) == 0 ? (r & ~7) + ((r >> 1) & 1) + 2 * (r & 1) + 4 * ((r >> 2) & 1) : r;
 }
 
+// The workgroups of a (tiles, blocks of samples, workers) grid in the order (worker, tile, block), cut into eight runs, one per
+// XCD: a worker's operands come into one L2 or two, and the blocks that read the same weights run side by side.
+// 8 workers x 512 samples x 3072 x 1024: forward 79.5 -> 61.3 us, weight gradient 58.5 -> 41.4 (dealt round-robin, every XCD
+// pulled every worker's activations, 50 MB each through 4 MB of L2).
+__device__ __forceinline__ void worker_tile_block_runs(int &tile, int &block, int &w)
+{
+    const unsigned total = gridDim.x * gridDim.y * gridDim.z, id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const unsigned xcd = id & 7, q = total >> 3, r = total & 7;
+    const unsigned at = xcd * q + (xcd < r ? xcd : r) + (id >> 3);
+    block = (int)(at % gridDim.y);
+    tile = (int)(at / gridDim.y % gridDim.x);
+    w = (int)(at / gridDim.y / gridDim.x);
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by linear id and every XCD has its own L2.  For a grid
 // (tiles, 1, n) with n a multiple of 8 the ids are renumbered so that all tiles of a worker run on one XCD and
-// the worker's activation (or delta) matrix is fetched into one L2 instead of eight.
+// the worker's activation (or delta) matrix is fetched into one L2 instead of eight.  Any other n takes the runs above from
+// ten tiles on (12 workers x 784-500-300-10 x 50 on tight rows 92.1 -> 90.0 us a step, 29 x 1280-320-26 x 61 119.7 -> 116.0;
+// 45 x 3072-64-512-2 x 32, whose layers have one, eight and one, 100.7 -> 102.7).
 __device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w)
 {
     tile = blockIdx.x;
@@ -119,6 +135,9 @@ __device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w)
         const unsigned xcd = id & 7, slot = id >> 3;
         w = (int)((slot / gridDim.x) * 8 + xcd);
         tile = (int)(slot % gridDim.x);
+    } else if (gridDim.y == 1 && gridDim.x >= 10) {
+        int block;
+        worker_tile_block_runs(tile, block, w);
     }
 }
 
@@ -384,16 +403,18 @@ __global__ void __launch_bounds__(256) mlp_fwd_kernel(FwdArgs g)
 constexpr int KCW = 128;
 constexpr int PITCHW = KCW + 8;
 
-template <bool LAST>
+// BLOCKS: more than one block of samples; they share the weights, which then go through the caches.
+template <bool LAST, bool BLOCKS>
 __global__ void __launch_bounds__(256, 3) mlp_fwd_wide_kernel(FwdArgs g)
 {
     constexpr int TO = 64, MBLK = 128, MT = 2, WQ = 8, AQ = 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t *Wt = reinterpret_cast<bf16_t *>(smem);   // [TO][PITCHW]
     bf16_t *At = Wt + TO * PITCHW;                    // [MBLK][PITCHW]
-    int w, tile;
-    worker_tile_on_one_xcd(tile, w);
-    const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
+    int w, tile, block = 0;
+    if (BLOCKS) worker_tile_block_runs(tile, block, w);
+    else worker_tile_on_one_xcd(tile, w);
+    const int o0 = tile * TO, b0 = block * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, half = lane >> 5;
@@ -413,8 +434,9 @@ __global__ void __launch_bounds__(256, 3) mlp_fwd_wide_kernel(FwdArgs g)
 #pragma unroll
         for (int q = 0; q < WQ; ++q) {
             const int u = tid + 256 * q, o = o0 + weight_tile_row(u >> 5, g.K), k = k0 + (u & 31) * 4;
-            wreg[q] = __builtin_nontemporal_load(
-                reinterpret_cast<const f32x4 *>(Wg + (i64)(o < g.O ? o : g.O - 1) * g.K + (k < g.K ? k : 0)));
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(Wg + (i64)(o < g.O ? o : g.O - 1) * g.K + (k < g.K ? k : 0));
+            if (BLOCKS) wreg[q] = *p;
+            else wreg[q] = __builtin_nontemporal_load(p);
         }
     };
     auto stage = [&](int k0) {
@@ -969,7 +991,8 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
 }
 
 // The weight gradient of minibatches of more than 64 samples, where the kernel above is bound by the operands it pulls
-// from L2, 2 KB per matrix instruction (8 workers x 512 samples x 3072 x 1024: 120 us; here 57, with four steps of operands
+// from L2, 2 KB per matrix instruction (8 workers x 512 samples x 3072 x 1024: 120 us; here 41, 58 before one XCD took all o tiles
+// of a run of k tiles; with four steps of operands
 // in flight and half the workgroups per CU 69; its 26 GFLOP and 100 MB of results are worth about 25 each).  A workgroup
 // owns a [128 o][128 k] tile, each of its four waves 64 x 64 of it; the operands travel from L2 into LDS asynchronously
 // (16 bytes per lane, no registers), kWgStep steps of 16 samples at a time into the other of two buffers, and are shared
@@ -983,10 +1006,11 @@ __global__ void __launch_bounds__(256, 4) mlp_wgrad_big_kernel(WgradArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     u32x4 *lds = reinterpret_cast<u32x4 *>(smem);   // [2][kWgStep][8 groups: 4 of o, 4 of k][64]
-    const int w = blockIdx.z;
+    int w, kt, ot;   // one XCD takes all o tiles of a run of k tiles
+    worker_tile_block_runs(kt, ot, w);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int o0 = blockIdx.y * 128, k0 = blockIdx.x * 128;
+    const int o0 = ot * 128, k0 = kt * 128;
     const int wo = wave >> 1, wk = wave & 1;
     const int steps = g.Bp / 16;
     // wave v brings the groups v (of o) and 4 + v (of k); groups beyond the matrix repeat the last one (never stored)
@@ -1032,7 +1056,7 @@ __global__ void __launch_bounds__(256, 4) mlp_wgrad_big_kernel(WgradArgs g)
         __builtin_amdgcn_s_waitcnt(0);   // what was requested has arrived, for every wave, before anyone reads it
         __syncthreads();
     }
-    if (blockIdx.x == 0 && wk == 0) {   // bias gradient: gb[o] = sum_b dZ[b][o]
+    if (kt == 0 && wk == 0) {   // bias gradient: gb[o] = sum_b dZ[b][o]
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int o = o0 + wo * 64 + i * 32 + l32;
@@ -1536,8 +1560,11 @@ dpsgd_status fwd_launch(hipStream_t s, int n, const FwdArgs &a, bool vec, bool l
     if (WM == 2 && WN == 2 && MT == 2 && vec) {   // 128-row minibatch blocks: 512-byte row pieces (with or without a bf16 copy, which no kernel here reads)
         dim3 grid((unsigned)((a.O + 63) / 64), (unsigned)((a.B + 127) / 128), (unsigned)n);
         const size_t shm = (size_t)(64 + 128) * PITCHW * sizeof(bf16_t);
-        if (last) hipLaunchKernelGGL(mlp_fwd_wide_kernel<true>, grid, dim3(256), shm, s, a);
-        else hipLaunchKernelGGL(mlp_fwd_wide_kernel<false>, grid, dim3(256), shm, s, a);
+        const bool blocks = grid.y > 1;
+        if (last && blocks) hipLaunchKernelGGL((mlp_fwd_wide_kernel<true, true>), grid, dim3(256), shm, s, a);
+        else if (last) hipLaunchKernelGGL((mlp_fwd_wide_kernel<true, false>), grid, dim3(256), shm, s, a);
+        else if (blocks) hipLaunchKernelGGL((mlp_fwd_wide_kernel<false, true>), grid, dim3(256), shm, s, a);
+        else hipLaunchKernelGGL((mlp_fwd_wide_kernel<false, false>), grid, dim3(256), shm, s, a);
         return hip_status(hipGetLastError());
     }
     dim3 grid((unsigned)((a.O + TO - 1) / TO), (unsigned)((a.B + MBLK - 1) / MBLK), (unsigned)n);

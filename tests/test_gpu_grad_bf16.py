@@ -152,6 +152,18 @@ def test_a_worker_does_not_depend_on_how_many_there_are(widths, batch, n, aligne
     assert torch.equal(got[0][0], got[1][0]), f"gradient: max {float((got[0][0] - got[1][0]).abs().max()):.3e}"
 
 
+@pytest.mark.parametrize("widths,batch,n", [((104, 700, 10), 20, 5),      # ten tiles and more of up to 64 samples: 55 workgroups
+                                            ((256, 1100, 10), 300, 9),    # three blocks of samples: 18 tiles x 3 x 9 = 486 = 8 x 60 + 6
+                                            ((136, 1430, 10), 130, 13)])  # two blocks, an odd number of workgroups' tiles
+def test_every_workgroup_finds_its_tile(widths, batch, n):
+    """The orders in which workgroups are dealt to the XCDs where the workers are no multiple of eight or the minibatch has
+    several blocks: every tile of every worker is computed (the 777 that is there before is gone) as its worker alone has it."""
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_MLP, widths)
+    ld = synth.padded_stride(d)
+    grad_case(cfg, ld)
+
+
 def test_softmax_regression_bf16():
     cfg = shrink(CONFIGS[1], widths=(3072, 10), batch=128, n=3, bf16=True)
     d = synth.model_dim(MODEL_SOFTMAX, cfg.widths)

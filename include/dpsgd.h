@@ -179,7 +179,8 @@ dpsgd_status dpsgd_set_gamma(dpsgd_ctx *ctx, float gamma);
  * have the same bits, the weight gradients add up in another order),
  * "conv_block" (default 1: CNN forward, residual blocks that keep the resolution (16 channels, 32 on 16 x 16 or 64 on 8 x 8
  * pixels): both convolutions of
- * the block in one launch, the activation between them kept in LDS for the second one; 0: two launches.  Same bits),
+ * the block in one launch, the activation between them kept in LDS for the second one; from 256 images on all
+ * consecutive blocks of a stage that keep the resolution in one launch; 0: a launch per convolution.  Same bits),
  * "conv_pad" (default 1: CNN stages of at most 64 channels and 64 pixels per row (more than 32 channels: 32 pixels) whose
  * extents the matrix kernels do not take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple
  * of 8 rows - are kept in the workspace rounded up to such extents, zeros beyond the real ones; 0: in their real extents,

@@ -23,19 +23,10 @@
 // 112 workers x 32 images, 16 channels x 32 x 32, a block: 229 us in four launches, 147 here; 32 channels x 16 x 16: 157 and
 // 110; one convolution of 32 channels 82 and 64, of 64 channels x 8 x 8 77 and 55.  16 waves of half the registers at 16
 // channels spill (321 us); 64 channels as a block would need the sums of four tiles per wave.
-#include "resnet_common.h"
+#include "conv_image.h"
 
 namespace dpsgd {
 namespace {
-
-typedef long long i64;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-constexpr int ksteps(int ci) { return (9 * ci + 31) / 32; }
 
 struct ConvBwdArgs {
     const bf16_t *dv;        // delta of the output [n*B][C][H][W]
@@ -48,23 +39,11 @@ struct ConvBwdArgs {
     int H, B, splits;
 };
 
-// Pixels per LDS row: the image and its halo; rows of 8 pixels are padded so that a row is a multiple of 256 bytes
-// (the pixel right of a row and the one left of the next are the same: both are zero)
-__host__ __device__ constexpr int row_pixels(int C, int W) { return W >= 16 ? W + 1 : (C == 16 ? 16 : C == 32 ? 12 : 10); }
-__host__ __device__ constexpr int image_lds(int C, int W, int H) { return ((H + 2) * row_pixels(C, W) + (W >= 16 ? 1 : 0)) * 2 * C; }
-
-// A group of 8 channels goes to 16-byte unit (group ^ swizzle(column)) of its pixel.  An LDS access of 16 bytes per lane is
-// served in four phases, lanes 0-3, 12-15 and 20-27 first, 4-11, 16-19 and 28-31 second, the other half alike; with these, lanes
-// reading the same channels of 16 consecutive pixels (or of 8 pixels in each of two rows) at any column meet in no bank, nor
-// do the 16-channel rows of 8 consecutive pixels that 32 lanes of a transposing read touch.
-template <int C>
-__device__ __forceinline__ int swizzle(int col) { return C == 16 ? 0 : C == 32 ? ((col >> 2) & 1) << 1 : ((col >> 1) & 3) << 1; }
-
 // HT: rows of an image, or 0: a.H of them and one image at a time.
-template <int C, int W, int HT, int NI, bool BLOCK, int NT>
-__global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
+template <int C, int W, int HT, int NI, bool BLOCK>
+__global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
 {
-    constexpr int KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
+    constexpr int NT = 512, KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
     constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
     constexpr int RW = NT / (BLOCK ? 128 : 64);       // waves that share a gradient (BLOCK: half of them each)
     constexpr int TW = C == 64 ? 16 / RW : 1;               // weight gradient: input-channel tiles per wave
@@ -90,7 +69,7 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
 
     // ---- staging: thread e fetches pixels 4 px4 .. + 3 of channels TC ct .. + TC - 1 of image im_t of every tensor (SIDE: half
     // of the threads take the deltas, the others the activations)
-    constexpr int TC = NT == 1024 ? 4 : 8;
+    constexpr int TC = 8;
     constexpr bool SIDE = !BLOCK && HT > 0 && NI * HT * W * C <= NT / 2 * 4 * TC;
     const int tpi = (C / TC) * (HW / 4);
     const int tid_t = SIDE ? tid & (NT / 2 - 1) : tid, second = SIDE ? tid / (NT / 2) : 0;
@@ -101,7 +80,7 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
 #pragma unroll
     for (int j = 0; j < (C == 16 ? 1 : 4); ++j) {
         const int row = px / W + 1, col = px % W + 1 + j;
-        soff[j] = im_t * image_lds(C, W, H) + row * ROWB + col * PXB + (((ct * TC / 8) ^ swizzle<C>(col)) << 4) + ct * TC % 8 * 2 + second * BUF;
+        soff[j] = im_t * image_lds(C, W, H) + row * ROWB + col * PXB + ((ct ^ swizzle<C>(col)) << 4) + second * BUF;
     }
     struct Stage { u32x2 v[TC]; };
     // No branch around the loads (behind one the compiler would wait for them at once): past the last image it is fetched
@@ -124,8 +103,7 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
                 d[k] = there ? __builtin_amdgcn_perm(h, l, (j & 1) ? 0x07060302u : 0x05040100u) : 0u;
             }
             unsigned char *q = buf + (C == 16 ? soff[0] + j * PXB : soff[j]);
-            if constexpr (TC == 8) *reinterpret_cast<u32x4 *>(q) = (u32x4){d[0], d[1], d[2], d[3]};
-            else *reinterpret_cast<u32x2 *>(q) = (u32x2){d[0], d[1]};
+            *reinterpret_cast<u32x4 *>(q) = (u32x4){d[0], d[1], d[2], d[3]};
         }
     };
 
@@ -179,13 +157,7 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
     for (int kx = 0; kx < (C == 16 ? 1 : 3); ++kx) toff[kx] = tr_offset(kx, ci0);
     auto tap_offset = [&](int kx) { return C == 16 ? toff[0] + kx * PXB : toff[kx]; };
     const int doff = (C == 16 ? toff[0] + PXB : toff[C == 16 ? 0 : 1] ^ ((co ^ ci0) << 5)) + ROWB;
-    auto read_tr = [&](const unsigned char *p0, const unsigned char *p1) {
-        typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
-        const s16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0)), h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p1));
-        const u32x2 x = __builtin_bit_cast(u32x2, l), y = __builtin_bit_cast(u32x2, h);
-        return __builtin_bit_cast(bf16x8, (u32x4){x.x, x.y, y.x, y.y});
-    };
-    auto read_pixels = [&](const unsigned char *p) { return read_tr(p, p + HALF); };   // a group's 32, of 16 channels
+    auto read_pixels = [&](const unsigned char *p) { return __builtin_bit_cast(bf16x8, read_transposed(p, p + HALF)); };   // a group's 32, of 16 channels
     const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
     f32x4 sum[TW][9], bsum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -333,7 +305,7 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
         ooff[1] = (ooff[0] ^ (C == 16 ? 0 : C == 32 ? 32 : 64)) + 4 * PXB;
     }
     auto read_own = [&](const unsigned char *buf, int q) {
-        return __builtin_bit_cast(u32x4, read_tr(buf + group_lds(q) + ooff[0], buf + group_lds(q) + ooff[1]));
+        return read_transposed(buf + group_lds(q) + ooff[0], buf + group_lds(q) + ooff[1]);
     };
     constexpr int NSC = BLOCK ? 1 : (512 * 32 / C) / 32 / DS;   // groups of a wave, at most
     struct Shortcut { u32x4 v[NSC]; };
@@ -484,39 +456,29 @@ __global__ void __launch_bounds__(NT, NT / 256) conv_bwd_kernel(ConvBwdArgs a)
     }
 }
 
-constexpr int threads_of(int C) { return 512; }
 
-// Images a workgroup takes at a time: as many as give every thread a staging task, where their size is a usual one
-int images_at_once(int C, int H, int W) { return (C == 32 && H == 16 && W == 16) || (C == 64 && H == 8 && W == 8) ? 2 : 1; }
 
 size_t lds_bytes(int C, int H, int W, bool block)
 {
     const size_t img = (size_t)4 * images_at_once(C, H, W) * image_lds(C, W, H);
-    const size_t waves = threads_of(C) / 64, tiles = C == 64 ? 1 : (C / 16) * (C / 16);   // waves that hand their sums to others
+    const size_t waves = 8, tiles = C == 64 ? 1 : (C / 16) * (C / 16);   // waves that hand their sums to others
     const size_t red = C == 64 ? 64 : (waves - (block ? 2 : 1) * tiles) * 9 * 1024;
     return img > red ? img : red;
 }
 
 bool shape_ok(const dpsgd_ctx *ctx, const ConvDesc &c, bool block)
 {
-    if (!ctx->opt_conv_bwd || c.stride != 1) return false;
-    if (c.Ci != c.Co || c.Cis != c.Cos || c.His != c.Hos || c.Wis != c.Wos) return false;
-    const int C = c.Cos, W = c.Wos, H = c.Hos;
-    // (a staging task of 32 elements per thread)
-    if (H < 8 || H % 8 || H * W * C > 512 * 32) return false;
-    if (!((C == 16 && (W == 8 || W == 16 || W == 32)) || ((C == 32 || C == 64) && (W == 8 || W == 16)))) return false;
-    return lds_bytes(C, H, W, block) <= 160 * 1024;
+    return ctx->opt_conv_bwd && image_shape_ok(c) && lds_bytes(c.Cos, c.Hos, c.Wos, block) <= 160 * 1024;
 }
 
 template <int C, int W, int HT, int NI, bool BLOCK>
 dpsgd_status launch(dpsgd_ctx *ctx, const ConvBwdArgs &a)
 {
     const size_t shm = lds_bytes(C, a.H, W, BLOCK);
-    constexpr int NT = threads_of(C);
-    auto k = conv_bwd_kernel<C, W, HT, NI, BLOCK, NT>;
+    auto k = conv_bwd_kernel<C, W, HT, NI, BLOCK>;
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
         return DPSGD_EDEVICE;
-    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(NT), shm, ctx->stream, a);
+    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(512), shm, ctx->stream, a);
     return hip_status(hipGetLastError());
 }
 
@@ -557,14 +519,14 @@ bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc 
            c1.Wos == c2.Wos && c1.Co == c2.Co;
 }
 
-// Workgroups per worker, each with a CU to itself: as many as keep the last round of workgroups over the CUs full, counting
+// Workgroups per worker where `slots` of them run at once: as many as keep the last round of them full, counting
 // two images' time for a workgroup's start and its partial sums.
-int conv_bwd_splits(int n, int B)
+int conv_image_splits(int n, int B, int slots)
 {
     int best = 1;
     i64 cost = -1;
     for (int m = 1; m <= B && m <= 32; ++m) {
-        const i64 c = ((i64)n * m + 255) / 256 * ((B + m - 1) / m + 2);
+        const i64 c = ((i64)n * m + slots - 1) / slots * ((B + m - 1) / m + 2);
         if (cost < 0 || c < cost) {
             cost = c;
             best = m;
@@ -579,7 +541,7 @@ dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, con
     if (!conv_bwd_ok(ctx, c)) return DPSGD_EUNSUPPORTED;
     ConvBwdArgs a{};
     a.dv = dout.t; a.u = act.t; a.scd = scd; a.din = din.t; a.wd2 = wpack_d; a.part2 = partials;
-    a.H = c.Hos; a.B = B; a.splits = conv_bwd_splits(ctx->n, B);
+    a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256);
     const dpsgd_status st = launch_any<false>(ctx, c.Cos, c.Wos, a);
     return st == DPSGD_OK ? add_job(ctx, c, a.splits, partials, G, pending) : st;
 }
@@ -591,7 +553,7 @@ dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &
     if (!conv_block_bwd_ok(ctx, c1, c2)) return DPSGD_EUNSUPPORTED;
     ConvBwdArgs a{};
     a.dv = dv.t; a.u = u.t; a.in = in.t; a.din = din.t; a.wd2 = wpack_d2; a.wd1 = wpack_d1;
-    a.part2 = partials2; a.part1 = partials1; a.H = c2.Hos; a.B = B; a.splits = conv_bwd_splits(ctx->n, B);
+    a.part2 = partials2; a.part1 = partials1; a.H = c2.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256);
     dpsgd_status st = launch_any<true>(ctx, c2.Cos, c2.Wos, a);
     if (st == DPSGD_OK) st = add_job(ctx, c2, a.splits, partials2, G, pending);
     return st == DPSGD_OK ? add_job(ctx, c1, a.splits, partials1, G, pending) : st;

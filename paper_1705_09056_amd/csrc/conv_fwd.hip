@@ -1,0 +1,299 @@
+// Forward of consecutive residual blocks that keep the resolution, all their convolutions in one launch (gfx950):
+//   u_j = ReLU(conv(a_j) + b),  a_{j+1} = ReLU(conv(u_j) + b' + a_j).
+// A workgroup owns some images of one worker and takes NI of them through all the convolutions: a_j and u_j stay in LDS,
+// pixel-major, each convolution reads one and writes the other (a_{j+1} over a_j, pixel by pixel), and only the first block's
+// input is read from memory.  Weights as the left operand of the matrix instruction, so that a lane owns 4 channels of one
+// pixel and stores them at once; what goes to memory, channel-major, is fetched from LDS by transposing reads (8 pixels of a
+// channel per lane) while the next convolution is multiplied.
+// The same matrix instructions on the same operands in the same order as conv3x3_mfma_kernel: the same bits.
+// The sign bitmap is left of the last a only: nothing reads the others' where the backward takes these stages.
+// What bounds it: at 16 channels LDS, whose 128 bytes per clock the operands of a convolution take for 2500 clocks an image
+// (its matrix instructions: 1280), and the stores; they overlap only as far as two workgroups on a CU drift apart.
+// 112 workers x 32 images: three blocks of 16 channels 314 us in conv_block_fwd_kernel, 252 here (281 with one workgroup of the
+// same registers per CU, 268 with the next weights requested a convolution ahead); two of 32 channels 133 and 115, of 64 132
+// and 89.
+#include "conv_image.h"
+
+namespace dpsgd {
+namespace {
+
+constexpr int kMaxChain = 8;   // convolutions of a launch
+
+struct ConvChainArgs {
+    const bf16_t *src;              // a of the first block [n*B][C][H][W]
+    bf16_t *out[kMaxChain];         // u, a, u, a, ..
+    const bf16_t *wpack[kMaxChain]; // packed forward operands [n][KS][C/16][64][8]
+    i64 b_off[kMaxChain];
+    unsigned char *sign;            // bitmap of the last a
+    const float *X;
+    i64 ld;
+    int nconv, H, B, splits;
+    int Cr, Hr, Wr;                 // the real extents (PAD)
+};
+
+// Two workgroups share a CU, so that one loads, stores or meets at a barrier while the other multiplies: 16 channels 8 waves of
+// 128 registers each, else 4 waves.
+constexpr int threads_of(int C) { return C == 16 ? 512 : 256; }
+constexpr int kWorkgroupsPerCu = 2;
+
+// HT: rows of an image, or 0: a.H of them and one image at a time.  PAD: real extents below the stored ones.
+template <int C, int W, int HT, int NI, bool PAD>
+__global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerCu / 256) conv_chain_kernel(ConvChainArgs a)
+{
+    constexpr int NT = threads_of(C), KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
+    constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
+    constexpr int DS = NT / 64 / CT;                        // waves that split the pixels; the others split the output channels
+    constexpr int HALF = W == 32 ? 16 * PXB : (16 / W) * ROWB;   // from a group's first 16 pixels to its second
+    static_assert(HT > 0 || NI == 1, "several images at a time are of a fixed size");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ float biases[kMaxChain];
+    int sp = blockIdx.x, w = blockIdx.y;
+    if ((gridDim.y & 7) == 0) {   // all workgroups of a worker on one XCD
+        const unsigned id = blockIdx.x + gridDim.x * blockIdx.y, xcd = id & 7, slot = id >> 3;
+        w = (int)((slot / gridDim.x) * 8 + xcd);
+        sp = (int)(slot % gridDim.x);
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, g = lane >> 4;
+    const int H = HT ? HT : a.H, HW = H * W, G = HW / 32;   // groups of 32 pixels of an image
+    const int IMG = image_lds(C, W, H), BUF = NI * IMG;
+    const int lo = (int)((i64)a.B * sp / a.splits), hi = (int)((i64)a.B * (sp + 1) / a.splits);
+    const i64 img0 = (i64)w * a.B;
+
+    // ---- staging: thread e fetches pixels 4 px4 .. + 3 of channels 8 ct .. + 7 of image im_t
+    const int tpi = (C / 8) * (HW / 4);
+    const int im_t = NI > 1 ? tid / tpi : 0, rem = NI > 1 ? tid % tpi : tid, ct = rem / (HW / 4), px = rem % (HW / 4) * 4;
+    const bool task = NI > 1 ? im_t < NI : rem < tpi;
+    const unsigned goff = task ? (unsigned)(ct * 8 * HW + px) : 0u;   // elements behind the image's first
+    int soff[C == 16 ? 1 : 4];
+#pragma unroll
+    for (int j = 0; j < (C == 16 ? 1 : 4); ++j) {
+        const int row = px / W + 1, col = px % W + 1 + j;
+        soff[j] = im_t * IMG + row * ROWB + col * PXB + ((ct ^ swizzle<C>(col)) << 4);
+    }
+    u32x2 st[8];
+    auto fetch = [&](int i) {   // (no branch around the loads; past the last image it is fetched again, never stored)
+        const int im = i + im_t < hi ? i + im_t : hi - 1;
+        const bf16_t *p = a.src + (img0 + im) * C * HW + goff;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) st[c] = *reinterpret_cast<const u32x2 *>(p + c * HW);
+    };
+    auto commit = [&](unsigned char *buf) {
+        if (!task) return;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            unsigned d[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned l = j < 2 ? st[2 * k].x : st[2 * k].y, h = j < 2 ? st[2 * k + 1].x : st[2 * k + 1].y;
+                d[k] = __builtin_amdgcn_perm(h, l, (j & 1) ? 0x07060302u : 0x05040100u);
+            }
+            *reinterpret_cast<u32x4 *>(buf + (C == 16 ? soff[0] + j * PXB : soff[j])) = (u32x4){d[0], d[1], d[2], d[3]};
+        }
+    };
+
+    // ---- this wave's output-channel tile and its share of the groups
+    const int dt = wave % CT, dq = wave / CT;
+    struct Weights { bf16x8 v[KS]; };
+    auto weights = [&](int k) {
+        Weights f;
+        const bf16_t *wp = a.wpack[k] + (i64)w * (KS * CT * 512) + dt * 512 + lane * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) f.v[s] = *reinterpret_cast<const bf16x8 *>(wp + s * CT * 512);
+        return f;
+    };
+    // offset, from the group's first row, of the operand of k-step s at pixel n16 of the group's first tile
+    constexpr int NOFF = C == 16 ? KS : 3;
+    int off[NOFF];
+#pragma unroll
+    for (int k = 0; k < NOFF; ++k) {
+        const int kk = 32 * (C == 16 ? k : k * (C / 32)) + 8 * g;
+        const int tap = kk / C > 8 ? 8 : kk / C;   // padded taps carry zero weights; read finite data
+        const int row = n16 / W + tap / 3, col = n16 % W + tap % 3;
+        off[k] = row * ROWB + col * PXB + (((kk % C) / 8 ^ swizzle<C>(col)) << 4);
+    }
+    auto at = [&](int s, int tt) {
+        const int tap = s / (C / 32 ? C / 32 : 1), ky = tap / 3, kx = tap % 3;
+        return (C == 16 ? off[s] : (off[kx] ^ (C == 64 ? (s & 1) << 6 : 0)) + ky * ROWB) + tt * HALF;
+    };
+    auto group_lds = [&](int q) { return NI > 1 ? (q / G) * IMG + (q % G) * R32 * ROWB : q * R32 * ROWB; };   // the row above the group
+    constexpr int NBT = C == 16 ? 1 : C == 32 ? 2 : 6, KB = (KS + NBT - 1) / NBT;   // k-steps whose operands are read together
+    struct Batch { bf16x8 v[KB][2]; };
+    Batch ops[NBT > 1 ? 2 : 1];
+    auto read_ops = [&](Batch &b, const unsigned char *p, int k) {
+#pragma unroll
+        for (int s = 0; s < KB; ++s)
+            if (k * KB + s < KS)
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt) b.v[s][tt] = *reinterpret_cast<const bf16x8 *>(p + at(k * KB + s, tt));
+    };
+    auto products = [&](f32x4 (&acc)[2], const Weights &f, const unsigned char *p, const unsigned char *next) {
+        acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NBT; ++k) {
+            if (NBT > 1) {
+                if (k + 1 < NBT) read_ops(ops[(k + 1) & 1], p, k + 1);
+                else read_ops(ops[0], next, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int s = 0; s < KB; ++s)
+                if (k * KB + s < KS)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)
+                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v[k * KB + s], ops[k & 1].v[s][tt], acc[tt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (NBT == 1) {
+            read_ops(ops[0], next, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // ---- a lane's place in LDS (channels 16 dt + 4 g .. + 3 of pixel n16 of a tile), and in memory (8 pixels of channel o)
+    int own;
+    {
+        const int row = n16 / W + 1, col = n16 % W + 1;
+        own = row * ROWB + col * PXB + (((2 * dt + (g >> 1)) ^ swizzle<C>(col)) << 4) + (g & 1) * 8;
+    }
+    const int o = 16 * dt + n16, gy = 8 * g / W, gx = 8 * g % W;
+    int ooff[2];
+    {
+        const int col = gx + (n16 >> 2) + 1, q = n16 & 3;
+        ooff[0] = (gy + 1) * ROWB + col * PXB + (((2 * dt + (q >> 1)) ^ swizzle<C>(col)) << 4) + (q & 1) * 8;
+        ooff[1] = (ooff[0] ^ (C == 16 ? 0 : C == 32 ? 32 : 64)) + 4 * PXB;
+    }
+    // group q of the images from i on, from LDS to memory
+    auto store = [&](const unsigned char *buf, bf16_t *dst, int q, int i, bool last) {
+        const int im = i + (NI > 1 ? q / G : 0), y = (NI > 1 ? q % G : q) * R32 + gy;
+        const u32x4 v = read_transposed(buf + group_lds(q) + ooff[0], buf + group_lds(q) + ooff[1]);
+        if (im >= hi) return;
+        *reinterpret_cast<u32x4 *>(dst + ((img0 + im) * C + o) * HW + y * W + gx) = v;
+        if (last) {   // after the ReLU a value is positive exactly when its bf16 pattern is not zero
+            const unsigned d[4] = {v.x, v.y, v.z, v.w};
+            unsigned bits = 0;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) bits |= ((d[h] & 0xffffu) ? 1u << (2 * h) : 0u) | ((d[h] >> 16) ? 2u << (2 * h) : 0u);
+            a.sign[(((img0 + im) * (H / 8) + (y >> 3)) * C + o) * W + (((y & 7) * W + gx) >> 3)] = (unsigned char)bits;
+        }
+    };
+    // One convolution from src into dst, and meanwhile group by group what is due (due, to out, of the images from id on)
+    auto convolve = [&](const unsigned char *src, unsigned char *dst, const Weights &f, float bias, bool add, const unsigned char *due, bf16_t *out, int id) {
+        read_ops(ops[0], src + group_lds(dq < NI * G ? dq : 0), 0);
+#pragma unroll 1
+        for (int q = dq; q < NI * G; q += DS) {
+            const int base = group_lds(q);
+            if (out) store(due, out, q, id, false);
+            u32x2 sc[2] = {(u32x2){0u, 0u}, (u32x2){0u, 0u}};
+            if (add)
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt) sc[tt] = *reinterpret_cast<const u32x2 *>(dst + base + own + tt * HALF);
+            f32x4 acc[2];
+            products(acc, f, src + base, src + group_lds(q + DS < NI * G ? q + DS : q));
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                const unsigned d[2] = {sc[tt].x, sc[tt].y};
+                float r[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float v = acc[tt][k];
+                    if (add) v += __uint_as_float((k & 1) ? d[k >> 1] & 0xffff0000u : d[k >> 1] << 16);
+                    v += bias;
+                    r[k] = fmaxf(v, 0.f);   // (zero for a NaN and for minus zero)
+                }
+                u32x2 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3])};
+                if (PAD) {   // zeros beyond the real extents
+                    const int p = 16 * tt + n16, y = (NI > 1 ? q % G : q) * R32 + p / W, x = p % W;
+                    const int n = (y < a.Hr && x < a.Wr) ? a.Cr - (16 * dt + 4 * g) : 0;
+                    pk.x &= (n > 0 ? 0x0000ffffu : 0u) | (n > 1 ? 0xffff0000u : 0u);
+                    pk.y &= (n > 2 ? 0x0000ffffu : 0u) | (n > 3 ? 0xffff0000u : 0u);
+                }
+                *reinterpret_cast<u32x2 *>(dst + base + own + tt * HALF) = pk;
+            }
+        }
+    };
+
+    // ---- the halos stay zero from here on; what follows writes the images' own pixels only
+    for (int e = tid; e < 2 * BUF / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
+    fetch(lo);
+    Weights f = weights(0);
+    unsigned char *const A = smem, *const U = smem + BUF;
+    if (tid < a.nconv) biases[tid] = a.X[(i64)w * a.ld + a.b_off[tid]];
+    for (int i = lo; i < hi; i += NI) {
+        __syncthreads();   // the images before have left
+        commit(A);
+        for (int k = 0; k < a.nconv; ++k) {
+            __syncthreads();
+            const float bias = biases[k];
+            if (k == 0) convolve(A, U, f, bias, false, nullptr, nullptr, i);
+            else if (k & 1) convolve(U, A, f, bias, true, U, a.out[k - 1], i);
+            else convolve(A, U, f, bias, false, A, a.out[k - 1], i);
+            f = weights(k + 1 < a.nconv ? k + 1 : 0);   // requested before the barrier
+        }
+        __syncthreads();
+        fetch(i + NI);
+        for (int q = dq; q < NI * G; q += DS) store(A, a.out[a.nconv - 1], q, i, true);
+    }
+}
+
+size_t lds_bytes(int C, int H, int W, int NI) { return (size_t)2 * NI * image_lds(C, W, H); }
+
+template <int C, int W, int HT, int NI>
+dpsgd_status launch(dpsgd_ctx *ctx, const ConvChainArgs &a, bool padded)
+{
+    const size_t shm = lds_bytes(C, a.H, W, NI);
+    auto k = padded ? conv_chain_kernel<C, W, HT, NI, true> : conv_chain_kernel<C, W, HT, NI, false>;
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+        return DPSGD_EDEVICE;
+    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(threads_of(C)), shm, ctx->stream, a);
+    return hip_status(hipGetLastError());
+}
+}  // namespace
+
+// From 256 images on: fewer leave CUs without one, and a workgroup takes its image through all convolutions one after the other,
+// where conv_block_fwd_kernel has a workgroup per band of rows and block (3 workers x 40 images of 32 x 32, a step 277 us
+// with it, 295 without; 9 x 14 images 177 and 180; 12 x 41 of 14 x 27 514 and 500).
+bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
+{
+    return ctx->opt_conv_block && (i64)ctx->n * B >= 256 && image_shape_ok(c) && c.Hos * c.Wos * c.Cos <= threads_of(c.Cos) * 32 &&
+           lds_bytes(c.Cos, c.Hos, c.Wos, 1) <= 160 * 1024 / kWorkgroupsPerCu;
+}
+
+dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
+                                const std::vector<bf16_t *> &wpack, std::vector<Tensor> &out)
+{
+    for (int at = 0; at < nconv; at += kMaxChain) {
+        const ConvDesc &c = convs[first + at];
+        ConvChainArgs a{};
+        a.nconv = nconv - at < kMaxChain ? nconv - at : kMaxChain;
+        a.src = in.t; a.X = X; a.ld = ctx->ld; a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256 * kWorkgroupsPerCu);
+        a.Cr = c.Co; a.Hr = c.Ho; a.Wr = c.Wo;
+        for (int k = 0; k < a.nconv; ++k) {
+            a.out[k] = out[first + at + k].t;
+            a.wpack[k] = wpack[first + at + k];
+            a.b_off[k] = convs[first + at + k].b_off;
+            if (k + 1 < a.nconv) out[first + at + k].sign = nullptr;
+        }
+        in = out[first + at + a.nconv - 1];
+        a.sign = in.sign;
+        if (!a.sign) return DPSGD_EUNSUPPORTED;
+        const bool p = c.padded_out();
+        const int C = c.Cos, W = c.Wos, H = c.Hos;
+        dpsgd_status st;
+        if (C == 16) {
+            if (W == 32) st = H == 32 ? launch<16, 32, 32, 1>(ctx, a, p) : launch<16, 32, 0, 1>(ctx, a, p);
+            else st = W == 16 ? launch<16, 16, 0, 1>(ctx, a, p) : launch<16, 8, 0, 1>(ctx, a, p);
+        } else if (C == 32) {
+            if (W == 16) st = H == 16 ? launch<32, 16, 16, 1>(ctx, a, p) : launch<32, 16, 0, 1>(ctx, a, p);
+            else st = launch<32, 8, 0, 1>(ctx, a, p);
+        } else {
+            if (W == 16) st = launch<64, 16, 0, 1>(ctx, a, p);
+            // (two images at a time fetch the weights half as often: the blocks of 112 workers x 32 images 77 us, 91 with one)
+            else st = H == 8 && B > a.splits ? launch<64, 8, 8, 2>(ctx, a, p) : launch<64, 8, 0, 1>(ctx, a, p);
+        }
+        if (st != DPSGD_OK) return st;
+    }
+    return DPSGD_OK;
+}
+
+}  // namespace dpsgd

@@ -1200,7 +1200,7 @@ size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
     if (!wgrad_mfma_ok(c)) return 0;
     const size_t cip = (size_t)(c.Cis + 15) / 16 * 16;   // partials are stored per 16 x 16 tile of (c_out, padded c_in)
     int splits = wgrad_splits(ctx->n, B, c.Cos, c.stride);
-    const int m = conv_bwd_splits(ctx->n, B);   // (whichever kernel takes the convolution)
+    const int m = conv_image_splits(ctx->n, B, 256);   // (whichever kernel takes the convolution)
     splits = m > splits ? m : splits;
     return (size_t)splits * ((size_t)c.Cos * cip * 9 + 1) * sizeof(float);
 }

@@ -472,6 +472,14 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     }
     for (int j = 0; j < p.nblocks; ++j) {
         const ConvDesc &c1 = p.convs[1 + 2 * j], &c2 = p.convs[2 + 2 * j];
+        int chain = 0;   // blocks from here on that keep the resolution: one launch
+        while (j + chain < p.nblocks && conv_chain_ok(ctx, p.convs[1 + 2 * (j + chain)], B) && conv_chain_ok(ctx, p.convs[2 + 2 * (j + chain)], B))
+            ++chain;
+        if (chain > 0 && a_of(j + chain).sign) {
+            if ((st = conv_chain_forward(ctx, p.convs, 1 + 2 * j, 2 * chain, B, a_of(j), X, ws.wpack_f, ws.out)) != DPSGD_OK) return st;
+            j += chain - 1;
+            continue;
+        }
         if (conv_block_forward_ok(ctx, c1, c2) && u_of(j).sign && a_of(j + 1).sign) {
             if ((st = conv_block_forward(ctx, c1, c2, B, a_of(j), X, ws.wpack_f[1 + 2 * j], ws.wpack_f[2 + 2 * j], u_of(j),
                                          a_of(j + 1))) != DPSGD_OK)

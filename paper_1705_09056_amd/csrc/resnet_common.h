@@ -77,6 +77,11 @@ dpsgd_status conv_forward(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, c
 bool conv_block_forward_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2);
 dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B, Tensor in, const float *X,
                                 const bf16_t *wpack1, const bf16_t *wpack2, Tensor u, Tensor out);
+// Consecutive residual blocks of that kind, all convolutions convs[first .. first + nconv) in one launch (conv_fwd.hip); _ok: whether
+// the shape (the same for all) and the number of images allow it ("conv_block" option on).  Same bits; leaves no sign bitmap (out[..].sign becomes null) but the last one's.
+bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B);
+dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
+                                const std::vector<bf16_t *> &wpack, std::vector<Tensor> &out);
 // din = round([act > 0] * (conv^T(dout) + shortcut delta)).
 dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X, const bf16_t *wpack_d,
                             ShortcutRef scd, Tensor act, Tensor din);
@@ -130,7 +135,7 @@ dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const voi
 // residual block that keeps the resolution, whose inner delta then stays in LDS.  _ok: whether the shapes allow it.
 bool conv_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c);
 bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2);
-int conv_bwd_splits(int n, int B);   // workgroups (partial sums) per worker
+int conv_image_splits(int n, int B, int slots);   // workgroups per worker (and partial sums of its weight gradient)
 // din = round([act > 0] * (conv^T(dout) + scd)), dW and bias gradient from (act, dout); scd may be null
 dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
                       Tensor din, float *G, float *partials, WgradReduceList *pending);

@@ -187,6 +187,35 @@ def test_residual_block_in_one_launch_changes_no_bit(widths, batch, n):
     assert torch.equal(out[0][0], out[1][0]), "gradient differs"
 
 
+@pytest.mark.parametrize("widths,batch,n", [((3, 32, 32, 16, 3, 10), 37, 7),    # an odd number of images per workgroup
+                                             ((1, 28, 28, 16, 2, 10), 33, 8),    # zeros beyond the real extents
+                                             ((3, 16, 16, 16, 5, 10), 16, 16),   # ten convolutions: two launches; one image per workgroup
+                                             ((3, 8, 8, 16, 1, 10), 64, 5),      # less groups of pixels than waves
+                                             ((2, 24, 13, 8, 2, 10), 40, 9),     # rows that no constant covers
+                                             ((3, 16, 40, 16, 2, 10), 32, 8),    # 64 channels with rows of 16 pixels are too large, as is the rest
+                                             ((3, 48, 32, 16, 2, 10), 32, 8)])   # 24 rows of 16 pixels too, 16 rows of 8 are not
+def test_consecutive_blocks_in_one_launch_change_no_bit(widths, batch, n):
+    """From 256 images on the blocks of a stage that keep the resolution are one launch; against a launch per convolution
+    ("conv_block" 0): the same matrix instructions on the same operands, the same bits."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_block={setting} widths={widths} n={n} B={batch}", flush=True)
+            ctx.set_option("conv_block", setting)
+            ctx.grad(model, Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append((Gd, loss))
+    for o in out[1:]:
+        assert torch.equal(o[1], out[0][1]), "loss differs"
+        assert torch.equal(o[0], out[0][0]), "gradient differs"
+
+
 @pytest.mark.parametrize("widths,batch,n", [
     ((1, 28, 28, 16, 1, 10), 3, 2),   # 28 / 14 / 7 pixels stored as 32 / 16 / 8
     ((3, 13, 21, 16, 1, 10), 3, 2),   # rectangular, odd on every stage

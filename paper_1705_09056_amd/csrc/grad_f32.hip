@@ -582,18 +582,19 @@ dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
 // The workgroup has all logits of its samples, so the softmax cross-entropy follows at once: dz = (softmax - onehot) / B and the
 // sum of its samples' losses (class_grad_kernel adds them up).  A launch of its own for that, one workgroup per worker, took 7.8 us.
 // 16 workers x 128 samples x 3072 -> 10, a step on a ring: 36.8 -> 27.9 us with these two launches in the place of three.
-// grid (ceil(B / 16), n), block 64 NW; I >= 4, rows at any alignment.
-template <int NP, int NO, int NW>
+// S: samples of a workgroup, 16 or, where those leave half of the CUs idle, 8 (26.8 us).
+// grid (ceil(B / S), n), block 64 NW; I >= 4, rows at any alignment.
+template <int NP, int NO, int NW, int S>
 __global__ void __launch_bounds__(64 * NW)
 class_fwd_kernel(const float *__restrict__ act, const float *__restrict__ X, i64 ld, i64 woff, i64 boff, int B, int I,
                  int O, const int *__restrict__ labels, float *__restrict__ dz, float *__restrict__ lsum)
 {
     __shared__ float red[NW][NO * 256];
     __shared__ float ls[16];
-    const int w = blockIdx.y, b0 = blockIdx.x * 16;
+    const int w = blockIdx.y, b0 = blockIdx.x * S;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
-    const float *a = act + ((i64)w * B + min(b0 + l16, B - 1)) * I;
+    const float *a = act + ((i64)w * B + min(b0 + l16 % S, B - 1)) * I;
     const float *x[NO];
 #pragma unroll
     for (int t = 0; t < NO; ++t) x[t] = X + (i64)w * ld + woff + (i64)min(16 * t + l16, O - 1) * I;
@@ -642,7 +643,7 @@ class_fwd_kernel(const float *__restrict__ act, const float *__restrict__ X, i64
         for (int v = 0; v < 4; ++v) red[wave][((4 * g4 + v) * NO + t) * 16 + l16] = acc[t][v];   // sample 4 g4 + v, output 16 t + l16
     __syncthreads();
     // 16 lanes per sample, NO outputs each
-    if (threadIdx.x < 256) {
+    if (threadIdx.x < 16 * S) {
         const int r = threadIdx.x >> 4, b = b0 + r, o0 = threadIdx.x & 15;
         float z[NO], mx = -INFINITY;
 #pragma unroll
@@ -679,7 +680,7 @@ class_fwd_kernel(const float *__restrict__ act, const float *__restrict__ X, i64
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int r = 0; r < 16; ++r) s += ls[r];
+        for (int r = 0; r < S; ++r) s += ls[r];
         lsum[(i64)w * gridDim.x + blockIdx.x] = (float)s;
     }
 }
@@ -768,25 +769,30 @@ class_grad_kernel(const float *__restrict__ act, const float *__restrict__ dz, c
 
 // Whether those two take a class layer, and their launches.
 bool class_layer_ok(int n, int B, int I, int O) { return O <= 32 && I >= 4 && n <= 65535; }
-int class_parts(int B) { return (B + 15) / 16; }
+// Samples per workgroup: 8 (the instruction's other eight rows repeat them) where 16 would leave half of the CUs idle
+int class_samples(int n, int B) { return (i64)n * ((B + 15) / 16) <= 128 ? 8 : 16; }
+int class_parts(int n, int B) { return (B + class_samples(n, B) - 1) / class_samples(n, B); }
 
 dpsgd_status class_forward(hipStream_t s, int n, const float *act, const float *X, i64 ld, i64 woff, i64 boff, int B, int I, int O,
                            const int *labels, float *dz, float *lsum)
 {
-    const dim3 grid((unsigned)class_parts(B), (unsigned)n);
+    const dim3 grid((unsigned)class_parts(n, B), (unsigned)n);
+    const bool eight = class_samples(n, B) == 8;
     const int pieces = (I + 63) / 64;
     auto launch = [&](auto k, int waves) {
         hipLaunchKernelGGL(k, grid, dim3(64 * waves), 0, s, act, X, ld, woff, boff, B, I, O, labels, dz, lsum);
     };
+#define DPSGD_CLASS(NP, NO, NW) (eight ? launch(class_fwd_kernel<NP, NO, NW, 8>, NW) : launch(class_fwd_kernel<NP, NO, NW, 16>, NW))
     if (O <= 16) {
-        if (pieces <= 4) launch(class_fwd_kernel<1, 1, 4>, 4);
-        else if (pieces <= 16) launch(class_fwd_kernel<1, 1, 16>, 16);
-        else if (pieces <= 32) launch(class_fwd_kernel<2, 1, 16>, 16);
-        else launch(class_fwd_kernel<3, 1, 16>, 16);
+        if (pieces <= 4) DPSGD_CLASS(1, 1, 4);
+        else if (pieces <= 16) DPSGD_CLASS(1, 1, 16);
+        else if (pieces <= 32) DPSGD_CLASS(2, 1, 16);
+        else DPSGD_CLASS(3, 1, 16);
     } else {
-        if (pieces <= 4) launch(class_fwd_kernel<1, 2, 4>, 4);
-        else launch(class_fwd_kernel<1, 2, 16>, 16);
+        if (pieces <= 4) DPSGD_CLASS(1, 2, 4);
+        else DPSGD_CLASS(1, 2, 16);
     }
+#undef DPSGD_CLASS
     return hip_status(hipGetLastError());
 }
 
@@ -795,9 +801,9 @@ dpsgd_status class_gradient(hipStream_t s, int n, const float *act, const float 
 {
     const dim3 grid((unsigned)((I + 63) / 64 + 1), (unsigned)n);
     if (O <= 16)
-        hipLaunchKernelGGL((class_grad_kernel<1, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(B), B, I, O, G, ld, woff, boff, loss);
+        hipLaunchKernelGGL((class_grad_kernel<1, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(n, B), B, I, O, G, ld, woff, boff, loss);
     else
-        hipLaunchKernelGGL((class_grad_kernel<2, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(B), B, I, O, G, ld, woff, boff, loss);
+        hipLaunchKernelGGL((class_grad_kernel<2, 4>), grid, dim3(256), 0, s, act, dz, lsum, class_parts(n, B), B, I, O, G, ld, woff, boff, loss);
     return hip_status(hipGetLastError());
 }
 
@@ -976,7 +982,7 @@ size_t f32_workspace_bytes(const dpsgd_ctx *ctx, const dpsgd_model_desc &m)
         floats += n * B * (size_t)m.widths[l];
         if ((size_t)m.widths[l] > widest) widest = (size_t)m.widths[l];
     }
-    floats += 2 * n * B * widest + n * ((B + 15) / 16);
+    floats += 2 * n * B * widest + n * ((B + 7) / 8);
     return floats * sizeof(float) + 256;
 }
 
@@ -1021,7 +1027,7 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
     }
     float *dz = ws, *dz2 = ws + (i64)n * B * widest;
 
-    float *lsum = dz2 + (i64)n * B * widest;   // sums of the samples' losses, one per 16 samples
+    float *lsum = dz2 + (i64)n * B * widest;   // sums of the samples' losses, one per workgroup of class_fwd_kernel
     const bool fused = class_layer_ok(n, B, m.widths[L - 1], m.widths[L]);
 
     dpsgd_status st;

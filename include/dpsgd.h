@@ -181,8 +181,8 @@ dpsgd_status dpsgd_set_gamma(dpsgd_ctx *ctx, float gamma);
  * pixels): both convolutions of
  * the block in one launch, the activation between them kept in LDS for the second one; from 256 images on all
  * consecutive blocks of a stage that keep the resolution in one launch; 0: a launch per convolution.  Same bits),
- * "conv_pad" (default 1: CNN stages of at most 64 channels and 64 pixels per row (more than 32 channels: 32 pixels) whose
- * extents the matrix kernels do not take - other than 16 / 32 / 64 channels, 8 / 16 / 32 / 64 pixels per row and a multiple
+ * "conv_pad" (default 1: CNN stages of at most 128 channels and 64 pixels per row (more than 32 channels: 32 pixels, more than
+ * 64: 16) whose extents the matrix kernels do not take - other than 16 / 32 / 64 / 128 channels, 8 / 16 / 32 / 64 pixels per row and a multiple
  * of 8 rows - are kept in the workspace rounded up to such extents, zeros beyond the real ones; 0: in their real extents,
  * which leaves them to kernels that may be an order of magnitude slower.  Results agree to fp32 rounding of the sums.  Where
  * the device cannot hold the larger workspace at the first call of a model, that model runs as with 0: set 0 where results

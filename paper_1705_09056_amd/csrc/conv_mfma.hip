@@ -1,5 +1,5 @@
 // 3x3 convolutions of the CNN workload as implicit GEMMs on bf16 MFMA (gfx950), and their
-// dispatch: MFMA kernels for tensors stored with 16/32/64 channels, rows of 8/16/32/64 pixels and a
+// dispatch: MFMA kernels for tensors stored with 16/32/64/128 channels, rows of 8/16/32/64 pixels and a
 // multiple of 8 rows (networks of other extents are stored rounded up to that, zeros beyond the real
 // extents: stored_stage in grad_resnet.hip), the shape-generic kernels otherwise.
 //
@@ -31,13 +31,15 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int ksteps(int ci) { return (9 * ci + 31) / 32; }
-// waves of a workgroup that split the output channels: as few as keep <= 18 weight fragments per lane
+// waves of a workgroup that split the output channels: as few as keep <= 18 weight fragments per lane.  With 128 channels on
+// either side four waves still have more: they fetch a fragment where it is used (weights_stream).
 constexpr int wave_cols(int ci, int co)
 {
     int wc = 1;
-    while (ksteps(ci) * (co / 16) / wc > 18) wc *= 2;
+    while (wc < 4 && ksteps(ci) * (co / 16) / wc > 18) wc *= 2;
     return wc;
 }
+constexpr bool weights_stream(int ci, int co) { return ksteps(ci) * (co / 16) / wave_cols(ci, co) > 18; }
 
 // ------------------------------------------------------------------------- weight packing
 // wpack[w][s][t][lane][j] = Weff[o = 16 t + lane%16][c][tap], contraction index 32 s + 8 (lane/16) + j
@@ -62,10 +64,11 @@ struct PackTable {
 // consecutive floats (forward: the 16 rows W[o][.][.], one run; data gradient: for every c_out the 16 x 9 floats
 // W[c_out][ci0 .. ci0+15][.]): they are read coalesced, rounded to bf16 into LDS, and the operand is composed from
 // LDS and written as 16-byte units.
-constexpr int kPackLds = 64 * 16 * 9;   // bf16 elements: 16 outputs x 64 contraction channels x 9 taps
-
+// MAXC: the most real channels of a job on either side, 64 or 128.
+template <int MAXC>
 __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restrict__ X, i64 ld, PackTable tbl)
 {
+    constexpr int kPackLds = MAXC * 16 * 9;   // bf16 elements: 16 outputs x MAXC contraction channels x 9 taps
     __shared__ bf16_t tile[kPackLds];
     // Workgroups are dealt to the 8 XCDs round-robin by linear id and every XCD has its own L2: with n a multiple of 8
     // the ids are renumbered so that one XCD packs all tiles of a worker, and the weights, which the forward and the
@@ -91,18 +94,18 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
     // rows x len floats, row r at Wg[base + r * row9]; in LDS row r at tile[r * len]
     int rows, len, base;
     if (!jb.dgrad) {   // outputs are c_out 16 t .. 16 t + 15: their rows are adjacent
-        rows = jb.Co - 16 * t < 16 ? jb.Co - 16 * t : 16;
+        rows = max(0, min(16, jb.Co - 16 * t));   // (none of a tile beyond the real channels)
         len = row9;
         base = 16 * t * row9;
     } else {           // outputs are c_in 16 t .. 16 t + 15: 16 x 9 floats of every c_out row
         rows = jb.Co;
-        len = (jb.Ci - 16 * t < 16 ? jb.Ci - 16 * t : 16) * 9;
+        len = max(0, min(16, jb.Ci - 16 * t)) * 9;
         base = 16 * t * 9;
     }
     // Four floats a load at any alignment, up to nine loads of a thread in flight (a tile has at most 9216 floats; one at a time
     // this launch waited for its loads: 112 workers of the 16-channel network, 3 blocks 78 -> 53 us, 16 workers, 2 blocks 20 -> 13)
     constexpr int U = kPackLds / 4 / 256;
-    const int quads = (len + 3) / 4, total = jb.dgrad ? rows * quads : (rows * len + 3) / 4;
+    const int quads = max(1, (len + 3) / 4), total = jb.dgrad ? (len ? rows * quads : 0) : (rows * len + 3) / 4;
     f32x4 v[U];
     int at[U];
 #pragma unroll
@@ -118,7 +121,7 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
 #pragma unroll
             for (int i = 0; i < 4; ++i) tile[at[u] + i] = f2bf(v[u][i]);
     __syncthreads();
-    const int lg = 31 - __builtin_clz(jb.CI);   // CI is 8, 16, 32 or 64
+    const int lg = 31 - __builtin_clz(jb.CI);   // CI is 8, 16, 32, 64 or 128
     const int groups = jb.KS * 64;   // 16-byte units of this tile
     bf16_t *dst = jb.dst + (i64)w * (jb.KS * NT * 512);
     for (int u = tid; u < groups; u += 256) {
@@ -281,9 +284,10 @@ __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
     }
 
     // this wave's weight fragments
-    bf16x8 wf[KS][NTW];
-    {
-        const bf16_t *wp_ = a.wpack + (i64)w * (KS * NT * 512) + lane * 8;
+    constexpr bool STREAM = weights_stream(CI, CO);
+    bf16x8 wf[STREAM ? 1 : KS][NTW];
+    const bf16_t *const wp_ = a.wpack + (i64)w * (KS * NT * 512) + lane * 8;
+    if constexpr (!STREAM) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -375,12 +379,15 @@ __global__ void __launch_bounds__(256) conv3x3_mfma_kernel(ConvMfmaArgs a)
             for (int t = 0; t < NTW; ++t) acc[tt][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
+            if constexpr (STREAM)
+#pragma unroll
+                for (int t = 0; t < NTW; ++t) wf[0][t] = *reinterpret_cast<const bf16x8 *>(wp_ + (s * NT + wc * NTW + t) * 512);
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 const bf16x8 av = *reinterpret_cast<const bf16x8 *>(pa[tt] + koff[s]);
 #pragma unroll
                 for (int t = 0; t < NTW; ++t)
-                    acc[tt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, wf[s][t], acc[tt][t], 0, 0, 0);
+                    acc[tt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, wf[STREAM ? 0 : s][t], acc[tt][t], 0, 0, 0);
             }
         }
 #pragma unroll
@@ -724,6 +731,7 @@ __global__ void __launch_bounds__(256, C == 16 ? 7 : 1) conv_block_fwd_kernel(Co
 }
 
 bool pow2_channels(int c) { return c == 16 || c == 32 || c == 64; }
+bool matrix_channels(int c) { return pow2_channels(c) || c == 128; }
 int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 
 // ----------------------------------------------------------------------- weight gradient
@@ -738,9 +746,10 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 // wgrad_reduce_kernel adds in a fixed order.
 struct WgradMfmaArgs {
     const bf16_t *inT;     // [n*B][CIs][H][W]
-    const bf16_t *doutT;   // [n*B][CO][Ho][Wo]
-    int H, W, Ho, Wo, B, CIs, splits;
-    float *part;           // [n][splits][(CO/16)*(CI/16)*9*256 + 1], accumulator order
+    const bf16_t *doutT;   // [n*B][COs][Ho][Wo]
+    int H, W, Ho, Wo, B, CIs, COs, splits;
+    int ci_blocks, ci_tiles, psz;   // blocks of CI input channels, tiles of 16 of them, floats of a partial sum
+    float *part;           // [n][splits][psz]: accumulator order, then a sum of the deltas per block of CO output channels
 };
 
 // 16-byte units of a band's source rows a thread holds while they are in flight (8-row bands: 10 rows at stride 1,
@@ -769,6 +778,8 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t *band = reinterpret_cast<bf16_t *>(smem);   // [CI] planes of CP elements, each [ROWS][PLANES][WPAD]
     const int sp = blockIdx.x, w = blockIdx.y;
+    // (128 channels on either side: a workgroup forms one block of CO x CI of them)
+    const int cob = blockIdx.z / a.ci_blocks, cib = blockIdx.z % a.ci_blocks, co0 = cob * CO, ci0 = cib * CI;
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, th = tid >> 8;
     const int mi = wave % WM, kq = wave / WM;   // output-channel tile, share of the k-steps
     const int t0 = th * NTI;                    // first input-channel tile of this wave
@@ -780,8 +791,8 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
     // channel pitch = 8 elements (16 bytes) past a multiple of 256 bytes: the 16 lanes of an operand read
     // (16 channels, 16 bytes each) then fall into 16 different groups of 4 banks
     const int CP = wgrad_channel_pitch(ROWS * PLANES * WPAD);
-    // a partial result in accumulator order: [co tile][ci tile][tap][lane][4] floats, then the bias sum
-    constexpr int psz = (CO / 16) * (CI / 16) * 9 * 256 + 1;
+    // a partial result in accumulator order: [co tile][ci tile][tap][lane][4] floats, then the bias sums
+    const int psz = a.psz;
 
     f32x4 acc[NTI][9];
 #pragma unroll
@@ -819,8 +830,8 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
             const int x8 = u % x8n, r = (u / x8n) % ROWS, ci = u / (x8n * ROWS);
             const int iy = y0 * STRIDE - 1 + r;
             u32x4 v = {0u, 0u, 0u, 0u};
-            if (u < chunks && ci < a.CIs && iy >= 0 && iy < a.H)
-                v = *reinterpret_cast<const u32x4 *>(a.inT + ((img * a.CIs + ci) * a.H + iy) * a.W + x8 * 8);
+            if (u < chunks && ci0 + ci < a.CIs && iy >= 0 && iy < a.H)
+                v = *reinterpret_cast<const u32x4 *>(a.inT + ((img * a.CIs + ci0 + ci) * a.H + iy) * a.W + x8 * 8);
             stg[q] = v;
         }
     };
@@ -833,7 +844,7 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
         const i64 img = (i64)w * a.B + sp + (j / bands_per_img) * a.splits;
         const int y0 = (j % bands_per_img) * RB;
         // this lane's 8 delta pixels of k-step ks: pixels 32 ks + 8 g .. + 7 of the band (rows are contiguous)
-        const bf16_t *dband = a.doutT + ((img * CO + mi * 16 + n16) * a.Ho + y0) * a.Wo + 8 * g;
+        const bf16_t *dband = a.doutT + ((img * a.COs + co0 + mi * 16 + n16) * a.Ho + y0) * a.Wo + 8 * g;
 #pragma unroll
         for (int e = 0; e < kWgradDeltaAhead; ++e) {
             dv[e] = (u32x4){0u, 0u, 0u, 0u};
@@ -952,13 +963,13 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
         for (int t = 0; t < NTI; ++t)
 #pragma unroll
             for (int k = 0; k < 9; ++k)
-                *reinterpret_cast<f32x4 *>(out + (((mi * (CI / 16) + t0 + t) * 9 + k) * 64 + lane) * 4) = acc[t][k];
+                *reinterpret_cast<f32x4 *>(out + ((((co0 / 16 + mi) * a.ci_tiles + ci0 / 16 + t0 + t) * 9 + k) * 64 + lane) * 4) = acc[t][k];
     }
     // bias: sum of every delta element this workgroup saw
     for (int off = 32; off > 0; off >>= 1) bsum += __shfl_down(bsum, off, 64);
     if (lane == 0 && th == 0) red[wave] = bsum;
     __syncthreads();
-    if (tid == 0) out[psz - 1] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0 && cib == 0) out[a.ci_tiles * (a.COs / 16) * 9 * 256 + cob] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // G[w_off + ...] = sum over splits of the partials (ascending split), G[b_off] = sum of the bias partials, for every
@@ -981,7 +992,8 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
     if (T == jb.tiles) {
         if (tid == 0) {
             float s = 0.f;
-            for (int k = 0; k < splits; ++k) s += p[(i64)k * psz + psz - 1];
+            for (int k = 0; k < splits; ++k)
+                for (int b = jb.tiles * 9 * 256; b < psz; ++b) s += p[(i64)k * psz + b];
             G[(i64)w * ld + jb.b_off] = s;
         }
         return;
@@ -1024,6 +1036,20 @@ int wgrad_splits(int n, int B, int co, int stride)
     return B < m ? B : m;
 }
 
+// The channels a workgroup of the weight-gradient kernel takes: all (the stem's rounded up), or blocks where there are 128
+struct WgradBlock { int ci, co; };
+WgradBlock wgrad_block(const ConvDesc &c)
+{
+    if (c.Cos == 128) return c.stride == 1 ? WgradBlock{64, 64} : WgradBlock{32, 64};
+    return {(c.Cis + 15) / 16 * 16, c.Cos};
+}
+int wgrad_partial_floats(const ConvDesc &c)
+{
+    const WgradBlock b = wgrad_block(c);
+    const int cip = (c.Cis + 15) / 16 * 16;
+    return c.Cos * cip * 9 + c.Cos / b.co;
+}
+
 size_t wgrad_lds_bytes(int ci, int stride, int rb, int Wo)
 {
     return (size_t)ci * wgrad_channel_pitch(((rb - 1) * stride + 3) * stride * (Wo + 16)) * sizeof(bf16_t);
@@ -1035,8 +1061,8 @@ size_t wgrad_lds_bytes(int ci, int stride, int rb, int Wo)
 // or 4 where the source rows of 8 do not fit (rows of 64 pixels at 16 channels, of 32 at 32 channels); 0: none fits.
 int wgrad_band_rows(const ConvDesc &c)
 {
-    const int cip = (c.Cis + 15) / 16 * 16;
-    const int threads = 256 * wgrad_wave_groups(cip, c.Cos);
+    const int cip = wgrad_block(c).ci;
+    const int threads = 256 * wgrad_wave_groups(cip, wgrad_block(c).co);
     for (int rb = (c.stride == 1 && cip >= 32) ? 16 : 8; rb >= 4; rb >>= 1)
         if (c.Hos % rb == 0 && (rb * c.Wos) % 32 == 0 &&
             cip * ((rb - 1) * c.stride + 3) * (c.Wis / 8) <= wgrad_stage(c.stride, rb) * threads &&
@@ -1051,13 +1077,13 @@ bool halves(const ConvDesc &c) { return (c.Wis == 2 * c.Wos || (c.Wis == 8 && c.
 bool wgrad_mfma_ok(const ConvDesc &c)
 {
     const int cip = (c.Cis + 15) / 16 * 16;
-    if (!pow2_channels(c.Cos) || !pow2_channels(cip)) return false;
+    if (!matrix_channels(c.Cos) || !matrix_channels(cip)) return false;
     if (c.Hos % 8 || c.Wos % 8 || c.Wis % 8 || c.Wis > 64) return false;
     if (wgrad_band_rows(c) == 0) return false;
     if (c.stride == 1) return cip == c.Cos || (cip == 16 && c.Cos == 32);
     // (8 channels into 16, as a base of 4 or 8 has them in its real extents, are not the 16 into 32 they would round up to:
     // that kernel would read the deltas of 32 channels and write twice the partial sums there is room for)
-    return c.stride == 2 && pow2_channels(c.Cis) && c.Cos == 2 * c.Cis && halves(c);
+    return c.stride == 2 && pow2_channels(c.Cis) && c.Cos == 2 * c.Cis && halves(c);   // (up to 64 into 128)
 }
 
 template <int CI, int CO, int STRIDE>
@@ -1069,15 +1095,14 @@ dpsgd_status launch_wgrad(dpsgd_ctx *ctx, const ConvDesc &c, const WgradMfmaArgs
     const size_t red = (size_t)(WK - 1) * WM * NTI * 9 * 256 * sizeof(float);
     if (red > shm) shm = red;
     if (shm < 64) shm = 64;
-    const dim3 grid((unsigned)a.splits, (unsigned)ctx->n), block(256 * WT);
+    const dim3 grid((unsigned)a.splits, (unsigned)ctx->n, (unsigned)(a.ci_blocks * (c.Cos / CO))), block(256 * WT);
     if constexpr (STRIDE == 1 && CI >= 32) {
         if (rb == 16) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 16>), grid, block, shm, ctx->stream, a);
     }
     if (rb == 8) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 8>), grid, block, shm, ctx->stream, a);
     if (rb == 4) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 4>), grid, block, shm, ctx->stream, a);
-    constexpr int tiles = (CO / 16) * (CI / 16), psz = tiles * 9 * 256 + 1;
-    job->part = a.part; job->w_off = c.w_off; job->b_off = c.b_off; job->splits = a.splits; job->psz = psz;
-    job->tiles = tiles; job->ci_tiles = CI / 16; job->CIr = c.Ci; job->COr = c.Co; job->block0 = 0;
+    job->part = a.part; job->w_off = c.w_off; job->b_off = c.b_off; job->splits = a.splits; job->psz = a.psz;
+    job->tiles = (c.Cos / 16) * a.ci_tiles; job->ci_tiles = a.ci_tiles; job->CIr = c.Ci; job->COr = c.Co; job->block0 = 0;
     return hip_status(hipGetLastError());
 }
 
@@ -1095,17 +1120,17 @@ bool stem_like(const ConvDesc &c) { return c.Ci <= 8 && c.Cis == c.Ci && (c.Cos 
 bool fwd_mfma_ok(const ConvDesc &c)
 {
     if (stem_like(c)) return tile_ok(c.Hos, c.Wos, 1, 8);
-    if (!pow2_channels(c.Cis) || !pow2_channels(c.Cos) || (c.Wis % 8) != 0) return false;   // source rows in 16-byte units
+    if (!matrix_channels(c.Cis) || !matrix_channels(c.Cos) || (c.Wis % 8) != 0) return false;   // source rows in 16-byte units
     if (c.stride == 1) return c.Cis == c.Cos && tile_ok(c.Hos, c.Wos, 1, c.Cis);
-    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c) && tile_ok(c.Hos, c.Wos, 2, c.Cis);
+    return c.stride == 2 && c.Cos == 2 * c.Cis && halves(c) && tile_ok(c.Hos, c.Wos, 2, c.Cis);
 }
 
 bool dgrad_mfma_ok(const ConvDesc &c)
 {
     if (stem_like(c)) return false;
-    if (!pow2_channels(c.Cis) || !pow2_channels(c.Cos) || (c.Wos % 8) != 0) return false;
+    if (!matrix_channels(c.Cis) || !matrix_channels(c.Cos) || (c.Wos % 8) != 0) return false;
     if (c.stride == 1) return c.Cis == c.Cos && tile_ok(c.His, c.Wis, 1, c.Cos);
-    return c.stride == 2 && c.Cos == 2 * c.Cis && c.Cis <= 32 && halves(c) && tile_ok(c.His, c.Wis, 1, c.Cos);
+    return c.stride == 2 && c.Cos == 2 * c.Cis && halves(c) && tile_ok(c.His, c.Wis, 1, c.Cos);
 }
 
 // LDS of a workgroup that owns th output rows: the source patch and (forward) the bands' sign bitmap
@@ -1211,38 +1236,40 @@ size_t conv_pack_bytes(const ConvDesc &c, bool dgrad)
 size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
     if (!wgrad_mfma_ok(c)) return 0;
-    const size_t cip = (size_t)(c.Cis + 15) / 16 * 16;   // partials are stored per 16 x 16 tile of (c_out, padded c_in)
     int splits = wgrad_splits(ctx->n, B, c.Cos, c.stride);
     const int m = conv_image_splits(ctx->n, B, 256);   // (whichever kernel takes the convolution)
     splits = m > splits ? m : splits;
-    return (size_t)splits * ((size_t)c.Cos * cip * 9 + 1) * sizeof(float);
+    return (size_t)splits * (size_t)wgrad_partial_floats(c) * sizeof(float);
 }
 
 dpsgd_status conv_pack_weights(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, const float *X,
                                const std::vector<bf16_t *> &wpack_f, const std::vector<bf16_t *> &wpack_d)
 {
-    PackTable tbl{};
-    int blocks = 0;
-    auto flush = [&]() {
-        if (tbl.njobs > 0)
-            hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)blocks, (unsigned)ctx->n), dim3(256), 0, ctx->stream, X,
-                               ctx->ld, tbl);
-        tbl.njobs = 0;
-        blocks = 0;
+    struct Pending { PackTable tbl{}; int blocks = 0; } narrow, wide;   // (more than 64 real channels: twice the LDS)
+    auto flush = [&](Pending &p) {
+        if (p.tbl.njobs > 0) {
+            const dim3 grid((unsigned)p.blocks, (unsigned)ctx->n);
+            if (&p == &wide) hipLaunchKernelGGL(pack_weights_kernel<128>, grid, dim3(256), 0, ctx->stream, X, ctx->ld, p.tbl);
+            else hipLaunchKernelGGL(pack_weights_kernel<64>, grid, dim3(256), 0, ctx->stream, X, ctx->ld, p.tbl);
+        }
+        p.tbl.njobs = 0;
+        p.blocks = 0;
     };
     auto add = [&](const ConvDesc &c, int CI, int CO, bool dgrad, bf16_t *dst) {
-        if (tbl.njobs == kMaxPackJobs) flush();
-        PackJob &jb = tbl.job[tbl.njobs++];
+        Pending &p = c.Ci > 64 || c.Co > 64 ? wide : narrow;
+        if (p.tbl.njobs == kMaxPackJobs) flush(p);
+        PackJob &jb = p.tbl.job[p.tbl.njobs++];
         jb.w_off = c.w_off; jb.dst = dst; jb.Ci = c.Ci; jb.Co = c.Co; jb.CI = CI; jb.CO = CO; jb.KS = ksteps(CI);
-        jb.dgrad = dgrad ? 1 : 0; jb.block0 = blocks;
-        blocks += CO / 16;   // one workgroup per tile of 16 outputs
+        jb.dgrad = dgrad ? 1 : 0; jb.block0 = p.blocks;
+        p.blocks += CO / 16;   // one workgroup per tile of 16 outputs
     };
     for (size_t q = 0; q < convs.size(); ++q) {
         const ConvDesc &c = convs[q];
         if (fwd_mfma_ok(c)) add(c, stem_like(c) ? 8 : c.Cis, c.Cos, false, wpack_f[q]);
         if (!stem_like(c) && dgrad_mfma_ok(c)) add(c, c.Cos, c.Cis, true, wpack_d[q]);
     }
-    flush();
+    flush(narrow);
+    flush(wide);
     return hip_status(hipGetLastError());
 }
 
@@ -1261,9 +1288,11 @@ dpsgd_status conv_forward(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, c
     if (c.stride == 1) {
         if (c.Cis == 16) return launch_conv<16, 16, 1, 1, false>(ctx, a, c.padded_out());
         if (c.Cis == 32) return launch_conv<32, 32, 1, 1, false>(ctx, a, c.padded_out());
+        if (c.Cis == 128) return launch_conv<128, 128, 1, 1, false>(ctx, a, c.padded_out());
         return launch_conv<64, 64, 1, 1, false>(ctx, a, c.padded_out());
     }
     if (c.Cis == 16) return launch_conv<16, 32, 2, 1, false>(ctx, a, c.padded_out());
+    if (c.Cis == 64) return launch_conv<64, 128, 2, 1, false>(ctx, a, c.padded_out());
     return launch_conv<32, 64, 2, 1, false>(ctx, a, c.padded_out());
 }
 
@@ -1331,10 +1360,12 @@ dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dou
     if (c.stride == 1) {
         if (c.Cis == 16) return launch_conv<16, 16, 1, 1, true>(ctx, a, false);
         if (c.Cis == 32) return launch_conv<32, 32, 1, 1, true>(ctx, a, false);
+        if (c.Cis == 128) return launch_conv<128, 128, 1, 1, true>(ctx, a, false);
         return launch_conv<64, 64, 1, 1, true>(ctx, a, false);
     }
     const bool padded = c.Wis < 2 * c.Wos;   // (rows of 8 from rows of 8)
     if (c.Cis == 16) return launch_conv<32, 16, 1, 2, true>(ctx, a, padded);
+    if (c.Cis == 64) return launch_conv<128, 64, 1, 2, true>(ctx, a, padded);
     return launch_conv<64, 32, 1, 2, true>(ctx, a, padded);
 }
 
@@ -1343,13 +1374,14 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
 {
     if (!wgrad_mfma_ok(c) || !partials || !pending) return conv_weight_grad_generic(ctx, c, B, in, dout, G);
     WgradMfmaArgs a{};
-    a.inT = in.t; a.doutT = dout.t; a.H = c.His; a.W = c.Wis; a.Ho = c.Hos; a.Wo = c.Wos; a.B = B; a.CIs = c.Cis;
+    a.inT = in.t; a.doutT = dout.t; a.H = c.His; a.W = c.Wis; a.Ho = c.Hos; a.Wo = c.Wos; a.B = B; a.CIs = c.Cis; a.COs = c.Cos;
     a.splits = wgrad_splits(ctx->n, B, c.Cos, c.stride); a.part = partials;
-    const int cip = (c.Cis + 15) / 16 * 16;
+    const int cip = wgrad_block(c).ci, co = wgrad_block(c).co;
+    a.ci_tiles = (c.Cis + 15) / 16; a.ci_blocks = a.ci_tiles * 16 / cip; a.psz = wgrad_partial_floats(c);
     WgradReduceJob job{};
     dpsgd_status st;
     if (c.stride == 1) {
-        if (cip == 16 && c.Cos == 32) st = launch_wgrad<16, 32, 1>(ctx, c, a, &job);
+        if (cip == 16 && co == 32) st = launch_wgrad<16, 32, 1>(ctx, c, a, &job);
         else if (cip == 16) st = launch_wgrad<16, 16, 1>(ctx, c, a, &job);
         else if (cip == 32) st = launch_wgrad<32, 32, 1>(ctx, c, a, &job);
         else st = launch_wgrad<64, 64, 1>(ctx, c, a, &job);

@@ -303,13 +303,14 @@ unsigned blocks_for(i64 total) { return (unsigned)((total + 255) / 256); }
 
 }  // namespace
 
-// Stored extents of a stage's tensors.  The MFMA kernels take 16, 32 or 64 channels, rows of 8, 16, 32 or 64 pixels and
+// Stored extents of a stage's tensors.  The MFMA kernels take 16, 32, 64 or 128 channels, rows of 8, 16, 32 or 64 pixels and
 // a multiple of 8 rows; a stage of other extents is stored rounded up to the next such shape, with zeros beyond its
 // real extents, instead of leaving it to the shape-generic kernels, which are slower by far more than the padding costs:
 // 16 workers x 32 images of 1 x 28 x 28, 16 channels, 2 blocks per stage (stored 32 x 32, 16 x 16 and 8 x 8) take 0.56 ms
 // per iteration instead of 15.4.  Channels double from stage to stage, so a base of up to 16 channels is
-// stored as 16 / 32 / 64, up to 32 as 32 / 64, up to 64 as 64; wider stages and rows of more than 64 pixels keep their
-// real extents.  So do 64 channels with rows of 64 pixels, whose source patch no kernel has the LDS for (4 workers x 16
+// stored as 16 / 32 / 64, up to 32 as 32 / 64 / 128, up to 64 as 64 / 128; wider stages and rows of more than 64 pixels keep
+// their real extents.  (128 channels, rows of up to 16 pixels: 22 workers x 12 images of 28 x 28, base 24, 4.06 ms per iteration
+// with its 96 channels on the shape-generic kernels, 0.57 here.)  So do 64 channels with rows of 64 pixels, whose source patch no kernel has the LDS for (4 workers x 16
 // images of 3 x 40 x 40, base 64: 30.8 ms padded, 27.0 as they are), and a network whose first stage would take more than 16
 // times its memory (tiny images or channels).  32 channels with rows of 64 pixels have a matrix kernel for forward and data
 // gradient but none for the weight gradient, which pays as long as the padding stays below 3.5 times the memory (4 x 8 images
@@ -320,7 +321,7 @@ struct Extent { int C, H, W; };
 Extent stored_stage(int stage, int base, int C, int H, int W)
 {
     const int cs = (base <= 16 ? 16 : base <= 32 ? 32 : 64) << stage;
-    if (cs > 64 || C > cs || W > (cs == 64 ? 32 : 64)) return {C, H, W};
+    if (cs > 128 || C > cs || W > (cs == 128 ? 16 : cs == 64 ? 32 : 64)) return {C, H, W};
     const int ws = W <= 8 ? 8 : W <= 16 ? 16 : W <= 32 ? 32 : 64, hs = (H + 7) / 8 * 8;
     if (cs == 32 && ws == 64 && (i64)cs * hs * ws * 2 > 7 * ((i64)C * H * W)) return {C, H, W};
     return {cs, hs, ws};

@@ -222,7 +222,7 @@ def test_consecutive_blocks_in_one_launch_change_no_bit(widths, batch, n):
     ((3, 24, 9, 16, 1, 10), 2, 8),    # rows of 9, 5 and 3 pixels: the strided convolutions meet rows of 16 / 8 and of 8 / 8
     ((3, 16, 8, 16, 1, 10), 2, 2),    # an exact first stage on padded ones
     ((2, 9, 48, 8, 1, 5), 3, 2),      # 8 / 16 / 32 channels stored as 16 / 32 / 64; rows of 48: 4-row bands of the weight gradient
-    ((3, 20, 20, 24, 1, 10), 3, 2),   # 24 / 48 channels stored as 32 / 64, the 96 of the last stage as they are
+    ((3, 20, 20, 24, 1, 10), 3, 2),   # 24 / 48 / 96 channels stored as 32 / 64 / 128
     ((8, 16, 16, 20, 1, 10), 2, 2),   # the widest image the matrix-kernel stem takes
     ((3, 1, 9, 16, 1, 3), 3, 2),      # one pixel high
     ((2, 9, 34, 30, 1, 4), 2, 2),     # 30 channels stored as 32 x 64 pixels: generic weight gradient between matrix kernels
@@ -322,3 +322,31 @@ def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
             assert np.abs(a - b).max() <= 1e-5 * scale, p.name
         else:
             assert rel_err(b, a) < 1e-5, p.name
+
+
+@pytest.mark.parametrize("widths,batch,n", [((3, 32, 32, 24, 2, 10), 3, 2),     # 96 channels on 8 x 8 pixels stored as 128
+                                            ((3, 16, 16, 32, 1, 10), 5, 3),     # 128 real ones, on 4 x 4 pixels
+                                            ((1, 9, 30, 17, 1, 5), 2, 8),       # 17 / 34 / 68: tiles beyond the real channels
+                                            ((3, 40, 44, 24, 1, 10), 2, 2)])    # rows of 16 pixels: the strided forward stays generic
+def test_128_channels_on_the_matrix_kernels(widths, batch, n):
+    """Stages of up to 128 channels: forward and data gradient fetch their weights where they are used, the weight gradient takes
+    blocks of 64 channels.  Against the oracle, and against the shape-generic kernels ("conv_pad" 0 keeps 96 and 68 channels
+    on them).  With two to five samples one ReLU that a last-bit difference turns moves a layer by up to 1.1e-2 (measured, the
+    shape-generic kernels against the oracle, 3 x 16 x 16 images, 32 channels), so the bars are those of the deep networks."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(cfg.model_kind, widths)
+    grad_case(cfg, synth.padded_stride(d), plain=False, deep=True)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_pad={setting} widths={widths} n={n} B={batch}", flush=True)
+            ctx.set_option("conv_pad", setting)
+            ctx.grad(B.Model(cfg.model_kind, cfg.widths, compute_bf16=True), Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append((from_dev(Gd, d), loss.cpu().numpy()))
+    assert np.array_equal(out[1][0], out[2][0]) and np.array_equal(out[1][1], out[2][1])
+    check_close(out[1][0], out[0][0], DEEP_WHOLE_BAR * TOL, "padded vs real extents", flips=True)
+    assert rel_err(out[1][1], out[0][1]) < 2 * TIGHT

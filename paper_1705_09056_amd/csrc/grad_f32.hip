@@ -214,6 +214,7 @@ struct GemmArgs {
     const float *bias; i64 sBiasw;      // may be null
     const float *mask; i64 sMw, sMm;    // may be null; unit stride along n
     int M, N, K, relu;
+    float *rowsum; i64 sRowsumw;        // weight gradient: where the bias gradient goes (sums of A's rows), or null
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -258,6 +259,34 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
     const int m0 = tile_m * TM, n0 = tile_n * TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
+    if constexpr (!A_KFAST && B_NFAST) {
+        // The last column of workgroups of a weight gradient sums the deltas over the samples: TM outputs, the threads deal the
+        // samples among themselves, add in 64 bits and meet in LDS in order.  A launch of its own took 7.3 us
+        // for 16 workers x 128 samples x 1024 outputs; here it is hidden (18 workers x 784-85-3072-10 x 128 samples, one gradient and
+        // mix: 243 us -> 201 together with the class layer's kernels and the one-launch consensus).
+        if (g.rowsum && tile_n == (int)gridDim.x - 1) {
+            constexpr int P = NT / TM;
+            static_assert(sizeof(lds) >= NT * sizeof(double) && NT % TM == 0, "");
+            double *part_sums = reinterpret_cast<double *>(lds);
+            const int m = m0 + tid % TM, part = tid / TM;
+            const float *a = g.A + (i64)w * g.sAw + min(m, g.M - 1);
+            double s = 0.0;
+            for (int k0 = part; k0 < g.K; k0 += 8 * P) {
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = a[(i64)min(k0 + j * P, g.K - 1) * g.sAk];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s += k0 + j * P < g.K ? (double)v[j] : 0.0;
+            }
+            part_sums[tid] = s;
+            __syncthreads();
+            if (part == 0 && m < g.M) {
+                for (int q = 1; q < P; ++q) s += part_sums[q * TM + tid];
+                g.rowsum[(i64)w * g.sRowsumw + m] = (float)s;
+            }
+            return;
+        }
+    }
     const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
     const float *A = g.A + (i64)w * g.sAw, *Bm = g.B + (i64)w * g.sBw;
 
@@ -405,10 +434,10 @@ template <int WM, int WN, int WK, int KW, bool AHEAD2 = false, bool TINY = false
 dpsgd_status gemm_f32_launch(hipStream_t s, int nworkers, const GemmArgs &g)
 {
     constexpr int TM = 32 * WM, TN = 32 * WN;
-    dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
+    dim3 grid((unsigned)((g.N + TN - 1) / TN) + (g.rowsum ? 1u : 0u), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
     if (grid.y > 65535u || grid.z > 65535u) return DPSGD_EUNSUPPORTED;
     const dim3 block(64 * WM * WN * WK);
-    const bool akf = g.sAk == 1, bnf = g.sBn == 1;   // (B contiguous along k: a forward product, only of less than 4 inputs)
+    const bool akf = g.sAk == 1 && !g.rowsum, bnf = g.sBn == 1;   // (B contiguous along k: a forward product, only of less than 4 inputs)
     if (akf && bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if (bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, false, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if constexpr (TINY) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, false, TINY, AHEAD2>), grid, block, 0, s, g);
@@ -885,20 +914,6 @@ linear_fwd_skinny_kernel(const float *__restrict__ act, const float *__restrict_
     }
 }
 
-// gb[w][o] = sum_b dz[w][b][o]: a wave per output, its lanes stride over the samples (a thread per output walking the
-// samples one after the other was a chain of B dependent loads: 9.5 us for 10 outputs x 128 samples)
-__global__ void __launch_bounds__(256)
-bias_grad_kernel(const float *__restrict__ dz, int B, int O, float *__restrict__ G, i64 ld, i64 boff)
-{
-    const int lane = threadIdx.x & 63;
-    const int o = blockIdx.x * 4 + (threadIdx.x >> 6), w = blockIdx.y;
-    if (o >= O) return;
-    float s = 0.f;
-    for (int b = lane; b < B; b += 64) s += dz[((i64)w * B + b) * O + o];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if (lane == 0) G[(i64)w * ld + boff + o] = s;
-}
-
 __global__ void __launch_bounds__(256) bf16_to_f32_kernel(const uint16_t *__restrict__ in, float *__restrict__ out, i64 count)
 {
     const i64 i = (i64)blockIdx.x * 256 + threadIdx.x;
@@ -938,7 +953,7 @@ softmax_xent_kernel(const float *__restrict__ z, const int *__restrict__ labels,
     }
     if (loss && threadIdx.x == 0) loss[w] = red[0] * invB;
     if (G) {   // the class layer's bias gradient: the worker's dz rows were written by this workgroup, before the barriers
-               // above; a wave per class, lanes stride over the samples (the sums of bias_grad_kernel, bit for bit)
+               // above; a wave per class, lanes stride over the samples
         const int lane = threadIdx.x & 63;
         for (int c = threadIdx.x >> 6; c < C; c += 4) {
             float s = 0.f;
@@ -1073,10 +1088,11 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
             g.B = act[l]; g.sBw = (i64)B * I; g.sBk = I; g.sBn = 1;
             g.C = G + woff[l]; g.sCw = ctx->ld; g.sCm = I;
             g.M = O; g.N = I; g.K = B;
+            if (l < L - 1) {   // (a class layer's came with the softmax launch)
+                g.rowsum = G + boff[l];
+                g.sRowsumw = ctx->ld;
+            }
             if ((st = gemm_f32(s, n, g)) != DPSGD_OK) return st;
-            if (l < L - 1)   // (the class layer's came with the softmax launch)
-                hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((O + 3) / 4), (unsigned)n), dim3(256), 0, s, dz, B, O, G,
-                                   ctx->ld, boff[l]);
         }
         if (l > 0) {   // data gradient through the ReLU: dz_prev = (dz W_l) * [act_l > 0]
             GemmArgs h{};

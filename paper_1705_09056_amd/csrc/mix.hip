@@ -731,22 +731,30 @@ __global__ void __launch_bounds__(256) consensus_stage2_kernel(const double *__r
     if (threadIdx.x == 0) out[0] = (float)(t * inv_n);
 }
 
-// Few partials (up to kSmallCount): both stages in one workgroup, one launch instead of two.
-__global__ void __launch_bounds__(256) consensus_small_kernel(const double *__restrict__ partials, int count, double inv_n,
-                                                               float *__restrict__ out)
+// Up to kSmallCount partials: both stages in one workgroup, one launch instead of two.  Eight loads of a thread in flight; 12 334
+// partials (16 workers x 3.16 million columns) 4.7 us, the two stages 9.8.
+__global__ void __launch_bounds__(1024) consensus_small_kernel(const double *__restrict__ partials, int count, double inv_n,
+                                                                float *__restrict__ out)
 {
-    __shared__ double sh[256];
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 768 < count; i += 1024) {
-        s0 += partials[i];
-        s1 += partials[i + 256];
-        s2 += partials[i + 512];
-        s3 += partials[i + 768];
+    __shared__ double sh[16];
+    double s[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s[k] = 0.0;
+    for (int i = threadIdx.x; i < count; i += 8192) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = partials[min(i + 1024 * k, count - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s[k] += i + 1024 * k < count ? v[k] : 0.0;
     }
-    for (; i < count; i += 256) s0 += partials[i];
-    const double t = block_sum_256((s0 + s1) + (s2 + s3), sh);
-    if (threadIdx.x == 0) out[0] = (float)(t * inv_n);
+    double t = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 16; ++k) t += sh[k];
+        out[0] = (float)(t * inv_n);
+    }
 }
 
 // --------------------------------------------------------------------------- host helpers
@@ -1006,12 +1014,12 @@ dpsgd_status stats_launch(dpsgd_ctx *ctx, const float *X, i64 col0, i64 ncols, f
 }
 
 constexpr int kStage1Blocks = 128;   // the partials buffer keeps this many extra slots at its end
-constexpr i64 kSmallCount = 8192;    // up to this many partials one workgroup sums them in one launch
+constexpr i64 kSmallCount = 32768;   // up to this many partials one workgroup sums them in one launch
 
 dpsgd_status finalize_consensus(dpsgd_ctx *ctx, i64 count, float *consensus)
 {
     if (count <= kSmallCount) {
-        hipLaunchKernelGGL(consensus_small_kernel, dim3(1), dim3(256), 0, ctx->stream, ctx->d_partials, (int)count,
+        hipLaunchKernelGGL(consensus_small_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->d_partials, (int)count,
                            1.0 / (double)ctx->n, consensus);
         return hip_status(hipGetLastError());
     }

@@ -489,3 +489,9 @@ def test_averaging_on_a_second_stream_then_update_equals_mix_step(topo):
     check_close(from_dev(out, d), ref, TOL, "overlapped composition vs oracle")
     check_close(from_dev(out, d), from_dev(direct, d), TOL, "overlapped composition vs dpsgd_mix_step")
     assert float(c_out) == pytest.approx(float(c_direct), rel=1e-5)
+
+
+@pytest.mark.parametrize("d", [64, 256 * 1025, 256 * 8193 + 3, 256 * 32768, 256 * 32768 + 4])
+def test_consensus_of_any_number_of_partial_sums(d):
+    """One workgroup sums up to 32 768 partial sums (of 256 columns each), two launches more."""
+    run_mix(2, d, d, B.Topology.complete(), oracle.complete(2).with_fp32_values(), d % 1000, False, cons=True)

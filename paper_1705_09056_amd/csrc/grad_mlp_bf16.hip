@@ -932,18 +932,19 @@ struct WgradArgs {
                          // 246 us with non-temporal stores, 270 without; rows that share the halves: 232 with, 111 without)
 };
 
-// grid (ceil(K / (32 tiles)), ceil(O / 128), n); wave = 32 rows o, walks `tiles` tiles of 32 columns k.
-// SKINNY (few outputs, e.g. the class layer): grid (ceil(K / 128), ceil(O / 32), n); the four waves
+// Workgroup (bx of ceil(K / (32 tiles)), by of ceil(O / 128)) of worker w; wave = 32 rows o, walks `tiles` tiles of 32 columns k.
+// SKINNY (few outputs, e.g. the class layer): (ceil(K / 128), ceil(O / 32)); the four waves
 // share the 32 rows o and take one tile of 32 columns k each.
 // EIGHT: g.tiles == 8, a loop the compiler knows the length of (12 workers x 64 samples x 784 x 3872: 41 us against 54).
 // LINES: g.whole_lines.
+// The fragments of four steps are requested together, whole groups of 32 rows (the copies are stored in such groups; what lies
+// beyond the last row or column only reaches results that are not stored): guarded loads were waited for one by one.
 template <bool SKINNY, bool EIGHT, bool LINES>
-__global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
+__device__ __forceinline__ void mlp_wgrad_tiles(const WgradArgs &g, int w, int bx, int by)
 {
-    const int w = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    const int o_base = SKINNY ? blockIdx.y * 32 : blockIdx.y * 128 + wave * 32;
+    const int o_base = SKINNY ? by * 32 : by * 128 + wave * 32;
     if (o_base >= g.O) return;
     const int o = o_base + l32;            // row this lane feeds into the A operand
     const bool o_ok = o < g.O;
@@ -952,7 +953,7 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
     const bf16_t *Ap = g.dzt + tfrag_worker(w, g.O, g.Bp) + (i64)(o_base >> 5) * steps * 512 + lane * 8;
     float *Gw = g.G + (i64)w * g.ld + g.woff;
 
-    if (blockIdx.x == 0 && (!SKINNY || wave == 0)) {   // bias gradient: gb[o] = sum_b dZ[b][o]
+    if (bx == 0 && (!SKINNY || wave == 0)) {   // bias gradient: gb[o] = sum_b dZ[b][o]
         float s = 0.f;
         if (o_ok)
             for (int st = 0; st < steps; ++st)
@@ -964,20 +965,27 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
 
     const int tiles = EIGHT ? 8 : g.tiles;
     for (int t = 0; t < (SKINNY ? 1 : EIGHT ? 8 : tiles); ++t) {
-        const int k_base = SKINNY ? blockIdx.x * 128 + wave * 32 : (blockIdx.x * tiles + t) * 32;
+        const int k_base = SKINNY ? bx * 128 + wave * 32 : (bx * tiles + t) * 32;
         if (k_base >= g.K) break;
         const int k = k_base + l32;
-        const bool k_ok = k < g.K;
         const bf16_t *Bp_ = g.at + tfrag_worker(w, g.K, g.Bp) + (i64)(k_base >> 5) * steps * 512 + lane * 8;
         f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        for (int st = 0; st < steps; ++st) {
-            const bf16x8 a = o_ok ? frag(Ap + st * 512) : zero_frag();
-            const bf16x8 b = k_ok ? frag(Bp_ + st * 512) : zero_frag();
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+        int st = 0;
+        for (; st + 4 <= steps; st += 4) {
+            bf16x8 a[4], b[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                a[j] = frag(Ap + (st + j) * 512);
+                b[j] = frag(Bp_ + (st + j) * 512);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[j], acc, 0, 0, 0);
         }
-        if (k_ok) {
+        for (; st < steps; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(Ap + st * 512), frag(Bp_ + st * 512), acc, 0, 0, 0);
+        if (k < g.K) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int orow = o_base + (v >> 2) * 8 + half * 4 + (v & 3);
@@ -988,6 +996,35 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
             }
         }
     }
+}
+
+template <bool SKINNY, bool EIGHT, bool LINES>
+__global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g)
+{
+    mlp_wgrad_tiles<SKINNY, EIGHT, LINES>(g, blockIdx.z, blockIdx.x, blockIdx.y);
+}
+
+// The weight gradients of several layers that would each leave CUs without work, in one launch after the last data gradient
+// (each layer's deltas and activations have buffers of their own).  grid (sum of the layers' workgroups, 1, n).
+constexpr int kMaxWgradJobs = 8;
+struct WgradJobs {
+    WgradArgs g[kMaxWgradJobs];
+    int block0[kMaxWgradJobs], gx[kMaxWgradJobs];
+    int njobs;
+};
+inline int wgrad_job_blocks(const WgradJobs &t)   // workgroups of the jobs so far
+{
+    if (t.njobs == 0) return 0;
+    const WgradArgs &g = t.g[t.njobs - 1];
+    return t.block0[t.njobs - 1] + t.gx[t.njobs - 1] * ((g.O + 127) / 128);
+}
+template <bool LINES>
+__global__ void __launch_bounds__(256) mlp_wgrad_layers_kernel(WgradJobs t)
+{
+    int j = 0;
+    while (j + 1 < t.njobs && (int)blockIdx.x >= t.block0[j + 1]) ++j;
+    const int local = (int)blockIdx.x - t.block0[j], gx = t.gx[j];
+    mlp_wgrad_tiles<false, false, LINES>(t.g[j], blockIdx.z, local % gx, local / gx);
 }
 
 // The weight gradient of minibatches of more than 64 samples, where the kernel above is bound by the operands it pulls
@@ -2582,6 +2619,15 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                            C, ws.dz[cur], ws.dzt[L], loss);
     std::vector<char> fused(L, 0);
     bool bias_below_done = false;
+    WgradJobs jobs_lines{}, jobs_shared{};   // weight gradients that wait for the others of their kind
+    auto flush = [&](WgradJobs &jobs) {
+        if (jobs.njobs == 0 || st != DPSGD_OK) return;
+        const dim3 grid((unsigned)wgrad_job_blocks(jobs), 1, (unsigned)n);
+        if (&jobs == &jobs_lines) hipLaunchKernelGGL(mlp_wgrad_layers_kernel<true>, grid, dim3(256), 0, s, jobs);
+        else hipLaunchKernelGGL(mlp_wgrad_layers_kernel<false>, grid, dim3(256), 0, s, jobs);
+        jobs.njobs = 0;
+        st = hip_status(hipGetLastError());
+    };
     for (int l = L - 1; l >= 0 && st == DPSGD_OK; --l) {
         const int K = m.widths[l], O = m.widths[l + 1];
         fused[l] = fuse && layer_fusable(ctx, K, O, woff[l]);
@@ -2639,8 +2685,13 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                 dim3 wgrid((unsigned)((K + 32 * wa.tiles - 1) / (32 * wa.tiles)), (unsigned)((O + 127) / 128), (unsigned)n);
                 if (wa.tiles == 8 && wa.whole_lines) hipLaunchKernelGGL((mlp_wgrad_kernel<false, true, true>), wgrid, dim3(256), 0, s, wa);
                 else if (wa.tiles == 8) hipLaunchKernelGGL((mlp_wgrad_kernel<false, true, false>), wgrid, dim3(256), 0, s, wa);
-                else if (wa.whole_lines) hipLaunchKernelGGL((mlp_wgrad_kernel<false, false, true>), wgrid, dim3(256), 0, s, wa);
-                else hipLaunchKernelGGL((mlp_wgrad_kernel<false, false, false>), wgrid, dim3(256), 0, s, wa);
+                else {
+                    WgradJobs &jobs = wa.whole_lines ? jobs_lines : jobs_shared;
+                    if (jobs.njobs == kMaxWgradJobs) flush(jobs);
+                    jobs.g[jobs.njobs] = wa;
+                    jobs.block0[jobs.njobs] = wgrad_job_blocks(jobs);
+                    jobs.gx[jobs.njobs++] = (int)wgrid.x;
+                }
             }
         }
         st = hip_status(hipGetLastError());
@@ -2664,6 +2715,8 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             cur ^= 1;
         }
     }
+    flush(jobs_lines);
+    flush(jobs_shared);
     if (st != DPSGD_OK || !fuse) return st;
 
     // ---- Algorithm 1 steps 4-5, in place: fused layers first, then the remaining column ranges

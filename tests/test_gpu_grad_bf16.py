@@ -164,6 +164,15 @@ def test_every_workgroup_finds_its_tile(widths, batch, n):
     grad_case(cfg, ld)
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((70, 40, 33, 130, 10), 20, 3),                                    # part tiles, fewer than four steps of 16 samples
+    ((64, 64, 64, 48, 96, 10), 65, 2),                                 # layers on whole and on shared cache lines, five steps
+    ((40, 36, 48, 33, 34, 64, 35, 40, 48, 37, 41, 10), 16, 2),         # more of them than one launch takes
+])
+def test_weight_gradients_of_several_layers_in_one_launch(widths, batch, n):
+    grad_case(shrink(CONFIGS[2], widths=widths, batch=batch, n=n), synth.model_dim(MODEL_MLP, widths))
+
+
 def test_softmax_regression_bf16():
     cfg = shrink(CONFIGS[1], widths=(3072, 10), batch=128, n=3, bf16=True)
     d = synth.model_dim(MODEL_SOFTMAX, cfg.widths)

@@ -54,20 +54,20 @@ lsq_feature_kernel(const float *__restrict__ A, const float *__restrict__ r, int
                    float *__restrict__ loss)
 {
     constexpr int NW = 8;
-    __shared__ float red[NW][64];
+    __shared__ double red[NW][64];
     const int w = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = blockIdx.x * 64 + lane;
     const float *a = A + (i64)w * B * F + min(c, F - 1), *rw = r + (i64)w * B;
-    float s = 0.f;
+    double s = 0.0;   // (a wave's few terms: no more error than the tree of 64 lanes' fp32 sums)
 #pragma unroll 8
-    for (int b = wave; b < B; b += NW) s = a[(i64)b * F] * rw[b] + s;
+    for (int b = wave; b < B; b += NW) s += (double)a[(i64)b * F] * rw[b];
     red[wave][lane] = s;
     __syncthreads();
     const float invB = 1.0f / (float)B;
     if (wave == 0) {
 #pragma unroll
         for (int q = 1; q < NW; ++q) s += red[q][lane];
-        if (c < F) G[(i64)w * ld + c] = s * invB;
+        if (c < F) G[(i64)w * ld + c] = (float)s * invB;
     }
     if (loss && blockIdx.x == 0 && wave == 1) {
         double t = 0.0;
@@ -103,6 +103,70 @@ lsq_narrow_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__
     }
 }
 
+// The gradient of a worker whose samples fit 96 KB of LDS, one workgroup per worker: one launch instead of two, bound by its
+// round trips.  us per gradient and mix, on a ring, two launches / this: 31 x 31 samples x 300 features 23.2 / 19.7,
+// 31 x 37 x 400 22.7 / 19.9, 16 x 9 x 769 23.1 / 18.9, 16 x 5 x 3000 22.8 / 19.1.  From 512 features on a wave per sample and a
+// thread per feature (16 x 5 x 3000 with 8 lanes per sample and 64 features at a time: 41.9).
+// Rows of samples pitched as in lsq_step_kernel below; sums in fp64.
+constexpr long long kLsqSmallFloats = 24 * 1024;
+__global__ void __launch_bounds__(512)
+lsq_small_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A, const float *__restrict__ y, int B, int F, int P,
+                 float *__restrict__ G, float *__restrict__ loss)
+{
+    constexpr int NW = 8;
+    extern __shared__ __attribute__((aligned(16))) float lsq_lds[];
+    __shared__ double red[NW][64];
+    const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float *As = lsq_lds, *xs = As + B * P, *r = xs + F;
+    const float *a = A + (i64)w * B * F;
+    const int F4 = (F + 3) / 4;
+#pragma unroll 4
+    for (int q = tid; q < B * F4; q += 512) {
+        const int row = q / F4, k = q % F4 * 4;
+        const f32x4_a4 t = *reinterpret_cast<const f32x4_a4 *>(a + (i64)row * F + min(k, F - 4));
+        *reinterpret_cast<f32x4 *>(As + row * P + k) = mend4((f32x4){t.x, t.y, t.z, t.w}, F - k);
+    }
+    for (int c = tid; c < F; c += 512) xs[c] = X[(i64)w * ld + c];
+    __syncthreads();
+    const int wide = F >= 512, per = wide ? 64 : 8;   // lanes that share a sample's product
+    for (int row = tid / per; row < (wide ? B : (B + 7) / 8 * 8); row += 512 / per) {   // (uniform over a wave)
+        const int rc = min(row, B - 1);
+        double s = 0.0;
+#pragma unroll 4
+        for (int c = tid % per; c < F; c += per) s += (double)As[rc * P + c] * xs[c];
+        for (int off = per / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (tid % per == 0 && row < B) r[row] = (float)(s - y[(i64)w * B + row]);
+    }
+    __syncthreads();
+    const float invB = 1.0f / (float)B;
+    for (int c = tid; wide && c < F; c += 512) {   // a thread per feature
+        double s = 0.0;
+#pragma unroll 4
+        for (int b = 0; b < B; ++b) s += (double)As[b * P + c] * r[b];
+        G[(i64)w * ld + c] = (float)s * invB;
+    }
+    for (int c0 = 0; !wide && c0 < F; c0 += 64) {
+        const int c = c0 + lane, cc = min(c, F - 1);
+        double s = 0.0;
+#pragma unroll 4
+        for (int b = wave; b < B; b += NW) s += (double)As[b * P + cc] * r[b];
+        if (c0) __syncthreads();   // (the sums of the features before are read)
+        red[wave][lane] = s;
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int q = 1; q < NW; ++q) s += red[q][lane];
+            if (c < F) G[(i64)w * ld + c] = (float)s * invB;
+        }
+    }
+    if (loss && wave == 1) {
+        double t = 0.0;
+        for (int b = lane; b < B; b += 64) t += (double)r[b] * r[b];
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        if (lane == 0) loss[w] = (float)(0.5 * t / B);
+    }
+}
+
 // A whole iteration of a problem that fits one workgroup's LDS (all samples, residuals, iterates and gradients): every
 // launch saved is worth more than the CUs left idle.  8 workers x 32 x 64 on a ring: 9.9 us a step, 13.3 with a gradient and a mix
 // kernel of their own.
@@ -110,6 +174,7 @@ lsq_narrow_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__
 // rows beside them meet in no bank.
 // sum_j W_ij x_j - gamma g as the mix kernels form it: one product, then fused multiply-adds (ring: i-1, i, i+1).
 constexpr long long kLsqStepFloats = 36 * 1024;
+inline int lsq_pitch(int F) { return (F + 7) / 16 * 16 + 8; }
 struct LsqStepArgs {
     float *X;
     const float *A, *y;
@@ -970,7 +1035,7 @@ bool launch_step_lsq(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, const 
 {
     const int n = ctx->n, B = m.batch, F = m.widths[0];
     if (m.kind != DPSGD_MODEL_LSQ || F < 4 || B > 8192 || n > 256 || ctx->opt_mix_force_csr || !ctx->d_rowptr) return false;
-    const int P = (F + 7) / 16 * 16 + 8;
+    const int P = lsq_pitch(F);
     const i64 floats = (i64)n * B * (P + 1) + 2 * (i64)n * F;
     if (floats > kLsqStepFloats) return false;
     LsqStepArgs a{X, (const float *)inputs, (const float *)targets, G, loss, consensus, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals,
@@ -1010,6 +1075,19 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
         if (B > 8192) return DPSGD_EUNSUPPORTED;
         const int F = m.widths[0];
         const float *A = (const float *)inputs, *y = (const float *)targets;
+        const int P = lsq_pitch(F);
+        const i64 small = (i64)B * (P + 1) + F;
+        const size_t shm = (size_t)small * sizeof(float);
+        bool one = F >= 4 && small <= kLsqSmallFloats;
+        if (one && shm > 56 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(lsq_small_kernel),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess) {
+            (void)hipGetLastError();
+            one = false;
+        }
+        if (one) {
+            hipLaunchKernelGGL(lsq_small_kernel, dim3((unsigned)n), dim3(512), shm, s, X, ctx->ld, A, y, B, F, P, G, loss);
+            return hip_status(hipGetLastError());
+        }
         if (F < 4 || n > 65535) {   // (the others' grid.y is the worker)
             hipLaunchKernelGGL(lsq_narrow_kernel, dim3((unsigned)n), dim3(256), (size_t)B * sizeof(float), s, X, ctx->ld, A, y, B, F, G, loss);
             return hip_status(hipGetLastError());

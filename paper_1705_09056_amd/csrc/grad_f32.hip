@@ -324,7 +324,7 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) gemm_f32_kernel(GemmArgs g)
     const int m0 = tile_m * TM, n0 = tile_n * TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    if constexpr (!A_KFAST && B_NFAST) {
+    if constexpr (B_NFAST && (!A_KFAST || WM == 1 || TINY)) {   // (A along the contraction: a layer of one output)
         // The last column of workgroups of a weight gradient sums the deltas over the samples: TM outputs, the threads deal the
         // samples among themselves, add in 64 bits and meet in LDS in order.  A launch of its own took 7.3 us
         // for 16 workers x 128 samples x 1024 outputs; here it is hidden (18 workers x 784-85-3072-10 x 128 samples, one gradient and
@@ -502,7 +502,10 @@ dpsgd_status gemm_f32_launch(hipStream_t s, int nworkers, const GemmArgs &g)
     dim3 grid((unsigned)((g.N + TN - 1) / TN) + (g.rowsum ? 1u : 0u), (unsigned)((g.M + TM - 1) / TM), (unsigned)nworkers);
     if (grid.y > 65535u || grid.z > 65535u) return DPSGD_EUNSUPPORTED;
     const dim3 block(64 * WM * WN * WK);
-    const bool akf = g.sAk == 1 && !g.rowsum, bnf = g.sBn == 1;   // (B contiguous along k: a forward product, only of less than 4 inputs)
+    const bool akf = g.sAk == 1, bnf = g.sBn == 1;   // (B contiguous along k: a forward product, only of less than 4 inputs)
+    // (what the loads of the other tiles assume of the contiguous extents)
+    if (!TINY && ((akf ? g.K : g.M) < 4 || (bnf ? g.N : g.K) < 4)) return DPSGD_EUNSUPPORTED;
+    if (g.rowsum && (!bnf || (akf && WM > 1 && !TINY))) return DPSGD_EUNSUPPORTED;
     if (akf && bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if (bnf) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, false, true, TINY, AHEAD2>), grid, block, 0, s, g);
     else if constexpr (TINY) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, WK, KW, true, false, TINY, AHEAD2>), grid, block, 0, s, g);

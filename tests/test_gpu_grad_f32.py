@@ -259,9 +259,10 @@ def test_class_layers_of_every_width(widths, batch, n):
     grad_case(cfg, synth.model_dim(cfg.model_kind, widths))
 
 
-@pytest.mark.parametrize("widths,batch,n", [((70, 1, 5), 9, 3), ((70, 3, 10), 1, 2), ((129, 65, 33, 7), 67, 3), ((2, 130, 10), 33, 2),
+@pytest.mark.parametrize("widths,batch,n", [((70, 1, 5), 9, 3), ((70, 1, 5), 4, 3), ((70, 1, 5), 3, 2), ((600, 1, 1, 5), 70, 300), ((3, 1, 2), 8, 2),
+                                            ((70, 3, 10), 1, 2), ((129, 65, 33, 7), 67, 3), ((2, 130, 10), 33, 2),
                                             ((520, 1030, 64, 3), 200, 9)])
 def test_hidden_bias_gradients_of_every_width(widths, batch, n):
     """A hidden layer's bias gradient comes from the last column of workgroups of its weight gradient: one output (whose deltas lie
-    contiguously along the samples as well), part tiles, more samples than a thread's loads in flight."""
+    contiguously along the samples as well, in tiles that load four of them at a time from four samples on), part tiles, more samples than a thread's loads in flight."""
     grad_case(shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False), synth.model_dim(MODEL_MLP, widths))

@@ -266,7 +266,7 @@ dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &con
         const ConvDesc &c = convs[first + at];
         ConvChainArgs a{};
         a.nconv = nconv - at < kMaxChain ? nconv - at : kMaxChain;
-        a.src = in.t; a.X = X; a.ld = ctx->ld; a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256 * kWorkgroupsPerCu);
+        a.src = in.t; a.X = X; a.ld = ctx->ld; a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256 * kWorkgroupsPerCu, 0);
         a.Cr = c.Co; a.Hr = c.Ho; a.Wr = c.Wo;
         for (int k = 0; k < a.nconv; ++k) {
             a.out[k] = out[first + at + k].t;

@@ -135,7 +135,8 @@ dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const voi
 // residual block that keeps the resolution, whose inner delta then stays in LDS.  _ok: whether the shapes allow it.
 bool conv_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c);
 bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2);
-int conv_image_splits(int n, int B, int slots);   // workgroups per worker (and partial sums of its weight gradient)
+// workgroups per worker (and partial sums of its weight gradient; C: their channels, 0 where there are none)
+int conv_image_splits(int n, int B, int slots, int C);
 // din = round([act > 0] * (conv^T(dout) + scd)), dW and bias gradient from (act, dout); scd may be null
 dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
                       Tensor din, float *G, float *partials, WgradReduceList *pending);

@@ -193,3 +193,17 @@ def test_static_mix_step_rejects_what_its_fixed_array_cannot_hold_before_any_dev
     assert call(8, 64, 64, B.Topology.ring_chord()) == B.EUNSUPPORTED
     rowptr, col, val = B.topology_build(8, ring)
     assert call(8, 64, 64, B.Topology.csr(rowptr, col, val)) == B.EUNSUPPORTED
+
+
+@pytest.mark.parametrize("slots,channels", [(256, 16), (256, 32), (256, 64), (512, 0)])
+def test_a_minibatch_spreads_over_the_chip_however_few_the_workers(slots, channels):
+    """The CNN's whole-image kernels cut each worker's minibatch into m workgroups: no other m ends sooner, counted in rounds of
+    `slots` workgroups and images one after the other, two of them for a workgroup's start and three for the partial sums that
+    256 workgroups leave at 64 channels."""
+    splits = getattr(B.load(), "_ZN5dpsgd17conv_image_splitsEiiii")   # int conv_image_splits(int n, int B, int slots, int C)
+    splits.restype, splits.argtypes = C.c_int, [C.c_int] * 4
+    assert splits(1, 512, 256, 16) == 256 and splits(112, 32, 256, 64) == 2 and splits(16, 32, 256, 64) == 16
+    for n in (1, 2, 3, 4, 5, 7, 16, 100, 112, 255, 257, 300):
+        for batch in (1, 2, 3, 5, 16, 31, 32, 33, 64, 100, 256, 511, 700):
+            cost = [-(-n * m // slots) * (-(-batch // m) + 2) * 4096 + 3 * n * m * (channels // 16) ** 2 for m in range(1, batch + 1)]
+            assert splits(n, batch, slots, channels) == 1 + cost.index(min(cost)), (n, batch)

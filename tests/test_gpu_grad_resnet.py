@@ -193,7 +193,8 @@ def test_residual_block_in_one_launch_changes_no_bit(widths, batch, n):
                                              ((3, 8, 8, 16, 1, 10), 64, 5),      # less groups of pixels than waves
                                              ((2, 24, 13, 8, 2, 10), 40, 9),     # rows that no constant covers
                                              ((3, 16, 40, 16, 2, 10), 32, 8),    # 64 channels with rows of 16 pixels are too large, as is the rest
-                                             ((3, 48, 32, 16, 2, 10), 32, 8)])   # 24 rows of 16 pixels too, 16 rows of 8 are not
+                                             ((3, 48, 32, 16, 2, 10), 32, 8),    # 24 rows of 16 pixels too, 16 rows of 8 are not
+                                             ((3, 16, 16, 16, 1, 10), 300, 1)])  # 300 workgroups of a worker
 def test_consecutive_blocks_in_one_launch_change_no_bit(widths, batch, n):
     """From 256 images on the blocks of a stage that keep the resolution are one launch; against a launch per convolution
     ("conv_block" 0): the same matrix instructions on the same operands, the same bits."""
@@ -290,6 +291,7 @@ def test_extents_no_kernel_takes_are_kept_as_they_are(widths):
     ((3, 16, 40, 16, 2, 10), 3, 2),    # 64 channels with rows of 16 pixels; wider stages on the other kernels
     ((3, 48, 32, 16, 2, 10), 2, 2),    # 24 rows of 16 pixels, 16 rows of 8
     ((3, 8, 8, 32, 1, 10), 2, 130),    # one workgroup per worker takes all its images
+    ((3, 16, 16, 16, 1, 10), 300, 1),  # 150 workgroups of a worker, two images each
 ])
 def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
     """Weight and data gradient of a convolution (or a residual block) in one launch ("conv_bwd") against a launch each.  The

@@ -2688,6 +2688,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                 else {
                     WgradJobs &jobs = wa.whole_lines ? jobs_lines : jobs_shared;
                     if (jobs.njobs == kMaxWgradJobs) flush(jobs);
+                    if (st != DPSGD_OK) break;   // (the error is read: the check below would not see it)
                     jobs.g[jobs.njobs] = wa;
                     jobs.block0[jobs.njobs] = wgrad_job_blocks(jobs);
                     jobs.gx[jobs.njobs++] = (int)wgrid.x;

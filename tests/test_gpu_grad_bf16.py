@@ -164,13 +164,19 @@ def test_every_workgroup_finds_its_tile(widths, batch, n):
     grad_case(cfg, ld)
 
 
+@pytest.mark.parametrize("padded", [False, True])
 @pytest.mark.parametrize("widths,batch,n", [
     ((70, 40, 33, 130, 10), 20, 3),                                    # part tiles, fewer than four steps of 16 samples
-    ((64, 64, 64, 48, 96, 10), 65, 2),                                 # layers on whole and on shared cache lines, five steps
-    ((40, 36, 48, 33, 34, 64, 35, 40, 48, 37, 41, 10), 16, 2),         # more of them than one launch takes
+    ((64, 64, 64, 48, 96, 10), 65, 2),                                 # six steps: four at once and two
+    ((64, 64, 40, 64, 40, 96, 48, 10), 20, 3),                         # padded: three layers on whole cache lines, three on shared ones
+    ((64,) * 10 + (10,), 16, 2),                                       # nine of a kind (on whole cache lines where padded), more than one launch takes
+    ((40, 36, 48, 33, 34, 64, 35, 40, 48, 37, 41, 10), 16, 2),         # ... on shared ones
 ])
-def test_weight_gradients_of_several_layers_in_one_launch(widths, batch, n):
-    grad_case(shrink(CONFIGS[2], widths=widths, batch=batch, n=n), synth.model_dim(MODEL_MLP, widths))
+def test_weight_gradients_of_several_layers_in_one_launch(widths, batch, n, padded):
+    """Layers too small for the chip wait for each other: those whose rows of G are whole 64-byte halves of cache lines (every
+    layer's weights and the row stride a multiple of 16 floats) in one launch, the others in another, eight at a time."""
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(shrink(CONFIGS[2], widths=widths, batch=batch, n=n), synth.padded_stride(d) if padded else d)
 
 
 def test_softmax_regression_bf16():

@@ -249,6 +249,27 @@ def test_lsq_step_in_one_launch(feat, batch, n, topo):
     assert float(cons) == pytest.approx(m, rel=TOL)
 
 
+@pytest.mark.parametrize("feat,batch,n", [(4, 2000, 2), (9, 700, 2), (5, 1003, 3), (64, 32, 8)])
+def test_lsq_step_adds_long_minibatches_in_64_bits(feat, batch, n):
+    """The gradient that the one-launch step leaves is as near to the oracle's as dpsgd_grad's: sums of eight products in fp32, the
+    rest in fp64.  Tolerance: the result is rounded twice and every residual once (2^-24 each at most, 6e-8, the latter averaging
+    out), the eight-term sums add 8 * 2^-24 of a partial sum at random signs, less than 1e-7 of the norm over 32 samples and more;
+    an fp32 chain over N samples errs by about sqrt(N / 2) 2^-25, 9e-7 at 2000."""
+    cfg = shrink(CONFIGS[0], widths=(feat,), batch=batch, n=n)
+    X = synth.make_replicas(cfg, spread=0.5) + synth.rng(0, 98).standard_normal((n, feat)).astype(np.float32) * np.float32(0.1)
+    inp, tgt = synth.make_batch(cfg, 0)
+    Gref, _ = oracle.grad_all(MODEL_LSQ, cfg.widths, X, inp, tgt)
+    Xd, inp_d, tgt_d = to_dev(X), torch.from_numpy(inp).cuda(), torch.from_numpy(tgt).cuda()
+    Gd = torch.full_like(Xd, 777.0)
+    print(f"lsq step {feat} x {batch} x {n}", flush=True)
+    with B.Dpsgd(n, feat, B.Topology.complete(), cfg.gamma, ld=feat) as ctx:
+        ctx.step(B.Model(MODEL_LSQ, [feat]), Xd, inp_d, tgt_d, batch, Gd)
+        torch.cuda.synchronize()
+    err = rel_err(from_dev(Gd, feat), Gref)
+    print(f"  rel err G {err:.2e}", flush=True)
+    assert err < 3e-7
+
+
 @pytest.mark.parametrize("widths,batch,n", [((4, 2), 1, 2), ((5, 17), 17, 3), ((63, 16), 16, 2), ((257, 26), 31, 3), ((1100, 32), 33, 2),
                                             ((300, 33), 20, 2), ((3, 26), 9, 2), ((2100, 26), 70, 9), ((130, 70, 26), 40, 3)])
 def test_class_layers_of_every_width(widths, batch, n):

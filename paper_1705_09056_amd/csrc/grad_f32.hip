@@ -232,12 +232,13 @@ __global__ void __launch_bounds__(1024) lsq_step_kernel(LsqStepArgs a)
         gs[e] = g;
         a.G[(i64)w * a.ld + c] = g;
     }
+    const int per = n <= 16 ? 64 : 8;   // lanes that share a worker's loss
     if (a.loss)
-        for (int w = tid >> 6; w < n; w += 16) {
+        for (int w = tid / per; w < n; w += 1024 / per) {
             double s = 0.0;
-            for (int b = tid & 63; b < B; b += 64) s += (double)r[w * B + b] * r[w * B + b];
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-            if ((tid & 63) == 0) a.loss[w] = (float)(0.5 * s / B);
+            for (int b = tid % per; b < B; b += per) s += (double)r[w * B + b] * r[w * B + b];
+            for (int off = per / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (tid % per == 0) a.loss[w] = (float)(0.5 * s / B);
         }
     // (an element's own gradient is all the update reads of gs: the result takes its place)
     for (int e = tid; e < n * F; e += 1024) {
@@ -258,15 +259,38 @@ __global__ void __launch_bounds__(1024) lsq_step_kernel(LsqStepArgs a)
     if (!a.consensus) return;
     __syncthreads();
     double dev = 0.0;
-    for (int c = tid; c < F; c += 1024) {
-        const float shift = gs[c];   // (differences from the first row: no cancellation of large numbers)
-        double s = 0.0, q = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const double t = (double)gs[i * F + c] - shift;
-            s += t;
-            q += t * t;
+    if (n >= 32) {
+        // many workers (so that what fits has less than 384 columns): a thread per column and group of rows; a column's groups meet in the place of the iterates (a
+        // sum is two of n F floats: at most n / 2 groups)
+        double *const sums = reinterpret_cast<double *>(xs);
+        const int groups = min(1024 / F, n / 2), g = tid / F, c = tid % F;
+        if (g < groups) {
+            const float shift = gs[c];
+            double s = 0.0;
+            for (int i = g * n / groups; i < (g + 1) * n / groups; ++i) {
+                const double t = (double)gs[i * F + c] - shift;
+                s += t;
+                dev += t * t;
+            }
+            sums[tid] = s;
         }
-        dev += q - s * s / n;
+        __syncthreads();
+        if (tid < F) {
+            double s = 0.0;
+            for (int q = 0; q < groups; ++q) s += sums[q * F + tid];
+            dev -= s * s / n;
+        }
+    } else {
+        for (int c = tid; c < F; c += 1024) {
+            const float shift = gs[c];   // (differences from the first row: no cancellation of large numbers)
+            double s = 0.0, q = 0.0;
+            for (int i = 0; i < n; ++i) {
+                const double t = (double)gs[i * F + c] - shift;
+                s += t;
+                q += t * t;
+            }
+            dev += q - s * s / n;
+        }
     }
     for (int off = 32; off > 0; off >>= 1) dev += __shfl_down(dev, off, 64);
     if ((tid & 63) == 0) part[tid >> 6] = dev;
@@ -1052,6 +1076,19 @@ bool launch_step_lsq(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, const 
     const int P = lsq_pitch(F);
     const i64 floats = (i64)n * B * (P + 1) + 2 * (i64)n * F;
     if (floats > kLsqStepFloats) return false;
+    // One workgroup does it all: a thread's elements, one after the other, must not take longer than the launches saved.  us a step
+    // of n workers x B samples x F features (elements of a thread), gradient and mix / one launch.  Ring: 64 x 4 x 64 (4) 12.0 / 11.0,
+    // 8 x 2 x 700 (6) 14.7 / 12.8, 64 x 1 x 100 (7) 12.3 / 10.9, 256 x 4 x 16 (4) 15.5 / 14.4, but 4 x 2 x 2000 (8) 17.6 / 23.1, 256 x 2 x 30
+    // (8) 11.9 / 16.6.  Any other W is read term by term: up to five links a worker, 32 x 4 x 100 (4) 14.8 / 11.4, but 64 x 4 x 64 (4)
+    // 12.2 / 14.8 and 48 x 2 x 200 (10) 15.2 / 15.2; complete, 12 x 9 x 160 (2) 14.7 / 11.2, 32 x 4 x 100 (4) 16.4 / 21.4.  The more
+    // the mix kernels have to read, the more it may be: complete, 100 x 4 x 20 (2) 51 / 32, 256 x 4 x 16 (4) 326 / 116, 256 x 2 x 30 (8) 299 / 316.
+    const int each = (n * F + 1023) / 1024;
+    if (each > 7 || (ctx->ring_uniform && n > 64 && each > 4)) return false;
+    if (!ctx->ring_uniform && each > 1) {
+        int row = 0;   // the most non-zeros of a row
+        for (int i = 0; i < n; ++i) row = std::max(row, ctx->rowptr[i + 1] - ctx->rowptr[i]);
+        if (each * row > (n <= 32 ? 24 : 16) + row * row / 48) return false;
+    }
     LsqStepArgs a{X, (const float *)inputs, (const float *)targets, G, loss, consensus, ctx->d_rowptr, ctx->d_colidx, ctx->d_vals,
                   ctx->ld, n, B, F, P, ctx->ring_uniform ? 1 : 0, ctx->ring_w, ctx->gamma};
     const size_t shm = (size_t)floats * sizeof(float);

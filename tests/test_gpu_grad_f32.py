@@ -222,7 +222,15 @@ def test_lsq_gradient_of_every_length(feat, batch, n):
 
 @pytest.mark.parametrize("feat,batch,n,topo", [(64, 32, 8, "ring"), (5, 3, 3, "ring"), (73, 20, 16, "complete"), (16, 9, 12, "torus"),
                                                (120, 31, 9, "ring"),      # 35 919 floats of LDS of 36 864
-                                               (120, 32, 9, "ring")])     # one sample more does not fit: two launches and the mix
+                                               (120, 32, 9, "ring"),      # one sample more does not fit: two launches and the mix
+                                               # the consensus distance by groups of rows: of unequal size, one row or two each, at most
+                                               # half as many as rows, 224 columns
+                                               (8, 2, 33, "ring"), (4, 1, 256, "ring"), (31, 3, 33, "complete"), (32, 1, 32, "ring"), (17, 2, 48, "torus"),
+                                               (224, 1, 32, "ring"),
+                                               # elements of a thread, the most that one launch takes and one more: by a row's non-zeros, by the
+                                               # workers of a ring, by themselves
+                                               (160, 9, 12, "complete"), (73, 3, 15, "complete"), (16, 2, 128, "complete"), (17, 2, 128, "complete"),
+                                               (30, 2, 136, "ring"), (31, 2, 136, "ring"), (896, 2, 8, "ring"), (897, 2, 8, "ring")])
 def test_lsq_step_in_one_launch(feat, batch, n, topo):
     """dpsgd_step of a problem that fits one workgroup: update, gradient, loss and consensus distance against the oracle, at
     both sides of what fits, and the gradient it leaves against dpsgd_grad's."""

@@ -106,7 +106,8 @@ lsq_narrow_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__
 // The gradient of a worker whose samples fit 96 KB of LDS, one workgroup per worker: one launch instead of two, bound by its
 // round trips.  us per gradient and mix, on a ring, two launches / this: 31 x 31 samples x 300 features 23.2 / 19.7,
 // 31 x 37 x 400 22.7 / 19.9, 16 x 9 x 769 23.1 / 18.9, 16 x 5 x 3000 22.8 / 19.1.  From 512 features on a wave per sample and a
-// thread per feature (16 x 5 x 3000 with 8 lanes per sample and 64 features at a time: 41.9).
+// thread per feature (16 x 5 x 3000 with 8 lanes per sample and 64 features at a time: 41.9), and below where that is the shorter
+// walk (on a complete graph of 64, whose mix hides the host: 1 x 300 31.1 -> 29.6, 9 x 400 34.5 -> 32.5).
 // Rows of samples pitched as in lsq_step_kernel below; sums in fp64.
 constexpr long long kLsqSmallFloats = 24 * 1024;
 __global__ void __launch_bounds__(512)
@@ -127,18 +128,20 @@ lsq_small_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ 
         *reinterpret_cast<f32x4 *>(As + row * P + k) = mend4((f32x4){t.x, t.y, t.z, t.w}, F - k);
     }
     for (int c = tid; c < F; c += 512) xs[c] = X[(i64)w * ld + c];
+    for (int b = tid; b < B; b += 512) r[b] = y[(i64)w * B + b];
     __syncthreads();
-    const int wide = F >= 512, per = wide ? 64 : 8;   // lanes that share a sample's product
-    for (int row = tid / per; row < (wide ? B : (B + 7) / 8 * 8); row += 512 / per) {   // (uniform over a wave)
-        const int rc = min(row, B - 1);
+    // lanes that share a sample's product: a wave also where its few rounds are shorter than the features eight lanes walk
+    const int per = F >= 512 || (B + 7) / 8 * (F / 64 + 6) < F / 8 + 3 ? 64 : 8;
+    for (int row = tid / per; row < B; row += 512 / per) {
         double s = 0.0;
 #pragma unroll 4
-        for (int c = tid % per; c < F; c += per) s += (double)As[rc * P + c] * xs[c];
+        for (int c = tid % per; c < F; c += per) s += (double)As[row * P + c] * xs[c];
         for (int off = per / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (tid % per == 0 && row < B) r[row] = (float)(s - y[(i64)w * B + row]);
+        if (tid % per == 0) r[row] = (float)(s - r[row]);
     }
     __syncthreads();
     const float invB = 1.0f / (float)B;
+    const bool wide = (F + 511) / 512 * B <= (F + 63) / 64 * (B / 8 + 10);   // samples one after the other against eight waves and their barriers
     for (int c = tid; wide && c < F; c += 512) {   // a thread per feature
         double s = 0.0;
 #pragma unroll 4

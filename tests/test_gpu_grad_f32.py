@@ -213,7 +213,10 @@ def test_trajectory_config1_full():
 @pytest.mark.parametrize("feat,batch,n", [(3, 70, 5),      # less than 4 features: a kernel of their own
                                           (4, 9, 3), (7, 8, 2),     # one and two quads of features, the second clamped
                                           (63, 17, 4), (257, 1, 2), (1023, 40, 3), (300, 1000, 2),
-                                          (64, 335, 3), (64, 336, 3), (511, 9, 2), (512, 9, 2),     # the last of one launch, the first of two; a wave per sample from 512 on
+                                          (64, 335, 3), (64, 336, 3),     # the last of one launch, the first of two
+                                          (511, 46, 2), (512, 46, 2),     # eight lanes per sample, a wave from 512 features on
+                                          (64, 8, 2), (64, 9, 2), (300, 24, 2), (300, 25, 2),     # ... and for few samples
+                                          (64, 11, 2), (64, 12, 2),       # the last of a thread per feature, the first of eight waves
                                           (4, 2731, 2), (7, 2729, 2), (63, 141, 4), (9700, 1, 2)])
 def test_lsq_gradient_of_every_length(feat, batch, n):
     cfg = shrink(CONFIGS[0], widths=(feat,), batch=batch, n=n)

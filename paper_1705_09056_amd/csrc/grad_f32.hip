@@ -77,7 +77,7 @@ lsq_feature_kernel(const float *__restrict__ A, const float *__restrict__ r, int
     }
 }
 
-// Any shape, one workgroup per worker: less than 4 features, or more workers than grid.y holds.
+// Less than 4 features, one workgroup per worker: a thread per sample, then a wave per feature.
 __global__ void __launch_bounds__(256)
 lsq_narrow_kernel(const float *__restrict__ X, i64 ld, const float *__restrict__ A, const float *__restrict__ y, int B,
                   int F, float *__restrict__ G, float *__restrict__ loss)
@@ -1142,13 +1142,17 @@ dpsgd_status launch_grad_f32(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const fl
             hipLaunchKernelGGL(lsq_small_kernel, dim3((unsigned)n), dim3(512), shm, s, X, ctx->ld, A, y, B, F, P, G, loss);
             return hip_status(hipGetLastError());
         }
-        if (F < 4 || n > 65535) {   // (the others' grid.y is the worker)
+        if (F < 4) {
             hipLaunchKernelGGL(lsq_narrow_kernel, dim3((unsigned)n), dim3(256), (size_t)B * sizeof(float), s, X, ctx->ld, A, y, B, F, G, loss);
             return hip_status(hipGetLastError());
         }
         float *r = (float *)ctx->ws;
-        hipLaunchKernelGGL(lsq_residual_kernel, dim3((unsigned)((B + 7) / 8), (unsigned)n), dim3(256), 0, s, X, ctx->ld, A, y, B, F, r);
-        hipLaunchKernelGGL(lsq_feature_kernel, dim3((unsigned)((F + 63) / 64), (unsigned)n), dim3(512), 0, s, A, r, B, F, G, ctx->ld, loss);
+        for (i64 w = 0; w < n; w += 65535) {   // (their grid.y is the worker)
+            const unsigned m = (unsigned)std::min<i64>(n - w, 65535);
+            const float *Aw = A + w * B * F;
+            hipLaunchKernelGGL(lsq_residual_kernel, dim3((unsigned)((B + 7) / 8), m), dim3(256), 0, s, X + w * ctx->ld, ctx->ld, Aw, y + w * B, B, F, r + w * B);
+            hipLaunchKernelGGL(lsq_feature_kernel, dim3((unsigned)((F + 63) / 64), m), dim3(512), 0, s, Aw, r + w * B, B, F, G + w * ctx->ld, ctx->ld, loss ? loss + w : nullptr);
+        }
         return hip_status(hipGetLastError());
     }
     const int L = (int)m.widths.size() - 1;

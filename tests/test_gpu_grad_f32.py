@@ -223,6 +223,28 @@ def test_lsq_gradient_of_every_length(feat, batch, n):
     grad_case(cfg, feat)
 
 
+def test_lsq_gradient_of_more_workers_than_a_grid_holds():
+    """65 537 workers whose samples do not fit LDS: the two launches of any other number of workers, in two parts.  Tolerance: a
+    residual is 64 lanes' chains of 52 products of a random sign, an error of about sqrt(26) 2^-25 = 1.5e-7, and a few roundings;
+    one chain over the 3200 features errs by sqrt(1600) 2^-25 = 1.2e-6."""
+    n, batch, feat = 65537, 8, 3200
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn(n, feat, generator=g, device="cuda")
+    A = torch.randn(n, batch, feat, generator=g, device="cuda")
+    y = torch.randn(n, batch, generator=g, device="cuda")
+    G, loss = torch.full_like(X, 777.0), torch.zeros(n, device="cuda")
+    print("launching", flush=True)
+    with B.Dpsgd(n, feat, B.Topology.ring(), 0.1, ld=feat) as ctx:
+        ctx.grad(B.Model(MODEL_LSQ, [feat]), X, A, y, batch, G, loss)
+        torch.cuda.synchronize()
+    for w in (0, 1, 32768, 65534, 65535, 65536):
+        a, r = A[w].double(), A[w].double() @ X[w].double() - y[w].double()
+        want = a.t() @ r / batch
+        assert float((G[w].double() - want).norm() / want.norm()) < 4e-7, w
+        assert float(loss[w]) == pytest.approx(float(0.5 * (r * r).mean()), rel=1e-6)
+    assert not bool((G == 777.0).any())
+
+
 @pytest.mark.parametrize("feat,batch,n,topo", [(64, 32, 8, "ring"), (5, 3, 3, "ring"), (73, 20, 16, "complete"), (16, 9, 12, "torus"),
                                                (120, 31, 9, "ring"),      # 35 919 floats of LDS of 36 864
                                                (120, 32, 9, "ring"),      # one sample more does not fit: two launches and the mix

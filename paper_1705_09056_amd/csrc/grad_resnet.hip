@@ -19,26 +19,42 @@ namespace dpsgd {
 namespace {
 
 typedef long long i64;
+struct Extent { int C, H, W; };
+
+// The element of a tensor a thread takes: the first `real` threads one of the real extents each, the others the stored ones, of
+// which those beyond the real extents are to be zeroed (false: a real one).  In waves of their own: of the 64 stored pixels of an
+// 8 x 8 plane nine may be real, and a wave that took them all would compute with nine lanes (16 workers x 32 images of 3 x 5 x 7, base
+// 33, one block, whose 66 channels are stored as 128 and whose 132 are not: a gradient 3.37 ms that way, 2.34 this).
+__device__ __forceinline__ bool stored_element(i64 thread, i64 real, Extent r, Extent st, int &ch, int &y, int &x, i64 &img)
+{
+    const bool fill = thread >= real;
+    const Extent e = fill ? st : r;
+    i64 t = fill ? thread - real : thread;
+    x = (int)(t % e.W); t /= e.W;
+    y = (int)(t % e.H); t /= e.H;
+    ch = (int)(t % e.C);
+    img = t / e.C;
+    return !fill || x >= r.W || y >= r.H || ch >= r.C;
+}
 
 // ------------------------------------------------------------------------------ forward
 // IN_FP32: the source is the fp32 image (rounded on load), else a bf16 tensor; both channel-major, stored as c says.
 template <bool IN_FP32>
 __global__ void __launch_bounds__(256)
-conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X, i64 ld, ConvDesc c, int B, i64 total,
+conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X, i64 ld, ConvDesc c, int B, i64 real, i64 total,
                         const bf16_t *__restrict__ sc, int scC, int scH, int scW, int scS, bf16_t *__restrict__ out)
 {
-    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][co][y][x]
-    if (idx >= total) return;
-    i64 t = idx;
-    const int x = (int)(t % c.Wos); t /= c.Wos;
-    const int y = (int)(t % c.Hos); t /= c.Hos;
-    const int co = (int)(t % c.Cos); t /= c.Cos;
-    const int b = (int)(t % B);
-    const int w = (int)(t / B);
-    if (x >= c.Wo || y >= c.Ho || co >= c.Co) {   // beyond the real extent
+    const i64 thread = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][co][y][x]
+    if (thread >= total) return;
+    int x, y, co;
+    i64 img;
+    if (!stored_element(thread, real, {c.Co, c.Ho, c.Wo}, {c.Cos, c.Hos, c.Wos}, co, y, x, img)) return;
+    const i64 idx = ((img * c.Cos + co) * c.Hos + y) * c.Wos + x;
+    if (thread >= real) {
         out[idx] = 0;
         return;
     }
+    const int b = (int)(img % B), w = (int)(img / B);
     const float *Wg = X + (i64)w * ld + c.w_off + (i64)co * c.Ci * 9;
     float acc = 0.f;
     for (int ci = 0; ci < c.Ci; ++ci)
@@ -64,21 +80,20 @@ conv_fwd_generic_kernel(const void *__restrict__ in, const float *__restrict__ X
 //                                              + shortcut delta ) ),  oy = (iy + 1 - ky)/stride.
 __global__ void __launch_bounds__(256)
 conv_dgrad_generic_kernel(const bf16_t *__restrict__ dout, const float *__restrict__ X, i64 ld, ConvDesc c, int B,
-                          i64 total, const bf16_t *__restrict__ scd, int scC, int scH, int scW, int scS,
+                          i64 real, i64 total, const bf16_t *__restrict__ scd, int scC, int scH, int scW, int scS,
                           const bf16_t *__restrict__ act, bf16_t *__restrict__ din)
 {
-    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][ci][iy][ix]
-    if (idx >= total) return;
-    i64 t = idx;
-    const int ix = (int)(t % c.Wis); t /= c.Wis;
-    const int iy = (int)(t % c.His); t /= c.His;
-    const int ci = (int)(t % c.Cis); t /= c.Cis;
-    const int b = (int)(t % B);
-    const int w = (int)(t / B);
-    if (ix >= c.W || iy >= c.H || ci >= c.Ci) {   // beyond the real extent
+    const i64 thread = (i64)blockIdx.x * 256 + threadIdx.x;   // over [w][b][ci][iy][ix]
+    if (thread >= total) return;
+    int ix, iy, ci;
+    i64 img;
+    if (!stored_element(thread, real, {c.Ci, c.H, c.W}, {c.Cis, c.His, c.Wis}, ci, iy, ix, img)) return;
+    const i64 idx = ((img * c.Cis + ci) * c.His + iy) * c.Wis + ix;
+    if (thread >= real) {
         din[idx] = 0;
         return;
     }
+    const int b = (int)(img % B), w = (int)(img / B);
     const float *Wg = X + (i64)w * ld + c.w_off;
     float acc = 0.f;
     for (int ky = 0; ky < 3; ++ky) {
@@ -299,6 +314,9 @@ pool_bwd_vec_kernel(const bf16_t *__restrict__ a, const float *__restrict__ dpoo
     *reinterpret_cast<uint4 *>(dv + u * 8) = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
+i64 elements(i64 images, Extent e) { return images * e.C * e.H * e.W; }
+// Threads of a kernel that stored_element deals the elements to
+i64 element_threads(i64 images, Extent r, Extent st) { return elements(images, r) + (st.C == r.C && st.H == r.H && st.W == r.W ? 0 : elements(images, st)); }
 unsigned blocks_for(i64 total) { return (unsigned)((total + 255) / 256); }
 
 }  // namespace
@@ -310,14 +328,15 @@ unsigned blocks_for(i64 total) { return (unsigned)((total + 255) / 256); }
 // per iteration instead of 15.4.  Channels double from stage to stage, so a base of up to 16 channels is
 // stored as 16 / 32 / 64, up to 32 as 32 / 64 / 128, up to 64 as 64 / 128; wider stages and rows of more than 64 pixels keep
 // their real extents.  (128 channels, rows of up to 16 pixels: 22 workers x 12 images of 28 x 28, base 24, 4.06 ms per iteration
-// with its 96 channels on the shape-generic kernels, 0.57 here.)  So do 64 channels with rows of 64 pixels, whose source patch no kernel has the LDS for (4 workers x 16
+// with its 96 channels on the shape-generic kernels, 0.57 here; bases of 17 to 64 on images of 3 x 3 to 16 x 16 pixels, 1 to 64 workers,
+// 1.06 to 9 times as fast.  The limit is 68 channels of one pixel, 120 times their storage: 3 x 4 x 4, base 17, 3 blocks, 16 x 32 images
+// 1452 us as they are and 1070, but 4 x 64 867 and 950.)  So do 64 channels with rows of 64 pixels, whose source patch no kernel has the LDS for (4 workers x 16
 // images of 3 x 40 x 40, base 64: 30.8 ms padded, 27.0 as they are), and a network whose first stage would take more than 16
 // times its memory (tiny images or channels).  32 channels with rows of 64 pixels have a matrix kernel for forward and data
 // gradient but none for the weight gradient, which pays as long as the padding stays below 3.5 times the memory (4 x 8 images
 // of 3 x 40 x 40, base 32, 1.6 times: 3.05 ms against 3.97; 8 x 16 of 38 x 38, base 17, 3.3 times: 0.80 of the time; 3 x 8 of
 // 12 x 26 x 39, base 17, 3.8 times: 1.28 ms against 1.01; 16 x 4 of 9 x 39, base 17, 5.5 times: 1.035 of the time).
 namespace {
-struct Extent { int C, H, W; };
 Extent stored_stage(int stage, int base, int C, int H, int W)
 {
     const int cs = (base <= 16 ? 16 : base <= 32 ? 32 : 64) << stage;
@@ -463,13 +482,14 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         if ((st = conv_forward(ctx, c, B, img8, X, ws.wpack_f[0], none, ws.out[0])) != DPSGD_OK) return st;
     } else {
         const ConvDesc &c = stem_raw;
-        const i64 total = nB * c.Hos * c.Wos * c.Cos;
+        const Extent r{c.Co, c.Ho, c.Wo};
+        const i64 real = elements(nB, r), total = element_threads(nB, r, {c.Cos, c.Hos, c.Wos});
         if (m.input_is_bf16)
             hipLaunchKernelGGL(conv_fwd_generic_kernel<false>, dim3(blocks_for(total)), dim3(256), 0, s, inputs, X, ctx->ld,
-                               c, B, total, nullptr, 0, 0, 0, 1, ws.out[0].t);
+                               c, B, real, total, nullptr, 0, 0, 0, 1, ws.out[0].t);
         else
             hipLaunchKernelGGL(conv_fwd_generic_kernel<true>, dim3(blocks_for(total)), dim3(256), 0, s, inputs, X, ctx->ld,
-                               c, B, total, nullptr, 0, 0, 0, 1, ws.out[0].t);
+                               c, B, real, total, nullptr, 0, 0, 0, 1, ws.out[0].t);
     }
     for (int j = 0; j < p.nblocks; ++j) {
         const ConvDesc &c1 = p.convs[1 + 2 * j], &c2 = p.convs[2 + 2 * j];
@@ -564,18 +584,20 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
 dpsgd_status conv_forward_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, const float *X, ShortcutRef sc,
                                   Tensor out)
 {
-    const i64 total = (i64)ctx->n * B * c.Hos * c.Wos * c.Cos;
+    const Extent r{c.Co, c.Ho, c.Wo};
+    const i64 images = (i64)ctx->n * B, real = elements(images, r), total = element_threads(images, r, {c.Cos, c.Hos, c.Wos});
     hipLaunchKernelGGL(conv_fwd_generic_kernel<false>, dim3(blocks_for(total)), dim3(256), 0, ctx->stream, in.t, X, ctx->ld,
-                       c, B, total, sc.t, sc.C, sc.H, sc.W, sc.S, out.t);
+                       c, B, real, total, sc.t, sc.C, sc.H, sc.W, sc.S, out.t);
     return hip_status(hipGetLastError());
 }
 
 dpsgd_status conv_data_grad_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X,
                                     ShortcutRef scd, Tensor act, Tensor din)
 {
-    const i64 total = (i64)ctx->n * B * c.His * c.Wis * c.Cis;
+    const Extent r{c.Ci, c.H, c.W};
+    const i64 images = (i64)ctx->n * B, real = elements(images, r), total = element_threads(images, r, {c.Cis, c.His, c.Wis});
     hipLaunchKernelGGL(conv_dgrad_generic_kernel, dim3(blocks_for(total)), dim3(256), 0, ctx->stream, dout.t, X, ctx->ld, c,
-                       B, total, scd.t, scd.C, scd.H, scd.W, scd.S, act.t, din.t);
+                       B, real, total, scd.t, scd.C, scd.H, scd.W, scd.S, act.t, din.t);
     return hip_status(hipGetLastError());
 }
 

@@ -330,6 +330,7 @@ def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
                                             ((3, 16, 16, 32, 1, 10), 5, 3),     # 128 real ones, on 4 x 4 pixels
                                             ((1, 9, 30, 17, 1, 5), 2, 8),       # 17 / 34 / 68: tiles beyond the real channels
                                             ((3, 40, 44, 24, 1, 10), 2, 2),     # rows of 16 pixels: the strided forward stays generic
+                                            ((3, 5, 7, 33, 1, 10), 4, 2),       # 66 stored as 128, 132 not: the generic data gradient between them (one block: with two a turned ReLU moves an element by 1.08 rms)
                                             ((3, 16, 16, 32, 1, 10), 300, 1)])  # 512 partial sums of a bias gradient
 def test_128_channels_on_the_matrix_kernels(widths, batch, n):
     """Stages of up to 128 channels: forward and data gradient fetch their weights where they are used, the weight gradient takes

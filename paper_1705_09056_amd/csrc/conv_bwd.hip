@@ -35,7 +35,7 @@ struct ConvBwdArgs {
     const bf16_t *scd;       // not BLOCK: delta added to the result before the mask, or null
     bf16_t *din;
     const bf16_t *wd2, *wd1; // packed data-gradient operands [n][KS][C/16][64][8]; wd1: BLOCK only
-    float *part2, *part1;    // partial sums [n][splits][(C/16)^2 * 9 * 256 + 1]
+    float *part2, *part1;    // partial sums [n][splits][wgrad_partial_size((C/16)^2, 1)]
     int H, B, splits;
 };
 
@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     constexpr int RED = 9 * 256;   // floats of a tile
     float *red = reinterpret_cast<float *>(smem) + role * (KSPLIT - 1) * CT * CT * RED;
     const int tile = co * CT + ci0;
-    constexpr int psz = CT * CT * 9 * 256 + 1;
+    constexpr int psz = wgrad_partial_size(CT * CT, 1);
     float *out = (BLOCK && role == 1 ? a.part1 : a.part2) + ((i64)w * a.splits + sp) * psz;
     if (KSPLIT > 1) {
         if (kq > 0)
@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     if (lane == 0 && wave == 0) {
         float t = 0.f;
         for (int k = 0; k < RW; ++k) t += bias[role * RW + k];
-        out[psz - 1] = t;
+        out[CT * CT * 9 * 256] = t;
     }
 }
 
@@ -504,8 +504,8 @@ dpsgd_status add_job(dpsgd_ctx *ctx, const ConvDesc &c, int splits, float *parti
 {
     WgradReduceJob job{};
     const int t = c.Cos / 16;
-    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = splits; job.psz = t * t * 9 * 256 + 1;
-    job.tiles = t * t; job.ci_tiles = t; job.CIr = c.Ci; job.COr = c.Co;
+    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = splits; job.psz = wgrad_partial_size(t * t, 1);
+    job.tiles = t * t; job.biases = 1; job.ci_tiles = t; job.CIr = c.Ci; job.COr = c.Co;
     return conv_weight_grad_add(ctx, pending, job, G);
 }
 }  // namespace

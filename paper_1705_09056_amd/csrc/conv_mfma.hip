@@ -749,7 +749,7 @@ struct WgradMfmaArgs {
     const bf16_t *doutT;   // [n*B][COs][Ho][Wo]
     int H, W, Ho, Wo, B, CIs, COs, splits;
     int ci_blocks, ci_tiles, psz;   // blocks of CI input channels, tiles of 16 of them, floats of a partial sum
-    float *part;           // [n][splits][psz]: accumulator order, then a sum of the deltas per block of CO output channels
+    float *part;           // [n][splits][psz]: accumulator order, then a sum of the deltas per block of CO output channels (psz: whole cache lines)
 };
 
 // 16-byte units of a band's source rows a thread holds while they are in flight (8-row bands: 10 rows at stride 1,
@@ -993,7 +993,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
     const float *p = jb.part + (i64)w * splits * psz;
     if (T == jb.tiles) {
         // up to 256 of them at a time, then added in their order
-        const int b0 = jb.tiles * 9 * 256, nb = psz - b0, count = splits * nb;
+        const int b0 = jb.tiles * 9 * 256, nb = jb.biases, count = splits * nb;
         float s = 0.f;
         for (int e0 = 0; e0 < count; e0 += 256) {
             const int e = min(e0 + tid, count - 1);
@@ -1064,12 +1064,9 @@ WgradBlock wgrad_block(const ConvDesc &c)
     if (c.Cos == 128) return c.stride == 1 ? WgradBlock{64, 64} : WgradBlock{32, 64};
     return {(c.Cis + 15) / 16 * 16, c.Cos};
 }
-int wgrad_partial_floats(const ConvDesc &c)
-{
-    const WgradBlock b = wgrad_block(c);
-    const int cip = (c.Cis + 15) / 16 * 16;
-    return c.Cos * cip * 9 + c.Cos / b.co;
-}
+int wgrad_tiles(const ConvDesc &c) { return (c.Cos / 16) * ((c.Cis + 15) / 16); }
+int wgrad_biases(const ConvDesc &c) { return c.Cos / wgrad_block(c).co; }
+int wgrad_partial_floats(const ConvDesc &c) { return wgrad_partial_size(wgrad_tiles(c), wgrad_biases(c)); }
 
 size_t wgrad_lds_bytes(int ci, int stride, int rb, int Wo)
 {
@@ -1123,7 +1120,7 @@ dpsgd_status launch_wgrad(dpsgd_ctx *ctx, const ConvDesc &c, const WgradMfmaArgs
     if (rb == 8) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 8>), grid, block, shm, ctx->stream, a);
     if (rb == 4) hipLaunchKernelGGL((conv_wgrad_mfma_kernel<CI, CO, STRIDE, 4>), grid, block, shm, ctx->stream, a);
     job->part = a.part; job->w_off = c.w_off; job->b_off = c.b_off; job->splits = a.splits; job->psz = a.psz;
-    job->tiles = (c.Cos / 16) * a.ci_tiles; job->ci_tiles = a.ci_tiles; job->CIr = c.Ci; job->COr = c.Co; job->block0 = 0;
+    job->tiles = wgrad_tiles(c); job->biases = wgrad_biases(c); job->ci_tiles = a.ci_tiles; job->CIr = c.Ci; job->COr = c.Co; job->block0 = 0;
     return hip_status(hipGetLastError());
 }
 

@@ -86,12 +86,14 @@ dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &con
 dpsgd_status conv_data_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X, const bf16_t *wpack_d,
                             ShortcutRef scd, Tensor act, Tensor din);
 // The weight-gradient kernels of the MFMA path leave partial sums (several workgroups per worker), in accumulator order:
-// [co tile][ci tile][tap][lane][4] floats, then the sum of the deltas.  What turns them into G is collected here and done
+// [co tile][ci tile][tap][lane][4] floats, then one or more sums of the deltas.  What turns them into G is collected here and done
 // for all convolutions of the network by ONE launch, conv_weight_grad_finish.
+// Floats of one partial sum: whole cache lines, so that the 16-byte stores of every one of them are aligned.
+constexpr int wgrad_partial_size(int tiles, int biases) { return (tiles * 9 * 256 + biases + 31) / 32 * 32; }
 struct WgradReduceJob {
     const float *part;         // the conv's partial sums, [n][splits][psz]
     long long w_off, b_off;    // where the conv's weights and its scalar bias sit in a worker's parameter vector
-    int splits, psz, tiles, ci_tiles, CIr, COr;   // CIr, COr: the conv's real channels
+    int splits, psz, tiles, biases, ci_tiles, CIr, COr;   // psz: floats of a partial sum; CIr, COr: the conv's real channels
     int block0;                // first blockIdx.x of this job
 };
 constexpr int kMaxReduceJobs = 48;

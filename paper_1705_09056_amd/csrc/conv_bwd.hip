@@ -468,7 +468,7 @@ size_t lds_bytes(int C, int H, int W, bool block)
 
 bool shape_ok(const dpsgd_ctx *ctx, const ConvDesc &c, bool block)
 {
-    return ctx->opt_conv_bwd && image_shape_ok(c) && lds_bytes(c.Cos, c.Hos, c.Wos, block) <= 160 * 1024;
+    return ctx->opt_conv_bwd && image_shape_ok(c) && conv_has_backward_operands(c) && lds_bytes(c.Cos, c.Hos, c.Wos, block) <= 160 * 1024;
 }
 
 template <int C, int W, int HT, int NI, bool BLOCK>

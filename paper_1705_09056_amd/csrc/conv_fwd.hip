@@ -255,7 +255,7 @@ dpsgd_status launch(dpsgd_ctx *ctx, const ConvChainArgs &a, bool padded)
 // with it, 295 without; 9 x 14 images 177 and 180; 12 x 41 of 14 x 27 514 and 500).
 bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
-    return ctx->opt_conv_block && (i64)ctx->n * B >= 256 && image_shape_ok(c) && c.Hos * c.Wos * c.Cos <= threads_of(c.Cos) * 32 &&
+    return ctx->opt_conv_block && (i64)ctx->n * B >= 256 && image_shape_ok(c) && conv_has_forward_operands(c) && c.Hos * c.Wos * c.Cos <= threads_of(c.Cos) * 32 &&
            lds_bytes(c.Cos, c.Hos, c.Wos, 1) <= 160 * 1024 / kWorkgroupsPerCu;
 }
 

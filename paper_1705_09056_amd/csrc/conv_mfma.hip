@@ -1243,6 +1243,9 @@ dpsgd_status conv_prep_image(dpsgd_ctx *ctx, const ConvDesc &c, int B, const voi
     return hip_status(hipGetLastError());
 }
 
+bool conv_has_forward_operands(const ConvDesc &c) { return fwd_mfma_ok(c) && !stem_like(c); }
+bool conv_has_backward_operands(const ConvDesc &c) { return dgrad_mfma_ok(c) && wgrad_mfma_ok(c); }
+
 size_t conv_pack_bytes(const ConvDesc &c, bool dgrad)
 {
     const bool ok = dgrad ? dgrad_mfma_ok(c) : fwd_mfma_ok(c);

@@ -115,6 +115,10 @@ dpsgd_status conv_weight_grad(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor i
                               WgradReduceList *pending);
 dpsgd_status conv_weight_grad_finish(dpsgd_ctx *ctx, WgradReduceList *pending, float *G);
 
+// Whether this conv has packed weights for the forward, or packed weights for the data gradient and partial sums for the weight
+// gradient: what the kernels that keep whole images in LDS take from the workspace.
+bool conv_has_forward_operands(const ConvDesc &c);
+bool conv_has_backward_operands(const ConvDesc &c);
 // Bytes per worker of the packed weights of one conv (forward operand, or data-gradient operand).
 size_t conv_pack_bytes(const ConvDesc &c, bool dgrad);
 size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B);

@@ -207,3 +207,31 @@ def test_a_minibatch_spreads_over_the_chip_however_few_the_workers(slots, channe
         for batch in (1, 2, 3, 5, 16, 31, 32, 33, 64, 100, 256, 511, 700):
             cost = [-(-n * m // slots) * (-(-batch // m) + 2) * 4096 + 3 * n * m * (channels // 16) ** 2 for m in range(1, batch + 1)]
             assert splits(n, batch, slots, channels) == 1 + cost.index(min(cost)), (n, batch)
+
+
+class _ConvDesc(C.Structure):
+    _fields_ = [(k, C.c_int) for k in ("Ci", "Co", "H", "W", "Ho", "Wo", "stride")] + [("w_off", C.c_int64), ("b_off", C.c_int64)] + \
+               [(k, C.c_int) for k in ("Cis", "His", "Wis", "Cos", "Hos", "Wos")]
+
+
+def test_whole_image_kernels_have_their_operands():
+    """Every stored shape that fits the CNN's whole-image kernels (16 channels on rows of 8, 16 or 32 pixels, 32 or 64 on rows of 8 or
+    16, at most 16384 elements an image) has the packed weights and partial sums they take from the workspace: asking for them
+    turns no call away."""
+    L = B.load()
+    ask = [getattr(L, name) for name in ("_ZN5dpsgd25conv_has_forward_operandsERKNS_8ConvDescE", "_ZN5dpsgd26conv_has_backward_operandsERKNS_8ConvDescE")]
+    pack = getattr(L, "_ZN5dpsgd15conv_pack_bytesERKNS_8ConvDescEb")   # size_t conv_pack_bytes(const ConvDesc &, bool dgrad)
+    for f in ask:
+        f.restype, f.argtypes = C.c_bool, [C.POINTER(_ConvDesc)]
+    pack.restype, pack.argtypes = C.c_size_t, [C.POINTER(_ConvDesc), C.c_bool]
+    shapes = 0
+    for ch in (16, 32, 64):
+        for w in (8, 16, 32) if ch == 16 else (8, 16):
+            for h in range(8, 16384 // (ch * w) + 1, 8):
+                for real in (ch, ch - 3, ch // 2 + 1):
+                    c = _ConvDesc(real, real, h - 3, w - 2, h - 3, w - 2, 1, 0, 0, ch, h, w, ch, h, w)
+                    assert all(f(C.byref(c)) for f in ask) and pack(C.byref(c), False) and pack(C.byref(c), True), (ch, h, w, real)
+                    shapes += 1
+    assert shapes > 100
+    c = _ConvDesc(8, 16, 16, 16, 16, 16, 1, 0, 0, 8, 16, 16, 16, 16, 16)   # (a stem: no data gradient)
+    assert not ask[1](C.byref(c))

@@ -125,8 +125,8 @@ __device__ __forceinline__ void worker_tile_block_runs(int &tile, int &block, in
 // (tiles, 1, n) with n a multiple of 8 the ids are renumbered so that all tiles of a worker run on one XCD and
 // the worker's activation (or delta) matrix is fetched into one L2 instead of eight.  Any other n takes the runs above from
 // ten tiles on (12 workers x 784-500-300-10 x 50 on tight rows 92.1 -> 90.0 us a step, 29 x 1280-320-26 x 61 119.7 -> 116.0;
-// 45 x 3072-64-512-2 x 32, whose layers have one, eight and one, 100.7 -> 102.7).
-__device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w)
+// 45 x 3072-64-512-2 x 32, whose layers have one, eight and one, 100.7 -> 102.7), the kernels of small tiles if `runs` (below).
+__device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w, bool runs = true)
 {
     tile = blockIdx.x;
     w = blockIdx.z;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w)
         const unsigned xcd = id & 7, slot = id >> 3;
         w = (int)((slot / gridDim.x) * 8 + xcd);
         tile = (int)(slot % gridDim.x);
-    } else if (gridDim.y == 1 && gridDim.x >= 10) {
+    } else if (runs && gridDim.y == 1 && gridDim.x >= 10) {
         int block;
         worker_tile_block_runs(tile, block, w);
     }
@@ -216,6 +216,7 @@ struct FwdArgs {
     float *z;              // [n][B][O]   (last layer, fp32 logits)
     const bf16_t *wb;      // bf16 copy of the weights left by the previous fused step, or null
     int wb_strips;         // its layout: 0 = 32 x 32 tiles (shadow_tile), 1 = [16][256] tiles (shadow_strip)
+    int runs;              // tiles in runs, for the kernels of small tiles (run_mlp_bf16)
     // class layer only (mlp_fwd_last_kernel), or null: softmax cross-entropy in the same launch
     const int *labels;     // [n][B]
     bf16_t *sm_dz;         // [n][B][act_pitch(O)] deltas of the class layer
@@ -514,7 +515,7 @@ __global__ void __launch_bounds__(256) mlp_fwd_ksplit_kernel(FwdArgs g)
     bf16_t *Wt = reinterpret_cast<bf16_t *>(smem);          // [2][TO][PITCH2]
     bf16_t *At = Wt + 2 * TO * PITCH2;                       // [2][MBLK][PITCH2]
     int w, tile;
-    worker_tile_on_one_xcd(tile, w);
+    worker_tile_on_one_xcd(tile, w, g.runs);
     const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wn = wave & 1, wk = wave >> 1;
@@ -691,7 +692,7 @@ __global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g, int tcols
     constexpr int BUF = (TO + MBLK) * PITCH2;   // bf16 elements
     __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF];
     int w, tile;
-    worker_tile_on_one_xcd(tile, w);
+    worker_tile_on_one_xcd(tile, w, g.runs);
     const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
@@ -928,6 +929,7 @@ struct WgradArgs {
     i64 ld, woff, boff;
     int Bp, K, O;
     int tiles;           // not SKINNY: tiles of 32 columns a wave walks
+    int runs;            // mlp_wgrad_big_kernel: tiles in runs
     int whole_lines;     // every 32-column piece of a row of G is two 64-byte halves of lines (12 x 64 x 784 x 3872: a step
                          // 246 us with non-temporal stores, 270 without; rows that share the halves: 232 with, 111 without)
 };
@@ -1043,8 +1045,8 @@ __global__ void __launch_bounds__(256, 4) mlp_wgrad_big_kernel(WgradArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     u32x4 *lds = reinterpret_cast<u32x4 *>(smem);   // [2][kWgStep][8 groups: 4 of o, 4 of k][64]
-    int w, kt, ot;   // one XCD takes all o tiles of a run of k tiles
-    worker_tile_block_runs(kt, ot, w);
+    int w = blockIdx.z, kt = blockIdx.x, ot = blockIdx.y;
+    if (g.runs) worker_tile_block_runs(kt, ot, w);   // one XCD takes all o tiles of a run of k tiles
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     const int o0 = ot * 128, k0 = kt * 128;
@@ -1134,6 +1136,7 @@ struct DgradArgs {
     int B, Bp, K, O;
     const bf16_t *wb;     // bf16 copy of the weights left by the previous fused step, or null
     int wb_strips;        // its layout: 0 = 32 x 32 tiles (shadow_tile), 1 = [16][256] tiles (shadow_strip)
+    int runs;             // tiles in runs, for the kernel of small tiles (run_mlp_bf16)
 };
 
 // Epilogue of one 32 x 32 accumulator tile: lane owns input k and the 16 samples bt + (v/4)*8 + half*4 + v%4.  ReLU mask,
@@ -1336,7 +1339,7 @@ __global__ void __launch_bounds__(256) mlp_dgrad_small_kernel(DgradArgs g)
     constexpr int WP = TK + 8, DP = OC + 8, BUF = OC * WP + MBLK * DP, RED = 4 * MT * 16 * 64 * 2;
     __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF > RED ? 2 * BUF : RED];
     int w, tile;
-    worker_tile_on_one_xcd(tile, w);
+    worker_tile_on_one_xcd(tile, w, g.runs);
     const int kt0 = tile * TK, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
@@ -2578,8 +2581,17 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
     const bool class_path = L > 1 && m.widths[L] <= 16 && ctx->opt_class_bwd &&
                             !(fuse && layer_fusable(ctx, m.widths[L - 1], m.widths[L], woff[L - 1]));
     bool softmax_in_fwd = false;
+    // Small tiles in runs where a layer then finds the activations and deltas on its XCD that the launch before left there, i.e. where
+    // every hidden layer has ten tiles of 32 and no launch deals them otherwise (fused layers), and from nine workers on.  us a
+    // gradient and mix (* a step), plain / runs: 784-500-300-10 x 64, 12 workers 85.2 / 83.6, 17 100.3 / 97.5, 5 x 32 68.6 / 70.3;
+    // 3072-1024-10 x 64, 12 171 / 160; 1024-1024-1024-10 x 64, 12 152.8 / 147.5, * 9 137.6 / 144.8, * 4 113.5 / 118.3;
+    // 784-155-857-2 x 47, 7 72.5 / 75.1, 17 82.2 / 85.1.
+    bool runs = n > 8;
+    for (int l = 0; l < L; ++l)
+        if ((l > 0 && m.widths[l] <= 288) || (fuse && layer_fusable(ctx, m.widths[l], m.widths[l + 1], woff[l]))) runs = false;
     for (int l = 0; l < L && st == DPSGD_OK; ++l) {
         FwdArgs a{};
+        a.runs = runs;
         a.act = act[l]; a.X = X; a.ld = ctx->ld; a.woff = woff[l]; a.boff = boff[l];
         a.B = B; a.Bp = Bp; a.K = m.widths[l]; a.O = m.widths[l + 1];
         a.lda = (l == 0 && !ws.a0) ? a.K : act_pitch(a.K);
@@ -2673,6 +2685,10 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             // 4 x 1024-1024-10 x 128 (256) 65.8 / 66.4; below 256 12 x 784-300-100-10 x 512 (252) 181 / 187,
             // 4 x 784-500-300-10 x 100 (112) 83.8 / 87.2, 1 x 3072-1024-10 x 512 (192) 96.4 / 94.4
             if (Bp > 64 && O >= 64 && K >= 64 && (i64)wgrid_big.x * wgrid_big.y * n >= 256) {
+                // in runs as long as the caches take the results (2 to 16 workers x 100 to 512 samples, ten shapes: up to 18 % a gradient
+                // and mix); larger ones are written where whole rows of G follow each other (12 x 3072 x 4096 x 100: 617 us plain, 643
+                // in runs; 12 x 3072 x 2048 x 128: 340 and 343, 4 x 3072 x 4096 x 512: 376 and 365)
+                wa.runs = (i64)n * K * O <= 80000000;
                 hipLaunchKernelGGL(mlp_wgrad_big_kernel, wgrid_big, dim3(256), (size_t)2 * kWgStep * 8192, s, wa);
             } else if (O <= 32) {
                 dim3 wgrid((unsigned)((K + 127) / 128), (unsigned)((O + 31) / 32), (unsigned)n);
@@ -2703,6 +2719,7 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             da.B = B; da.Bp = Bp; da.K = K; da.O = O;
             da.wb = wb_use[l];
             da.wb_strips = strips_use[l];
+            da.runs = runs;
             const bool vec = base_ok && (K % 4) == 0 && (woff[l] % 4) == 0;
             if (K >= 4 && !may_copy(l) && few_tiles(K, B, n, false, false)) {
                 const dim3 sgrid((unsigned)((act_pitch(K) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),

@@ -2634,9 +2634,16 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
     WgradJobs jobs_lines{}, jobs_shared{};   // weight gradients that wait for the others of their kind
     auto flush = [&](WgradJobs &jobs) {
         if (jobs.njobs == 0 || st != DPSGD_OK) return;
-        const dim3 grid((unsigned)wgrad_job_blocks(jobs), 1, (unsigned)n);
-        if (&jobs == &jobs_lines) hipLaunchKernelGGL(mlp_wgrad_layers_kernel<true>, grid, dim3(256), 0, s, jobs);
-        else hipLaunchKernelGGL(mlp_wgrad_layers_kernel<false>, grid, dim3(256), 0, s, jobs);
+        const bool lines = &jobs == &jobs_lines;
+        if (jobs.njobs == 1) {   // (without the table: 5 x 784-500-300-10 x 32, two layers of different kinds, 5.0 + 4.6 us with it, 4.4 + 4.4 without)
+            const dim3 grid((unsigned)jobs.gx[0], (unsigned)((jobs.g[0].O + 127) / 128), (unsigned)n);
+            if (lines) hipLaunchKernelGGL((mlp_wgrad_kernel<false, false, true>), grid, dim3(256), 0, s, jobs.g[0]);
+            else hipLaunchKernelGGL((mlp_wgrad_kernel<false, false, false>), grid, dim3(256), 0, s, jobs.g[0]);
+        } else {
+            const dim3 grid((unsigned)wgrad_job_blocks(jobs), 1, (unsigned)n);
+            if (lines) hipLaunchKernelGGL(mlp_wgrad_layers_kernel<true>, grid, dim3(256), 0, s, jobs);
+            else hipLaunchKernelGGL(mlp_wgrad_layers_kernel<false>, grid, dim3(256), 0, s, jobs);
+        }
         jobs.njobs = 0;
         st = hip_status(hipGetLastError());
     };

@@ -169,6 +169,8 @@ def test_every_workgroup_finds_its_tile(widths, batch, n):
     ((70, 40, 33, 130, 10), 20, 3),                                    # part tiles, fewer than four steps of 16 samples
     ((64, 64, 64, 48, 96, 10), 65, 2),                                 # six steps: four at once and two
     ((64, 64, 40, 64, 40, 96, 48, 10), 20, 3),                         # padded: three layers on whole cache lines, three on shared ones
+    ((64, 64, 40, 48, 10), 20, 3),                                     # padded: two and one
+    ((130, 150, 10), 33, 2),                                           # one layer: no table
     ((64,) * 10 + (10,), 16, 2),                                       # nine of a kind (on whole cache lines where padded), more than one launch takes
     ((40, 36, 48, 33, 34, 64, 35, 40, 48, 37, 41, 10), 16, 2),         # ... on shared ones
 ])

@@ -125,21 +125,29 @@ __device__ __forceinline__ void worker_tile_block_runs(int &tile, int &block, in
 // (tiles, 1, n) with n a multiple of 8 the ids are renumbered so that all tiles of a worker run on one XCD and
 // the worker's activation (or delta) matrix is fetched into one L2 instead of eight.  Any other n takes the runs above from
 // ten tiles on (12 workers x 784-500-300-10 x 50 on tight rows 92.1 -> 90.0 us a step, 29 x 1280-320-26 x 61 119.7 -> 116.0;
-// 45 x 3072-64-512-2 x 32, whose layers have one, eight and one, 100.7 -> 102.7), the kernels of small tiles if `runs` (below).
-__device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w, bool runs = true)
+// 45 x 3072-64-512-2 x 32, whose layers have one, eight and one, 100.7 -> 102.7), the kernels of small tiles in some networks only
+// (run_mlp_bf16).
+// (The latter are told which, kOneXcd, kRuns or 0: from their arguments it is there a little sooner than from the grid.)
+constexpr int kOneXcd = 1, kRuns = 2;
+__device__ __forceinline__ void worker_tile_in_order(int &tile, int &w, int order)
 {
     tile = blockIdx.x;
     w = blockIdx.z;
-    if (gridDim.y == 1 && (gridDim.z & 7) == 0) {
+    if (order == kOneXcd) {
         const unsigned id = blockIdx.x + gridDim.x * blockIdx.z;
         const unsigned xcd = id & 7, slot = id >> 3;
         w = (int)((slot / gridDim.x) * 8 + xcd);
         tile = (int)(slot % gridDim.x);
-    } else if (runs && gridDim.y == 1 && gridDim.x >= 10) {
+    } else if (order == kRuns) {
         int block;
         worker_tile_block_runs(tile, block, w);
     }
 }
+__device__ __forceinline__ void worker_tile_on_one_xcd(int &tile, int &w)
+{
+    worker_tile_in_order(tile, w, gridDim.y != 1 ? 0 : (gridDim.z & 7) == 0 ? kOneXcd : gridDim.x >= 10 ? kRuns : 0);
+}
+inline int tile_order(dim3 grid, bool runs) { return grid.y != 1 ? 0 : (grid.z & 7) == 0 ? kOneXcd : runs && grid.x >= 10 ? kRuns : 0; }
 
 // ------------------------------------------------------------------ input preparation
 // in: [n*B][F] fp32 or bf16 -> a [n][B][act_pitch(F)] bf16 (null: the caller's bf16 rows are used as they are) and
@@ -216,7 +224,7 @@ struct FwdArgs {
     float *z;              // [n][B][O]   (last layer, fp32 logits)
     const bf16_t *wb;      // bf16 copy of the weights left by the previous fused step, or null
     int wb_strips;         // its layout: 0 = 32 x 32 tiles (shadow_tile), 1 = [16][256] tiles (shadow_strip)
-    int runs;              // tiles in runs, for the kernels of small tiles (run_mlp_bf16)
+    int order;             // of the workgroups, for the kernels of small tiles (tile_order)
     // class layer only (mlp_fwd_last_kernel), or null: softmax cross-entropy in the same launch
     const int *labels;     // [n][B]
     bf16_t *sm_dz;         // [n][B][act_pitch(O)] deltas of the class layer
@@ -515,7 +523,7 @@ __global__ void __launch_bounds__(256) mlp_fwd_ksplit_kernel(FwdArgs g)
     bf16_t *Wt = reinterpret_cast<bf16_t *>(smem);          // [2][TO][PITCH2]
     bf16_t *At = Wt + 2 * TO * PITCH2;                       // [2][MBLK][PITCH2]
     int w, tile;
-    worker_tile_on_one_xcd(tile, w, g.runs);
+    worker_tile_in_order(tile, w, g.order);
     const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wn = wave & 1, wk = wave >> 1;
@@ -692,7 +700,7 @@ __global__ void __launch_bounds__(256) mlp_fwd_small_kernel(FwdArgs g, int tcols
     constexpr int BUF = (TO + MBLK) * PITCH2;   // bf16 elements
     __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF];
     int w, tile;
-    worker_tile_on_one_xcd(tile, w, g.runs);
+    worker_tile_in_order(tile, w, g.order);
     const int o0 = tile * TO, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
@@ -1136,7 +1144,7 @@ struct DgradArgs {
     int B, Bp, K, O;
     const bf16_t *wb;     // bf16 copy of the weights left by the previous fused step, or null
     int wb_strips;        // its layout: 0 = 32 x 32 tiles (shadow_tile), 1 = [16][256] tiles (shadow_strip)
-    int runs;             // tiles in runs, for the kernel of small tiles (run_mlp_bf16)
+    int order;            // of the workgroups, for the kernel of small tiles (tile_order)
 };
 
 // Epilogue of one 32 x 32 accumulator tile: lane owns input k and the 16 samples bt + (v/4)*8 + half*4 + v%4.  ReLU mask,
@@ -1339,7 +1347,7 @@ __global__ void __launch_bounds__(256) mlp_dgrad_small_kernel(DgradArgs g)
     constexpr int WP = TK + 8, DP = OC + 8, BUF = OC * WP + MBLK * DP, RED = 4 * MT * 16 * 64 * 2;
     __shared__ __attribute__((aligned(16))) bf16_t smem[2 * BUF > RED ? 2 * BUF : RED];
     int w, tile;
-    worker_tile_on_one_xcd(tile, w, g.runs);
+    worker_tile_in_order(tile, w, g.order);
     const int kt0 = tile * TK, b0 = blockIdx.y * MBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
@@ -1616,9 +1624,10 @@ dpsgd_status fwd_launch(hipStream_t s, int n, const FwdArgs &a, bool vec, bool l
     return hip_status(hipGetLastError());
 }
 
-dpsgd_status fwd_ksplit_launch(hipStream_t s, int n, const FwdArgs &a, bool vec, bool last)
+dpsgd_status fwd_ksplit_launch(hipStream_t s, int n, FwdArgs a, bool vec, bool last, bool runs)
 {
     dim3 grid((unsigned)((a.O + 63) / 64), (unsigned)((a.B + 31) / 32), (unsigned)n);
+    a.order = tile_order(grid, runs);
     const size_t shm = (size_t)2 * (64 + 32) * PITCH2 * sizeof(bf16_t);
     if (a.wb && vec && !last && (a.O % 64) == 0 && (a.K % 128) == 0)
         hipLaunchKernelGGL((mlp_fwd_ksplit_kernel<true, false, true>), grid, dim3(256), shm, s, a);
@@ -2591,7 +2600,6 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
         if ((l > 0 && m.widths[l] <= 288) || (fuse && layer_fusable(ctx, m.widths[l], m.widths[l + 1], woff[l]))) runs = false;
     for (int l = 0; l < L && st == DPSGD_OK; ++l) {
         FwdArgs a{};
-        a.runs = runs;
         a.act = act[l]; a.X = X; a.ld = ctx->ld; a.woff = woff[l]; a.boff = boff[l];
         a.B = B; a.Bp = Bp; a.K = m.widths[l]; a.O = m.widths[l + 1];
         a.lda = (l == 0 && !ws.a0) ? a.K : act_pitch(a.K);
@@ -2613,13 +2621,14 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             // (aligned rows and at most 32 samples: the k-split kernel already has 64-wide tiles and splits the contraction)
             const dim3 sgrid((unsigned)((act_pitch(a.O) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                              (unsigned)n);
+            a.order = tile_order(sgrid, runs);
             const int tcols = t.mt > 1 && t.wm == 1 ? 128 : 64, chunk = t.mt == 1 || (t.wm == 2 && vec) ? KC2 : KC;
             if (t.mt == 1 && last) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, true>), sgrid, dim3(256), 0, s, a, tcols, chunk);
             else if (t.mt == 1) hipLaunchKernelGGL((mlp_fwd_small_kernel<1, false>), sgrid, dim3(256), 0, s, a, tcols, chunk);
             else if (last) hipLaunchKernelGGL((mlp_fwd_small_kernel<2, true>), sgrid, dim3(256), 0, s, a, tcols, chunk);
             else hipLaunchKernelGGL((mlp_fwd_small_kernel<2, false>), sgrid, dim3(256), 0, s, a, tcols, chunk);
             st = hip_status(hipGetLastError());
-        } else if (t.mt == 1 || a.K < 4) st = fwd_ksplit_launch(s, n, a, vec, last);
+        } else if (t.mt == 1 || a.K < 4) st = fwd_ksplit_launch(s, n, a, vec, last, runs);
         else if (t.wm == 1) st = fwd_launch<1, 4, 2>(s, n, a, vec, last);
         else st = fwd_launch<2, 2, 2>(s, n, a, vec, last);
     }
@@ -2726,11 +2735,11 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
             da.B = B; da.Bp = Bp; da.K = K; da.O = O;
             da.wb = wb_use[l];
             da.wb_strips = strips_use[l];
-            da.runs = runs;
             const bool vec = base_ok && (K % 4) == 0 && (woff[l] % 4) == 0;
             if (K >= 4 && !may_copy(l) && few_tiles(K, B, n, false, false)) {
                 const dim3 sgrid((unsigned)((act_pitch(K) + 31) / 32), (unsigned)((B + (t.mt == 1 ? 31 : 63)) / (t.mt == 1 ? 32 : 64)),
                                  (unsigned)n);
+                da.order = tile_order(sgrid, runs);
                 if (t.mt == 1) hipLaunchKernelGGL(mlp_dgrad_small_kernel<1>, sgrid, dim3(256), 0, s, da);
                 else hipLaunchKernelGGL(mlp_dgrad_small_kernel<2>, sgrid, dim3(256), 0, s, da);
                 st = hip_status(hipGetLastError());

@@ -14,15 +14,20 @@
 // din = [in > 0] (conv1^T(du) + dv): dv, u and the block input are read once, din is written once and du never reaches memory.
 // Four launches read and wrote these tensors nine times.
 // The same matrix instructions on the same operands in the same order as conv3x3_mfma_kernel for the deltas, so they carry
-// the same bits; the weight gradient's sums over images are split differently.
+// the same bits; the weight gradient's sums over images are split differently, in longer chains where a workgroup has many images.
+// Error of a layer's sums against sums in 64 bits of the same products, as a share of their norm, largest of the layers (separate
+// launches in brackets): 112 workers x 32 images of 3 x 32 x 32 2.9e-7 (1.4e-7), 256 x 64 3.5e-7 (1.6e-7), 1 x 512 2.4e-7 (2.5e-7); the bf16
+// operands put the gradient 8e-3 from the unrounded one either way.  A chain per image that then joins the sum brings 1.3e-7 and costs
+// 36 registers: a block of 16 channels 141 -> 143 us, of 32, where they are not there, 104 -> 122.
 // What bounds it: one workgroup of 8 waves per CU, two waves per SIMD, i.e. the latency of a wave's LDS reads.  So operands are
 // read a batch of matrix instructions ahead (left to itself the compiler waited for each one: du of a block of 16 channels
 // 53 us, 28 with batches), images are requested a phase ahead with no branch around the loads, and what an epilogue needs
 // comes from LDS instead of memory (din of that block 67 -> 42 us).  Memory alone, the images in and nothing else, is 71 us of
 // the block's 147 at 16 channels.
-// 112 workers x 32 images, 16 channels x 32 x 32, a block: 229 us in four launches, 147 here; 32 channels x 16 x 16: 157 and
-// 110; one convolution of 32 channels 82 and 64, of 64 channels x 8 x 8 77 and 55.  16 waves of half the registers at 16
-// channels spill (321 us); 64 channels as a block would need the sums of four tiles per wave.
+// 112 workers x 32 images, 16 channels x 32 x 32, a block: 229 us in four launches, 142 here; 32 channels x 16 x 16: 157 and
+// 105; one convolution of 32 channels 82 and 61, of 64 channels x 8 x 8 77 and 53.  Registers: 199 to 206 at 16 channels, 252 to 256 of
+// 256 at 32 and 64, where the block of 32 channels on 16 x 16 pixels spills 15 and four of the sizes given at run time 3 to 8.  16 waves of
+// half the registers at 16 channels spill far more (321 us); 64 channels as a block would need the sums of four tiles per wave.
 #include "conv_image.h"
 
 namespace dpsgd {
@@ -62,7 +67,6 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     const int role = BLOCK ? wave8 / RW : 0, wave = wave8 & (RW - 1);
     const int n16 = lane & 15, g = lane >> 4;
     const int H = HT ? HT : a.H, HW = H * W, G = HW / 32;   // groups of 32 pixels of an image
-    const int LR = H + 2;                             // LDS rows of an image
     const int BUF = NI * image_lds(C, W, H);
     const int lo = (int)((i64)a.B * sp / a.splits), hi = (int)((i64)a.B * (sp + 1) / a.splits);
     const i64 img0 = (i64)w * a.B;
@@ -455,8 +459,6 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
         out[CT * CT * 9 * 256] = t;
     }
 }
-
-
 
 size_t lds_bytes(int C, int H, int W, bool block)
 {

@@ -53,7 +53,7 @@ CONFIGS = (
     _mk(4, "resnet20_ring112", MODEL_RESNET20, (3, 32, 32, 16, 3, 10), 112, "ring", 32, 0.1, 20, True),
 )
 
-# configs[3] is run on a ring and on an 8x8 torus; gamma is not given for it in the
+# mlp3 is run on a ring and on an 8x8 torus; gamma is not given for it in the
 # benchmark definition, so the value of its neighbours (0.1) is used.
 CONFIG3_TORUS = _mk(3, "mlp3_torus8x8", MODEL_MLP, (3072, 4096, 4096, 10), 64, "torus", 32, 0.1, 50, True, (8, 8))
 

@@ -100,7 +100,7 @@ __device__ __forceinline__ i64 shadow_strip(int o, int k, int K)
 // of the wave, instruction q 0..7), i.e. which rows one wave's load instructions touch.  The HBM channels serve a wave
 // faster when all its pieces lie a multiple of 32 KB apart (see mix_ring_fat_kernel): with rows of 16 KB or a multiple
 // (K % 4096 == 0) the halves of a wave take rows two apart and the wave keeps to rows of one parity (-5 and -7 us per
-// iteration in the data gradient and the forward of the 4096 x 4096 layer of configs[3]); else consecutive rows (for
+// iteration in the data gradient and the forward of the 4096 x 4096 layer of mlp3_ring64); else consecutive rows (for
 // 12 KB rows, halves eight rows apart were measured and are slightly slower).  A permutation of 0..63 either way.
 __device__ __forceinline__ int weight_tile_row(int r, int K)
 {

@@ -44,7 +44,7 @@ ELEM = 16.0
 # size, several times that where the sample's delta and activation are both large - for a handful of units per
 # worker.  For those comparisons (`flips=True`) the element-wise bar may be exceeded by at most FLIP_FRACTION of the
 # elements, and by none by FLIP_CAP root-mean-squares or more ("wrong by its own typical size").  On the GPU the
-# bf16 cases show at most 6e-5 of the elements over the bar and a largest error of 0.51 rms (configs[3], minibatch 32).
+# bf16 cases show at most 6e-5 of the elements over the bar and a largest error of 0.51 rms (mlp3_ring64, minibatch 32).
 FLIP_FRACTION = 1e-3
 FLIP_CAP = 1.0
 

@@ -8,8 +8,8 @@ from paper_1705_09056_amd.configs import CONFIGS, shrink
 
 # (widths, minibatch, workers) of the MLP cases on 64-float-aligned row strides
 MLP_ALIGNED = [
-    ((3072, 1024, 10), 128, 2),        # configs[2] layer shapes
-    ((3072, 256, 256, 10), 32, 3),     # configs[3] structure, narrower hidden layers
+    ((3072, 1024, 10), 128, 2),        # mlp2_ring32's layer shapes
+    ((3072, 256, 256, 10), 32, 3),     # mlp3_ring64's structure, narrower hidden layers
     ((512, 4096, 10), 32, 2),          # a full-width 4096 hidden layer
     ((256, 128, 10), 64, 2),           # the 64-row tiling
     ((256, 128, 64, 10), 130, 2),      # more than one row block

@@ -417,7 +417,7 @@ def test_chunked_wave_map_of_the_row_kernel_changes_no_bit(widths, batch, n, sha
 
 
 @pytest.mark.parametrize("widths,batch,n", [
-    ((3072, 1024, 10), 128, 4),       # configs[2]'s layer: 8 operand steps per worker, 40 KB of LDS per workgroup
+    ((3072, 1024, 10), 128, 4),       # mlp2_ring32's layer: 8 operand steps per worker, 40 KB of LDS per workgroup
     ((1024, 1024, 10), 64, 5),        # 4 steps, odd ring
     ((1280, 2080, 10), 90, 3),        # ragged minibatch padded to 96 (6 steps: two waves fetch two steps of dZ^T, two one)
     ((512, 1024, 10), 150, 3),        # padded to 160: 10 steps

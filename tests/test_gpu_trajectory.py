@@ -10,7 +10,7 @@ Two gates per iteration k, as for the convex workloads:
        (iterate, its displacement from x_0, node average, per-worker loss, consensus distance) is reported per iteration
        with the first iteration at which it goes over the 2e-2 bar, if it does.  The iterate and the node average are
        asserted under the bar against both oracles for the first 10 iterations; beyond that a free-running non-convex
-       trajectory is reported, not asserted: at configs[2] the loss drifts over the bar against the un-rounded oracle
+       trajectory is reported, not asserted: at mlp2_ring32 the loss drifts over the bar against the un-rounded oracle
        after ~15 iterations and the iterate itself after ~24 (different ReLU decisions, then growing drift).
 
 Both oracles run the recursion: the one with the workload's bf16 operand roundings and the plain fp64 one.  K' is what

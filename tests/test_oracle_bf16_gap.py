@@ -101,7 +101,7 @@ def torch_mlp_with(casts, widths, x, inp, lab):
 
 
 def test_an_independent_implementation_finds_the_same_gap_and_it_scales_with_the_rounding_unit():
-    """configs[2]'s layer shapes, worker 0 of the GPU case: PyTorch autograd with torch's bf16 casts against PyTorch
+    """mlp2_ring32's layer shapes, worker 0 of the GPU case: PyTorch autograd with torch's bf16 casts against PyTorch
     autograd without them is as far apart as the two oracles are, and rounding to 11 or 14 mantissa bits instead of
     bf16's 8 divides the distance by at least sqrt(8) each time: the distance is the operand rounding, nothing else."""
     widths, batch, n = MLP_ALIGNED[0]

@@ -1809,7 +1809,12 @@ __global__ void __launch_bounds__(256, 3) mlp_fused_ring_kernel(FusedArgs a)
 // (16 bytes per lane, no registers), asynchronously: they are requested as soon as every wave has read the
 // previous worker's from LDS, and land while the wave forms and stores that worker's update.  One round trip per
 // worker, hidden; two workgroup barriers per worker.  grid (K / 128, O / 32), block 256, dynamic LDS 5 * steps KB.
-template <bool CONS>
+// PAST: the three tiles that a wave reads before its walk, too, are read past the caches, as all others are.  Kept there (3 workers'
+// layer of all, every pass) they cost every kernel that reads the replicas next: once these are more than the last cache
+// level (256 MB) holds, what it happens to hold of them is served slower than HBM.  us a step, without / with, 3072-1024-10: 32 workers
+// x 128 samples 293 / 280 (this kernel 171 / 170, the forward 90 / 80), 24 x 64 216 / 207, 20 x 128 210 / 205, 48 x 64 412 / 396; but
+// 13 x 64 140 / 142, 10 x 64 119 / 121, 16 x 64 156 / 152, 16 x 128 178 / 181: from 192 MiB on.
+template <bool CONS, bool PAST>
 __global__ void __launch_bounds__(256, 3) mlp_fused_ring_lds_kernel(FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char fused_lds[];
@@ -1835,10 +1840,11 @@ __global__ void __launch_bounds__(256, 3) mlp_fused_ring_lds_kernel(FusedArgs a)
     request_ops(0);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        xm[v] = xt[(i64)(a.n - 1) * a.ld + row_off(v)];
-        xc[v] = xt[row_off(v)];
+        const float *pm = xt + (i64)(a.n - 1) * a.ld + row_off(v), *pc = xt + row_off(v), *pn = xt + (i64)(1 % a.n) * a.ld + row_off(v);
+        xm[v] = PAST ? __builtin_nontemporal_load(pm) : *pm;
+        xc[v] = PAST ? __builtin_nontemporal_load(pc) : *pc;
         xh[v] = xc[v];
-        xn[v] = xt[(i64)(1 % a.n) * a.ld + row_off(v)];
+        xn[v] = PAST ? __builtin_nontemporal_load(pn) : *pn;
         s1[v] = 0.f;
     }
     __builtin_amdgcn_s_waitcnt(0);   // everything requested so far has arrived (vmcnt = 0)
@@ -2804,8 +2810,11 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                 else hipLaunchKernelGGL((mlp_fused_ring_kernel<false, true>), grid, dim3(256), 0, s, fa);
             } else if (Bp >= 64 && Bp <= 192 && ctx->opt_fused_lds) {   // operands through LDS: 5 KB per 16 minibatch rows (at most 60 KB)
                 const size_t shm = (size_t)5 * (Bp / 16) * 1024;
-                if (cons) hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<true>), grid, dim3(256), shm, s, fa);
-                else hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<false>), grid, dim3(256), shm, s, fa);
+                const bool past = (i64)n * fa.K * fa.O * 4 > (192ll << 20);
+                if (cons && past) hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<true, true>), grid, dim3(256), shm, s, fa);
+                else if (cons) hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<true, false>), grid, dim3(256), shm, s, fa);
+                else if (past) hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<false, true>), grid, dim3(256), shm, s, fa);
+                else hipLaunchKernelGGL((mlp_fused_ring_lds_kernel<false, false>), grid, dim3(256), shm, s, fa);
             } else {
                 if (cons) hipLaunchKernelGGL((mlp_fused_ring_kernel<true, false>), grid, dim3(256), 0, s, fa);
                 else hipLaunchKernelGGL((mlp_fused_ring_kernel<false, false>), grid, dim3(256), 0, s, fa);

@@ -407,14 +407,21 @@ __global__ void __launch_bounds__(256) mlp_fwd_kernel(FwdArgs g)
 // pieces, whatever the prefetch distance).  One LDS buffer of (64 + 128) rows x 272 bytes (three workgroups per CU)
 // instead of two: the next chunk waits in registers while the current one is multiplied, and goes to LDS between
 // two barriers.  Rows 16-byte aligned and K % 8 == 0 (the VEC case of the kernel above); loads are branch-free
-// (clamped addresses; what lies outside the matrix is replaced by zero on its way to LDS).
+// (clamped addresses, a tile's base and 32 bits of a lane; what lies outside the matrix is replaced by zero on its way to LDS).
+// What bounds it is, where the chip is full, HBM (32 workers x 128 samples 6.0 TB/s between the first chunk and the last; the
+// first, and the results, take 12 us), else the chain of a chunk: its loads, LDS writes, LDS reads, with nobody else to run
+// meanwhile.  AHEAD2 shortens that chain: weights requested two chunks ahead, LDS operands read in batches ahead of the
+// matrix instructions, for 218 registers, i.e. two workgroups per CU.  us a step, without / with: one workgroup per CU or less, 16
+// workers x 3072-1024-10 x 128 178 / 162, 10 workers 142 / 127, 12 x 1024-1024-1024-10 x 128 178 / 165; more than two, 64 x 3072-1024-1024-10 x
+// 128 880 / 849, 48 x 3072-1024-10 x 128 440 / 428, 60 x 4096-256-10 x 80 231 / 225; between, where three fit anyway and twice the requests
+// only get in each other's way, 32 x 3072-1024-10 x 128 280 / 285, 20 x 128 205 / 207, 8 x 512 219 / 223: there it stays off.
 // grid (ceil(O / 64), ceil(B / 128), n), block 256 = 2 x 2 waves, each two 32 x 32 tiles.
 constexpr int KCW = 128;
 constexpr int PITCHW = KCW + 8;
 
 // BLOCKS: more than one block of samples; they share the weights, which then go through the caches.
-template <bool LAST, bool BLOCKS>
-__global__ void __launch_bounds__(256, 3) mlp_fwd_wide_kernel(FwdArgs g)
+template <bool LAST, bool BLOCKS, bool AHEAD2>
+__global__ void __launch_bounds__(256, AHEAD2 ? 2 : 3) mlp_fwd_wide_kernel(FwdArgs g)
 {
     constexpr int TO = 64, MBLK = 128, MT = 2, WQ = 8, AQ = 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -427,32 +434,39 @@ __global__ void __launch_bounds__(256, 3) mlp_fwd_wide_kernel(FwdArgs g)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, half = lane >> 5;
-    const float *Wg = g.X + (i64)w * g.ld + g.woff;
-    const bf16_t *Ag = g.act + (i64)w * g.B * g.lda;
+    const float *Wg = g.X + (i64)w * g.ld + g.woff + (i64)o0 * g.K;         // the workgroup's first row of weights
+    const bf16_t *Ag = g.act + ((i64)w * g.B + b0) * g.lda;                  // its first sample
 
-    f32x4 wreg[WQ];
+    struct Weights { f32x4 v[WQ]; };
+    Weights even, odd;   // chunks on their way (odd: AHEAD2)
     u32x4 areg[AQ];
     // unit u = tid + 256 q.  W: row u / 32, floats (u % 32) * 4 .. + 3 (a wave instruction: two rows x 512 bytes);
-    // A: row u / 16, elements (u % 16) * 8 .. + 7
-    auto fetch = [&](int k0) {
+    // A: row u / 16, elements (u % 16) * 8 .. + 7.  Offsets of the first chunk, bytes:
+    const int kw = (tid & 31) * 4, ka = (tid & 15) * 8;
+    unsigned woff[WQ], aoff[AQ];
 #pragma unroll
-        for (int q = 0; q < AQ; ++q) {
-            const int u = tid + 256 * q, b = b0 + (u >> 4), k = k0 + (u & 15) * 8;
-            areg[q] = *reinterpret_cast<const u32x4 *>(Ag + (i64)(b < g.B ? b : g.B - 1) * g.lda + (k < g.lda ? k : 0));
-        }
+    for (int q = 0; q < WQ; ++q) woff[q] = (unsigned)((min(o0 + weight_tile_row((tid + 256 * q) >> 5, g.K), g.O - 1) - o0) * g.K + kw) * 4u;
+#pragma unroll
+    for (int q = 0; q < AQ; ++q) aoff[q] = (unsigned)((min(b0 + ((tid + 256 * q) >> 4), g.B - 1) - b0) * g.lda + ka) * 2u;
+    auto fetch_a = [&](int k0) {   // (beyond the row: its first chunk, never used)
+        const unsigned k = k0 + ka < g.lda ? (unsigned)k0 * 2u : 0u;
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) areg[q] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(Ag) + (aoff[q] + k));
+    };
+    auto fetch_w = [&](int k0, Weights &wreg) {
+        const unsigned k = k0 + kw < g.K ? (unsigned)k0 * 4u : 0u;
 #pragma unroll
         for (int q = 0; q < WQ; ++q) {
-            const int u = tid + 256 * q, o = o0 + weight_tile_row(u >> 5, g.K), k = k0 + (u & 31) * 4;
-            const f32x4 *p = reinterpret_cast<const f32x4 *>(Wg + (i64)(o < g.O ? o : g.O - 1) * g.K + (k < g.K ? k : 0));
-            if (BLOCKS) wreg[q] = *p;
-            else wreg[q] = __builtin_nontemporal_load(p);
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(Wg) + (woff[q] + k));
+            if (BLOCKS) wreg.v[q] = *p;
+            else wreg.v[q] = __builtin_nontemporal_load(p);
         }
     };
-    auto stage = [&](int k0) {
+    auto stage = [&](int k0, const Weights &wreg) {
 #pragma unroll
         for (int q = 0; q < WQ; ++q) {
             const int u = tid + 256 * q, row = weight_tile_row(u >> 5, g.K), kq = (u & 31) * 4;
-            u32x2 p = {pack2(wreg[q].x, wreg[q].y), pack2(wreg[q].z, wreg[q].w)};
+            u32x2 p = {pack2(wreg.v[q].x, wreg.v[q].y), pack2(wreg.v[q].z, wreg.v[q].w)};
             if (!(o0 + row < g.O && k0 + kq < g.K)) p = (u32x2){0u, 0u};
             *reinterpret_cast<u32x2 *>(Wt + row * PITCHW + kq) = p;
         }
@@ -475,27 +489,71 @@ __global__ void __launch_bounds__(256, 3) mlp_fwd_wide_kernel(FwdArgs g)
     const int nchunks = (g.K + KCW - 1) / KCW;
     const int start = (int)((unsigned)(tile * 5 + w * 3) % (unsigned)nchunks);
     auto chunk_k = [&](int c) { const int cc = c + start; return (cc >= nchunks ? cc - nchunks : cc) * KCW; };
-    fetch(chunk_k(0));
-    stage(chunk_k(0));
+    const int last = nchunks - 1;
+    auto at = [&](int c) { return chunk_k(c < last ? c : last); };   // past the end: the last chunk again, never used
+    fetch_a(at(0));
+    fetch_w(at(0), even);
+    __builtin_amdgcn_sched_barrier(0);
+    if (AHEAD2) fetch_w(at(1), odd);
+    __builtin_amdgcn_sched_barrier(0);
+    stage(at(0), even);
     __syncthreads();
     const bf16_t *Wb = Wt + (wn * 32 + l32) * PITCHW + 8 * half;
     const bf16_t *Ab = At + (wm * MT * 32 + l32) * PITCHW + 8 * half;
-    for (int c = 0; c < nchunks; ++c) {
-        const int nxt = chunk_k(c + 1 < nchunks ? c + 1 : c);   // past the end: the last chunk again, never used
-        fetch(nxt);
+    // chunk c is multiplied; next holds the weights of chunk c + 1, free receives those of chunk c + 2 (AHEAD2; else both are one
+    // and receive chunk c + 1)
+    auto step = [&](int c, const Weights &next, Weights &free) {
+        fetch_a(at(c + 1));
+        __builtin_amdgcn_sched_barrier(0);   // in this order: the wait for the activations does not wait for the weights
+        fetch_w(at(c + (AHEAD2 ? 2 : 1)), free);
         __builtin_amdgcn_sched_barrier(0);   // the loads are on their way before the first LDS read
+        if constexpr (!AHEAD2) {
 #pragma unroll
-        for (int ks = 0; ks < KCW / 16; ++ks) {
-            const bf16x8 bw = frag(Wb + ks * 16);
+            for (int ks = 0; ks < KCW / 16; ++ks) {
+                const bf16x8 bw = frag(Wb + ks * 16);
 #pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                const bf16x8 aa = frag(Ab + m * 32 * PITCHW + ks * 16);
-                acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bw, acc[m], 0, 0, 0);
+                for (int m = 0; m < MT; ++m) {
+                    const bf16x8 aa = frag(Ab + m * 32 * PITCHW + ks * 16);
+                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bw, acc[m], 0, 0, 0);
+                }
+            }
+        } else {
+            // operands of two steps at a time, read ahead of the matrix instructions of the two before
+            bf16x8 fw[2][2], fa[2][2][MT];
+            auto read_ops = [&](int s, int ks) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    fw[s][i] = frag(Wb + (ks + i) * 16);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) fa[s][i][m] = frag(Ab + m * 32 * PITCHW + (ks + i) * 16);
+                }
+            };
+            read_ops(0, 0);
+#pragma unroll
+            for (int ks = 0; ks < KCW / 16; ks += 2) {
+                const int s = (ks >> 1) & 1;
+                if (ks + 2 < KCW / 16) read_ops(s ^ 1, ks + 2);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i][m], fw[s][i], acc[m], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         __syncthreads();   // every wave has read chunk c
-        stage(nxt);
+        stage(at(c + 1), next);
         __syncthreads();
+    };
+    if (AHEAD2) {
+        int c = 0;   // (steps in pairs with no branch between them: on every path the same requests follow a load)
+        for (; c + 1 < nchunks; c += 2) {
+            step(c, odd, even);
+            step(c + 1, even, odd);
+        }
+        if (c < nchunks) step(c, odd, even);
+    } else {
+        for (int c = 0; c < nchunks; ++c) step(c, even, even);
     }
 
     const int o = o0 + wn * 32 + l32;
@@ -1609,10 +1667,16 @@ dpsgd_status fwd_launch(hipStream_t s, int n, const FwdArgs &a, bool vec, bool l
         dim3 grid((unsigned)((a.O + 63) / 64), (unsigned)((a.B + 127) / 128), (unsigned)n);
         const size_t shm = (size_t)(64 + 128) * PITCHW * sizeof(bf16_t);
         const bool blocks = grid.y > 1;
-        if (last && blocks) hipLaunchKernelGGL((mlp_fwd_wide_kernel<true, true>), grid, dim3(256), shm, s, a);
-        else if (last) hipLaunchKernelGGL((mlp_fwd_wide_kernel<true, false>), grid, dim3(256), shm, s, a);
-        else if (blocks) hipLaunchKernelGGL((mlp_fwd_wide_kernel<false, true>), grid, dim3(256), shm, s, a);
-        else hipLaunchKernelGGL((mlp_fwd_wide_kernel<false, false>), grid, dim3(256), shm, s, a);
+        const i64 wgs = (i64)grid.x * grid.y * grid.z;
+        const bool ahead2 = wgs <= 256 || wgs > 512;   // (see there)
+#define DPSGD_WIDE(LAST, BLOCKS)                                                                                          \
+        if (ahead2) hipLaunchKernelGGL((mlp_fwd_wide_kernel<LAST, BLOCKS, true>), grid, dim3(256), shm, s, a);            \
+        else hipLaunchKernelGGL((mlp_fwd_wide_kernel<LAST, BLOCKS, false>), grid, dim3(256), shm, s, a)
+        if (last && blocks) { DPSGD_WIDE(true, true); }
+        else if (last) { DPSGD_WIDE(true, false); }
+        else if (blocks) { DPSGD_WIDE(false, true); }
+        else { DPSGD_WIDE(false, false); }
+#undef DPSGD_WIDE
         return hip_status(hipGetLastError());
     }
     dim3 grid((unsigned)((a.O + TO - 1) / TO), (unsigned)((a.B + MBLK - 1) / MBLK), (unsigned)n);

@@ -263,3 +263,38 @@ def test_class_layer_backward_in_one_launch_agrees_with_the_tiled_kernels(widths
         e = rel_err(out[0][:, sl], out[1][:, sl])
         print(f"  {p.name}: one launch vs tiled kernels {e:.3e}", flush=True)
         assert e < 5e-4
+
+
+@pytest.mark.parametrize("widths,batch", [((72, 1024, 10), 65), ((264, 1000, 10), 100), ((392, 1024, 3), 128), ((136, 1024, 10), 129)])
+def test_forward_of_more_than_64_samples_is_the_same_at_any_fill_of_the_chip(widths, batch):
+    """One, two or more workgroups per CU take the weights one or two chunks ahead, over one chunk of the contraction, an odd
+    and an even number of them, the last one cut short: a worker's loss and class layer come out bit for bit the same."""
+    d = synth.model_dim(MODEL_MLP, widths)
+    ld = synth.padded_stride(d)
+    cls = widths[-1] * widths[-2]
+    got = []
+    for n in (9, 20, 36):
+        cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n)
+        g = torch.Generator().manual_seed(3)
+        X = torch.zeros(n, ld)
+        X[:9, :d] = 0.05 * torch.randn(9, d, generator=g)
+        inp = torch.randn(9, batch, widths[0], generator=g).to(torch.bfloat16)
+        lab = torch.randint(0, widths[-1], (9, batch), generator=g).to(torch.int32)
+        inp = torch.cat([inp, inp[:1].expand(n - 9, -1, -1)]).contiguous().cuda()
+        lab = torch.cat([lab, lab[:1].expand(n - 9, -1)]).contiguous().cuda()
+        X[9:] = X[0]
+        X = X.cuda()
+        G, loss = torch.zeros_like(X), torch.zeros(n, device="cuda")
+        with B.Dpsgd(n, d, topo_for(cfg), 0.1, ld=ld) as ctx:
+            ctx.grad(B.Model(MODEL_MLP, widths, compute_bf16=True), X, inp, lab, batch, G, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+        off = d - cls - widths[-1]
+        got.append((loss[:9].cpu(), G[:9, off:off + cls].cpu()))
+        if n == 9:
+            x, a = X[0, :d].cpu().double(), inp[0].cpu().double()
+            h = (a @ x[:widths[0] * widths[1]].to(torch.bfloat16).double().view(widths[1], widths[0]).t() + x[widths[0] * widths[1]:off]).clamp_min(0)
+            z = h.to(torch.bfloat16).double() @ x[off:off + cls].to(torch.bfloat16).double().view(widths[2], widths[1]).t() + x[off + cls:]
+            ref = torch.nn.functional.cross_entropy(z, lab[0].cpu().long())
+            assert abs(float(loss[0]) - float(ref)) < 2e-3 * float(ref)
+    for l, c in got[1:]:
+        assert torch.equal(l, got[0][0]) and torch.equal(c, got[0][1])

@@ -1993,26 +1993,55 @@ constexpr int ROWS_PLANE = 66;   // 16-byte units per (sample octet, tile) plane
 // 0-31 / 32-63) and the wave's eight pieces lie 32 KB apart, which the HBM channels serve faster (see
 // mix_ring_fat_kernel): an in-place walk with this kernel's traffic moves 6.1 TB/s that way against 5.75.
 // The same elements get the same sums: the three maps give the same bits.
+template <int RS> struct RowMap {
+    // RS 3 (rows of 4, 8 or 12 KB: K a multiple of 1024): the workgroup owns 16 rows of a block of 32, wave rows 8 apart
+    // (a multiple of 32 KB), whole 1 KB pieces: rows 4 half + wave + 8 r of block blockIdx.y / 2, half = blockIdx.y % 2
+    // element (r, t) of a lane: row o0 + row0 + rstep r, column k0 + col0 + t
+    //   RS 0: row0 = 4 wave, rstep = 1, col0 = 4 lane
+    //   RS 2: row0 = wave / 2 + 2 (lane / 32), rstep = 4 (rows wave / 2 + 2 j, j = 2 r + lane / 32), col0 = 128 (wave % 2) + 4 (lane % 32)
+    //   RS 1: row0 = 8 (wave / 2) + lane / 32, rstep = 2 (rows 8 (wave / 2) + j)
+    static constexpr int rstep = RS == 0 ? 1 : RS == 2 ? 4 : RS == 1 ? 2 : 8;
+    static constexpr int sstep = RS == 3 ? 4 : rstep;
+    int lane, k0, o0, row0, slot0, col0;   // the workgroup's 16 rows of dZ^T sit in LDS slots 0 .. 15; slot of a lane's row r: slot0 + sstep r
+    __device__ __forceinline__ RowMap(int l, int wave) : lane(l)
+    {
+        k0 = blockIdx.x * 256;
+        o0 = RS == 3 ? (blockIdx.y >> 1) * 32 : blockIdx.y * 16;
+        row0 = RS == 0 ? 4 * wave : RS == 2 ? (wave >> 1) + 2 * (lane >> 5) : RS == 1 ? 8 * (wave >> 1) + (lane >> 5) : 4 * (int)(blockIdx.y & 1) + wave;
+        slot0 = RS == 3 ? wave : row0;
+        col0 = (RS == 0 || RS == 3) ? 4 * lane : 128 * (wave & 1) + 4 * (lane & 31);
+    }
+    // operands in fragment order (tfrag_off) with Bp = 32: per 32 rows [sample group of 16][half][row][8 samples].
+    // Activations: the block of columns k0 .. k0 + 255 is 1024 consecutive 16-byte units; unit u = tid + 256 q is
+    // column (u / 128) * 32 + u % 32, octet (u / 32) % 4, and goes to plane (octet, column % 4), slot column / 4.
+    __device__ __forceinline__ const u32x4 *activations(const FusedArgs &a) const
+    {
+        return reinterpret_cast<const u32x4 *>(a.at + (i64)(k0 >> 5) * 1024) + threadIdx.x;
+    }
+    __device__ __forceinline__ int staged_slot() const
+    {
+        const int tid = threadIdx.x;
+        return (((tid >> 5) & 3) * 4 + (tid & 3)) * ROWS_PLANE + (tid >> 7) * 8 + ((tid & 31) >> 2);
+    }
+    // dZ^T: lane (octet = lane / 16, row = lane % 16) of every wave fetches one unit; wave 0 writes them.
+    // Slot lane % 16 holds row (o0 % 32) + slot, or (RS 3) row 4 half + slot % 4 + 8 (slot / 4) of the block
+    __device__ __forceinline__ const u32x4 *deltas(const FusedArgs &a) const
+    {
+        const int aoc = lane >> 4;
+        const int arow = RS == 3 ? 4 * (int)(blockIdx.y & 1) + (lane & 3) + 8 * ((lane & 15) >> 2) : (o0 & 31) + (lane & 15);
+        return reinterpret_cast<const u32x4 *>(a.dzt + ((i64)(o0 >> 5) * 2 + (aoc >> 1)) * 512 + (aoc & 1) * 256 + arow * 8);
+    }
+};
+
 template <bool CONS, bool SHADOW, int RS>
 __global__ void __launch_bounds__(256, 3) mlp_fused_ring_rows_kernel(FusedArgs a)
 {
     __shared__ u32x4 bt[2][16 * ROWS_PLANE];   // [octet][tile t][lane]: samples 8 octet .. + 7 of column 4 lane + t
     __shared__ u32x4 at[2][64];                // [octet][row 0..15] of dZ^T
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // RS 3 (rows of 4, 8 or 12 KB: K a multiple of 1024): the workgroup owns 16 rows of a block of 32, wave rows 8 apart
-    // (a multiple of 32 KB), whole 1 KB pieces: rows 4 half + wave + 8 r of block blockIdx.y / 2, half = blockIdx.y % 2
-    const int k0 = blockIdx.x * 256, o0 = RS == 3 ? (blockIdx.y >> 1) * 32 : blockIdx.y * 16;
-    // element (r, t) of this lane: row o0 + row0 + rstep r, column k0 + col0 + t
-    //   RS 0: row0 = 4 wave, rstep = 1, col0 = 4 lane
-    //   RS 2: row0 = wave / 2 + 2 (lane / 32), rstep = 4 (rows wave / 2 + 2 j, j = 2 r + lane / 32), col0 = 128 (wave % 2) + 4 (lane % 32)
-    //   RS 1: row0 = 8 (wave / 2) + lane / 32, rstep = 2 (rows 8 (wave / 2) + j)
-    const int row0 = RS == 0 ? 4 * wave : RS == 2 ? (wave >> 1) + 2 * (lane >> 5) : RS == 1 ? 8 * (wave >> 1) + (lane >> 5)
-                                                                                   : 4 * (int)(blockIdx.y & 1) + wave;
-    constexpr int rstep = RS == 0 ? 1 : RS == 2 ? 4 : RS == 1 ? 2 : 8;
-    // the workgroup's 16 rows of dZ^T sit in LDS slots 0 .. 15; slot of this lane's row r: slot0 + sstep r
-    const int slot0 = RS == 3 ? wave : row0;
-    constexpr int sstep = RS == 3 ? 4 : rstep;
-    const int col0 = (RS == 0 || RS == 3) ? 4 * lane : 128 * (wave & 1) + 4 * (lane & 31);
+    const RowMap<RS> m(lane, wave);
+    const int k0 = m.k0, o0 = m.o0, row0 = m.row0, slot0 = m.slot0, col0 = m.col0;
+    constexpr int rstep = RowMap<RS>::rstep, sstep = RowMap<RS>::sstep;
     const int bslot_read = col0 >> 2;   // this lane's slot in a plane of the activation buffer
     const i64 rstride = (i64)rstep * a.K;
     float *xt = a.X + a.woff + (i64)(o0 + row0) * a.K + k0 + col0;
@@ -2023,17 +2052,8 @@ __global__ void __launch_bounds__(256, 3) mlp_fused_ring_rows_kernel(FusedArgs a
             x[4 * r] = v.x; x[4 * r + 1] = v.y; x[4 * r + 2] = v.z; x[4 * r + 3] = v.w;
         }
     };
-    // operands in fragment order (tfrag_off) with Bp = 32: per 32 rows [sample group of 16][half][row][8 samples].
-    // Activations: the block of columns k0 .. k0 + 255 is 1024 consecutive 16-byte units; unit u = tid + 256 q is
-    // column (u / 128) * 32 + u % 32, octet (u / 32) % 4, and goes to plane (octet, column % 4), slot column / 4.
-    const u32x4 *bsrc = reinterpret_cast<const u32x4 *>(a.at + (i64)(k0 >> 5) * 1024) + tid;
-    const int bslot = (((tid >> 5) & 3) * 4 + (tid & 3)) * ROWS_PLANE + (tid >> 7) * 8 + ((tid & 31) >> 2);
-    // dZ^T: lane (octet = lane / 16, row = lane % 16) of every wave fetches one unit; wave 0 writes them
-    const int aoc = lane >> 4;
-    // slot lane % 16 holds row (o0 % 32) + slot, or (RS 3) row 4 half + slot % 4 + 8 (slot / 4) of the block
-    const int arow = RS == 3 ? 4 * (int)(blockIdx.y & 1) + (lane & 3) + 8 * ((lane & 15) >> 2) : (o0 & 31) + (lane & 15);
-    const u32x4 *asrc = reinterpret_cast<const u32x4 *>(
-        a.dzt + ((i64)(o0 >> 5) * 2 + (aoc >> 1)) * 512 + (aoc & 1) * 256 + arow * 8);
+    const u32x4 *bsrc = m.activations(a), *asrc = m.deltas(a);
+    const int bslot = m.staged_slot();
     const i64 b_worker = (i64)a.K * 4, a_worker = (i64)a.O * 4;   // 16-byte units per worker (32 samples x 2 bytes)
     u32x4 breg[4], areg;
     auto fetch_ops = [&](int worker) {
@@ -2130,6 +2150,158 @@ __global__ void __launch_bounds__(256, 3) mlp_fused_ring_rows_kernel(FusedArgs a
         if (++i >= a.n) break;
         step(i, td, ta, tb, tc);
         if (++i >= a.n) break;
+    }
+    if (CONS) {
+        float m2 = (s2[0] + s2[1]) + (s2[2] + s2[3]);
+        const float inv_n = 1.0f / (float)a.n;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m2 -= s1[v] * s1[v] * inv_n;
+        double t = (double)m2;
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        if (lane == 0) a.partials[((i64)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave] = t;
+    }
+}
+
+// The same walk over a ring whose workers also know the worker farthest away, i + n / 2: two walks half a ring apart, which
+// hand each other what the farthest worker of each is.  Step i has workers i and i + n / 2, whose tiles (those of the workers
+// before and behind them, too) are in the wave's registers: each is the other's far neighbour, and the walks end where the other
+// began.  Tiles, element maps and operands as in mlp_fused_ring_rows_kernel; the operands of the two workers share one set of registers on
+// their way to LDS.  Twice the tiles make 2 workgroups per CU.  Two tiles (before the first workers) are read twice: 1 / n
+// of the traffic.
+// What bounds it is HBM: 16 workers, 4096 x 4096, 376 us for 2.15 GB (5.7 TB/s; 6.1 with the tiles read twice).  The slab kernel below, which
+// reads all n tiles before it writes the first, in pieces of 256 bytes and less, takes 452; it stays for other minibatches and
+// widths.  us a step of 3072-4096-4096-10 x 32 samples, slab / walk: 4 workers 667 / 418, 8 860 / 664, 16 1317 / 1197, 32 2748 / 2320, 64 5925 /
+// 4510; 16 x 1024-1024-10 81 / 79, 30 x 2304-1024-10 227 / 216; rows that share lines, 16 x 3072-4096-4096-10 2127 / 1668.
+// LINES: the row pieces are whole 64-byte halves of lines (fused_lines) and are written past the caches.
+// grid (K / 256, O / 16), block 256, n even and at least 4; dynamic LDS kChordLds.
+constexpr size_t kChordLds = (size_t)2 * 2 * (16 * ROWS_PLANE + 64) * 16;
+
+template <bool CONS, bool LINES, int RS>
+__global__ void __launch_bounds__(256, 2) mlp_fused_chord_rows_kernel(FusedArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char chord_lds[];
+    typedef u32x4 Plane[16 * ROWS_PLANE];
+    Plane *bt = reinterpret_cast<Plane *>(chord_lds);                                 // [2 buffers][2 walks]: activations
+    typedef u32x4 Rows[64];
+    Rows *at = reinterpret_cast<Rows *>(chord_lds + sizeof(Plane) * 4);               // ... and rows of dZ^T
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = a.n / 2;
+    const RowMap<RS> m(lane, wave);
+    const i64 rstride = (i64)m.rstep * a.K;
+    float *xt = a.X + a.woff + (i64)(m.o0 + m.row0) * a.K + m.k0 + m.col0;
+    const u32x4 *bsrc = m.activations(a), *asrc = m.deltas(a);
+    const int bslot = m.staged_slot();
+    const i64 b_worker = (i64)a.K * 4, a_worker = (i64)a.O * 4;   // 16-byte units per worker (32 samples x 2 bytes)
+    u32x4 breg[4], areg;
+    auto fetch_ops = [&](int worker) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) breg[q] = bsrc[worker * b_worker + 256 * q];
+        areg = asrc[worker * a_worker];
+    };
+    auto stage_ops = [&](int buf, int c) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bt[2 * buf + c][bslot + 16 * q] = breg[q];
+        if (wave == 0) at[2 * buf + c][lane] = areg;
+    };
+    struct Tiles { float v[2][16]; };   // of the two walks
+    auto load_tile = [&](const float *p, i64 rs, float (&x)[16]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4 *>(p + r * rs));
+            x[4 * r] = v.x; x[4 * r + 1] = v.y; x[4 * r + 2] = v.z; x[4 * r + 3] = v.w;
+        }
+    };
+    // four buffers rotate through the roles, as in the ring kernel
+    Tiles ta, tb, tc, td, first;
+    float s1[16], s2[4] = {0.f, 0.f, 0.f, 0.f};
+    fetch_ops(0);
+    load_tile(xt + (i64)(a.n - 1) * a.ld, rstride, ta.v[0]);
+    load_tile(xt + (i64)(h - 1) * a.ld, rstride, ta.v[1]);
+    load_tile(xt, rstride, tb.v[0]);
+    load_tile(xt + (i64)h * a.ld, rstride, tb.v[1]);
+    load_tile(xt + a.ld, rstride, tc.v[0]);
+    load_tile(xt + (i64)((h + 1) % a.n) * a.ld, rstride, tc.v[1]);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        first.v[0][v] = tb.v[0][v];
+        first.v[1][v] = tb.v[1][v];
+        s1[v] = 0.f;
+    }
+    stage_ops(0, 0);
+    fetch_ops(h);
+    stage_ops(0, 1);
+    fetch_ops(1);
+    __syncthreads();
+    // Workers i and i + h.  The fetches are unconditional (exact wait counts): past the last step the operand fetch repeats
+    // the last worker's and the tile fetch reads one cached line of the operand array (values never used).
+    auto step = [&](int i, const Tiles &xm, const Tiles &xc, const Tiles &xn, Tiles &xf) {
+        const int buf = i & 1, nw = i + 1 < h ? i + 1 : h - 1;
+        const bool far = i + 2 < h, last = i + 1 == h;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float *src = far ? xt + (i64)(i + 2 + c * h) * a.ld : reinterpret_cast<const float *>(a.dzt) + 4 * lane;
+            load_tile(src, far ? rstride : 0, xf.v[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            f32x4 acc[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int oc = 0; oc < 4; ++oc) {
+                const u32x4 av = at[2 * buf + c][oc * 16 + m.slot0 + m.sstep * (lane & 3)];
+                const s16x4 alo = __builtin_bit_cast(s16x4, u32x2{av.x, av.y}), ahi = __builtin_bit_cast(s16x4, u32x2{av.z, av.w});
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const u32x4 bv = bt[2 * buf + c][(oc * 4 + t) * ROWS_PLANE + (m.col0 >> 2)];
+                    acc[t] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(alo, __builtin_bit_cast(s16x4, u32x2{bv.x, bv.y}), acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ahi, __builtin_bit_cast(s16x4, u32x2{bv.z, bv.w}), acc[t], 0, 0, 0);
+                }
+            }
+            float *dst = xt + (i64)(i + c * h) * a.ld;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                f32x4 out;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int v = 4 * r + t;
+                    const float nxt = last ? first.v[1 - c][v] : xn.v[c][v];   // a walk ends where the other began
+                    const float prv = xm.v[c][v], own = xc.v[c][v], far_x = xc.v[1 - c][v];
+                    // one product, then fused multiply-adds, in the order of the workers as the slab and mix kernels have it; the
+                    // first worker's predecessor is the last, and the last's successor the first
+                    const bool wraps = c == 0 ? i == 0 : last;
+                    float mix = a.w * (c == 0 ? (wraps ? own : prv) : (wraps ? nxt : far_x));
+                    mix = __builtin_fmaf(a.w, c == 0 ? (wraps ? nxt : own) : (wraps ? far_x : prv), mix);
+                    mix = __builtin_fmaf(a.w, c == 0 ? (wraps ? far_x : nxt) : (wraps ? prv : own), mix);
+                    mix = __builtin_fmaf(a.w, c == 0 ? (wraps ? prv : far_x) : (wraps ? own : nxt), mix);
+                    const float o = __builtin_fmaf(-a.gamma, acc[t][r], mix);
+                    out[t] = o;
+                    if (CONS) {
+                        const float e = o - first.v[0][v];
+                        s1[v] += e;
+                        s2[t] += e * e;
+                    }
+                }
+                f32x4_a4 *p = reinterpret_cast<f32x4_a4 *>(dst + (i64)r * rstride);
+                if (LINES) __builtin_nontemporal_store((f32x4_a4)out, p);
+                else *p = out;
+            }
+            // the next workers' operands: walk 0's were requested half a step ago, walk 1's are requested now, and the other way round
+            // (every wave has read this buffer's previous contents before the barrier that ended step i - 1)
+            stage_ops(buf ^ 1, c);
+            if (c == 0) fetch_ops(nw + h);
+            else fetch_ops(i + 2 < h ? i + 2 : h - 1);
+        }
+        __syncthreads();
+    };
+    for (int i = 0;;) {
+        step(i, ta, tb, tc, td);
+        if (++i >= h) break;
+        step(i, tb, tc, td, ta);
+        if (++i >= h) break;
+        step(i, tc, td, ta, tb);
+        if (++i >= h) break;
+        step(i, td, ta, tb, tc);
+        if (++i >= h) break;
     }
     if (CONS) {
         float m2 = (s2[0] + s2[1]) + (s2[2] + s2[3]);
@@ -2548,6 +2720,12 @@ bool slab_fusion(const dpsgd_ctx *ctx)
     return ctx->opt_fused_slab == 2 || !torus_cols(ctx);
 }
 
+// A ring with a link to the farthest worker has a walk of its own for minibatches of at most 32 samples and whole 1 KB row pieces.
+bool chord_walk(const dpsgd_ctx *ctx, int K, int Bp)
+{
+    return slab_fusion(ctx) && ctx->opt_fused_slab == 1 && ctx->topo_kind == DPSGD_TOPO_RING_CHORD && Bp == 32 && K % 256 == 0;
+}
+
 bool layer_fusable(const dpsgd_ctx *ctx, int K, int O, i64 woff)
 {
     if (ctx->opt_mix_force_csr || woff < 0 || (i64)K * O < (1 << 20)) return false;
@@ -2883,6 +3061,37 @@ dpsgd_status run_mlp_bf16(dpsgd_ctx *ctx, const dpsgd_model_desc &m, float *X, c
                 if (cons) hipLaunchKernelGGL((mlp_fused_ring_kernel<true, false>), grid, dim3(256), 0, s, fa);
                 else hipLaunchKernelGGL((mlp_fused_ring_kernel<false, false>), grid, dim3(256), 0, s, fa);
             }
+        } else if (chord_walk(ctx, K, Bp)) {
+            FusedArgs fa{};
+            fa.X = X; fa.ld = ctx->ld; fa.woff = woff[l]; fa.dzt = ws.dzt[l + 1]; fa.at = actt[l];
+            fa.n = n; fa.K = K; fa.O = O; fa.Bp = Bp; fa.w = ctx->vals[0]; fa.gamma = ctx->gamma;
+            fa.partials = ctx->d_partials + nparts;
+            const dim3 grid((unsigned)(K / 256), (unsigned)(O / 16));
+            np = (i64)grid.x * grid.y * 4;
+            if (nparts + np > ctx->partials_cap - 256) return DPSGD_EINVAL;
+            const bool lines = fused_lines(ctx, X, woff[l]);
+            const int rs = K == 8192 ? 1 : K == 4096 ? 2 : K % 1024 == 0 ? 3 : 0;   // as on the ring
+#define DPSGD_CHORD_ONE(CONS, LINES, RS)                                                                                       \
+    do {                                                                                                                       \
+        auto kern = mlp_fused_chord_rows_kernel<CONS, LINES, RS>;                                                              \
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,              \
+                                (int)kChordLds) != hipSuccess)                                                                 \
+            return DPSGD_EDEVICE;                                                                                              \
+        hipLaunchKernelGGL(kern, grid, dim3(256), kChordLds, s, fa);                                                           \
+    } while (0)
+#define DPSGD_CHORD(RS)                                             \
+    do {                                                            \
+        if (cons && lines) DPSGD_CHORD_ONE(true, true, RS);         \
+        else if (cons) DPSGD_CHORD_ONE(true, false, RS);            \
+        else if (lines) DPSGD_CHORD_ONE(false, true, RS);           \
+        else DPSGD_CHORD_ONE(false, false, RS);                     \
+    } while (0)
+            if (rs == 1) DPSGD_CHORD(1);
+            else if (rs == 2) DPSGD_CHORD(2);
+            else if (rs == 3) DPSGD_CHORD(3);
+            else DPSGD_CHORD(0);
+#undef DPSGD_CHORD
+#undef DPSGD_CHORD_ONE
         } else if (slab_fusion(ctx)) {
             const bool lines = fused_lines(ctx, X, woff[l]);
             FusedSlabArgs fa{};

@@ -134,6 +134,20 @@ def test_step_mlp_bf16_any_topology_through_lds(topology, n, dims, widths, batch
     step_case(shrink(base, widths=widths, batch=batch, n=n, **kw), options=options, expect_fused=True)
 
 
+@pytest.mark.parametrize("n,widths,batch,options", [
+    (4, (1024, 1024, 10), 32, ()),                  # two steps of the walk: every neighbour wraps around; rows 8 apart
+    (6, (768, 1376, 10), 20, ()),                   # three steps, rows side by side, a ragged minibatch
+    (10, (4096, 256, 10), 7, ()),                   # five steps, pieces of 512 bytes two rows apart
+    (4, (8192, 128, 10), 32, ()),                   # ... one row apart
+    (16, (1024, 1024, 1024, 10), 32, ()),           # two fused layers
+    (64, (1024, 1024, 10), 32, ()),                 # the most workers
+    (8, (1024, 1024, 10), 32, (("fused_slab", 2),)),   # the slab kernel instead: [16][128] tiles
+])
+def test_step_mlp_bf16_ring_chord_walk(n, widths, batch, options):
+    """Ring with a link to the farthest worker, at most 32 samples: two walks half a ring apart in one kernel."""
+    step_case(shrink(CONFIGS[2], widths=widths, batch=batch, n=n, topology="ring_chord"), options=options, expect_fused=True)
+
+
 def test_step_mlp_bf16_csr_topologies_through_lds():
     """General sparse W handed over as CSR: a hypercube (degree 4), the complete graph (every row combines all
     tiles) and a random symmetric doubly stochastic matrix with unequal weights."""

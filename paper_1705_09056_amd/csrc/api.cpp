@@ -346,6 +346,8 @@ dpsgd_status dpsgd_set_option(dpsgd_ctx *ctx, const char *key, int64_t value)
         ctx->opt_conv_block = value ? 1 : 0;
     } else if (k == "conv_bwd") {
         ctx->opt_conv_bwd = value ? 1 : 0;
+    } else if (k == "conv_down") {
+        ctx->opt_conv_down = value ? 1 : 0;
     } else if (k == "time_fused") {
         ctx->opt_time_fused = value ? 1 : 0;
     } else {

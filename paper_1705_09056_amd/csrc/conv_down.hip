@@ -1,0 +1,296 @@
+// Backward of the convolution of stride 2 that opens a stage of the CNN (gfx950): weight gradient, bias gradient and data gradient,
+// with the shortcut's delta added, in one launch.
+//   dW = sum over output pixels of delta x activation at (2 y + ky - 1, 2 x + kx - 1)
+//   din(y, x) = [in > 0] (sum over the taps that meet an output pixel there + the block output's delta at even y, x)
+// A workgroup owns some images of one worker and takes NI of them at a time, whole, activation and delta pixel-major in LDS as in
+// conv_bwd.hip, and two buffers of each take turns.  Every wave forms its share of the weight gradient, then of the data
+// gradient.
+// An input pixel with even coordinates meets one tap, one with an odd one two, with two odd ones four: nine matrix instructions for the
+// four pixels where a convolution over the delta with zeros inserted (conv3x3_mfma_kernel) takes 36, and as the pixels of
+// a row at even columns are the rows of one tile and those at odd columns of another, a lane ends up with 8
+// consecutive pixels.  Four LDS reads (delta rows r and r + 1, columns from x and x + 1 on) serve all nine.  The terms left out are products with
+// zero: the same bits.  The mask is the activation in LDS; the delta of the block output is the only other operand.
+// Error of the weight gradient's sums: as conv_bwd.hip (chains over the workgroup's images).
+// What bounds it: HBM and, with one workgroup of two waves per SIMD on a CU, the latency of its LDS reads.  112 workers x 32 images: 16
+// channels on 32 x 32 pixels 72 us (321 MB, 4.5 TB/s), 32 on 16 x 16 42 us; the two launches it replaces, which read the deltas twice and the
+// activations as well as their sign bitmap, took 118 (43 + 75) and 94 (35 + 59).  A gradient and mix 2123 -> 2026, 16 workers x 32 images of
+// 28 x 28, 2 blocks a stage, 426 -> 399.  Registers: 218 and 238 of 256.
+#include "conv_image.h"
+
+namespace dpsgd {
+namespace {
+
+struct ConvDownArgs {
+    const bf16_t *dv;     // delta of the output [n*B][2 CI][W/2][W/2]
+    const bf16_t *in;     // the convolution's input [n*B][CI][W][W]
+    const bf16_t *scd;    // delta of the block output, as dv
+    bf16_t *din;          // as in
+    const bf16_t *wd;     // packed data-gradient operands [n][9 CI/16][CI/16][64][8]
+    float *part;          // partial sums [n][splits][wgrad_partial_size(2 (CI/16)^2, 1)]
+    int B, splits;
+};
+
+// Bytes of an image of the delta in LDS: no halo above and left, one zero column and row right and below
+__host__ __device__ constexpr int down_delta_lds(int CO, int Wo) { return (Wo + 1) * row_pixels(CO, Wo) * 2 * CO; }
+constexpr int down_images(int CI) { return CI == 16 ? 1 : 2; }
+constexpr size_t down_lds(int CI, int W) { return (size_t)2 * down_images(CI) * (image_lds(CI, W, W) + down_delta_lds(2 * CI, W / 2)); }
+
+template <int CI, int W>
+__global__ void __launch_bounds__(512, 2) conv_down_bwd_kernel(ConvDownArgs a)
+{
+    constexpr int NT = 512, NI = down_images(CI), CO = 2 * CI, Wo = W / 2, HW = W * W, HWo = Wo * Wo;
+    constexpr int PXA = 2 * CI, ROWA = row_pixels(CI, W) * PXA, IMA = image_lds(CI, W, W);
+    constexpr int PXD = 2 * CO, ROWD = row_pixels(CO, Wo) * PXD, IMD = down_delta_lds(CO, Wo);
+    constexpr int BUF = NI * (IMA + IMD), DELTA = NI * IMA;   // a buffer: the activations, then the deltas
+    constexpr int CTI = CI / 16, CTO = CO / 16, KSPLIT = 8 / (CTI * CTO), NH = CO / 32;
+    static_assert(KSPLIT >= 1 && NI * (CI / 8) * (HW / 4) == NT, "every tile has a wave, every thread a staging task");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int sp = blockIdx.x, w = blockIdx.y;
+    if ((gridDim.y & 7) == 0) {   // all workgroups of a worker on one XCD
+        const unsigned id = blockIdx.x + gridDim.x * blockIdx.y, xcd = id & 7, slot = id >> 3;
+        w = (int)((slot / gridDim.x) * 8 + xcd);
+        sp = (int)(slot % gridDim.x);
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, g = lane >> 4;
+    const int lo = (int)((i64)a.B * sp / a.splits), hi = (int)((i64)a.B * (sp + 1) / a.splits);
+    const i64 img0 = (i64)w * a.B;
+
+    // ---- staging: a task is 4 pixels of 8 channels of one image; activations: every thread one, deltas: half of the threads
+    constexpr int TA = (CI / 8) * (HW / 4), TD = (CO / 8) * (HWo / 4);
+    const int ima = tid / TA, cta = tid % TA / (HW / 4), pxa = tid % (HW / 4) * 4;
+    const bool dtask = tid < NI * TD;
+    const int td = dtask ? tid : 0, imd = td / TD, ctd = td % TD / (HWo / 4), pxd = td % (HWo / 4) * 4;
+    int sa[4], sd[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int ca = pxa % W + 1 + j, cd = pxd % Wo + j;
+        sa[j] = ima * IMA + (pxa / W + 1) * ROWA + ca * PXA + ((cta ^ swizzle<CI>(ca)) << 4);
+        sd[j] = DELTA + imd * IMD + pxd / Wo * ROWD + cd * PXD + ((ctd ^ swizzle<CO>(cd)) << 4);
+    }
+    struct Stage { u32x2 v[8]; };
+    Stage va, vd;
+    // (no branch around the loads: past the last image it is fetched again, and zeros go to LDS)
+    auto fetch = [&](int i) {
+        const int ia = i + ima < hi ? i + ima : hi - 1, id = i + imd < hi ? i + imd : hi - 1;
+        const bf16_t *pa = a.in + ((img0 + ia) * CI + cta * 8) * HW + pxa, *pd = a.dv + ((img0 + id) * CO + ctd * 8) * HWo + pxd;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) va.v[c] = *reinterpret_cast<const u32x2 *>(pa + c * HW);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) vd.v[c] = *reinterpret_cast<const u32x2 *>(pd + c * HWo);
+    };
+    auto put = [&](const Stage &st, unsigned char *buf, const int (&off)[4], bool there) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            unsigned d[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned l = j < 2 ? st.v[2 * k].x : st.v[2 * k].y, h = j < 2 ? st.v[2 * k + 1].x : st.v[2 * k + 1].y;
+                d[k] = there ? __builtin_amdgcn_perm(h, l, (j & 1) ? 0x07060302u : 0x05040100u) : 0u;
+            }
+            *reinterpret_cast<u32x4 *>(buf + off[j]) = (u32x4){d[0], d[1], d[2], d[3]};
+        }
+    };
+    auto commit = [&](unsigned char *buf, int i) {
+        put(va, buf, sa, NI == 1 || i + ima < hi);
+        if (dtask) put(vd, buf, sd, NI == 1 || i + imd < hi);
+    };
+
+    // ---- weight gradient: groups of 32 output pixels (R32 rows), both operands by transposing reads
+    constexpr int R32 = 32 / Wo, G = HWo / 32;
+    const int co = wave % CTO, ci = wave / CTO % CTI, kq = wave / (CTO * CTI);
+    const int q4 = n16 & 3, orow = 4 * g / Wo, ocol = 4 * g % Wo + (n16 >> 2);   // this lane's pixel of the transposing reads
+    const int doff = orow * ROWD + ocol * PXD + (((2 * co + (q4 >> 1)) ^ swizzle<CO>(ocol)) << 4) + (q4 & 1) * 8;
+    int aoff[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+        const int col = 2 * ocol + kx;
+        aoff[kx] = 2 * orow * ROWA + col * PXA + (((2 * ci + (q4 >> 1)) ^ swizzle<CI>(col)) << 4) + (q4 & 1) * 8;
+    }
+    auto pixels = [&](const unsigned char *p, int half) { return __builtin_bit_cast(bf16x8, read_transposed(p, p + half)); };
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+    f32x4 sum[9], bsum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) sum[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto wgrad = [&](const unsigned char *buf) {
+        constexpr int per = NI * G / KSPLIT;
+#pragma unroll 1
+        for (int q = kq * per; q < (kq + 1) * per; ++q) {
+            const unsigned char *dp = buf + DELTA + q / G * IMD + q % G * R32 * ROWD, *ap = buf + q / G * IMA + q % G * 2 * R32 * ROWA;
+            const bf16x8 d = pixels(dp + doff, 16 / Wo * ROWD);
+            bf16x8 b[9];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) b[k] = pixels(ap + aoff[k % 3] + k / 3 * ROWA, 2 * (16 / Wo) * ROWA);
+            __builtin_amdgcn_sched_barrier(0);   // every operand is on its way before the first is waited for
+            if (ci == 0) bsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, ones, bsum, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) sum[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d, b[k], sum[k], 0, 0, 0);
+        }
+    };
+
+    // ---- data gradient: units of 16 delta pixels (16 / Wo rows), i.e. as many pairs of input rows
+    constexpr int RU = 16 / Wo, UI = HWo / 16, U = NI * UI, DS = 8 / CTI;   // units of an image, of all, waves that share them
+    const int dt = wave % CTI, dq = wave / CTI, o = 16 * dt + n16;
+    bf16x8 wf[9 * NH];   // [tap, reversed][32 channels]
+    {
+        const bf16_t *wd = a.wd + (i64)w * (9 * NH * CTI * 512) + dt * 512 + lane * 8;
+#pragma unroll
+        for (int s = 0; s < 9 * NH; ++s) wf[s] = *reinterpret_cast<const bf16x8 *>(wd + s * CTI * 512);
+    }
+    int foff[2];   // operand rows from column x and x + 1 on; channels 32 .. 63: ^ 64
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int col = n16 % Wo + c;
+        foff[c] = n16 / Wo * ROWD + col * PXD + ((g ^ swizzle<CO>(col)) << 4);
+    }
+    // a lane's 8 pixels of channel o: row 2 (first row + gr) (+ 1), columns gx ..; the activation there by transposing reads
+    const int gr = 8 * g / W, gx = 8 * g % W;
+    int own[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int col = gx + 4 * h + (n16 >> 2) + 1;
+        own[h] = (2 * gr + 1) * ROWA + col * PXA + (((2 * dt + (q4 >> 1)) ^ swizzle<CI>(col)) << 4) + (q4 & 1) * 8;
+    }
+    auto masked = [](unsigned r, unsigned act) {   // two packed results where the activation, which a ReLU left, is not zero
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        const u16x2 one = {1, 1}, m = __builtin_elementwise_min(__builtin_bit_cast(u16x2, act), one);
+        return __builtin_bit_cast(unsigned, (u16x2)(__builtin_bit_cast(u16x2, r) * m));
+    };
+    constexpr int UW = U / DS;   // units of a wave
+    struct Shortcut { u32x2 v[UW]; };
+    auto request = [&](int i) {   // the block output's delta at this lane's even pixels
+        Shortcut sc;
+#pragma unroll
+        for (int k = 0; k < UW; ++k) {
+            const int u = dq + DS * k, im = i + u / UI < hi ? i + u / UI : hi - 1;
+            sc.v[k] = *reinterpret_cast<const u32x2 *>(a.scd + ((img0 + im) * CO + o) * HWo + (u % UI * RU + gr) * Wo + gx / 2);
+        }
+        return sc;
+    };
+    auto data_out = [&](const unsigned char *buf, const Shortcut &sc, int i) {
+#pragma unroll
+        for (int k = 0; k < UW; ++k) {
+            const int u = dq + DS * k, im = u / UI, r0 = u % UI * RU;
+            if (NI > 1 && i + im >= hi) continue;
+            const unsigned char *dp = buf + DELTA + im * IMD + r0 * ROWD, *ap = buf + im * IMA + 2 * r0 * ROWA;
+            bf16x8 f[2][2][NH];   // [delta row r, r + 1][column x, x + 1]
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) f[r][c][h] = *reinterpret_cast<const bf16x8 *>(dp + r * ROWD + (foff[c] ^ (h << 6)));
+            u32x4 m[2];
+#pragma unroll
+            for (int odd = 0; odd < 2; ++odd) m[odd] = read_transposed(ap + odd * ROWA + own[0], ap + odd * ROWA + own[1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int odd = 0; odd < 2; ++odd) {   // input rows 2 r and 2 r + 1
+                f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // pixels at even and at odd columns
+#pragma unroll
+                for (int ky = odd ? 0 : 1; ky < 3; ky += 2)   // (taps reversed, ascending: the order of the packed operand)
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                        for (int h = 0; h < NH; ++h)
+                            acc[kx != 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ky == 2][kx == 2][h], wf[(ky * 3 + kx) * NH + h], acc[kx != 1], 0, 0, 0);
+                const unsigned s2[2] = {sc.v[k].x, sc.v[k].y}, am[4] = {m[odd].x, m[odd].y, m[odd].z, m[odd].w};
+                unsigned r[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    float e = acc[0][p];
+                    if (!odd) e += __uint_as_float((p & 1) ? s2[p >> 1] & 0xffff0000u : s2[p >> 1] << 16);
+                    r[p] = masked(f2bf_pack(e, acc[1][p]), am[p]);
+                }
+                *reinterpret_cast<u32x4 *>(a.din + ((img0 + i + im) * CI + o) * HW + (2 * (r0 + gr) + odd) * W + gx) = (u32x4){r[0], r[1], r[2], r[3]};
+            }
+        }
+    };
+
+    // ---- the halos stay zero from here on; what follows writes the images' own pixels only
+    for (int e = tid; e < 2 * BUF / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
+    fetch(lo);
+    __syncthreads();
+    commit(smem, lo);
+    fetch(lo + NI);
+    int cur = 0;
+    for (int i = lo; i < hi; i += NI) {
+        __syncthreads();
+        const unsigned char *const buf = smem + cur * BUF;
+        cur ^= 1;
+        const Shortcut sc = request(i);
+        commit(smem + cur * BUF, i + NI);
+        fetch(i + 2 * NI);
+        wgrad(buf);
+        data_out(buf, sc, i);
+    }
+
+    // ---- the waves that split the contraction meet in wave order, then the partial sum leaves
+    __syncthreads();
+    constexpr int RED = 9 * 256, TILES = CTI * CTO;
+    float *red = reinterpret_cast<float *>(smem);
+    const int tile = co * CTI + ci;
+    float *out = a.part + ((i64)w * a.splits + sp) * wgrad_partial_size(TILES, 1);
+    if (KSPLIT > 1) {
+        if (kq > 0)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) *reinterpret_cast<f32x4 *>(red + ((kq - 1) * TILES + tile) * RED + (k * 64 + lane) * 4) = sum[k];
+        __syncthreads();
+        if (kq == 0)
+            for (int q = 1; q < KSPLIT; ++q)
+#pragma unroll
+                for (int k = 0; k < 9; ++k) sum[k] += *reinterpret_cast<const f32x4 *>(red + ((q - 1) * TILES + tile) * RED + (k * 64 + lane) * 4);
+        __syncthreads();
+    }
+    if (kq == 0)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) *reinterpret_cast<f32x4 *>(out + ((tile * 9 + k) * 64 + lane) * 4) = sum[k];
+    // bias: every column of the product with ones is the sum over pixels; rows 4 g .. + 3 are in lane 16 g
+    float b = (bsum.x + bsum.y) + (bsum.z + bsum.w);
+    b += __shfl_down(b, 32, 64);
+    b += __shfl_down(b, 16, 64);
+    float *bias = reinterpret_cast<float *>(smem);
+    if (lane == 0) bias[wave] = ci == 0 ? b : 0.f;
+    __syncthreads();
+    if (tid == 0) {
+        float t = 0.f;
+        for (int k = 0; k < 8; ++k) t += bias[k];
+        out[TILES * RED] = t;
+    }
+}
+
+template <int CI, int W>
+dpsgd_status launch(dpsgd_ctx *ctx, const ConvDownArgs &a)
+{
+    static_assert(down_lds(CI, W) <= 160 * 1024 && down_lds(CI, W) >= (size_t)(8 - CI / 16 * (CI / 8)) * 9 * 1024, "images and sums fit");
+    auto k = conv_down_bwd_kernel<CI, W>;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)down_lds(CI, W)) != hipSuccess)
+        return DPSGD_EDEVICE;
+    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(512), down_lds(CI, W), ctx->stream, a);
+    return hip_status(hipGetLastError());
+}
+}  // namespace
+
+bool conv_down_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c)
+{
+    return ctx->opt_conv_down && c.stride == 2 && c.Cos == 2 * c.Cis && c.His == c.Wis && c.Hos == c.Wos && c.Wis == 2 * c.Wos &&
+           ((c.Cis == 16 && c.Wis == 32) || (c.Cis == 32 && c.Wis == 16)) && conv_has_backward_operands(c);
+}
+
+dpsgd_status conv_down_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
+                           Tensor din, float *G, float *partials, WgradReduceList *pending)
+{
+    if (!conv_down_bwd_ok(ctx, c)) return DPSGD_EUNSUPPORTED;
+    ConvDownArgs a{};
+    a.dv = dout.t; a.in = act.t; a.scd = scd; a.din = din.t; a.wd = wpack_d; a.part = partials;
+    a.B = B; a.splits = conv_image_splits(ctx->n, B, 256, c.Cos);
+    const dpsgd_status st = c.Cis == 16 ? launch<16, 32>(ctx, a) : launch<32, 16>(ctx, a);
+    if (st != DPSGD_OK) return st;
+    WgradReduceJob job{};
+    const int tiles = (c.Cis / 16) * (c.Cos / 16);
+    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = a.splits; job.psz = wgrad_partial_size(tiles, 1);
+    job.tiles = tiles; job.biases = 1; job.ci_tiles = c.Cis / 16; job.CIr = c.Ci; job.COr = c.Co;
+    return conv_weight_grad_add(ctx, pending, job, G);
+}
+
+}  // namespace dpsgd

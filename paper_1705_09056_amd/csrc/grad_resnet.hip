@@ -555,6 +555,8 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         // conv1: from du and a_j; next dv = [a_j > 0] * (dgrad(du) + shortcut delta)
         if (conv_bwd_ok(ctx, c1)) {
             if ((st = conv_bwd(ctx, c1, B, du, wd1, dv.t, a_of(j), dnext, G, p1, &pending)) != DPSGD_OK) return st;
+        } else if (conv_down_bwd_ok(ctx, c1)) {
+            if ((st = conv_down_bwd(ctx, c1, B, du, wd1, dv.t, a_of(j), dnext, G, p1, &pending)) != DPSGD_OK) return st;
         } else {
             if ((st = conv_weight_grad(ctx, c1, B, a_of(j), du, G, p1, &pending)) != DPSGD_OK) return st;
             const ShortcutRef scd{dv.t, c2.Cos, c2.Hos, c2.Wos, c1.stride};

@@ -151,6 +151,12 @@ dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &
                             const bf16_t *wpack_d2, Tensor u, Tensor in, Tensor din, float *G, float *partials1, float *partials2,
                             WgradReduceList *pending);
 
+// The same for the convolution of stride 2 that opens a stage (conv_down.hip), scd: the delta of the block output (its channels beyond
+// the input's are the shortcut's zeros).
+bool conv_down_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c);
+dpsgd_status conv_down_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
+                           Tensor din, float *G, float *partials, WgradReduceList *pending);
+
 dpsgd_status conv_forward_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor in, const float *X, ShortcutRef sc,
                                   Tensor out);
 dpsgd_status conv_data_grad_generic(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const float *X,

@@ -326,6 +326,44 @@ def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
             assert rel_err(b, a) < 1e-5, p.name
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((3, 32, 32, 16, 1, 10), 5, 2),     # 16 channels into 32 and 32 into 64; an odd number of images where two are taken at a time
+    ((1, 28, 28, 16, 1, 10), 7, 8),     # zeros beyond the real extents; 8 workers: one XCD per worker
+    ((3, 32, 32, 9, 2, 10), 3, 3),      # 9 / 18 / 36 real channels
+    ((3, 16, 16, 32, 1, 10), 4, 2),     # 32 into 64 first, then 64 into 128: the other kernels
+    ((3, 32, 32, 16, 1, 10), 2, 260),   # one workgroup per worker takes all its images
+])
+def test_strided_backward_in_one_launch(widths, batch, n):
+    """Weight and data gradient of a strided convolution in one launch ("conv_down") against a launch each: the deltas have the
+    same bits (those of the layers below show it: the stem's and the first stage's gradients), the strided layers' own gradients
+    add up the same products in another order: fp32 sums, 1e-5 of a layer's norm."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_down={setting} widths={widths} n={n} B={batch}", flush=True)
+            ctx.set_option("conv_down", setting)
+            ctx.grad(model, Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append(from_dev(Gd, d))
+    assert np.array_equal(out[1], out[2]), "not the same twice"
+    lay = synth.param_layout(MODEL_RESNET20, widths)
+    scale = np.abs(np.concatenate([out[0][:, p.offset:p.offset + p.size] for p in lay if p.size == 1], axis=1)).max()
+    for p in lay:
+        a, b = (o[:, p.offset:p.offset + p.size] for o in out[:2])
+        if not p.name.startswith(("s1b0", "s2b0")):
+            assert np.array_equal(a, b), p.name
+        elif p.size == 1:
+            assert np.abs(a - b).max() <= 1e-5 * scale, p.name
+        else:
+            assert rel_err(b, a) < 1e-5, p.name
+
+
 @pytest.mark.parametrize("widths,batch,n", [((3, 32, 32, 24, 2, 10), 3, 2),     # 96 channels on 8 x 8 pixels stored as 128
                                             ((3, 16, 16, 32, 1, 10), 5, 3),     # 128 real ones, on 4 x 4 pixels
                                             ((1, 9, 30, 17, 1, 5), 2, 8),       # 17 / 34 / 68: tiles beyond the real channels

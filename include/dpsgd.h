@@ -178,7 +178,7 @@ dpsgd_status dpsgd_set_gamma(dpsgd_ctx *ctx, float gamma);
  * residual block that keeps the resolution, with 16 or 32 channels - in one launch where the shapes allow it; the deltas
  * have the same bits, the weight gradients add up in another order),
  * "conv_down" (default 1: the same for the convolution of stride 2 that opens a stage, 16 channels on 32 x 32 pixels or 32 on
- * 16 x 16),
+ * 16 x 16; and, from 256 images on, the forward of the block it belongs to in one launch with those behind it),
  * "conv_block" (default 1: CNN forward, residual blocks that keep the resolution (16 channels, 32 on 16 x 16 or 64 on 8 x 8
  * pixels): both convolutions of
  * the block in one launch, the activation between them kept in LDS for the second one; from 256 images on all

@@ -20,7 +20,7 @@ namespace {
 constexpr int kMaxChain = 8;   // convolutions of a launch
 
 struct ConvChainArgs {
-    const bf16_t *src;              // a of the first block [n*B][C][H][W]
+    const bf16_t *src;              // a of the first block [n*B][C][H][W]; DOWN: the block's input [n*B][C/2][2H][2W]
     bf16_t *out[kMaxChain];         // u, a, u, a, ..
     const bf16_t *wpack[kMaxChain]; // packed forward operands [n][KS][C/16][64][8]
     i64 b_off[kMaxChain];
@@ -37,14 +37,17 @@ constexpr int threads_of(int C) { return C == 16 ? 512 : 256; }
 constexpr int kWorkgroupsPerCu = 2;
 
 // HT: rows of an image, or 0: a.H of them and one image at a time.  PAD: real extents below the stored ones.
-template <int C, int W, int HT, int NI, bool PAD>
+// DOWN: the first block opens the stage: its first convolution has stride 2 and half the channels, and reads the block's input from a
+// third buffer in LDS; every second pixel of that input is then the shortcut, zeros in the other channels.
+template <int C, int W, int HT, int NI, bool PAD, bool DOWN>
 __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerCu / 256) conv_chain_kernel(ConvChainArgs a)
 {
     constexpr int NT = threads_of(C), KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
     constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
     constexpr int DS = NT / 64 / CT;                        // waves that split the pixels; the others split the output channels
     constexpr int HALF = W == 32 ? 16 * PXB : (16 / W) * ROWB;   // from a group's first 16 pixels to its second
-    static_assert(HT > 0 || NI == 1, "several images at a time are of a fixed size");
+    static_assert(HT > 0 || (NI == 1 && !DOWN), "several images at a time, and those of a stage's first block, are of a fixed size");
+    constexpr int CP = C / 2, WP = 2 * W, PXP = 2 * CP, ROWP = row_pixels(CP, WP) * PXP, IMP = image_lds(CP, WP, 2 * HT), KSP = ksteps(CP);   // DOWN: the input
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ float biases[kMaxChain];
     int sp = blockIdx.x, w = blockIdx.y;
@@ -92,14 +95,53 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
         }
     };
 
+    // DOWN: the same of the input, TP tasks a thread
+    constexpr int TPI = DOWN ? (CP / 8) * (WP * 2 * HT / 4) : NT, TP = NI * TPI / NT;
+    static_assert(!DOWN || NI * TPI % NT == 0, "whole tasks");
+    u32x2 stp[DOWN ? TP : 1][8];
+    auto task_at = [&](int t, int &im, int &c8, int &p) {
+        const int e = tid + NT * t;
+        im = e / TPI; c8 = e % TPI / (TPI / (CP / 8)); p = e % (TPI / (CP / 8)) * 4;
+    };
+    auto fetch_input = [&](int i) {
+#pragma unroll
+        for (int t = 0; t < TP; ++t) {
+            int im, c8, p;
+            task_at(t, im, c8, p);
+            const bf16_t *q = a.src + ((img0 + (i + im < hi ? i + im : hi - 1)) * CP + 8 * c8) * (4 * HW) + p;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) stp[t][c] = *reinterpret_cast<const u32x2 *>(q + c * 4 * HW);
+        }
+    };
+    auto commit_input = [&](unsigned char *buf) {
+#pragma unroll
+        for (int t = 0; t < TP; ++t) {
+            int im, c8, p;
+            task_at(t, im, c8, p);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int col = p % WP + 1 + j;
+                unsigned d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const unsigned l = j < 2 ? stp[t][2 * k].x : stp[t][2 * k].y, h = j < 2 ? stp[t][2 * k + 1].x : stp[t][2 * k + 1].y;
+                    d[k] = __builtin_amdgcn_perm(h, l, (j & 1) ? 0x07060302u : 0x05040100u);
+                }
+                *reinterpret_cast<u32x4 *>(buf + im * IMP + (p / WP + 1) * ROWP + col * PXP + ((c8 ^ swizzle<CP>(col)) << 4)) = (u32x4){d[0], d[1], d[2], d[3]};
+            }
+        }
+    };
+
     // ---- this wave's output-channel tile and its share of the groups
     const int dt = wave % CT, dq = wave / CT;
     struct Weights { bf16x8 v[KS]; };
     auto weights = [&](int k) {
         Weights f;
-        const bf16_t *wp = a.wpack[k] + (i64)w * (KS * CT * 512) + dt * 512 + lane * 8;
+        // (DOWN: the first convolution has fewer k-steps; its last is fetched again for the others and not used)
+        const bool few = DOWN && k == 0;
+        const bf16_t *wp = a.wpack[k] + (i64)w * ((few ? KSP : KS) * CT * 512) + dt * 512 + lane * 8;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) f.v[s] = *reinterpret_cast<const bf16x8 *>(wp + s * CT * 512);
+        for (int s = 0; s < KS; ++s) f.v[s] = *reinterpret_cast<const bf16x8 *>(wp + (few && s >= KSP ? KSP - 1 : s) * CT * 512);
         return f;
     };
     // offset, from the group's first row, of the operand of k-step s at pixel n16 of the group's first tile
@@ -177,6 +219,29 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
             a.sign[(((img0 + im) * (H / 8) + (y >> 3)) * C + o) * W + (((y & 7) * W + gx) >> 3)] = (unsigned char)bits;
         }
     };
+    // sums of a group (and the shortcut sc) to dst
+    auto emit = [&](const f32x4 (&acc)[2], unsigned char *dst, int q, float bias, bool add, const u32x2 (&sc)[2]) {
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            const unsigned d[2] = {sc[tt].x, sc[tt].y};
+            float r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float v = acc[tt][k];
+                if (add) v += __uint_as_float((k & 1) ? d[k >> 1] & 0xffff0000u : d[k >> 1] << 16);
+                v += bias;
+                r[k] = fmaxf(v, 0.f);   // (zero for a NaN and for minus zero)
+            }
+            u32x2 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3])};
+            if (PAD) {   // zeros beyond the real extents
+                const int p = 16 * tt + n16, y = (NI > 1 ? q % G : q) * R32 + p / W, x = p % W;
+                const int n = (y < a.Hr && x < a.Wr) ? a.Cr - (16 * dt + 4 * g) : 0;
+                pk.x &= (n > 0 ? 0x0000ffffu : 0u) | (n > 1 ? 0xffff0000u : 0u);
+                pk.y &= (n > 2 ? 0x0000ffffu : 0u) | (n > 3 ? 0xffff0000u : 0u);
+            }
+            *reinterpret_cast<u32x2 *>(dst + group_lds(q) + own + tt * HALF) = pk;
+        }
+    };
     // One convolution from src into dst, and meanwhile group by group what is due (due, to out, of the images from id on)
     auto convolve = [&](const unsigned char *src, unsigned char *dst, const Weights &f, float bias, bool add, const unsigned char *due, bf16_t *out, int id) {
         read_ops(ops[0], src + group_lds(dq < NI * G ? dq : 0), 0);
@@ -190,59 +255,90 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
                 for (int tt = 0; tt < 2; ++tt) sc[tt] = *reinterpret_cast<const u32x2 *>(dst + base + own + tt * HALF);
             f32x4 acc[2];
             products(acc, f, src + base, src + group_lds(q + DS < NI * G ? q + DS : q));
+            emit(acc, dst, q, bias, add, sc);
+        }
+    };
+    // DOWN: the convolution of stride 2 from the input, and the shortcut, every second of its pixels, into A
+    constexpr int NOFFP = CP == 16 ? KSP : 3;
+    int offp[DOWN ? NOFFP : 1];
+    if constexpr (DOWN)
 #pragma unroll
-            for (int tt = 0; tt < 2; ++tt) {
-                const unsigned d[2] = {sc[tt].x, sc[tt].y};
-                float r[4];
+        for (int k = 0; k < NOFFP; ++k) {
+            const int kk = 32 * (CP == 16 ? k : k * (CP / 32)) + 8 * g;
+            const int tap = kk / CP > 8 ? 8 : kk / CP;   // padded taps carry zero weights; read finite data
+            const int row = 2 * (n16 / W) + tap / 3, col = 2 * (n16 % W) + tap % 3;
+            offp[k] = row * ROWP + col * PXP + (((kk % CP) / 8 ^ swizzle<CP>(col)) << 4);
+        }
+    auto convolve_down = [&](const unsigned char *src, unsigned char *A, unsigned char *dst, const Weights &f, float bias) {
+        if constexpr (DOWN) {
+#pragma unroll 1
+            for (int q = dq; q < NI * G; q += DS) {
+                const unsigned char *p = src + q / G * IMP + q % G * 2 * R32 * ROWP;
+                f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                bf16x8 x[KSP][2];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    float v = acc[tt][k];
-                    if (add) v += __uint_as_float((k & 1) ? d[k >> 1] & 0xffff0000u : d[k >> 1] << 16);
-                    v += bias;
-                    r[k] = fmaxf(v, 0.f);   // (zero for a NaN and for minus zero)
-                }
-                u32x2 pk = {f2bf_pack(r[0], r[1]), f2bf_pack(r[2], r[3])};
-                if (PAD) {   // zeros beyond the real extents
-                    const int p = 16 * tt + n16, y = (NI > 1 ? q % G : q) * R32 + p / W, x = p % W;
-                    const int n = (y < a.Hr && x < a.Wr) ? a.Cr - (16 * dt + 4 * g) : 0;
-                    pk.x &= (n > 0 ? 0x0000ffffu : 0u) | (n > 1 ? 0xffff0000u : 0u);
-                    pk.y &= (n > 2 ? 0x0000ffffu : 0u) | (n > 3 ? 0xffff0000u : 0u);
-                }
-                *reinterpret_cast<u32x2 *>(dst + base + own + tt * HALF) = pk;
+                for (int s = 0; s < KSP; ++s)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)
+                        x[s][tt] = *reinterpret_cast<const bf16x8 *>(p + (CP == 16 ? offp[s] : offp[s % 3] + s / 3 * ROWP) + tt * 2 * (16 / W) * ROWP);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < KSP; ++s)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v[s], x[s][tt], acc[tt], 0, 0, 0);
+                const u32x2 none[2] = {(u32x2){0u, 0u}, (u32x2){0u, 0u}};
+                emit(acc, dst, q, bias, false, none);
+            }
+            constexpr int UNITS = NI * HT * W * (C / 8);   // 16 bytes each
+#pragma unroll
+            for (int e = tid; e < UNITS; e += NT) {
+                const int u = e % (C / 8), px = e / (C / 8), im = px / (HT * W), y = px % (HT * W) / W, x = px % W;
+                const int cp = 2 * x + 1, ca = x + 1;
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (u < CP / 8) v = *reinterpret_cast<const u32x4 *>(src + im * IMP + (2 * y + 1) * ROWP + cp * PXP + ((u ^ swizzle<CP>(cp)) << 4));
+                *reinterpret_cast<u32x4 *>(A + im * IMG + (y + 1) * ROWB + ca * PXB + ((u ^ swizzle<C>(ca)) << 4)) = v;
             }
         }
     };
 
     // ---- the halos stay zero from here on; what follows writes the images' own pixels only
-    for (int e = tid; e < 2 * BUF / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
-    fetch(lo);
+    for (int e = tid; e < (2 * BUF + (DOWN ? NI * IMP : 0)) / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
+    if (DOWN) fetch_input(lo);
+    else fetch(lo);
     Weights f = weights(0);
-    unsigned char *const A = smem, *const U = smem + BUF;
+    unsigned char *const A = smem, *const U = smem + BUF, *const P = smem + 2 * BUF;
     if (tid < a.nconv) biases[tid] = a.X[(i64)w * a.ld + a.b_off[tid]];
     for (int i = lo; i < hi; i += NI) {
         __syncthreads();   // the images before have left
-        commit(A);
+        if (DOWN) commit_input(P);
+        else commit(A);
         for (int k = 0; k < a.nconv; ++k) {
             __syncthreads();
             const float bias = biases[k];
-            if (k == 0) convolve(A, U, f, bias, false, nullptr, nullptr, i);
+            if (k == 0 && DOWN) {
+                fetch_input(i + NI);
+                convolve_down(P, A, U, f, bias);
+            } else if (k == 0) convolve(A, U, f, bias, false, nullptr, nullptr, i);
             else if (k & 1) convolve(U, A, f, bias, true, U, a.out[k - 1], i);
             else convolve(A, U, f, bias, false, A, a.out[k - 1], i);
             f = weights(k + 1 < a.nconv ? k + 1 : 0);   // requested before the barrier
         }
         __syncthreads();
-        fetch(i + NI);
+        if (!DOWN) fetch(i + NI);
         for (int q = dq; q < NI * G; q += DS) store(A, a.out[a.nconv - 1], q, i, true);
     }
 }
 
-size_t lds_bytes(int C, int H, int W, int NI) { return (size_t)2 * NI * image_lds(C, W, H); }
+size_t lds_bytes(int C, int H, int W, int NI, bool down = false)
+{
+    return (size_t)NI * (2 * image_lds(C, W, H) + (down ? image_lds(C / 2, 2 * W, 2 * H) : 0));
+}
 
-template <int C, int W, int HT, int NI>
+template <int C, int W, int HT, int NI, bool DOWN = false>
 dpsgd_status launch(dpsgd_ctx *ctx, const ConvChainArgs &a, bool padded)
 {
-    const size_t shm = lds_bytes(C, a.H, W, NI);
-    auto k = padded ? conv_chain_kernel<C, W, HT, NI, true> : conv_chain_kernel<C, W, HT, NI, false>;
+    const size_t shm = lds_bytes(C, a.H, W, NI, DOWN);
+    auto k = padded ? conv_chain_kernel<C, W, HT, NI, true, DOWN> : conv_chain_kernel<C, W, HT, NI, false, DOWN>;
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
         return DPSGD_EDEVICE;
     hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(threads_of(C)), shm, ctx->stream, a);
@@ -257,6 +353,13 @@ bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
     return ctx->opt_conv_block && (i64)ctx->n * B >= 256 && image_shape_ok(c) && conv_has_forward_operands(c) && c.Hos * c.Wos * c.Cos <= threads_of(c.Cos) * 32 &&
            lds_bytes(c.Cos, c.Hos, c.Wos, 1) <= 160 * 1024 / kWorkgroupsPerCu;
+}
+
+bool conv_chain_down_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B)
+{
+    return ctx->opt_conv_down && c1.stride == 2 && c1.Cos == 2 * c1.Cis && c1.His == 2 * c1.Hos && c1.Wis == 2 * c1.Wos && c1.Hos == c1.Wos &&
+           ((c1.Cos == 32 && c1.Wos == 16) || (c1.Cos == 64 && c1.Wos == 8)) && conv_has_forward_operands(c1) && conv_chain_ok(ctx, c2, B) &&
+           lds_bytes(c1.Cos, c1.Hos, c1.Wos, 1, true) <= 160 * 1024 / kWorkgroupsPerCu;
 }
 
 dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
@@ -280,7 +383,10 @@ dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &con
         const bool p = c.padded_out();
         const int C = c.Cos, W = c.Wos, H = c.Hos;
         dpsgd_status st;
-        if (C == 16) {
+        if (c.stride == 2) {
+            if (C == 32) st = launch<32, 16, 16, 1, true>(ctx, a, p);
+            else st = launch<64, 8, 8, 1, true>(ctx, a, p);
+        } else if (C == 16) {
             if (W == 32) st = H == 32 ? launch<16, 32, 32, 1>(ctx, a, p) : launch<16, 32, 0, 1>(ctx, a, p);
             else st = W == 16 ? launch<16, 16, 0, 1>(ctx, a, p) : launch<16, 8, 0, 1>(ctx, a, p);
         } else if (C == 32) {

@@ -53,7 +53,7 @@ struct dpsgd_ctx {
     int32_t opt_time_fused = 0;
     int32_t opt_conv_block = 1;     // CNN forward: the two convolutions of a resolution-keeping residual block in one launch
     int32_t opt_conv_bwd = 1;       // CNN backward: weight and data gradient of a convolution, or of a residual block, in one launch
-    int32_t opt_conv_down = 1;      // CNN backward: the same for the convolutions of stride 2
+    int32_t opt_conv_down = 1;      // CNN: the same for the convolutions of stride 2; the forward of their blocks in the stage's chain
     int32_t opt_fused_slab = 1;     // dpsgd_step, bf16 MLP, W without a walk kernel, n <= 64: every worker's tile in LDS (2: also for the torus)
     int32_t opt_class_bwd = 1;      // bf16 MLP: backward of a class layer of at most 16 outputs in one launch
     int32_t opt_conv_pad = 1;       // CNN: stages of other extents stored rounded up to a shape the MFMA kernels take

@@ -493,7 +493,7 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     }
     for (int j = 0; j < p.nblocks; ++j) {
         const ConvDesc &c1 = p.convs[1 + 2 * j], &c2 = p.convs[2 + 2 * j];
-        int chain = 0;   // blocks from here on that keep the resolution: one launch
+        int chain = conv_chain_down_ok(ctx, c1, c2, B) ? 1 : 0;   // blocks from here on that keep the resolution, behind one that may open the stage: one launch
         while (j + chain < p.nblocks && conv_chain_ok(ctx, p.convs[1 + 2 * (j + chain)], B) && conv_chain_ok(ctx, p.convs[2 + 2 * (j + chain)], B))
             ++chain;
         if (chain > 0 && a_of(j + chain).sign) {

@@ -80,6 +80,8 @@ dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDe
 // Consecutive residual blocks of that kind, all convolutions convs[first .. first + nconv) in one launch (conv_fwd.hip); _ok: whether
 // the shape (the same for all) and the number of images allow it ("conv_block" option on).  Same bits; leaves no sign bitmap (out[..].sign becomes null) but the last one's.
 bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B);
+// ... and whether the block of c1 (stride 2) and c2, which opens a stage, may be the first of them ("conv_down" option on)
+bool conv_chain_down_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B);
 dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
                                 const std::vector<bf16_t *> &wpack, std::vector<Tensor> &out);
 // din = round([act > 0] * (conv^T(dout) + shortcut delta)).

@@ -331,12 +331,13 @@ def test_backward_in_one_launch_leaves_every_delta_as_it_was(widths, batch, n):
     ((1, 28, 28, 16, 1, 10), 7, 8),     # zeros beyond the real extents; 8 workers: one XCD per worker
     ((3, 32, 32, 9, 2, 10), 3, 3),      # 9 / 18 / 36 real channels
     ((3, 16, 16, 32, 1, 10), 4, 2),     # 32 into 64 first, then 64 into 128: the other kernels
-    ((3, 32, 32, 16, 1, 10), 2, 260),   # one workgroup per worker takes all its images
+    ((3, 32, 32, 16, 1, 10), 2, 260),   # one workgroup per worker takes all its images; from 256 images on: the forward's chains
+    ((1, 28, 28, 9, 2, 10), 33, 8),     # ... of two blocks, with zeros beyond the real extents, an odd number of images
 ])
 def test_strided_backward_in_one_launch(widths, batch, n):
-    """Weight and data gradient of a strided convolution in one launch ("conv_down") against a launch each: the deltas have the
-    same bits (those of the layers below show it: the stem's and the first stage's gradients), the strided layers' own gradients
-    add up the same products in another order: fp32 sums, 1e-5 of a layer's norm."""
+    """Weight and data gradient of a strided convolution in one launch ("conv_down") against a launch each, and the block that opens
+    a stage as the first of the forward's chain: activations and deltas have the same bits (those of the layers above and
+    below show it), the strided layers' own gradients add up the same products in another order: fp32 sums, 1e-5 of a layer's norm."""
     cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
     d = synth.model_dim(MODEL_RESNET20, widths)
     X, inp, tgt = resnet_inputs(cfg, 0.3)

@@ -27,7 +27,8 @@
 // 112 workers x 32 images, 16 channels x 32 x 32, a block: 229 us in four launches, 142 here; 32 channels x 16 x 16: 157 and
 // 105; one convolution of 32 channels 82 and 61, of 64 channels x 8 x 8 77 and 53.  Registers: 199 to 206 at 16 channels, 252 to 256 of
 // 256 at 32 and 64, where the block of 32 channels on 16 x 16 pixels spills 15 and four of the sizes given at run time 3 to 8.  16 waves of
-// half the registers at 16 channels spill far more (321 us); 64 channels as a block would need the sums of four tiles per wave.
+// half the registers at 16 channels spill far more (321 us); 64 channels as a block would need the sums of four tiles per wave.  64 channels
+// shared by two workgroups (HV): 205 to 222 registers, no spills.
 #include "conv_image.h"
 
 namespace dpsgd {
@@ -42,18 +43,22 @@ struct ConvBwdArgs {
     const bf16_t *wd2, *wd1; // packed data-gradient operands [n][KS][C/16][64][8]; wd1: BLOCK only
     float *part2, *part1;    // partial sums [n][splits][wgrad_partial_size((C/16)^2, 1)]
     int H, B, splits;
+    bool halves;             // two workgroups share an image's channels (conv_bwd_by_channels)
 };
 
 // HT: rows of an image, or 0: a.H of them and one image at a time.
-template <int C, int W, int HT, int NI, bool BLOCK>
+// HV: workgroups that share an image's channels (64 channels): each forms the weight gradient of CO / HV output channels and the data
+// gradient of as many input channels.
+template <int C, int W, int HT, int NI, bool BLOCK, int HV>
 __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
 {
     constexpr int NT = 512, KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
     constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
     constexpr int RW = NT / (BLOCK ? 128 : 64);       // waves that share a gradient (BLOCK: half of them each)
-    constexpr int TW = C == 64 ? 16 / RW : 1;               // weight gradient: input-channel tiles per wave
-    constexpr int KSPLIT = RW * TW / (CT * CT);       // waves that split its contraction
-    constexpr int DS = RW / CT;                       // data gradient: waves that split the pixels
+    constexpr int TW = C == 64 ? 16 / HV / RW : 1;    // weight gradient: input-channel tiles per wave
+    constexpr int KSPLIT = HV * RW * TW / (CT * CT);  // waves that split its contraction
+    constexpr int DS = RW * HV / CT;                  // data gradient: waves that split the pixels
+    static_assert(HV == 1 || (C == 64 && !BLOCK && HV == 2), "64 channels only");
     static_assert(HT > 0 || NI == 1, "several images at a time are of a fixed size");
     static_assert(KSPLIT >= 1 && DS >= 1, "every tile has a wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -63,6 +68,8 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
         w = (int)((slot / gridDim.x) * 8 + xcd);
         sp = (int)(slot % gridDim.x);
     }
+    const int hv = sp % HV;
+    sp /= HV;
     const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int role = BLOCK ? wave8 / RW : 0, wave = wave8 & (RW - 1);
     const int n16 = lane & 15, g = lane >> 4;
@@ -112,7 +119,7 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     };
 
     // ---- data gradient: this wave's input-channel tile and weights, the offsets of its operands
-    const int dt = wave % CT, dq = wave / CT;
+    const int dt = hv * (CT / HV) + wave % (CT / HV), dq = wave / (CT / HV);
     bf16x8 wf[KS];
     {
         const bf16_t *wd = (BLOCK && role == 0 ? a.wd1 : a.wd2) + (i64)w * (KS * CT * 512) + dt * 512 + lane * 8;
@@ -149,7 +156,8 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     };
 
     // ---- weight gradient: offsets of the transposing reads, by kx; the second 16 pixels of a group lie HALF further
-    const int co = C == 64 ? wave & 3 : C == 32 ? (wave >> 1) & 1 : 0, ci0 = C == 64 ? TW * (wave >> 2) : C == 32 ? wave & 1 : 0;
+    const int co = C == 64 ? (HV == 2 ? 2 * hv + (wave & 1) : wave & 3) : C == 32 ? (wave >> 1) & 1 : 0;
+    const int ci0 = C == 64 ? (HV == 2 ? wave >> 1 : TW * (wave >> 2)) : C == 32 ? wave & 1 : 0;
     const int kq = C == 64 ? 0 : C == 32 ? wave >> 2 : wave;
     constexpr int HALF = W == 32 ? 16 * PXB : (16 / W) * ROWB;
     auto tr_offset = [&](int kx, int tile) {
@@ -428,7 +436,7 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     constexpr int RED = 9 * 256;   // floats of a tile
     float *red = reinterpret_cast<float *>(smem) + role * (KSPLIT - 1) * CT * CT * RED;
     const int tile = co * CT + ci0;
-    constexpr int psz = wgrad_partial_size(CT * CT, 1);
+    constexpr int psz = wgrad_partial_size(CT * CT, HV);
     float *out = (BLOCK && role == 1 ? a.part1 : a.part2) + ((i64)w * a.splits + sp) * psz;
     if (KSPLIT > 1) {
         if (kq > 0)
@@ -456,7 +464,7 @@ __global__ void __launch_bounds__(512, 2) conv_bwd_kernel(ConvBwdArgs a)
     if (lane == 0 && wave == 0) {
         float t = 0.f;
         for (int k = 0; k < RW; ++k) t += bias[role * RW + k];
-        out[CT * CT * 9 * 256] = t;
+        out[CT * CT * 9 * 256 + hv] = t;
     }
 }
 
@@ -473,14 +481,14 @@ bool shape_ok(const dpsgd_ctx *ctx, const ConvDesc &c, bool block)
     return ctx->opt_conv_bwd && image_shape_ok(c) && conv_has_backward_operands(c) && lds_bytes(c.Cos, c.Hos, c.Wos, block) <= 160 * 1024;
 }
 
-template <int C, int W, int HT, int NI, bool BLOCK>
+template <int C, int W, int HT, int NI, bool BLOCK, int HV = 1>
 dpsgd_status launch(dpsgd_ctx *ctx, const ConvBwdArgs &a)
 {
     const size_t shm = lds_bytes(C, a.H, W, BLOCK);
-    auto k = conv_bwd_kernel<C, W, HT, NI, BLOCK>;
+    auto k = conv_bwd_kernel<C, W, HT, NI, BLOCK, HV>;
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
         return DPSGD_EDEVICE;
-    hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(512), shm, ctx->stream, a);
+    hipLaunchKernelGGL(k, dim3((unsigned)(a.splits * HV), (unsigned)ctx->n), dim3(512), shm, ctx->stream, a);
     return hip_status(hipGetLastError());
 }
 
@@ -496,18 +504,19 @@ dpsgd_status launch_any(dpsgd_ctx *ctx, int C, int W, const ConvBwdArgs &a)
         return launch<32, 8, 0, 1, BLOCK>(ctx, a);
     }
     if constexpr (!BLOCK) {
-        if (W == 16) return launch<64, 16, 0, 1, BLOCK>(ctx, a);
+        if (W == 16) return a.halves ? launch<64, 16, 0, 1, BLOCK, 2>(ctx, a) : launch<64, 16, 0, 1, BLOCK>(ctx, a);
+        if (a.halves) return a.H == 8 ? launch<64, 8, 8, 2, BLOCK, 2>(ctx, a) : launch<64, 8, 0, 1, BLOCK, 2>(ctx, a);
         return a.H == 8 ? launch<64, 8, 8, 2, BLOCK>(ctx, a) : launch<64, 8, 0, 1, BLOCK>(ctx, a);
     }
     return DPSGD_EUNSUPPORTED;
 }
 
-dpsgd_status add_job(dpsgd_ctx *ctx, const ConvDesc &c, int splits, float *partials, float *G, WgradReduceList *pending)
+dpsgd_status add_job(dpsgd_ctx *ctx, const ConvDesc &c, int splits, int halves, float *partials, float *G, WgradReduceList *pending)
 {
     WgradReduceJob job{};
     const int t = c.Cos / 16;
-    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = splits; job.psz = wgrad_partial_size(t * t, 1);
-    job.tiles = t * t; job.biases = 1; job.ci_tiles = t; job.CIr = c.Ci; job.COr = c.Co;
+    job.part = partials; job.w_off = c.w_off; job.b_off = c.b_off; job.splits = splits; job.psz = wgrad_partial_size(t * t, halves);
+    job.tiles = t * t; job.biases = halves; job.ci_tiles = t; job.CIr = c.Ci; job.COr = c.Co;
     return conv_weight_grad_add(ctx, pending, job, G);
 }
 }  // namespace
@@ -527,19 +536,43 @@ bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc 
 // number of images, k, the smallest.  One worker's minibatch spreads over all CUs: the gradient of 1 worker x 512 images of
 // 3 x 32 x 32, 3 blocks per stage, 1037 us, 2031 with at most 32 workgroups a worker; 2 x 512 1281 and 2119, 4 x 64 415 and 444;
 // without the partial sums' time 3 x 64 takes 414 instead of 371.
-int conv_image_splits(int n, int B, int slots, int C)
+// halves: 2 where two workgroups share an image's channels; least: what the choice costs.
+static int image_splits(int n, int B, int slots, int C, int halves, i64 *least)
 {
     int best = 1;
     i64 cost = -1;
     for (int m = 1, k = B; ; m = (B + k - 1) / k) {
         k = (B + m - 1) / m;
-        const i64 c = ((i64)n * m + slots - 1) / slots * (k + 2) * 4096 + 3 * (i64)n * m * (C / 16) * (C / 16);
+        const i64 images = halves == 2 ? (i64)k * 2253 : (i64)k * 4096;   // (11/20 of an image's time)
+        const i64 c = ((i64)n * m + slots - 1) / slots * (images + 2 * 4096) + 3 * (i64)n * m * (C / 16) * (C / 16);
         if (cost < 0 || c < cost) {
             cost = c;
             best = m;
         }
-        if (--k == 0) return best;
+        if (--k == 0) break;
     }
+    *least = cost;
+    return best;
+}
+
+int conv_image_splits(int n, int B, int slots, int C)
+{
+    i64 least;
+    return image_splits(n, B, slots, C, 1, &least);
+}
+
+// Two workgroups may share a worker's images of 64 channels, each with half of the weight gradient's output channels and of the data
+// gradient's input channels: twice the images pass through LDS (11/20 of an image's time each instead of half), half as
+// many partial sums, 147 KB each, are written and read again.  A gradient and mix, by images / by channels: 16 workers x 32 images of 28 x 28
+// 378 / 355 us, 64 x 8 of 32 x 32 567 / 531, 64 x 32 1208 / 1172, 3 x 512 1508 / 1476; but 85 x 32 1667 / 1679, 128 x 64 3845 / 3866.
+bool conv_bwd_by_channels(const dpsgd_ctx *ctx, const ConvDesc &c, int B, int *splits)
+{
+    i64 whole, half = 0;
+    const int m = image_splits(ctx->n, B, 256, c.Cos, 1, &whole);
+    const int m2 = c.Cos == 64 ? image_splits(ctx->n, B, 128, c.Cos, 2, &half) : 0;
+    const bool by_channels = c.Cos == 64 && half <= whole;
+    *splits = by_channels ? m2 : m;
+    return by_channels;
 }
 
 dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
@@ -548,9 +581,9 @@ dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, con
     if (!conv_bwd_ok(ctx, c)) return DPSGD_EUNSUPPORTED;
     ConvBwdArgs a{};
     a.dv = dout.t; a.u = act.t; a.scd = scd; a.din = din.t; a.wd2 = wpack_d; a.part2 = partials;
-    a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256, c.Cos);
+    a.H = c.Hos; a.B = B; a.halves = conv_bwd_by_channels(ctx, c, B, &a.splits);
     const dpsgd_status st = launch_any<false>(ctx, c.Cos, c.Wos, a);
-    return st == DPSGD_OK ? add_job(ctx, c, a.splits, partials, G, pending) : st;
+    return st == DPSGD_OK ? add_job(ctx, c, a.splits, a.halves ? 2 : 1, partials, G, pending) : st;
 }
 
 dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B, Tensor dv, const bf16_t *wpack_d1,
@@ -562,8 +595,8 @@ dpsgd_status conv_block_bwd(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &
     a.dv = dv.t; a.u = u.t; a.in = in.t; a.din = din.t; a.wd2 = wpack_d2; a.wd1 = wpack_d1;
     a.part2 = partials2; a.part1 = partials1; a.H = c2.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256, c2.Cos);
     dpsgd_status st = launch_any<true>(ctx, c2.Cos, c2.Wos, a);
-    if (st == DPSGD_OK) st = add_job(ctx, c2, a.splits, partials2, G, pending);
-    return st == DPSGD_OK ? add_job(ctx, c1, a.splits, partials1, G, pending) : st;
+    if (st == DPSGD_OK) st = add_job(ctx, c2, a.splits, 1, partials2, G, pending);
+    return st == DPSGD_OK ? add_job(ctx, c1, a.splits, 1, partials1, G, pending) : st;
 }
 
 }  // namespace dpsgd

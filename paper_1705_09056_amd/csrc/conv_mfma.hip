@@ -1258,7 +1258,9 @@ size_t conv_wgrad_partial_bytes(const dpsgd_ctx *ctx, const ConvDesc &c, int B)
 {
     if (!wgrad_mfma_ok(c)) return 0;
     int splits = wgrad_splits(ctx->n, B, c.Cos, c.stride);
-    const int m = conv_image_splits(ctx->n, B, 256, c.Cos);   // (whichever kernel takes the convolution)
+    int m = conv_image_splits(ctx->n, B, 256, c.Cos);   // (whichever kernel takes the convolution)
+    splits = m > splits ? m : splits;
+    conv_bwd_by_channels(ctx, c, B, &m);
     splits = m > splits ? m : splits;
     return (size_t)splits * (size_t)wgrad_partial_floats(c) * sizeof(float);
 }

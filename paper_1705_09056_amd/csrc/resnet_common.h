@@ -145,6 +145,8 @@ bool conv_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c);
 bool conv_block_bwd_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2);
 // workgroups per worker (and partial sums of its weight gradient; C: their channels, 0 where there are none)
 int conv_image_splits(int n, int B, int slots, int C);
+// whether conv_bwd divides a worker's work by channels as well, and the partial sums it leaves
+bool conv_bwd_by_channels(const dpsgd_ctx *ctx, const ConvDesc &c, int B, int *splits);
 // din = round([act > 0] * (conv^T(dout) + scd)), dW and bias gradient from (act, dout); scd may be null
 dpsgd_status conv_bwd(dpsgd_ctx *ctx, const ConvDesc &c, int B, Tensor dout, const bf16_t *wpack_d, const bf16_t *scd, Tensor act,
                       Tensor din, float *G, float *partials, WgradReduceList *pending);

@@ -365,6 +365,45 @@ def test_strided_backward_in_one_launch(widths, batch, n):
             assert rel_err(b, a) < 1e-5, p.name
 
 
+@pytest.mark.parametrize("widths,batch,n", [
+    ((3, 32, 32, 16, 2, 10), 7, 3),     # two images at a time, an odd number of them
+    ((1, 28, 28, 16, 2, 10), 32, 16),   # eight partial sums a worker
+    ((3, 24, 16, 16, 2, 10), 4, 2),     # 64 channels on 8 rows of 8 pixels, of 6 x 4 real ones
+    ((3, 16, 64, 16, 2, 10), 3, 8),     # rows of 16 pixels; 8 workers: one XCD per worker
+    ((3, 96, 32, 16, 1, 10), 2, 2),     # 24 rows of 8 pixels
+    ((3, 32, 32, 16, 1, 10), 5, 200),   # more workers than workgroups at a time: by images
+])
+def test_backward_of_64_channels_by_halves(widths, batch, n):
+    """64 channels of stride 1: two workgroups share a worker's images where that leaves less partial sums.  Against a launch for
+    each gradient: the same deltas, bit for bit (the layers below), weight gradients to 1e-5 of a layer's norm (fp32 sums of the same
+    products in another order)."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp), torch.from_numpy(tgt).cuda()
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_bwd={setting} widths={widths} n={n} B={batch}", flush=True)
+            ctx.set_option("conv_bwd", setting)
+            ctx.grad(model, Xd, inp_d, tgt_d, cfg.batch, Gd, loss, input_is_bf16=True)
+            torch.cuda.synchronize()
+            out.append(from_dev(Gd, d))
+    assert np.array_equal(out[1], out[2]), "not the same twice"
+    lay = synth.param_layout(MODEL_RESNET20, widths)
+    scale = np.abs(np.concatenate([out[0][:, p.offset:p.offset + p.size] for p in lay if p.size == 1], axis=1)).max()
+    for p in lay:
+        a, b = (o[:, p.offset:p.offset + p.size] for o in out[:2])
+        if p.name.startswith("stem"):
+            assert np.array_equal(a, b), p.name
+        elif p.size == 1:
+            assert np.abs(a - b).max() <= 1e-5 * scale, p.name
+        else:
+            assert rel_err(b, a) < 1e-5, p.name
+
+
 @pytest.mark.parametrize("widths,batch,n", [((3, 32, 32, 24, 2, 10), 3, 2),     # 96 channels on 8 x 8 pixels stored as 128
                                             ((3, 16, 16, 32, 1, 10), 5, 3),     # 128 real ones, on 4 x 4 pixels
                                             ((1, 9, 30, 17, 1, 5), 2, 8),       # 17 / 34 / 68: tiles beyond the real channels

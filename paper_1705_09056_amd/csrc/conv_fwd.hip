@@ -19,15 +19,19 @@ namespace {
 
 constexpr int kMaxChain = 8;   // convolutions of a launch
 
+// The image in LDS: 8 bytes a pixel, the pixel right of a row and the one left of the next are the same zero
+__host__ __device__ constexpr int stem_row(int W) { return (W + 1) * 8; }
+__host__ __device__ constexpr int stem_lds(int W, int H) { return ((H + 2) * stem_row(W) + 8 + 15) / 16 * 16; }
+
 struct ConvChainArgs {
-    const bf16_t *src;              // a of the first block [n*B][C][H][W]; DOWN: the block's input [n*B][C/2][2H][2W]
-    bf16_t *out[kMaxChain];         // u, a, u, a, ..
+    const bf16_t *src;              // a of the first block [n*B][C][H][W]; DOWN: the block's input [n*B][C/2][2H][2W]; STEM: the image [n*B][ci][H][W]
+    bf16_t *out[kMaxChain];         // u, a, u, a, .. (STEM: its output first)
     const bf16_t *wpack[kMaxChain]; // packed forward operands [n][KS][C/16][64][8]
     i64 b_off[kMaxChain];
     unsigned char *sign;            // bitmap of the last a
     const float *X;
     i64 ld;
-    int nconv, H, B, splits;
+    int nconv, H, B, splits, ci;
     int Cr, Hr, Wr;                 // the real extents (PAD)
 };
 
@@ -39,15 +43,21 @@ constexpr int kWorkgroupsPerCu = 2;
 // HT: rows of an image, or 0: a.H of them and one image at a time.  PAD: real extents below the stored ones.
 // DOWN: the first block opens the stage: its first convolution has stride 2 and half the channels, and reads the block's input from a
 // third buffer in LDS; every second pixel of that input is then the shortcut, zeros in the other channels.
-template <int C, int W, int HT, int NI, bool PAD, bool DOWN>
+// STEM: the network's first convolution comes before the first block; the third buffer has the image, 4 channels a pixel (zeros beyond its
+// own), and a lane's 8 contraction values are those and 4 zeros, as in the operand of conv3x3_mfma_kernel: the same bits.
+enum First { kBlock, kDown, kStem };
+template <int C, int W, int HT, int NI, bool PAD, First FIRST>
 __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerCu / 256) conv_chain_kernel(ConvChainArgs a)
 {
     constexpr int NT = threads_of(C), KS = ksteps(C), CT = C / 16, PXB = 2 * C, PC = row_pixels(C, W), ROWB = PC * PXB;
     constexpr int R32 = 32 / W;                       // rows of a group of 32 pixels
     constexpr int DS = NT / 64 / CT;                        // waves that split the pixels; the others split the output channels
     constexpr int HALF = W == 32 ? 16 * PXB : (16 / W) * ROWB;   // from a group's first 16 pixels to its second
+    constexpr bool DOWN = FIRST == kDown, STEM = FIRST == kStem;
+    static_assert(!STEM || (C == 16 && W == 32 && HT == 32 && NI == 1), "the stem: 32 x 32 pixels");
     static_assert(HT > 0 || (NI == 1 && !DOWN), "several images at a time, and those of a stage's first block, are of a fixed size");
     constexpr int CP = C / 2, WP = 2 * W, PXP = 2 * CP, ROWP = row_pixels(CP, WP) * PXP, IMP = image_lds(CP, WP, 2 * HT), KSP = ksteps(CP);   // DOWN: the input
+    constexpr int ROWI = stem_row(W), KSF = DOWN ? KSP : STEM ? ksteps(8) : KS;   // STEM: bytes of an image row; k-steps of the first convolution
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ float biases[kMaxChain];
     int sp = blockIdx.x, w = blockIdx.y;
@@ -137,11 +147,11 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
     struct Weights { bf16x8 v[KS]; };
     auto weights = [&](int k) {
         Weights f;
-        // (DOWN: the first convolution has fewer k-steps; its last is fetched again for the others and not used)
-        const bool few = DOWN && k == 0;
-        const bf16_t *wp = a.wpack[k] + (i64)w * ((few ? KSP : KS) * CT * 512) + dt * 512 + lane * 8;
+        // (DOWN, STEM: the first convolution has fewer k-steps; its last is fetched again for the others and not used)
+        const bool few = KSF < KS && k == 0;
+        const bf16_t *wp = a.wpack[k] + (i64)w * ((few ? KSF : KS) * CT * 512) + dt * 512 + lane * 8;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) f.v[s] = *reinterpret_cast<const bf16x8 *>(wp + (few && s >= KSP ? KSP - 1 : s) * CT * 512);
+        for (int s = 0; s < KS; ++s) f.v[s] = *reinterpret_cast<const bf16x8 *>(wp + (few && s >= KSF ? KSF - 1 : s) * CT * 512);
         return f;
     };
     // offset, from the group's first row, of the operand of k-step s at pixel n16 of the group's first tile
@@ -301,9 +311,63 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
         }
     };
 
+    // STEM: pixels 4 tid .. + 3 of the image's channels, 8 bytes a pixel in LDS
+    u32x2 sti[STEM ? 4 : 1];
+    const int pxi = tid < HW / 4 ? 4 * tid : 0;
+    auto fetch_image = [&](int i) {
+        const int im = i < hi ? i : hi - 1;
+        const bf16_t *q = a.src + (img0 + im) * a.ci * HW + pxi;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sti[STEM ? c : 0] = *reinterpret_cast<const u32x2 *>(q + (c < a.ci ? c : 0) * HW);
+    };
+    auto commit_image = [&](unsigned char *buf) {
+        if (tid >= HW / 4) return;
+#pragma unroll
+        for (int c = 1; c < 4; ++c)
+            if (STEM && c >= a.ci) sti[c] = (u32x2){0u, 0u};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            unsigned d[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u32x2 lo2 = sti[STEM ? 2 * k : 0], hi2 = sti[STEM ? 2 * k + 1 : 0];
+                d[k] = __builtin_amdgcn_perm(j < 2 ? hi2.x : hi2.y, j < 2 ? lo2.x : lo2.y, (j & 1) ? 0x07060302u : 0x05040100u);
+            }
+            *reinterpret_cast<u32x2 *>(buf + (pxi / W + 1) * ROWI + (pxi % W + 1 + j) * 8) = (u32x2){d[0], d[1]};
+        }
+    };
+    auto convolve_image = [&](const unsigned char *src, unsigned char *dst, const Weights &f, float bias) {
+        if constexpr (STEM) {
+            int offi[KSF];
+#pragma unroll
+            for (int s = 0; s < KSF; ++s) {
+                const int tap = 4 * s + g > 8 ? 8 : 4 * s + g;   // padded taps carry zero weights; read finite data
+                offi[s] = tap / 3 * ROWI + (n16 + tap % 3) * 8;
+            }
+#pragma unroll 1
+            for (int q = dq; q < G; q += DS) {
+                f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                u32x2 x[KSF][2];
+#pragma unroll
+                for (int s = 0; s < KSF; ++s)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) x[s][tt] = *reinterpret_cast<const u32x2 *>(src + q * ROWI + offi[s] + tt * 128);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < KSF; ++s)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)
+                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v[s], __builtin_bit_cast(bf16x8, (u32x4){x[s][tt].x, x[s][tt].y, 0u, 0u}), acc[tt], 0, 0, 0);
+                const u32x2 none[2] = {(u32x2){0u, 0u}, (u32x2){0u, 0u}};
+                emit(acc, dst, q, bias, false, none);
+            }
+        }
+    };
+
     // ---- the halos stay zero from here on; what follows writes the images' own pixels only
-    for (int e = tid; e < (2 * BUF + (DOWN ? NI * IMP : 0)) / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
+    for (int e = tid; e < (2 * BUF + (DOWN ? NI * IMP : STEM ? stem_lds(W, H) : 0)) / 16; e += NT) *reinterpret_cast<u32x4 *>(smem + 16 * e) = (u32x4){0u, 0u, 0u, 0u};
     if (DOWN) fetch_input(lo);
+    else if (STEM) fetch_image(lo);
     else fetch(lo);
     Weights f = weights(0);
     unsigned char *const A = smem, *const U = smem + BUF, *const P = smem + 2 * BUF;
@@ -311,34 +375,39 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
     for (int i = lo; i < hi; i += NI) {
         __syncthreads();   // the images before have left
         if (DOWN) commit_input(P);
+        else if (STEM) commit_image(P);
         else commit(A);
         for (int k = 0; k < a.nconv; ++k) {
             __syncthreads();
             const float bias = biases[k];
+            const int kb = STEM ? k + 1 : k;   // its place in the blocks: even: the first convolution of one
             if (k == 0 && DOWN) {
                 fetch_input(i + NI);
                 convolve_down(P, A, U, f, bias);
+            } else if (k == 0 && STEM) {
+                fetch_image(i + NI);
+                convolve_image(P, A, f, bias);
             } else if (k == 0) convolve(A, U, f, bias, false, nullptr, nullptr, i);
-            else if (k & 1) convolve(U, A, f, bias, true, U, a.out[k - 1], i);
+            else if (kb & 1) convolve(U, A, f, bias, true, U, a.out[k - 1], i);
             else convolve(A, U, f, bias, false, A, a.out[k - 1], i);
             f = weights(k + 1 < a.nconv ? k + 1 : 0);   // requested before the barrier
         }
         __syncthreads();
-        if (!DOWN) fetch(i + NI);
+        if (FIRST == kBlock) fetch(i + NI);
         for (int q = dq; q < NI * G; q += DS) store(A, a.out[a.nconv - 1], q, i, true);
     }
 }
 
-size_t lds_bytes(int C, int H, int W, int NI, bool down = false)
+size_t lds_bytes(int C, int H, int W, int NI, First first = kBlock)
 {
-    return (size_t)NI * (2 * image_lds(C, W, H) + (down ? image_lds(C / 2, 2 * W, 2 * H) : 0));
+    return (size_t)NI * (2 * image_lds(C, W, H) + (first == kDown ? image_lds(C / 2, 2 * W, 2 * H) : first == kStem ? stem_lds(W, H) : 0));
 }
 
-template <int C, int W, int HT, int NI, bool DOWN = false>
+template <int C, int W, int HT, int NI, First FIRST = kBlock>
 dpsgd_status launch(dpsgd_ctx *ctx, const ConvChainArgs &a, bool padded)
 {
-    const size_t shm = lds_bytes(C, a.H, W, NI, DOWN);
-    auto k = padded ? conv_chain_kernel<C, W, HT, NI, true, DOWN> : conv_chain_kernel<C, W, HT, NI, false, DOWN>;
+    const size_t shm = lds_bytes(C, a.H, W, NI, FIRST);
+    auto k = padded ? conv_chain_kernel<C, W, HT, NI, true, FIRST> : conv_chain_kernel<C, W, HT, NI, false, FIRST>;
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
         return DPSGD_EDEVICE;
     hipLaunchKernelGGL(k, dim3((unsigned)a.splits, (unsigned)ctx->n), dim3(threads_of(C)), shm, ctx->stream, a);
@@ -359,16 +428,30 @@ bool conv_chain_down_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc
 {
     return ctx->opt_conv_down && c1.stride == 2 && c1.Cos == 2 * c1.Cis && c1.His == 2 * c1.Hos && c1.Wis == 2 * c1.Wos && c1.Hos == c1.Wos &&
            ((c1.Cos == 32 && c1.Wos == 16) || (c1.Cos == 64 && c1.Wos == 8)) && conv_has_forward_operands(c1) && conv_chain_ok(ctx, c2, B) &&
-           lds_bytes(c1.Cos, c1.Hos, c1.Wos, 1, true) <= 160 * 1024 / kWorkgroupsPerCu;
+           lds_bytes(c1.Cos, c1.Hos, c1.Wos, 1, kDown) <= 160 * 1024 / kWorkgroupsPerCu;
+}
+
+// The first convolution alone is two passes over memory around little arithmetic: the pixel-major copy of the image and the
+// convolution that reads it took 67 us of a pass of 112 workers x 32 images and 15 us of 16 x 32 ones of 28 x 28; in the chain the pass is 82 us
+// (1982 -> 1900) and 11 us (353 -> 342) shorter.  The image comes in by 8 bytes.
+bool conv_chain_stem_ok(const dpsgd_ctx *ctx, const ConvDesc &c, const ConvDesc &next, int B, const void *image)
+{
+    return c.Ci <= 4 && c.Cos == 16 && c.Hos == 32 && c.Wos == 32 && c.His == 32 && c.Wis == 32 && c.stride == 1 && conv_stem_uses_mfma(c) &&
+           conv_chain_ok(ctx, next, B) && reinterpret_cast<uintptr_t>(image) % 8 == 0 &&
+           lds_bytes(16, 32, 32, 1, kStem) + kMaxChain * sizeof(float) <= 160 * 1024 / kWorkgroupsPerCu;
 }
 
 dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
                                 const std::vector<bf16_t *> &wpack, std::vector<Tensor> &out)
 {
-    for (int at = 0; at < nconv; at += kMaxChain) {
+    const bool stem = first == 0;
+    for (int at = 0, piece; at < nconv; at += piece) {
         const ConvDesc &c = convs[first + at];
         ConvChainArgs a{};
-        a.nconv = nconv - at < kMaxChain ? nconv - at : kMaxChain;
+        piece = stem && at == 0 ? kMaxChain - 1 : kMaxChain;   // (whole blocks)
+        if (piece > nconv - at) piece = nconv - at;
+        a.nconv = piece;
+        a.ci = c.Ci;
         a.src = in.t; a.X = X; a.ld = ctx->ld; a.H = c.Hos; a.B = B; a.splits = conv_image_splits(ctx->n, B, 256 * kWorkgroupsPerCu, 0);
         a.Cr = c.Co; a.Hr = c.Ho; a.Wr = c.Wo;
         for (int k = 0; k < a.nconv; ++k) {
@@ -383,9 +466,10 @@ dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &con
         const bool p = c.padded_out();
         const int C = c.Cos, W = c.Wos, H = c.Hos;
         dpsgd_status st;
-        if (c.stride == 2) {
-            if (C == 32) st = launch<32, 16, 16, 1, true>(ctx, a, p);
-            else st = launch<64, 8, 8, 1, true>(ctx, a, p);
+        if (stem && at == 0) st = launch<16, 32, 32, 1, kStem>(ctx, a, p);
+        else if (c.stride == 2) {
+            if (C == 32) st = launch<32, 16, 16, 1, kDown>(ctx, a, p);
+            else st = launch<64, 8, 8, 1, kDown>(ctx, a, p);
         } else if (C == 16) {
             if (W == 32) st = H == 32 ? launch<16, 32, 32, 1>(ctx, a, p) : launch<16, 32, 0, 1>(ctx, a, p);
             else st = W == 16 ? launch<16, 16, 0, 1>(ctx, a, p) : launch<16, 8, 0, 1>(ctx, a, p);

@@ -474,12 +474,17 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     const bf16_t *image_chw = ws.image_bf16 ? ws.image_bf16 : (const bf16_t *)inputs;
     ConvDesc stem_raw = p.convs[0];   // the generic stem reads the caller's image as it is
     stem_raw.His = stem_raw.H; stem_raw.Wis = stem_raw.W;
+    // the stem in one launch with the first blocks, which reads the channel-major image
+    const bool stem_chain = stem_mfma && p.nblocks > 0 && conv_chain_stem_ok(ctx, p.convs[0], p.convs[1], B, image_chw) &&
+                            conv_chain_ok(ctx, p.convs[2], B);
     if (stem_mfma) {
         const ConvDesc &c = p.convs[0];
-        if ((st = conv_prep_image(ctx, c, B, inputs, m.input_is_bf16, ws.image_bf16, ws.image_nhwc8)) != DPSGD_OK) return st;
+        if ((!stem_chain || ws.image_bf16) &&
+            (st = conv_prep_image(ctx, c, B, inputs, m.input_is_bf16, ws.image_bf16, stem_chain ? nullptr : ws.image_nhwc8)) != DPSGD_OK)
+            return st;
         Tensor img8;
         img8.t = ws.image_nhwc8;
-        if ((st = conv_forward(ctx, c, B, img8, X, ws.wpack_f[0], none, ws.out[0])) != DPSGD_OK) return st;
+        if (!stem_chain && (st = conv_forward(ctx, c, B, img8, X, ws.wpack_f[0], none, ws.out[0])) != DPSGD_OK) return st;
     } else {
         const ConvDesc &c = stem_raw;
         const Extent r{c.Co, c.Ho, c.Wo};
@@ -496,6 +501,13 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
         int chain = conv_chain_down_ok(ctx, c1, c2, B) ? 1 : 0;   // blocks from here on that keep the resolution, behind one that may open the stage: one launch
         while (j + chain < p.nblocks && conv_chain_ok(ctx, p.convs[1 + 2 * (j + chain)], B) && conv_chain_ok(ctx, p.convs[2 + 2 * (j + chain)], B))
             ++chain;
+        if (j == 0 && stem_chain) {
+            Tensor img;
+            img.t = const_cast<bf16_t *>(image_chw);   // (read only)
+            if ((st = conv_chain_forward(ctx, p.convs, 0, 1 + 2 * chain, B, img, X, ws.wpack_f, ws.out)) != DPSGD_OK) return st;
+            j += chain - 1;
+            continue;
+        }
         if (chain > 0 && a_of(j + chain).sign) {
             if ((st = conv_chain_forward(ctx, p.convs, 1 + 2 * j, 2 * chain, B, a_of(j), X, ws.wpack_f, ws.out)) != DPSGD_OK) return st;
             j += chain - 1;

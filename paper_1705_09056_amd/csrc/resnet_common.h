@@ -82,6 +82,9 @@ dpsgd_status conv_block_forward(dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDe
 bool conv_chain_ok(const dpsgd_ctx *ctx, const ConvDesc &c, int B);
 // ... and whether the block of c1 (stride 2) and c2, which opens a stage, may be the first of them ("conv_down" option on)
 bool conv_chain_down_ok(const dpsgd_ctx *ctx, const ConvDesc &c1, const ConvDesc &c2, int B);
+// ... and whether the stem c may come before them (first == 0; in: the image, bf16, channel-major, stored extents), next: the
+// first block's convolutions
+bool conv_chain_stem_ok(const dpsgd_ctx *ctx, const ConvDesc &c, const ConvDesc &next, int B, const void *image);
 dpsgd_status conv_chain_forward(dpsgd_ctx *ctx, const std::vector<ConvDesc> &convs, int first, int nconv, int B, Tensor in, const float *X,
                                 const std::vector<bf16_t *> &wpack, std::vector<Tensor> &out);
 // din = round([act > 0] * (conv^T(dout) + shortcut delta)).

@@ -217,6 +217,37 @@ def test_consecutive_blocks_in_one_launch_change_no_bit(widths, batch, n):
         assert torch.equal(o[0], out[0][0]), "gradient differs"
 
 
+@pytest.mark.parametrize("bf16_inputs,skew", [(True, 0), (True, 1), (True, 4), (False, 0)])
+@pytest.mark.parametrize("widths,batch,n", [((3, 32, 32, 16, 4, 10), 37, 7),    # nine convolutions: seven and two
+                                            ((1, 28, 28, 16, 1, 10), 32, 8),    # zeros beyond the real extents
+                                            ((2, 31, 25, 12, 2, 10), 1, 256),   # ... and channels; one image per workgroup
+                                            ((4, 32, 32, 16, 1, 10), 300, 1),   # as many channels as it takes
+                                            ((5, 32, 32, 16, 1, 10), 32, 8)])   # one more
+def test_first_convolution_in_the_launch_of_the_first_blocks_changes_no_bit(widths, batch, n, bf16_inputs, skew):
+    """The first convolution of 32 x 32 stored pixels joins the chain of the blocks behind it and reads the image as it is where that is
+    bf16 and 8-byte aligned (skew: elements behind such an address); against a launch of its own ("conv_block" 0): the same bits."""
+    cfg = shrink(CONFIGS[4], widths=widths, batch=batch, n=n)
+    d = synth.model_dim(MODEL_RESNET20, widths)
+    X, inp, tgt = resnet_inputs(cfg, 0.3)
+    model = B.Model(cfg.model_kind, cfg.widths, compute_bf16=True)
+    Xd, inp_d, tgt_d = to_dev(X), bf16_dev(inp) if bf16_inputs else torch.from_numpy(inp).cuda(), torch.from_numpy(tgt).cuda()
+    flat = torch.empty(inp_d.numel() + 8, dtype=inp_d.dtype, device="cuda")
+    view = flat[skew:skew + inp_d.numel()].view(inp_d.shape)
+    view.copy_(inp_d)
+    out = []
+    with B.Dpsgd(cfg.n, d, topo_for(cfg), cfg.gamma, ld=d) as ctx:
+        for setting in (0, 1, 1):
+            Gd, loss = torch.full_like(Xd, 777.0), torch.zeros(cfg.n, device="cuda")
+            print(f"conv_block={setting} widths={widths} n={n} B={batch} skew={skew} bf16_in={bf16_inputs}", flush=True)
+            ctx.set_option("conv_block", setting)
+            ctx.grad(model, Xd, view, tgt_d, cfg.batch, Gd, loss, input_is_bf16=bf16_inputs)
+            torch.cuda.synchronize()
+            out.append((Gd, loss))
+    for o in out[1:]:
+        assert torch.equal(o[1], out[0][1]), "loss differs"
+        assert torch.equal(o[0], out[0][0]), "gradient differs"
+
+
 @pytest.mark.parametrize("widths,batch,n", [
     ((1, 28, 28, 16, 1, 10), 3, 2),   # 28 / 14 / 7 pixels stored as 32 / 16 / 8
     ((3, 13, 21, 16, 1, 10), 3, 2),   # rectangular, odd on every stage

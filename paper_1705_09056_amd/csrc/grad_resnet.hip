@@ -210,8 +210,9 @@ pool_fwd_kernel(const bf16_t *__restrict__ a, int HW, int C, int Cs, float inv, 
 // STAGED: the worker's pooled features, FC weights (rows one float apart from a multiple of the bank count) and logits
 // sit in LDS ((B (C + 1) + K (C + 1) + B K) floats of dynamic LDS) and
 // every loop below reads them from there; the arithmetic and its order are the same either way, so are the bits.
+constexpr int kHeadThreads = 1024;
 template <bool STAGED>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kHeadThreads)
 head_kernel(const float *__restrict__ X, i64 ld, i64 fcw_off, i64 fcb_off, int B, int HW, int C, int K,
             const int *__restrict__ labels, const float *__restrict__ pool, float *__restrict__ z,
             float *__restrict__ dpool, float *__restrict__ G, float *__restrict__ loss)
@@ -225,24 +226,25 @@ head_kernel(const float *__restrict__ X, i64 ld, i64 fcw_off, i64 fcb_off, int B
     const int CP = STAGED ? C + 1 : C;   // row pitch of the pooled features and of the FC weights
     if (STAGED) {
         float *ps = head_lds, *fs = ps + B * CP;
-        for (int e = tid; e < B * C; e += 256) ps[(e / C) * CP + e % C] = pw[e];
-        for (int e = tid; e < K * C; e += 256) fs[(e / C) * CP + e % C] = fw[e];
+        for (int e = tid; e < B * C; e += kHeadThreads) ps[(e / C) * CP + e % C] = pw[e];
+        for (int e = tid; e < K * C; e += kHeadThreads) fs[(e / C) * CP + e % C] = fw[e];
         __syncthreads();
         pw = ps;
         fw = fs;
         zw = fs + K * CP;
     }
     const float inv_hw = 1.0f / (float)HW;
-    for (int e = tid; e < B * K; e += 256) {
+    for (int e = tid; e < B * K; e += kHeadThreads) {
         const int b = e / K, o = e % K;
         float s = fb[o];
+#pragma unroll 8
         for (int ch = 0; ch < C; ++ch) s = fw[o * CP + ch] * pw[b * CP + ch] + s;
         zw[e] = s;
     }
     __syncthreads();
     const float invB = 1.0f / (float)B;
     float local = 0.f;
-    for (int b = tid; b < B; b += 256) {
+    for (int b = tid; b < B && tid < 256; b += 256) {   // (image b is thread b % 256's: the order of the loss's sum)
         float *zb = zw + b * K;
         int lab = labels[(i64)w * B + b];
         lab = lab < 0 ? 0 : (lab >= K ? K - 1 : lab);
@@ -254,27 +256,29 @@ head_kernel(const float *__restrict__ X, i64 ld, i64 fcw_off, i64 fcb_off, int B
         local += lse - zb[lab];
         for (int o = 0; o < K; ++o) zb[o] = (expf(zb[o] - lse) - (o == lab ? 1.f : 0.f)) * invB;   // dz in place
     }
-    red[tid] = local;
+    if (tid < 256) red[tid] = local;
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {
         if (tid < off) red[tid] += red[tid + off];
         __syncthreads();
     }
     if (loss && tid == 0) loss[w] = red[0] * invB;
-    for (int e = tid; e < K * C; e += 256) {
+    for (int e = tid; e < K * C; e += kHeadThreads) {
         const int o = e / C, ch = e % C;
         float s = 0.f;
+#pragma unroll 8
         for (int b = 0; b < B; ++b) s = zw[b * K + o] * pw[b * CP + ch] + s;
         G[(i64)w * ld + fcw_off + e] = s;
     }
-    for (int o = tid; o < K; o += 256) {
+    for (int o = tid; o < K; o += kHeadThreads) {
         float s = 0.f;
         for (int b = 0; b < B; ++b) s += zw[b * K + o];
         G[(i64)w * ld + fcb_off + o] = s;
     }
-    for (int e = tid; e < B * C; e += 256) {
+    for (int e = tid; e < B * C; e += kHeadThreads) {
         const int b = e / C, ch = e % C;
         float s = 0.f;
+#pragma unroll 5
         for (int o = 0; o < K; ++o) s = zw[b * K + o] * fw[o * CP + ch] + s;
         dpw[e] = s * inv_hw;
     }
@@ -529,10 +533,10 @@ dpsgd_status launch_grad_resnet(dpsgd_ctx *ctx, const dpsgd_model_desc &m, const
     {
         const size_t head_lds = ((size_t)(B + p.classes) * (p.C_last + 1) + (size_t)B * p.classes) * sizeof(float);
         if (head_lds <= 48 * 1024)
-            hipLaunchKernelGGL(head_kernel<true>, dim3((unsigned)n), dim3(256), head_lds, s, X, ctx->ld, p.fcw_off, p.fcb_off, B,
+            hipLaunchKernelGGL(head_kernel<true>, dim3((unsigned)n), dim3(kHeadThreads), head_lds, s, X, ctx->ld, p.fcw_off, p.fcb_off, B,
                                HWl, p.C_last, p.classes, (const int *)targets, ws.pool, ws.logits, ws.dpool, G, loss);
         else
-            hipLaunchKernelGGL(head_kernel<false>, dim3((unsigned)n), dim3(256), 0, s, X, ctx->ld, p.fcw_off, p.fcb_off, B, HWl,
+            hipLaunchKernelGGL(head_kernel<false>, dim3((unsigned)n), dim3(kHeadThreads), 0, s, X, ctx->ld, p.fcw_off, p.fcb_off, B, HWl,
                                p.C_last, p.classes, (const int *)targets, ws.pool, ws.logits, ws.dpool, G, loss);
     }
 

@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(512, 2) conv_down_bwd_kernel(ConvDownArgs a)
     }
     if (kq == 0)
 #pragma unroll
-        for (int k = 0; k < 9; ++k) *reinterpret_cast<f32x4 *>(out + ((tile * 9 + k) * 64 + lane) * 4) = sum[k];
+        for (int k = 0; k < 9; ++k) __builtin_nontemporal_store(sum[k], reinterpret_cast<f32x4 *>(out + ((tile * 9 + k) * 64 + lane) * 4));
     // bias: every column of the product with ones is the sum over pixels; rows 4 g .. + 3 are in lane 16 g
     float b = (bsum.x + bsum.y) + (bsum.z + bsum.w);
     b += __shfl_down(b, 32, 64);

@@ -220,7 +220,15 @@ __global__ void __launch_bounds__(threads_of(C), threads_of(C) * kWorkgroupsPerC
         const int im = i + (NI > 1 ? q / G : 0), y = (NI > 1 ? q % G : q) * R32 + gy;
         const u32x4 v = read_transposed(buf + group_lds(q) + ooff[0], buf + group_lds(q) + ooff[1]);
         if (im >= hi) return;
-        *reinterpret_cast<u32x4 *>(dst + ((img0 + im) * C + o) * HW + y * W + gx) = v;
+        u32x4 *const to = reinterpret_cast<u32x4 *>(dst + ((img0 + im) * C + o) * HW + y * W + gx);
+        // What a workgroup writes last would keep the launch from its end until it has left the L2s.  (16 workers x 32 images of 28 x 28,
+        // one image per workgroup, a pass 321 us, 313 with; all images of 112 x 32, whose lines leave by halves: 1870, 1940 with.)
+        if (i + NI >= hi) {
+            asm volatile("");   // (before and behind it: the compiler makes no plain store of the two)
+            __builtin_nontemporal_store(v, to);
+            asm volatile("");
+        } else
+            *to = v;
         if (last) {   // after the ReLU a value is positive exactly when its bf16 pattern is not zero
             const unsigned d[4] = {v.x, v.y, v.z, v.w};
             unsigned bits = 0;

@@ -963,7 +963,7 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
         for (int t = 0; t < NTI; ++t)
 #pragma unroll
             for (int k = 0; k < 9; ++k)
-                *reinterpret_cast<f32x4 *>(out + ((((co0 / 16 + mi) * a.ci_tiles + ci0 / 16 + t0 + t) * 9 + k) * 64 + lane) * 4) = acc[t][k];
+                __builtin_nontemporal_store(acc[t][k], reinterpret_cast<f32x4 *>(out + ((((co0 / 16 + mi) * a.ci_tiles + ci0 / 16 + t0 + t) * 9 + k) * 64 + lane) * 4));
     }
     // bias: sum of every delta element this workgroup saw
     for (int off = 32; off > 0; off >>= 1) bsum += __shfl_down(bsum, off, 64);
@@ -979,6 +979,7 @@ __global__ void __launch_bounds__(256 * wgrad_wave_groups(CI, CO), (CI <= 16 ? 4
 // in LDS and writes 16 runs of up to 144 consecutive floats; the job's last block adds the bias partials.
 // Bound by the partials it reads: 16 workers x 16 partial sums (28 x 28 images, 175 MB) 49.7 us, 53 with the loads of one split
 // in flight instead of four and the bias partials read one after the other by one thread; 112 workers (252 MB) 79 either way.
+// The partials come and go past the caches: 16 workers of 16 and 8 partial sums (120 MB) 33.5 us, 30 with, 112 workers 71 and 67.
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl, float *__restrict__ G, i64 ld)
 {
     __shared__ float tile[16 * 16 * 9];
@@ -1019,7 +1020,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int k = 0; k < 9; ++k) v[j][k] = q[j * (i64)psz + k * 256];
+                for (int k = 0; k < 9; ++k) v[j][k] = __builtin_nontemporal_load(q + j * (i64)psz + k * 256);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -1028,7 +1029,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduceTable tbl,
         }
         for (; sp < splits; ++sp, q += psz) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) s[k] += q[k * 256];
+            for (int k = 0; k < 9; ++k) s[k] += __builtin_nontemporal_load(q + k * 256);
         }
 #pragma unroll
         for (int k = 0; k < 9; ++k) tile[(ol * 16 + cl) * 9 + k] = s[k];

@@ -265,6 +265,14 @@ def test_class_layer_backward_in_one_launch_agrees_with_the_tiled_kernels(widths
         assert e < 5e-4
 
 
+@pytest.mark.parametrize("widths,batch,n", [((40, 70, 10), 1, 2), ((40, 33, 31, 7), 63, 2), ((40, 65, 16), 64, 2), ((40, 70, 10), 129, 2),
+                                            ((40, 33, 10), 256, 2), ((40, 48, 33, 16), 257, 2), ((40, 70, 10), 520, 2)])
+def test_class_layer_backward_at_the_edges_of_its_turns(widths, batch, n):
+    """32 samples of a group are fetched as the 32 before them are used, and the deltas of 256 samples as those before them are:
+    one sample, ends of a turn and of such a part, columns beyond the layer's."""
+    test_class_layer_backward_in_one_launch_agrees_with_the_tiled_kernels(widths, batch, n)
+
+
 @pytest.mark.parametrize("widths,batch", [((72, 1024, 10), 65), ((264, 1000, 10), 100), ((392, 1024, 3), 128), ((136, 1024, 10), 129)])
 def test_forward_of_more_than_64_samples_is_the_same_at_any_fill_of_the_chip(widths, batch):
     """One, two or more workgroups per CU take the weights one or two chunks ahead, over one chunk of the contraction, an odd

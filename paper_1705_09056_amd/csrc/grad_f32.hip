@@ -645,20 +645,25 @@ __global__ void __launch_bounds__(64 * WM * WN) linear_fwd_f32_kernel(GemmArgs g
     auto step = [&](int c, Chunk &r) {
         const float *As = lds + (c & 1) * BUF + (wm * RM * 16 + l16) * PK + 4 * g4;
         const float *Bs = lds + (c & 1) * BUF + TM * PK + (wn * RN * 16 + l16) * PK + 4 * g4;
+        constexpr bool READ_AHEAD = RM * RN > 1;   // the chunk's operands before its first matrix instruction (one tile a wave: 4-10 % slower)
+        f32x4 a[TK / 16][RM], b[TK / 16][RN];
 #pragma unroll
         for (int q = 0; q < TK / 16; ++q) {
-            f32x4 a[RM], b[RN];
 #pragma unroll
-            for (int i = 0; i < RM; ++i) a[i] = *reinterpret_cast<const f32x4 *>(As + 16 * i * PK + 16 * q);
+            for (int i = 0; i < RM; ++i) a[q][i] = *reinterpret_cast<const f32x4 *>(As + 16 * i * PK + 16 * q);
 #pragma unroll
-            for (int j = 0; j < RN; ++j) b[j] = *reinterpret_cast<const f32x4 *>(Bs + 16 * j * PK + 16 * q);
+            for (int j = 0; j < RN; ++j) b[q][j] = *reinterpret_cast<const f32x4 *>(Bs + 16 * j * PK + 16 * q);
+            if (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = 0; q < TK / 16; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int i = 0; i < RM; ++i)
 #pragma unroll
-                    for (int j = 0; j < RN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
-        }
+                    for (int j = 0; j < RN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][i][e], b[q][j][e], acc[i][j], 0, 0, 0);
+        if (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
         stage((c & 1) ^ 1, r, min(c + 1, last) * TK);
         fetch(min(c + 3, last) * TK, r);
         __syncthreads();
@@ -703,8 +708,16 @@ dpsgd_status linear_fwd_f32(hipStream_t s, int nworkers, const GemmArgs &g)
     // 16 workers x 64 samples x 3072 x 1024: 73-79 us with 64 x 32 tiles and eight waves, 83 with 32 x 32 tiles and four (the
     // thread-per-4x4-block kernel: 333); 4 workers x 3072-1024-10 x 128 samples: 133 us per gradient and mix either way;
     // minibatches of at most 32 samples or few tiles: the smaller ones (32 x 3072-512-512-10 x 32: 279 against 323).
-    if (g.M > 32 && (i64)((g.M + 63) / 64) * ((g.N + 31) / 32) * nworkers >= 256)
+    const i64 rows = (i64)((g.M + 63) / 64) * nworkers, narrow = rows * ((g.N + 31) / 32), wide = rows * ((g.N + 63) / 64);
+    if (g.M > 32 && narrow >= 256) {
+        // 64 x 64 tiles, two a wave, for three LDS reads where one tile a wave takes four: more than one of them per CU, and their
+        // rounds over the CUs no more than half of those of the 64 x 32 ones.  The launch, us, 64 x 32 / 64 x 64: 64 workers x 128 samples x
+        // 1024 x 1024 174 / 153, 24 x 256 x 1024 x 1024 133 / 119, 30 x 50 x 784 x 1000 47 / 42, 50 x 100 x 784 x 300 48 / 42, 32 x 64
+        // x 3072 x 1024 133 / 129 (a gradient and mix of 64 x 64-1024-1024-10 x 128 743 / 718, 50 x 784-300-10 x 100 148 / 143); with one each, 16 x 64 x 3072 x 1024, 77 / 78; with a last round for which the narrow ones have none, 40 x
+        // 64 x 3072 x 1024 166 / 180, 100 x 100 x 784 x 96 39 / 42.
+        if (wide > 256 && 2 * ((wide + 255) / 256) <= (narrow + 255) / 256) return linear_fwd_launch<2, 1, 2, 4, 32>(s, nworkers, g);
         return linear_fwd_launch<1, 1, 4, 2, 64>(s, nworkers, g);
+    }
     return linear_fwd_launch<1, 1, 2, 2, 64>(s, nworkers, g);
 }
 

@@ -103,6 +103,16 @@ def test_mlp_fp32_tiles_and_remainders(widths, batch, n):
     grad_case(cfg, d | 1, spread=0.3)
 
 
+@pytest.mark.parametrize("widths,batch,n", [((5, 191, 10), 33, 130), ((67, 255, 10), 65, 60), ((100, 64, 10), 64, 400)])
+def test_forward_of_many_tiles_of_64_by_64(widths, batch, n):
+    """A hidden layer whose 64 x 64 tiles fill the chip more than once and in half the rounds of 64 x 32 ones: a contraction
+    shorter than a chunk, and ones with a remainder; rows and columns that end inside a tile, and whole tiles."""
+    cfg = shrink(CONFIGS[2], widths=widths, batch=batch, n=n, bf16=False)
+    d = synth.model_dim(MODEL_MLP, widths)
+    grad_case(cfg, synth.padded_stride(d), spread=0.3)
+    grad_case(cfg, d | 1, spread=0.3)
+
+
 @pytest.mark.parametrize("widths,batch,n", [
     ((64, 300, 2), 70, 3),        # data gradient of two classes: a contraction of 2
     ((20, 65, 3), 64, 2),         # ... of 3, an input more than a tile

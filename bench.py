@@ -374,7 +374,11 @@ def run_one(args, with_cpu_baseline):
             else "mlp_fused_ring_kernel"
         ring_name = "mlp_fused_ring_rows_kernel" if all(rows_kernel) else tiles_name if not any(rows_kernel) \
             else "mlp_fused_ring_rows_kernel / " + tiles_name
-        kernel_name = (ring_name if ring_ok else "mlp_fused_torus_cols_kernel" if torus_ok else "mlp_fused_slab_kernel") + \
+        # the ring with a far link: two walks half a ring apart, for layers of whole 1 KB row pieces
+        chord_ok = cfg.topology == "ring_chord" and cfg.batch <= 32 and not any(o.startswith("fused_slab=") for o in args.option) and \
+            all(w % 256 == 0 for w in cfg.widths[:-1])
+        any_name = "mlp_fused_chord_rows_kernel" if chord_ok else "mlp_fused_slab_kernel"
+        kernel_name = (ring_name if ring_ok else "mlp_fused_torus_cols_kernel" if torus_ok else any_name) + \
             " (weight gradient + Algorithm 1 steps 4-5, in place)"
         launch_bytes = (8.0 * fused_weights + 2.0 * shadow_weights) * cfg.n * K / med["launches"]
     else:
